@@ -25,6 +25,7 @@
 #include <cmath>
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "corm.h"
 
@@ -175,10 +176,16 @@ int corm_evict_mask(const corm_desc* desc, const void* score_ring, const int32_t
   if (!score_ring || !lens || !pos || !t || !t_first || !keep) return CORM_EINVAL;
   if (misaligned4(score_ring) || misaligned4(lens) || misaligned4(pos) || misaligned4(t) || misaligned4(t_first))
     return CORM_EINVAL;
-  dim3 grid((desc->Lcap + WG - 1) / WG, desc->B * desc->Hkv);
-  hipLaunchKernelGGL(corm_evict_mask_kernel, grid, dim3(WG), 0, (hipStream_t)stream, score_ring,
-                     (int)desc->score_dtype, lens, pos, t, t_first, keep, desc->Hq, desc->Hkv,
-                     desc->Lcap, desc->Tcap, desc->w, desc->r, desc->thr_scale);
+  const dim3 grid((desc->Lcap + 63) / 64, desc->B * desc->Hkv), wg(MASK_WAVES * 64);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, wg, 0, (hipStream_t)stream, score_ring, lens, pos, t, t_first, keep, desc->Hq,
+                       desc->Hkv, desc->Lcap, desc->Tcap, desc->w, desc->r, desc->thr_scale);
+  };
+  switch (desc->score_dtype) {
+    case CORM_BIT: launch(corm_evict_mask_kernel<CORM_BIT>); break;
+    case CORM_BF16: launch(corm_evict_mask_kernel<CORM_BF16>); break;
+    default: launch(corm_evict_mask_kernel<CORM_F32>); break;
+  }
   return launch_status();
 }
 

@@ -32,46 +32,108 @@ __global__ __launch_bounds__(64) void corm_append_kernel(char* K, char* V, int32
   }
 }
 
-// literal windowed OR over the ring (Def. 4.1 + recent r + group rule)
-__global__ __launch_bounds__(WG) void corm_evict_mask_kernel(const void* ring, int ring_mode, const int32_t* lens,
-                                                             const int32_t* pos, const int32_t* t,
-                                                             const int32_t* t_first, uint8_t* keep, int Hq, int Hkv,
-                                                             int Lcap, int Tcap, int w, int r, float c) {
+// The literal rule's look-up, in two halves so that many loads can be in flight: the word of a ring row that holds
+// position pi, and whether it says "score >= thr" (bit ring: the recorded boolean itself).
+template <int MODE>
+__device__ __forceinline__ uint32_t ring_word(uint64_t row, int pi) {   // row: address in global memory
+#define CORM_GLOBAL(T) reinterpret_cast<const __attribute__((address_space(1))) T*>(row)
+  if (MODE == CORM_BIT) return CORM_GLOBAL(uint32_t)[pi >> 5];
+  return MODE == CORM_BF16 ? (uint32_t)CORM_GLOBAL(uint16_t)[pi] : CORM_GLOBAL(uint32_t)[pi];
+#undef CORM_GLOBAL
+}
+template <int MODE>
+__device__ __forceinline__ bool ring_word_hit(uint32_t word, int pi, float thr) {
+  if (MODE == CORM_BIT) return (word >> (pi & 31)) & 1u;
+  return __uint_as_float(MODE == CORM_BF16 ? word << 16 : word) >= thr;
+}
+
+// Literal windowed OR over the ring (Def. 4.1 + recent r + group rule).
+// Bound by the latency of the w * G reads per key and, where keys are rarely important, by the bytes of the window.  One
+// workgroup takes 64 consecutive slots, one per lane, and its eight waves share the window's (row, head) pairs, newest
+// row first, up to eight loads in flight each.  After every round the waves pool what they found and stop once all 64 keys
+// are decided; the first round is short (16 pairs, then 64), since most keys are found important within a few rows.
+// Measured against one thread per key that walked the window alone (a load, a division and a modulo per row, in series):
+// 16 units of ~1460 keys, w 256, G 2: 197 -> 18 us; 512 units of 4096 keys, w 1024, G 1, nearly all kept: 1528 -> 407 us,
+// 64 % evicted: 932 -> 322 us (bit ring 819 -> 129 us).
+constexpr int MASK_WAVES = 8;
+
+template <int MODE>
+__global__ __launch_bounds__(MASK_WAVES * 64) void corm_evict_mask_kernel(const void* ring, const int32_t* lens,
+                                                                          const int32_t* pos, const int32_t* t,
+                                                                          const int32_t* t_first, uint8_t* keep, int Hq,
+                                                                          int Hkv, int Lcap, int Tcap, int w, int r,
+                                                                          float c) {
+  __shared__ unsigned long long sh_hit;
   const int unit = blockIdx.y;
   const int b = unit / Hkv, hkv = unit - b * Hkv;
-  const int G = Hq / Hkv;
+  const int G = Hq / Hkv;   // a power of two
+  const int gshift = 31 - __clz(G);
   int L = lens[unit];
   L = L < 0 ? 0 : (L > Lcap ? Lcap : L);
-  const int i = blockIdx.x * WG + threadIdx.x;
-  if (i >= L) return;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x * 64 >= L) return;
+  const int i = blockIdx.x * 64 + lane;
   const int tcur = t[b];
   const int tf = t_first[b];
-  bool k = i >= L - r;
   const bool full = tcur - tf + 1 >= w;
-  if (!full) k = true;
-  const int pi = pos[(size_t)unit * Lcap + i];
-  if (!k && pi >= 0 && pi < Tcap) {
-    const int lo = max(max(tf, tcur - w + 1), 1);
-    for (int tau = tcur; tau >= lo && !k; --tau) {
-      if (pi > tau - 1) break;  // the key did not exist at step tau (nor earlier): minor there
-      const float thr = importance_threshold(c, tau);
-      const int slot = (tau - 1) % w;
-      for (int g = 0; g < G; ++g) {
-        const size_t row = (size_t)(b * Hq + hkv * G + g) * w + slot;
-        if (ring_mode == CORM_BIT) {   // the recorded boolean itself
-          const uint32_t word = reinterpret_cast<const uint32_t*>(ring)[row * ((Tcap + 31) >> 5) + (size_t)(pi >> 5)];
-          k |= ((word >> (pi & 31)) & 1u) != 0;
-        } else {
-          const size_t ri = row * Tcap + (size_t)pi;
-          const float v = ring_mode == CORM_BF16
-                              ? __uint_as_float((uint32_t) reinterpret_cast<const uint16_t*>(ring)[ri] << 16)
-                              : reinterpret_cast<const float*>(ring)[ri];
-          k |= (v >= thr);
-        }
-      }
+  const bool kept = !full || i >= L - r;   // decided without the ring
+  const int pi = i < L ? pos[(size_t)unit * Lcap + i] : -1;
+  const bool look = !kept && pi >= 0 && pi < Tcap;
+  const int lo = max(max(tf, tcur - w + 1), 1);
+  const long long pairs = tcur >= lo ? (long long)(tcur - lo + 1) << gshift : 0;
+  const size_t row0 = (size_t)(b * Hq + hkv * G) * w;   // ring rows of the group's first head
+  if (threadIdx.x == 0) sh_hit = 0ull;
+  __syncthreads();
+
+  const unsigned long long todo = __ballot(look);   // the same in every wave
+  unsigned long long open = todo;
+  bool hit = false;
+  const int slot0 = pairs > 0 ? (tcur - 1) % w : 0;   // ring slot of the newest row
+  const size_t rowb = MODE == CORM_BIT ? (size_t)((Tcap + 31) >> 5) * 4 : (size_t)Tcap * (MODE == CORM_BF16 ? 2 : 4);
+  // Pair k: head k % G of step tcur - k / G.  What belongs to a pair and not to a key (the row's address, the IEEE quotient
+  // of its threshold, the newest position its query saw) is formed by the lanes at once, one pair each.
+  auto round = [&](auto batch, long long k0) {
+    constexpr int N = decltype(batch)::value;
+    const long long k = k0 + (lane & (N - 1));
+    const int back = (int)(k >> gshift);   // (< w, like the window's rows, wherever the pair is looked up)
+    const int slot = slot0 - back + (slot0 < back ? w : 0);
+    const float thr = importance_threshold(c, max(tcur - back, 1));
+    // (a key younger than the row did not exist at its step: minor there)
+    const int seen = k < pairs ? tcur - back - 1 : -1;
+    const uint64_t at = reinterpret_cast<uint64_t>(ring) + (row0 + (size_t)(k & (G - 1)) * w + (size_t)slot) * rowb;
+    const bool mine = (open >> lane) & 1ull;
+    uint32_t word[N];
+    bool ok[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const uint64_t row = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(at >> 32), j) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)at, j);
+      ok[j] = mine & (pi <= __builtin_amdgcn_readlane(seen, j));
+      word[j] = 0u;
+      if (ok[j]) word[j] = ring_word<MODE>(row, pi);
     }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const float thr_j = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(thr), j));
+      hit |= ok[j] & ring_word_hit<MODE>(word[j], pi, thr_j);
+    }
+  };
+  for (long long k0 = 0; k0 < pairs && open != 0ull;) {   // (uniform over the workgroup)
+    if (k0 == 0) {
+      round(std::integral_constant<int, 2>(), wv * 2);
+      k0 += MASK_WAVES * 2;
+    } else {
+      round(std::integral_constant<int, 8>(), k0 + wv * 8);
+      k0 += MASK_WAVES * 8;
+    }
+    const unsigned long long found = __ballot(hit);
+    if (lane == 0 && found != 0ull) atomicOr(&sh_hit, found);
+    __syncthreads();
+    open = todo & ~sh_hit;
+    __syncthreads();   // (every wave has read the pool before the next round adds to it)
   }
-  keep[(size_t)unit * Lcap + i] = k ? 1 : 0;
+  if (wv == 0 && i < L) keep[(size_t)unit * Lcap + i] = (kept || ((sh_hit >> lane) & 1ull)) ? 1 : 0;
 }
 
 __global__ __launch_bounds__(WG) void corm_evict_mask_summary_kernel(const int32_t* last_hit, const int32_t* lens,

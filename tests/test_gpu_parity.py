@@ -633,6 +633,51 @@ def test_evict_mask_standalone_random_ring():
                         assert not want.all()
 
 
+@pytest.mark.parametrize("score_dtype", ["f32", "bf16", "bit"])
+@pytest.mark.parametrize("G,w,recorded", [(1, 1, 1), (1, 16, 16), (1, 17, 17), (2, 40, 40), (4, 81, 81), (8, 10, 10),
+                                          (8, 9, 8), (1, 145, 145)])
+def test_evict_mask_rounds_and_slot_groups(score_dtype, G, w, recorded):
+    """corm_evict_mask looks (row, head) pairs up in rounds (16 pairs, then 64) for groups of 64 slots: windows that end
+    inside, at and just past a round, units that end inside, at and past a group, single hits in the newest and oldest
+    row, hits in rows older than the key, positions outside the ring.  Integers and exact compares: no tolerance."""
+    lens = [1, 63, 64, 65, 130, 0]
+    B, Hkv, Lcap, Tcap, r, d = 1, len(lens), 130, 400, 1, 64
+    tcur = 333
+    kv = "f32" if score_dtype == "f32" else "bf16"
+    st = corm.LayerState(B, G * Hkv, Hkv, d, Lcap, Tcap, w, r, kv, device=DEV, want_masks=True,
+                         score_dtype="bit" if score_dtype == "bit" else None)
+    g = torch.Generator().manual_seed(11 * w + G)
+    pos = torch.stack([torch.sort(torch.randperm(tcur, generator=g)[:Lcap]).values for _ in range(Hkv)])
+    pos[:, -1] = Tcap + 3           # a position the ring has no column for
+    hit = torch.rand(Hkv, G, w, Tcap, generator=g) < 1.0 / (2 * G * w)   # about half the keys have one
+    thr = 1.0 / tcur
+    st.lens.copy_(torch.tensor(lens, dtype=torch.int32).view(B, Hkv))
+    st.pos.copy_(pos.view(B, Hkv, Lcap).int())
+    if score_dtype == "bit":
+        pad = torch.zeros(Hkv * G, w, (Tcap + 31) // 32 * 32, dtype=torch.uint8)
+        pad[..., :Tcap] = hit.view(Hkv * G, w, Tcap)
+        words = np.packbits(pad.numpy(), axis=-1, bitorder="little").view(np.int32)
+        st.ring.copy_(torch.from_numpy(words.copy()).view(st.ring.shape))
+    else:
+        st.ring.copy_(torch.where(hit, 2.0 / (tcur - w), 0.25 * thr).view(st.ring.shape))
+    t = torch.full((B,), tcur, dtype=torch.int32, device=DEV)
+    tf = torch.full((B,), tcur - recorded + 1, dtype=torch.int32, device=DEV)
+    st.keep.fill_(7)
+    say("evict_mask rounds", score_dtype, G, w, recorded)
+    corm.corm_evict_mask(st.desc, st.ring, st.lens, st.pos, t, tf, st.keep)
+    torch.cuda.synchronize()
+    for h, l in enumerate(lens):
+        want = np.zeros(l, dtype=bool)
+        for i in range(l):
+            p = int(pos[h, i])
+            want[i] = recorded < w or i >= l - r
+            if p < Tcap:
+                want[i] |= any(hit[h, gg, (tau - 1) % w, p] for tau in range(tcur - recorded + 1, tcur + 1) if p < tau
+                               for gg in range(G))
+        assert np.array_equal(st.keep[0, h, :l].cpu().numpy().astype(bool), want), (score_dtype, G, w, h)
+        assert (st.keep[0, h, l:].cpu() == 7).all()
+
+
 def test_attend_edge_lengths_and_status_flags():
     """decode_attend on lens 0 / 1 / split boundaries, and the device status bits (no faults)."""
     B, Hq, Hkv, d, Lcap, Tcap, w, r = 1, 6, 6, 128, 1100, 1100, 8, 8
