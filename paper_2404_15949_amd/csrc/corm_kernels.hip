@@ -356,9 +356,10 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
   a.scale_log2 = (desc->sm_scale > 0.f ? desc->sm_scale : 1.0f / sqrtf((float)desc->d)) * LOG2E;
   const int units = desc->B * desc->Hkv;
   a.units = units;
-  if ((long long)PREFILL_XCDS * ((units + PREFILL_XCDS - 1) / PREFILL_XCDS) * wl.seed_nkb > 2147483647LL)
-    return CORM_EUNSUPPORTED;
-  const dim3 grid((unsigned)(PREFILL_XCDS * ((units + PREFILL_XCDS - 1) / PREFILL_XCDS) * wl.seed_nkb));
+  const long long key_blocks = (long long)PREFILL_XCDS * ((units + PREFILL_XCDS - 1) / PREFILL_XCDS) * wl.seed_nkb;
+  if (key_blocks > 2147483647LL) return CORM_EUNSUPPORTED;
+  seed_segments(desc, m, key_blocks, &a.nseg, &a.seg_blocks);
+  const dim3 grid((unsigned)(key_blocks * a.nseg));
   const dim3 mgrid(desc->B * desc->Hq, (m + 255) / 256);
   if (a.ring_bits && score_ring) {
     hipLaunchKernelGGL(corm_prefill_clear_bits_kernel, dim3(desc->B * desc->Hq, (m + 15) / 16), dim3(256), 0, s, a);

@@ -340,12 +340,27 @@ int launch_compact(const corm_desc* d, const WorkspaceLayout& wl, void* workspac
   return launch_status();
 }
 
+// How many workgroups share the query blocks of a key block (prompt seeding): one while the key blocks alone
+// fill the chip, else enough for about SEED_WGS workgroups, of at least SEED_MIN_BLOCKS query blocks each (a
+// workgroup loads its keys once, whatever the number of blocks).  16 units x 2000 fp32 keys, 8 blocks of queries:
+// one workgroup per key block 48 + 74 us for the two passes, four 30 + 39 us.
+constexpr int SEED_WGS = 1024, SEED_MIN_BLOCKS = 2;
+void seed_segments(const corm_desc* d, int m, long long key_blocks, int32_t* nseg, int32_t* seg_blocks) {
+  const int qt = (row_bytes(d) <= 256 ? PrefillGeom<256>::QT : PrefillGeom<512>::QT);
+  const int blocks = ((m + 15) / 16 * (d->Hq / d->Hkv) + qt - 1) / qt;
+  const long long want = (SEED_WGS + key_blocks - 1) / key_blocks;
+  const int n = (int)std::max(1LL, std::min(want, (long long)(blocks / SEED_MIN_BLOCKS)));
+  *seg_blocks = (blocks + n - 1) / n;
+  *nseg = (blocks + *seg_blocks - 1) / *seg_blocks;
+}
+
 template <typename DT, int D>
 int launch_prefill_dt(const PrefillArgs& a, dim3 grid, dim3 mgrid, int KB, hipStream_t s) {
   hipLaunchKernelGGL((corm_prefill_stats_kernel<DT, D>), grid, dim3(WG), 0, s, a);
   hipLaunchKernelGGL(corm_prefill_merge_kernel, mgrid, dim3(256), 0, s, a, KB);
-  if (a.ring_bits) hipLaunchKernelGGL((corm_prefill_scores_kernel<DT, D, true>), grid, dim3(WG), 0, s, a);
-  else hipLaunchKernelGGL((corm_prefill_scores_kernel<DT, D, false>), grid, dim3(WG), 0, s, a);
+  if (a.ring_bits) hipLaunchKernelGGL((corm_prefill_scores_kernel<DT, D, SEED_BITS>), grid, dim3(WG), 0, s, a);
+  else if (a.ring_bf16) hipLaunchKernelGGL((corm_prefill_scores_kernel<DT, D, SEED_BF16>), grid, dim3(WG), 0, s, a);
+  else hipLaunchKernelGGL((corm_prefill_scores_kernel<DT, D, SEED_F32>), grid, dim3(WG), 0, s, a);
   return launch_status();
 }
 

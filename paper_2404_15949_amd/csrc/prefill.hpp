@@ -15,13 +15,18 @@ namespace {
 // Key-major decomposition, the same inner loop twice:
 //   pass 1   workgroup = 256 (128) keys of a unit, loops over all query tiles: per query the max and the
 //            sum of exp over its keys -> partials [head, key block, query]
-//   merge    per query: max and 1/sum over the key blocks
+//   merge    per query: max and 1/sum over the key blocks, and what pass 2 compares with
 //   pass 2   same loop; p = exp2(s - max) / sum, stored to the ring row of the query's step at the key's
 //            position, and per key the latest step whose stored score reaches the threshold
-// The workgroup keeps its keys in registers as the A operand (lane l: key l%16 of a 16-key tile, the
+// The workgroup keeps its keys in registers as the A operand (lane l: row l%16 of a 16-key tile, the
 // 16 bytes 64*c + 16*(l/16) .. of each 64-byte chunk c of the row); a tile of 16 queries is the B
 // operand in the same layout, read from LDS, where the workgroup stages the queries in double-buffered
-// blocks.  D: lane l holds query l%16, keys 4*(l/16) .. +3 of the tile.
+// blocks.  D: lane l holds query l%16 and rows 4*(l/16) .. +3 of each key tile.
+//
+// Query tiles are walked in the order (16 queries, head of the group): tile tt = (queries 16*(tt/G) .., head
+// tt%G).  The step of a lane's query never falls from one tile to the next, so one register per key holds its
+// latest hit over all heads.  A launch with few units deals the tiles of a key block to several workgroups
+// (segments); their last_hit then meet in an atomic max.
 
 constexpr int PREFILL_XCDS = 8;   // accelerator dies of the device
 
@@ -34,10 +39,11 @@ struct PrefillArgs {
   const int32_t* t;
   void* ring;
   float2* part;    // [B*Hq, nkb, w]  (max, sum) per key block
-  float4* stats;   // [B*Hq, w]       (max, 1/sum, threshold of the query's step, unused)
+  float4* stats;   // [B*Hq, w]       per query: see prefill_query_stats
   int32_t* status;
   int32_t Hq, Hkv, Lcap, Tcap, w, m, nkb, ring_bf16;
   int32_t units;                   // B * Hkv
+  int32_t nseg, seg_blocks;        // workgroups that share the query blocks of a key block, blocks each
   int32_t ring_bits, ring_words;   // boolean message: one bit per (row, position), words per row
   float thr_scale, scale_log2;
 };
@@ -68,16 +74,60 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// the score of a raw logit: the one formula every ring type starts from
+__device__ __forceinline__ float prefill_score(float d, float scale_log2, float ms, float inv) {
+  return fast_exp2(fmaf(d, scale_log2, -ms)) * inv;
+}
+
+// (x << 1) | this lane's bit of the mask, in one instruction
+__device__ __forceinline__ uint32_t shift_in(uint32_t x, unsigned long long mask) {
+  unsigned long long carry_out;
+  asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(x), "=s"(carry_out) : "s"(mask));
+  return x;
+}
+
+// What the ring holds: which form of Def. 3.1 pass 2 evaluates (an instance each).
+enum { SEED_BF16 = 0, SEED_F32 = 1, SEED_BITS = 2 };
+
+// Per query, for pass 2: x = max, y = 1/sum and, so that pass 2 neither unpacks what it stores nor forms scores
+// that it does not store,
+//   score rings   z = the smallest fp32 score whose stored value reaches thr.  bf16: rounding to nearest even is
+//                 monotone, so "stored >= thr" is "score >= z" with z the midpoint below the smallest bf16 >= thr
+//                 (or the next fp32, where that midpoint rounds down).  fp32: z = thr.
+//   boolean ring  [z, w): raw logits at or above w are important, those below z are not, and only those between
+//                 need the score itself.  The band is the threshold in the logit domain -+ a bound on every
+//                 rounding between a logit and its score (products, fma, exp2, 1/sum, the logarithms here: together
+//                 below 2e-6 of the terms), so the decisions are bit for bit those of the score.
+__device__ __forceinline__ float4 prefill_query_stats(const PrefillArgs& a, float ms, float z, float thr) {
+  float4 s = make_float4(ms, z > 0.f ? 1.0f / z : 0.f, thr, 0.f);
+  if (a.ring_bits) {
+    const float lt = log2f(thr), lz = log2f(z);
+    const float at = ms + lt + lz, pad = 1e-5f + 2e-6f * (fabsf(ms) + fabsf(lt) + fabsf(lz));
+    s.z = (at - pad) / a.scale_log2;
+    s.w = (at + pad) / a.scale_log2;
+    // thresholds 0, infinite or near the end of the fp32 range: decide by the score throughout
+    if (!(lt + lz > -100.f) || !(fabsf(s.z) < 1e30f) || !(fabsf(s.w) < 1e30f)) {
+      s.z = neg_inf();
+      s.w = -neg_inf();
+    }
+  } else if (a.ring_bf16) {
+    const uint32_t up = (__float_as_uint(thr) + 0xffffu) >> 16;   // the smallest bf16 >= thr (thr >= 0)
+    s.z = up ? __uint_as_float(((up - 1u) << 16) + 0x8000u + (up & 1u)) : 0.f;
+  }
+  return s;
+}
+
 // Pass 1 on one wave tile (16 queries x 16*T keys): per query, max of the scaled logits and the sum of
-// exp2 relative to it, over the keys the query sees.  MASKED = false when every query sees every key.
+// exp2 relative to it, over the keys the query sees.  seen: bit 4*tl + r of this lane (MASKED only).
 template <bool MASKED, int T>
-__device__ __forceinline__ void prefill_stats_tile(const f32x4_t (&d)[T], const int (&kp)[T][4], int vis,
-                                                   float scale_log2, float& mx_out, float& z_out) {
+__device__ __forceinline__ void prefill_stats_tile(const f32x4_t (&d)[T], uint32_t seen, float scale_log2,
+                                                   float& mx_out, float& z_out) {
   float mx = neg_inf();   // of the raw logits: the scale is positive and keeps their order
 #pragma unroll
   for (int tl = 0; tl < T; ++tl)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) mx = fmaxf(mx, (!MASKED || kp[tl][r] <= vis) ? d[tl][r] : neg_inf());
+    for (int r = 0; r < 4; ++r)
+      mx = fmaxf(mx, (!MASKED || ((seen >> (4 * tl + r)) & 1u)) ? d[tl][r] : neg_inf());
   mx = rows_allreduce_max(mx);
   const float ms = mx == neg_inf() ? 0.f : mx * scale_log2;
   float z = 0.f;
@@ -86,69 +136,51 @@ __device__ __forceinline__ void prefill_stats_tile(const f32x4_t (&d)[T], const 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float e = fast_exp2(fmaf(d[tl][r], scale_log2, -ms));
-      z += (!MASKED || kp[tl][r] <= vis) ? e : 0.f;
+      z += (!MASKED || ((seen >> (4 * tl + r)) & 1u)) ? e : 0.f;
     }
   z = rows_allreduce_sum(z);
   mx_out = mx == neg_inf() ? mx : ms;
   z_out = z;
 }
 
-// Pass 2 on one wave tile, bf16 ring: the stored scores (packed) and, per key, the step of this query
-// where its stored score reaches the threshold.  st = (max, 1/sum) of this lane's query.
-template <bool MASKED, int T>
-__device__ __forceinline__ void prefill_scores_bf16(const f32x4_t (&d)[T], const int (&kp)[T][4], int vis,
-                                                    float scale_log2, float4 st, float thr, int tau,
-                                                    uint32_t (&pk)[T][2], int (&hmg)[T][4]) {
-#pragma unroll
-  for (int tl = 0; tl < T; ++tl) {
-    float pv[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float e = fast_exp2(fmaf(d[tl][r], scale_log2, -st.x)) * st.y;
-      pv[r] = (!MASKED || kp[tl][r] <= vis) ? e : 0.f;
-    }
-    pk[tl][0] = pack_bf16x2(pv[0], pv[1]);
-    pk[tl][1] = pack_bf16x2(pv[2], pv[3]);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint32_t w = pk[tl][r >> 1];
-      const float stored = __uint_as_float((r & 1) ? (w & 0xffff0000u) : (w << 16));
-      const bool hit = stored >= thr && (!MASKED || kp[tl][r] <= vis);
-      hmg[tl][r] = hit ? tau : hmg[tl][r];
-    }
-  }
-}
-
-constexpr int PREFILL_SEG = 512;   // queries whose pass-1 partials a workgroup holds in LDS at a time
-
 template <int ROWB>
 struct PrefillGeom {
   static constexpr int NCH = ROWB / 64;            // 64-byte chunks of a row
   static constexpr int T = NCH <= 4 ? 4 : 2;       // 16-key tiles per wave
-  static constexpr int KB = WAVES * T * 16;        // keys per workgroup
+  static constexpr int WKEYS = T * 16;             // keys per wave
+  static constexpr int KB = WAVES * WKEYS;         // keys per workgroup
   static constexpr int QBLK = ROWB <= 256 ? 64 : 32;   // queries staged in LDS at a time
+  static constexpr int QT = QBLK / 16;             // query tiles of a block
+  static constexpr int FLUSH = 512 / QBLK;         // blocks whose pass-1 partials a workgroup holds in LDS at a time
   static constexpr int QROW = ROWB + 16;           // LDS row pitch (padded against bank conflicts)
   static constexpr int QLOADS = QBLK * ROWB / (WG * 16);   // 16-byte loads per thread and block
   static_assert(QBLK * ROWB % (WG * 16) == 0 && QBLK <= WG, "a block is loaded in whole passes of the workgroup");
 };
 
-template <typename DT, int D, int PASS, bool BITS>
+template <typename DT, int D, int PASS, int MODE>
 __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
   constexpr int ROWB = D * DT::ESZ;
   using Geo = PrefillGeom<ROWB>;
-  constexpr int NCH = Geo::NCH, T = Geo::T, KB = Geo::KB;
+  constexpr int NCH = Geo::NCH, T = Geo::T, KB = Geo::KB, WKEYS = Geo::WKEYS, QT = Geo::QT;
+  constexpr int QBLK = Geo::QBLK, QROW = Geo::QROW, QLOADS = Geo::QLOADS, FLUSH = Geo::FLUSH;
   constexpr int NEVER = 0x7fffffff;   // position of a slot that holds no key: visible to no query
+  // Which key of the wave sits in row 4*lg + r of key tile tl: where a lane's 4*T values leave as bf16 or as bits,
+  // 4*T consecutive keys (they pack into whole words of the lane); fp32 scores leave per key tile, 64
+  // consecutive bytes per query.
+  constexpr bool RUN = PASS == 2 && MODE != SEED_F32;
 
-  // One-dimensional grid of 8 * ceil(units / 8) * nkb workgroups.  Workgroups are dealt round-robin to the 8
+  // One-dimensional grid of 8 * ceil(units / 8) * nkb * nseg workgroups.  Workgroups are dealt round-robin to the 8
   // XCDs, so id % 8 names the XCD; each XCD takes a contiguous range of units and runs the key blocks of a unit
   // one after the other: they all read the same tail queries, which then stay in that XCD's L2.
   const int per_xcd = (a.units + PREFILL_XCDS - 1) / PREFILL_XCDS;
   const int li = (int)(blockIdx.x / PREFILL_XCDS);
-  const int unit = (int)(blockIdx.x % PREFILL_XCDS) * per_xcd + li / a.nkb;
-  const int kb = li % a.nkb;
-  if (li / a.nkb >= per_xcd || unit >= a.units) return;
+  const int seg = li % a.nseg, lk = li / a.nseg;
+  const int unit = (int)(blockIdx.x % PREFILL_XCDS) * per_xcd + lk / a.nkb;
+  const int kb = lk % a.nkb;
+  if (lk / a.nkb >= per_xcd || unit >= a.units) return;
   const int b = unit / a.Hkv, hkv = unit - b * a.Hkv;
   const int G = a.Hq / a.Hkv;
+  const int lgG = 31 - __clz(G);   // G is a power of two
   int L = a.lens[unit];
   L = L < 0 ? 0 : (L > a.Lcap ? a.Lcap : L);
   const int key_blk = kb * KB;
@@ -163,288 +195,404 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
   }
   const int s0 = (tau0 - 1) % a.w;   // ring slot of tail query 0
 
+  __shared__ __attribute__((aligned(16))) char sh_q[2][QBLK * QROW];     // query blocks, double buffered
+  __shared__ __attribute__((aligned(16))) float4 sh_st[2][PASS == 2 ? QBLK : 1];   // prefill_query_stats per query
+  __shared__ __attribute__((aligned(16))) int32_t sh_pos[KB];            // positions of the workgroup's keys
+  __shared__ float2 sh_part[PASS == 1 ? WAVES : 1][PASS == 1 ? FLUSH * QBLK : 1];
+  // Pass 2, bf16 ring: a wave's tile of stored scores is turned through LDS so that every query's consecutive
+  // positions leave as one piece of its ring row (16 bytes per lane).  Rows are padded by 16 bytes.
+  constexpr int TROW = WKEYS + 8;
+  constexpr bool TURN = PASS == 2 && MODE == SEED_BF16;
+  __shared__ __attribute__((aligned(16))) uint16_t sh_t[TURN ? WAVES : 1][TURN ? 16 : 1][TURN ? TROW : 1];
+
   const char* Kb = reinterpret_cast<const char*>(a.K) + (size_t)unit * a.Lcap * ROWB;
   const int32_t* posb = a.pos + (size_t)unit * a.Lcap;
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(Kb, (uint32_t)L * ROWB);
-  const int wkey0 = key_blk + wv * (T * 16);   // first key of this wave
+  const int wkey0 = key_blk + wv * WKEYS;   // first key of this wave
 
   uint4 ka[T][NCH];
-  int kp[T][4];      // positions of this lane's keys 4*lg .. 4*lg+3 of each tile
-  bool quad[T];      // the four are consecutive positions: one vector store per query
 #pragma unroll
   for (int tl = 0; tl < T; ++tl) {
+    const int row = wkey0 + (RUN ? (n >> 2) * (4 * T) + tl * 4 + (n & 3) : tl * 16 + n);
 #pragma unroll
-    for (int c = 0; c < NCH; ++c)
-      ka[tl][c] = buffer_load16(rk, (uint32_t)(wkey0 + tl * 16 + n) * ROWB + (uint32_t)(c * 64 + 16 * lg));
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int key = wkey0 + tl * 16 + 4 * lg + r;
-      int pk = key < L ? posb[key] : NEVER;
-      if (key < L && (pk < 0 || pk >= a.Tcap)) {
-        if (a.status) atomicOr(a.status, CORM_DEV_BAD_STEP);
-        pk = NEVER;
-      }
-      kp[tl][r] = pk;
-    }
-    quad[tl] = kp[tl][3] != NEVER && kp[tl][1] == kp[tl][0] + 1 && kp[tl][2] == kp[tl][0] + 2 &&
-               kp[tl][3] == kp[tl][0] + 3;
+    for (int c = 0; c < NCH; ++c) ka[tl][c] = buffer_load16(rk, (uint32_t)row * ROWB + (uint32_t)(c * 64 + 16 * lg));
   }
+  int my_pos = NEVER;   // of key wkey0 + lane
+  if (lane < WKEYS && wkey0 + lane < L) {
+    my_pos = posb[wkey0 + lane];
+    if (my_pos < 0 || my_pos >= a.Tcap) {
+      if (a.status) atomicOr(a.status, CORM_DEV_BAD_STEP);
+      my_pos = NEVER;
+    }
+  }
+  if (lane < WKEYS) sh_pos[wv * WKEYS + lane] = my_pos;
+  // every slot of the wave holds a key; its positions are consecutive; the first and the last of them
+  const bool wave_whole = __all(lane >= WKEYS || my_pos != NEVER);
+  const int pos_w0 = __builtin_amdgcn_readfirstlane(my_pos), pos_wlast = __shfl(my_pos, WKEYS - 1);
+  const bool wave_run = wave_whole && __all(lane >= WKEYS || my_pos == pos_w0 + lane);
+  // Pass 2 stores whole pieces of a row where the wave's keys are consecutive and every piece is aligned (rows of
+  // the ring then start at multiples of a piece as well).
+  const bool rows_ok = a.ring == nullptr ||
+                       (wave_run && (MODE == SEED_BF16  ? ((pos_w0 | a.Tcap) & 7) == 0
+                                     : MODE == SEED_F32 ? ((pos_w0 | a.Tcap) & 3) == 0
+                                                        : WKEYS % 32 == 0 && (pos_w0 & 31) == 0));
+  const int pos_wmax = wave_whole ? pos_wlast : NEVER;
   // Positions ascend with the slot, so queries before the one that sees the block's first key see none of it.
   const int pfirst = posb[key_blk];
   const int jt_first = max(pfirst - tau0 + 1, 0) / 16;
 
-  constexpr int QBLK = Geo::QBLK, QROW = Geo::QROW, QLOADS = Geo::QLOADS;
-  __shared__ float2 sh_part[PASS == 1 ? WAVES : 1][PASS == 1 ? PREFILL_SEG : 1];
-  __shared__ __attribute__((aligned(16))) char sh_q[2][QBLK * QROW];     // query blocks, double buffered
-  __shared__ __attribute__((aligned(16))) float4 sh_st[2][PASS == 2 ? QBLK : 1];   // (max, 1/sum, threshold, -) per query
-  // Pass 2, bf16 ring: a wave's 16 x 64 tile of stored scores is turned through LDS so that every query's
-  // 64 consecutive positions leave as one 128-byte piece of its ring row (16 bytes per lane) instead of
-  // sixteen 8-byte pieces.  Rows are padded to 144 bytes.
-  constexpr int TROW = 72;
-  __shared__ __attribute__((aligned(16))) uint16_t sh_t[PASS == 2 ? WAVES : 1][PASS == 2 ? 16 : 1][TROW];
-  // ... possible when the wave's 64 slots hold consecutive positions starting at a multiple of 8 (and rows
-  // of the ring start at multiples of 8 elements), for query tiles that see all of them
-  bool wave_rows = false, wave_bitrows = false;
-  // every slot of the wave holds a key (then pos_wlast is the largest position among them)
-  const bool wave_whole = wkey0 + T * 16 <= L;
-  const int pos_w0 = __shfl(kp[0][0], 0);
-  const int pos_wlast = __shfl(kp[T - 1][3], 63);
-  if (PASS == 2 && T == 4) {
-    bool ok = true;
+  const int ntt = ((a.m + 15) / 16) << lgG;                    // query tiles of the group
+  const int blk_end = min((seg + 1) * a.seg_blocks, (ntt + QT - 1) / QT);
+  const int blk_vis = min((jt_first << lgG) / QT, blk_end);    // first block with a query that sees a key
+  const int blk_seg = seg * a.seg_blocks;                      // first block of this workgroup
+  const int blk_beg = max(blk_seg, blk_vis);
+  const char* qg = reinterpret_cast<const char*>(a.q_tail) + (size_t)(b * a.Hq + hkv * G) * a.m * ROWB;
+  const float4* stats = a.stats + (size_t)(b * a.Hq + hkv * G) * a.w;
+
+  // Queries reach the waves through LDS, QBLK at a time: the block after the current one is in flight
+  // (registers) while the current one is worked on, so the loop never waits on a load it has just
+  // issued.  Two LDS buffers, one barrier per block.  Loads and stores share one in-order counter: the registers
+  // go to LDS at the end of each of the two paths through a block, where the number of ring stores issued
+  // behind the loads is known to the compiler -- after the join it would have to wait for all of them.
+  u32x4_t qr[QLOADS];
+  float4 str = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto fetch = [&](int blk, u32x4_t (&qr)[QLOADS], float4& str) __attribute__((always_inline)) {
+    constexpr int RPP = WG * 16 / ROWB;   // rows per pass of the workgroup
+    const int half = __builtin_amdgcn_readfirstlane(tid >> 7);
 #pragma unroll
-    for (int tl = 0; tl < T; ++tl) ok = ok && quad[tl] && kp[tl][0] == pos_w0 + tl * 16 + 4 * lg;
-    wave_rows = __all(ok) && a.ring_bf16 && (pos_w0 & 7) == 0 && (a.Tcap & 7) == 0;
-    // boolean message: the wave's 64 consecutive positions are exactly two words of a row
-    wave_bitrows = BITS && __all(ok) && (pos_w0 & 31) == 0;
-  }
+    for (int i = 0; i < QLOADS; ++i) {
+      const int tt = min(blk * QT + (i * RPP) / 16 + (RPP == 32 ? half : 0), ntt - 1);   // (uniform over the wave)
+      const int j = min((tt >> lgG) * 16 + ((i * RPP + tid / (ROWB / 16)) & 15), a.m - 1);   // (past the last: masked)
+      const char* q = qg + (size_t)(tt & (G - 1)) * a.m * ROWB;
+      qr[i] = *reinterpret_cast<const u32x4_t*>(q + (uint32_t)j * ROWB + (tid * 16) % ROWB);
+    }
+    if (PASS == 2) {   // (every wave the same QBLK queries: no branch, whose join would cost the exact wait count)
+      const int tt = min(blk * QT + (tid % QBLK) / 16, ntt - 1);
+      const int j = min((tt >> lgG) * 16 + (tid & 15), a.m - 1);
+      str = stats[(size_t)(tt & (G - 1)) * a.w + j];
+    }
+  };
+  auto mma_tile = [&](int cur, int ti, f32x4_t (&d)[T]) __attribute__((always_inline)) {
+    uint4 qb[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      qb[c] = *reinterpret_cast<const uint4*>(&sh_q[cur][(ti * 16 + n) * QROW + c * 64 + 16 * lg]);
+#pragma unroll
+    for (int tl = 0; tl < T; ++tl) d[tl] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int tl = 0; tl < T; ++tl) d[tl] = PrefillMma<DT>::mma(ka[tl][c], qb[c], d[tl]);
+  };
+  // Fast blocks store through a buffer descriptor of one head's ring: 32-bit offsets, and without a ring a
+  // descriptor of length 0, which drops the stores (no branch around them).
+  const uint64_t head_bytes = (uint64_t)a.w * (MODE == SEED_BITS ? (uint64_t)a.ring_words * 4 : (uint64_t)a.Tcap * (MODE == SEED_BF16 ? 2 : 4));
+  const uint32_t row_bytes = (uint32_t)(head_bytes / a.w);
+  const bool offsets32 = head_bytes < (1ull << 31);
+  auto head_ring = [&](int g) __attribute__((always_inline)) {
+    char* p = reinterpret_cast<char*>(a.ring);
+    return make_rsrc(p ? p + (uint64_t)(b * a.Hq + hkv * G + g) * head_bytes : p, a.ring ? (uint32_t)head_bytes : 0u);
+  };
+  // ring slot of query j; row of the ring that query j of head g is recorded in
+  auto slot_of = [&](int j) __attribute__((always_inline)) -> uint32_t {
+    const int slot = s0 + j;
+    return (uint32_t)(slot >= a.w ? slot - a.w : slot);
+  };
+  auto ring_row = [&](int g, int j) __attribute__((always_inline)) -> size_t {
+    return (size_t)(b * a.Hq + hkv * G + g) * a.w + slot_of(j);
+  };
+
   int hm[T][4];   // pass 2: latest step at which one of the group's queries found the key important
 #pragma unroll
   for (int tl = 0; tl < T; ++tl)
 #pragma unroll
     for (int r = 0; r < 4; ++r) hm[tl][r] = 0;
 
-  for (int g = 0; g < G; ++g) {
-    const int head = b * a.Hq + hkv * G + g;
-    int hmg[T][4];   // the same for this head alone (its steps ascend, so the last hit is the latest)
+  auto stage = [&](int buf, const u32x4_t (&qr)[QLOADS], const float4& str) __attribute__((always_inline)) {
 #pragma unroll
-    for (int tl = 0; tl < T; ++tl)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) hmg[tl][r] = 0;
-    const char* qh = reinterpret_cast<const char*>(a.q_tail) + (size_t)head * a.m * ROWB;
-    const __amdgpu_buffer_rsrc_t rq = make_rsrc(qh, (uint32_t)a.m * ROWB);
-    const float4* stats = a.stats + (size_t)head * a.w;
+    for (int i = 0; i < QLOADS; ++i) {
+      const int o = (i * WG + tid) * 16;   // row o / ROWB, column o % ROWB
+      *reinterpret_cast<u32x4_t*>(&sh_q[buf][(o / ROWB) * QROW + (o % ROWB)]) = qr[i];
+    }
+    if (PASS == 2) sh_st[buf][tid % QBLK] = str;
+  };
+  if (blk_beg < blk_end) {
+    fetch(blk_beg, qr, str);
+    stage(blk_beg & 1, qr, str);
+  }
+  // pass 1 empties its partials every FLUSH blocks; pass 2 has one stretch
+  for (int grp = PASS == 1 ? blk_seg : blk_beg; grp < blk_end; grp += PASS == 1 ? FLUSH : blk_end) {
+    const int grp_end = PASS == 1 ? min(grp + FLUSH, blk_end) : blk_end;
+    if (PASS == 1) {
+      for (int i = tid; i < WAVES * FLUSH * QBLK; i += WG) (&sh_part[0][0])[i] = make_float2(neg_inf(), 0.f);
+    }
+    for (int blk = max(grp, blk_beg); blk < grp_end; ++blk) {
+      const int cur = blk & 1;
+      __syncthreads();   // block blk is staged; nobody reads the other buffer any more
+      fetch(min(blk + 1, blk_end - 1), qr, str);
+      const int tt0 = blk * QT;
 
-    for (int seg0 = 0; seg0 < a.m; seg0 += PREFILL_SEG) {
-      const int seg1 = min(seg0 + PREFILL_SEG, a.m);
-      if (PASS == 1) {
-        for (int i = tid; i < WAVES * PREFILL_SEG; i += WG) (&sh_part[0][0])[i] = make_float2(neg_inf(), 0.f);
-        __syncthreads();
-      }
-      // Queries reach the waves through LDS, QBLK at a time: the block after the current one is in flight
-      // (registers) while the current one is worked on, so the loop never waits on a load it has just
-      // issued -- nor, with it, on the acknowledgement of the ring stores of the tile before (loads and
-      // stores share one in-order counter).  Two LDS buffers, one barrier per block.
-      const int blk_first = max(jt_first * 16, seg0) / QBLK * QBLK;
-      uint4 qr[QLOADS];
-      float4 str = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (blk_first < seg1) {
+      // (uniform over the wave) every query of the block exists and sees every key of the wave, and pass 2 can
+      // store whole pieces: straight-line code, the next tile's MFMAs under this tile's tail
+      const bool fast = tt0 + QT <= ntt && ((tt0 + QT - 1) >> lgG) * 16 + 15 < a.m &&
+                        pos_wmax <= tau0 + (tt0 >> lgG) * 16 - 1 && (PASS == 1 || (rows_ok && offsets32));
+      if (fast) {
+        f32x4_t dn[T];
+        mma_tile(cur, 0, dn);
 #pragma unroll
-        for (int i = 0; i < QLOADS; ++i)   // (past the last query the descriptor's range check returns zeros)
-          qr[i] = buffer_load16(rq, (uint32_t)blk_first * ROWB + (uint32_t)((i * WG + tid) * 16));
-        if (PASS == 2 && tid < QBLK && blk_first + tid < a.m) str = stats[blk_first + tid];
-      }
-      __syncthreads();   // the last block of the previous head / segment has been read by every wave
-      for (int blk = blk_first; blk < seg1; blk += QBLK) {
-        const int cur = (blk / QBLK) & 1;
+        for (int ti = 0; ti < QT; ++ti) {
+          f32x4_t d[T];
 #pragma unroll
-        for (int i = 0; i < QLOADS; ++i) {
-          const int o = (i * WG + tid) * 16;   // byte offset inside the block: row o / ROWB, column o % ROWB
-          *reinterpret_cast<uint4*>(&sh_q[cur][(o / ROWB) * QROW + (o % ROWB)]) = qr[i];
-        }
-        if (PASS == 2 && tid < QBLK) sh_st[cur][tid] = str;
-        __syncthreads();
-        if (blk + QBLK < seg1) {
-#pragma unroll
-          for (int i = 0; i < QLOADS; ++i)
-            qr[i] = buffer_load16(rq, (uint32_t)(blk + QBLK) * ROWB + (uint32_t)((i * WG + tid) * 16));
-          str = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (PASS == 2 && tid < QBLK && blk + QBLK + tid < a.m) str = stats[blk + QBLK + tid];
-        }
-#pragma unroll
-       for (int ti = 0; ti < QBLK / 16; ++ti) {   // unrolled: the next tile's MFMAs can start under this tile's tail
-        const int jt = blk / 16 + ti;
-        if (jt < jt_first || jt * 16 >= seg1) continue;   // (uniform) no key of this workgroup is visible / past the end
-        uint4 qb[NCH];
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-          qb[c] = *reinterpret_cast<const uint4*>(&sh_q[cur][(jt * 16 - blk + n) * QROW + c * 64 + 16 * lg]);
-        float4 st = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (PASS == 2) st = sh_st[cur][jt * 16 - blk + n];
-
-        f32x4_t d[T];
-#pragma unroll
-        for (int tl = 0; tl < T; ++tl) {
-          d[tl] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) d[tl] = PrefillMma<DT>::mma(ka[tl][c], qb[c], d[tl]);
-        }
-        const int j = jt * 16 + n;                 // this lane's query
-        const int tau = tau0 + j;
-        const int vis = j < a.m ? tau - 1 : -1;   // the query sees positions <= vis
-        // (uniform over the wave) every query of the tile exists and sees every key of the wave: no masking
-        const bool all_seen = wave_whole && jt * 16 + 15 < a.m && pos_wlast <= tau0 + jt * 16 - 1;
-
-        if (PASS == 1) {
-          float mx, z;
-          if (all_seen) prefill_stats_tile<false, T>(d, kp, vis, a.scale_log2, mx, z);
-          else prefill_stats_tile<true, T>(d, kp, vis, a.scale_log2, mx, z);
-          if (lg == 0 && j < seg1) sh_part[wv][j - seg0] = make_float2(mx, z);
-        } else {
-          const float thr = st.z;
-          int slot = s0 + j;
-          if (slot >= a.w) slot -= a.w;
-          const size_t rowbase = ((size_t)head * a.w + (size_t)(j < a.m ? slot : 0)) * a.Tcap;
-          const bool rows_now = wave_rows && all_seen;
-          if (BITS) {
-            // boolean message: the fp32 score itself is compared; bit tl*16 + 4*lg + r of the wave's 64 positions
+          for (int tl = 0; tl < T; ++tl) d[tl] = dn[tl];
+          if (ti + 1 < QT) mma_tile(cur, ti + 1, dn);
+          const int tt = tt0 + ti, g = tt & (G - 1), j = (tt >> lgG) * 16 + n, tau = tau0 + j;
+          if (PASS == 1) {
+            float mx, z;
+            prefill_stats_tile<false, T>(d, 0u, a.scale_log2, mx, z);
+            if (lg == 0) sh_part[wv][(blk - grp) * QBLK + ti * 16 + n] = make_float2(mx, z);
+          } else if (MODE == SEED_BITS) {
+            const float4 st = sh_st[cur][ti * 16 + n];
+            unsigned long long unsure = 0ull;
             uint32_t hbits = 0u;
+#pragma unroll
+            for (int i = 4 * T - 1; i >= 0; --i) {   // key i of the lane's run: row i % 4 of key tile i / 4
+              const float x = d[i >> 2][i & 3];
+              const bool hit = x >= st.w;
+              const unsigned long long hits = __ballot(hit);
+              hm[i >> 2][i & 3] = hit ? tau : hm[i >> 2][i & 3];
+              hbits = shift_in(hbits, hits);
+              unsure |= __ballot(x >= st.z) ^ hits;
+            }
+            if (unsure) {   // (uniform, rare) what lies in the band is decided by the score; the rest stays
+              const float thr = importance_threshold(a.thr_scale, tau);
+#pragma unroll 1
+              for (int tl = 0; tl < T; ++tl) {
+                const f32x4_t x = tl == 0 ? d[0] : tl == 1 ? d[1] : tl == 2 ? d[T > 2 ? 2 : 0] : d[T > 2 ? 3 : 0];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                  hbits |= (prefill_score(x[r], a.scale_log2, st.x, st.y) >= thr ? 1u : 0u) << (4 * tl + r);
+              }
+#pragma unroll
+              for (int i = 0; i < 4 * T; ++i) hm[i >> 2][i & 3] = (hbits >> i) & 1u ? tau : hm[i >> 2][i & 3];
+            }
+            // the wave owns whole words of every query's row: plain stores
+            const __amdgpu_buffer_rsrc_t rr = head_ring(g);
+            const uint32_t at = slot_of(j) * row_bytes + (uint32_t)(pos_w0 >> 5) * 4;
+            if (T == 4) {   // 16 keys per lane: two lane groups to a word
+              const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
+              __builtin_amdgcn_raw_buffer_store_b32(sw[0] | (sw[1] << 16), rr, (lg & 1) ? DEAD_OFFSET : at + (lg >> 1) * 4, 0, 0);
+            } else {        // 8 keys per lane: four lane groups to a word
+              const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
+              __builtin_amdgcn_raw_buffer_store_b32(w, rr, lg ? DEAD_OFFSET : at, 0, 0);
+            }
+          } else {
+            const float4 st = sh_st[cur][ti * 16 + n];
+            float pv[T][4];
 #pragma unroll
             for (int tl = 0; tl < T; ++tl)
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
-                const float e = fast_exp2(fmaf(d[tl][r], a.scale_log2, -st.x)) * st.y;
-                const bool hit = kp[tl][r] <= vis && e >= thr;
-                hmg[tl][r] = hit ? tau : hmg[tl][r];
-                hbits |= (uint32_t)hit << (tl * 4 + r);
+                pv[tl][r] = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
+                hm[tl][r] = pv[tl][r] >= st.z ? tau : hm[tl][r];
+                // (said to be read here: left alone, the compiler keeps the compares of all tiles of the block in
+                // scalar registers, spills those, and selects at the end)
+                asm volatile("" : "+v"(hm[tl][r]));
               }
-            if (a.ring) {
-              uint32_t* roww = reinterpret_cast<uint32_t*>(a.ring) +
-                               ((size_t)head * a.w + (size_t)(j < a.m ? slot : 0)) * a.ring_words;
-              if (wave_bitrows) {   // (uniform) the wave owns two whole words of every query's row: plain stores
-                uint32_t w0 = (((hbits >> 0) & 0xfu) << (4 * lg)) | (((hbits >> 4) & 0xfu) << (16 + 4 * lg));
-                uint32_t w1 = 0u;
-                if (T == 4) w1 = (((hbits >> 8) & 0xfu) << (4 * lg)) | (((hbits >> 12) & 0xfu) << (16 + 4 * lg));
-                w0 = rows_allreduce_or(w0);
-                w1 = rows_allreduce_or(w1);
-                if (j < a.m && lg < 2) roww[(pos_w0 >> 5) + lg] = lg == 0 ? w0 : w1;
-              } else {              // rows were cleared by the launch before: set single bits
-#pragma unroll
-                for (int tl = 0; tl < T; ++tl)
-#pragma unroll
-                  for (int r = 0; r < 4; ++r)
-                    if ((hbits >> (tl * 4 + r)) & 1u) atomicOr(&roww[kp[tl][r] >> 5], 1u << (kp[tl][r] & 31));
-              }
-            }
-          } else if (a.ring_bf16) {
-            uint32_t pk[T][2];   // stored scores, two bf16 per word
-            if (all_seen) prefill_scores_bf16<false, T>(d, kp, vis, a.scale_log2, st, thr, tau, pk, hmg);
-            else prefill_scores_bf16<true, T>(d, kp, vis, a.scale_log2, st, thr, tau, pk, hmg);
-            uint16_t* row = reinterpret_cast<uint16_t*>(a.ring) + rowbase;
-            if (!a.ring) {
-              // summary-only state: nothing is recorded but last_hit
-            } else if (rows_now) {
-#pragma unroll
-              for (int tl = 0; tl < T; ++tl)
-                *reinterpret_cast<uint2*>(&sh_t[wv][n][tl * 16 + 4 * lg]) = make_uint2(pk[tl][0], pk[tl][1]);
-              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
-#pragma unroll
-              for (int hh = 0; hh < 2; ++hh) {
-                const int qi = hh * 8 + (lane >> 3), ch = lane & 7;   // query of the tile, 16-byte piece of its row
-                const uint4 v = *reinterpret_cast<const uint4*>(&sh_t[wv][qi][ch * 8]);
-                int sl = s0 + jt * 16 + qi;
-                if (sl >= a.w) sl -= a.w;
-                uint16_t* dst =
-                    reinterpret_cast<uint16_t*>(a.ring) + ((size_t)head * a.w + sl) * a.Tcap + pos_w0 + ch * 8;
-                __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t*>(dst));
-              }
-              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            } else {
+            const __amdgpu_buffer_rsrc_t rr = head_ring(g);
+            if (MODE == SEED_F32) {
+              const uint32_t at = slot_of(j) * row_bytes + (uint32_t)(pos_w0 + 4 * lg) * 4;
 #pragma unroll
               for (int tl = 0; tl < T; ++tl) {
-                if (quad[tl] && kp[tl][3] <= vis && ((rowbase + (size_t)kp[tl][0]) & 3) == 0) {
-                  *reinterpret_cast<uint2*>(row + kp[tl][0]) = make_uint2(pk[tl][0], pk[tl][1]);
-                } else {
-#pragma unroll
-                  for (int r = 0; r < 4; ++r)
-                    if (kp[tl][r] <= vis) row[kp[tl][r]] = (uint16_t)(pk[tl][r >> 1] >> (16 * (r & 1)));
-                }
+                const u32x4_t v = {__float_as_uint(pv[tl][0]), __float_as_uint(pv[tl][1]), __float_as_uint(pv[tl][2]),
+                                   __float_as_uint(pv[tl][3])};
+                __builtin_amdgcn_raw_buffer_store_b128(v, rr, at + tl * 64, 0, 0);
               }
+            } else {
+              constexpr int PIECES = WKEYS / 8;        // 16-byte pieces of a query's row
+              constexpr int RPS = 64 / PIECES;         // rows per store of the wave
+              uint32_t pk[2 * T];
+#pragma unroll
+              for (int i = 0; i < 2 * T; ++i) pk[i] = pack_bf16x2(pv[i >> 1][2 * (i & 1)], pv[i >> 1][2 * (i & 1) + 1]);
+#pragma unroll
+              for (int h = 0; h < T / 2; ++h)
+                *reinterpret_cast<uint4*>(&sh_t[wv][n][lg * (4 * T) + h * 8]) =
+                    make_uint4(pk[4 * h], pk[4 * h + 1], pk[4 * h + 2], pk[4 * h + 3]);
+              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
+#pragma unroll
+              for (int h = 0; h < 16 / RPS; ++h) {
+                const int qi = h * RPS + lane / PIECES, ch = lane % PIECES;
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(&sh_t[wv][qi][ch * 8]);
+                __builtin_amdgcn_raw_buffer_store_b128(
+                    v, rr, slot_of((tt >> lgG) * 16 + qi) * row_bytes + (uint32_t)(pos_w0 + ch * 8) * 2, 0, 2);
+              }
+              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
-          } else {
-            float* row = reinterpret_cast<float*>(a.ring) + rowbase;
+          }
+        }
+        stage(cur ^ 1, qr, str);
+        asm volatile("; (keeps the two paths' staging from being merged behind the join)");
+        continue;
+      }
+
+      // the general block: queries that see a part of the keys, units with holes, the ends of tails and units
+#pragma unroll 1
+      for (int ti = 0; ti < QT; ++ti) {
+        const int tt = tt0 + ti, jt = tt >> lgG, g = tt & (G - 1);
+        if (tt >= ntt || jt < jt_first || wkey0 >= L) continue;   // (uniform) past the end / no key to be seen
+        f32x4_t d[T];
+        mma_tile(cur, ti, d);
+        const int j = jt * 16 + n;                 // this lane's query
+        const int tau = tau0 + j;
+        const int vis = j < a.m ? tau - 1 : -1;    // the query sees positions <= vis
+        int kp[T][4];                              // positions of this lane's keys
+        uint32_t seen = 0u;
 #pragma unroll
-            for (int tl = 0; tl < T; ++tl) {
-              float pv[4];
+        for (int tl = 0; tl < T; ++tl) {
+          const int4 v = *reinterpret_cast<const int4*>(
+              &sh_pos[wv * WKEYS + (RUN ? lg * (4 * T) + tl * 4 : tl * 16 + 4 * lg)]);
+          kp[tl][0] = v.x; kp[tl][1] = v.y; kp[tl][2] = v.z; kp[tl][3] = v.w;
 #pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const bool seen = kp[tl][r] <= vis;
-                const float e = fast_exp2(fmaf(d[tl][r], a.scale_log2, -st.x)) * st.y;
-                pv[r] = seen ? e : 0.f;
-                hmg[tl][r] = (seen && pv[r] >= thr) ? tau : hmg[tl][r];
-              }
-              if (!a.ring) {
-              } else if (quad[tl] && kp[tl][3] <= vis && ((rowbase + (size_t)kp[tl][0]) & 3) == 0) {
-                *reinterpret_cast<float4*>(row + kp[tl][0]) = make_float4(pv[0], pv[1], pv[2], pv[3]);
+          for (int r = 0; r < 4; ++r) seen |= (kp[tl][r] <= vis ? 1u : 0u) << (4 * tl + r);
+        }
+        if (PASS == 1) {
+          float mx, z;
+          prefill_stats_tile<true, T>(d, seen, a.scale_log2, mx, z);
+          if (lg == 0) sh_part[wv][(blk - grp) * QBLK + ti * 16 + n] = make_float2(mx, z);
+          continue;
+        }
+        const float4 st = sh_st[cur][ti * 16 + n];
+        const float thr = MODE == SEED_BITS ? importance_threshold(a.thr_scale, tau) : st.z;
+        float pv[T][4];
+        uint32_t hbits = 0u;
+#pragma unroll
+        for (int tl = 0; tl < T; ++tl)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const bool s = (seen >> (4 * tl + r)) & 1u;
+            const float e = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
+            pv[tl][r] = s ? e : 0.f;
+            const bool hit = s && e >= thr;
+            hm[tl][r] = hit ? tau : hm[tl][r];
+            hbits |= (hit ? 1u : 0u) << (4 * tl + r);
+          }
+        if (!a.ring) continue;   // summary-only state: nothing is recorded but last_hit
+        const size_t row = ring_row(g, min(j, a.m - 1));   // (no lane stores for a query past the last)
+        if (MODE == SEED_BITS) {
+          uint32_t* roww = reinterpret_cast<uint32_t*>(a.ring) + row * a.ring_words;
+          if (rows_ok) {        // (uniform) whole words
+            if (T == 4) {
+              const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
+              if (!(lg & 1) && j < a.m) roww[(pos_w0 >> 5) + (lg >> 1)] = sw[0] | (sw[1] << 16);
+            } else {
+              const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
+              if (lg == 0 && j < a.m) roww[pos_w0 >> 5] = w;
+            }
+          } else {              // rows were cleared by the launch before: set single bits
+#pragma unroll
+            for (int tl = 0; tl < T; ++tl)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if ((hbits >> (4 * tl + r)) & 1u) atomicOr(&roww[kp[tl][r] >> 5], 1u << (kp[tl][r] & 31));
+          }
+        } else {
+#pragma unroll
+          for (int tl = 0; tl < T; ++tl) {
+            // four consecutive positions, all seen, whole and aligned: one store
+            const bool quad = ((seen >> (4 * tl)) & 15u) == 15u && kp[tl][1] == kp[tl][0] + 1 &&
+                              kp[tl][2] == kp[tl][0] + 2 && kp[tl][3] == kp[tl][0] + 3 &&
+                              ((row * a.Tcap + (size_t)kp[tl][0]) & 3) == 0;
+            if (MODE == SEED_BF16) {
+              uint16_t* dst = reinterpret_cast<uint16_t*>(a.ring) + row * a.Tcap;
+              const uint32_t p0 = pack_bf16x2(pv[tl][0], pv[tl][1]), p1 = pack_bf16x2(pv[tl][2], pv[tl][3]);
+              if (quad) {
+                *reinterpret_cast<uint2*>(dst + kp[tl][0]) = make_uint2(p0, p1);
               } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                  if (kp[tl][r] <= vis) row[kp[tl][r]] = pv[r];
+                  if ((seen >> (4 * tl + r)) & 1u)
+                    dst[kp[tl][r]] = (uint16_t)((r & 2 ? p1 : p0) >> (16 * (r & 1)));
+              }
+            } else {
+              float* dst = reinterpret_cast<float*>(a.ring) + row * a.Tcap;
+              if (quad) {
+                *reinterpret_cast<float4*>(dst + kp[tl][0]) = make_float4(pv[tl][0], pv[tl][1], pv[tl][2], pv[tl][3]);
+              } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                  if ((seen >> (4 * tl + r)) & 1u) dst[kp[tl][r]] = pv[tl][r];
               }
             }
           }
         }
-       }
       }
-      if (PASS == 1) {
-        __syncthreads();
-        float2* part = a.part + ((size_t)head * a.nkb + kb) * a.w;
-        for (int j = seg0 + tid; j < seg1; j += WG) {
-          float mx = neg_inf();
-#pragma unroll
-          for (int i = 0; i < WAVES; ++i) mx = fmaxf(mx, sh_part[i][j - seg0].x);
-          const float ms = mx == neg_inf() ? 0.f : mx;
-          float z = 0.f;
-#pragma unroll
-          for (int i = 0; i < WAVES; ++i) z = fmaf(sh_part[i][j - seg0].y, fast_exp2(sh_part[i][j - seg0].x - ms), z);
-          part[j] = make_float2(mx, z);
-        }
-        __syncthreads();
-      }
+      stage(cur ^ 1, qr, str);
     }
+    if (PASS == 1) {
+      __syncthreads();
+      for (int e = tid; e < (grp_end - grp) * QBLK; e += WG) {
+        const int tt = grp * QT + e / 16, j = (tt >> lgG) * 16 + (e & 15);
+        if (tt >= ntt || j >= a.m) continue;
+        float mx = neg_inf();
 #pragma unroll
-    for (int tl = 0; tl < T; ++tl)
+        for (int i = 0; i < WAVES; ++i) mx = fmaxf(mx, sh_part[i][e].x);
+        const float ms = mx == neg_inf() ? 0.f : mx;
+        float z = 0.f;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) hm[tl][r] = max(hm[tl][r], hmg[tl][r]);
+        for (int i = 0; i < WAVES; ++i) z = fmaf(sh_part[i][e].y, fast_exp2(sh_part[i][e].x - ms), z);
+        const int head = b * a.Hq + hkv * G + (tt & (G - 1));
+        a.part[((size_t)head * a.nkb + kb) * a.w + j] = make_float2(mx, z);
+      }
+      __syncthreads();
+    }
   }
 
   if (PASS == 2) {
-    int32_t* lhb = a.last_hit + (size_t)unit * a.Lcap;
+    // the latest hit of every key over the 16 queries of a tile, one key per lane (through LDS: a lane's 4*T keys
+    // read and written one after the other cost as many memory latencies)
+    __syncthreads();   // sh_pos of this wave is free
 #pragma unroll
-    for (int tl = 0; tl < T; ++tl)
+    for (int tl = 0; tl < T; ++tl) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         int v = hm[tl][r];
         v = max(v, __shfl_xor(v, 1));
         v = max(v, __shfl_xor(v, 2));
         v = max(v, __shfl_xor(v, 4));
-        v = max(v, __shfl_xor(v, 8));
-        const int key = wkey0 + tl * 16 + 4 * lg + r;
-        if (n == 0 && key < L && v > lhb[key]) lhb[key] = v;
+        hm[tl][r] = max(v, __shfl_xor(v, 8));
       }
+      if (n == 0)
+        *reinterpret_cast<int4*>(&sh_pos[wv * WKEYS + (RUN ? lg * (4 * T) + tl * 4 : tl * 16 + 4 * lg)]) =
+            make_int4(hm[tl][0], hm[tl][1], hm[tl][2], hm[tl][3]);
+    }
+    __syncthreads();
+    const int key = wkey0 + lane;
+    if (lane < WKEYS && key < L) {
+      int32_t* lh = a.last_hit + (size_t)unit * a.Lcap + key;
+      const int v = sh_pos[wv * WKEYS + lane];
+      if (v > *lh) {
+        if (a.nseg == 1) *lh = v;
+        else atomicMax(lh, v);
+      }
+    }
   }
 }
 
 // Pass 1 has a light tail (max, exp, sum) and is latency-bound at two waves per SIMD: held to the registers
-// and LDS of three (0.91 -> 0.64 ms per layer on config 3).  Pass 2 needs its registers.
+// and LDS of three (0.91 -> 0.64 ms for 512 heads x 1024 queries x 4096 keys).  Pass 2 needs the registers of two
+// (205; held to three it spills: 1.27 -> 1.76 ms).  Both are bound by vector instructions: per tile of 16 queries x
+// 64 keys 16 MFMAs and about 90 (pass 1), 102 (bf16 scores), 80 (bits) others.  Measured: bf16 scores 1.39 -> 1.27 ms
+// (ring written at 3.4 TB/s); bits, 512 heads x 1024 x 8192, 3.22 -> 2.07 ms (one wave per SIMD and a score per pair
+// before); fp32, 16 units of 2000 keys, 74 -> 39 us (the queries of a key block shared by several workgroups).
 template <typename DT, int D>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void corm_prefill_stats_kernel(
     const PrefillArgs a) {
-  prefill_pass<DT, D, 1, false>(a);
+  prefill_pass<DT, D, 1, SEED_F32>(a);
 }
 
-template <typename DT, int D, bool BITS>
-__global__ __launch_bounds__(WG) void corm_prefill_scores_kernel(const PrefillArgs a) {
-  prefill_pass<DT, D, 2, BITS>(a);
+template <typename DT, int D, int MODE>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void corm_prefill_scores_kernel(
+    const PrefillArgs a) {
+  prefill_pass<DT, D, 2, MODE>(a);
 }
 
 // boolean message: zero the words of the rows of steps tau_0 .. tau_{m-1} that pass 2 may set bits in
@@ -486,7 +634,7 @@ __global__ __launch_bounds__(256) void corm_prefill_merge_kernel(const PrefillAr
   }
   const int tau = a.t[head / a.Hq] - a.m + 1 + j;
   a.stats[(size_t)head * a.w + j] =
-      make_float4(ms, z > 0.f ? 1.0f / z : 0.f, importance_threshold(a.thr_scale, tau >= 1 ? tau : 1), 0.f);
+      prefill_query_stats(a, ms, z, importance_threshold(a.thr_scale, tau >= 1 ? tau : 1));
 }
 
 // Def. 4.1 + recent r from last_hit for whole units (no append): wave ballots and survivors per chunk

@@ -1,0 +1,76 @@
+"""GPU: the branches of the launch rules, each at the sizes where it can go wrong, device against device or against
+plain torch (the parity of the paths themselves with the oracle is test_gpu_parity.py)."""
+import pytest
+import torch
+
+from paper_2404_15949_amd import corm
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# kv dtype, G, Hkv, d, P, m, Tcap, position of the first key, thr_scale, holes
+SEEDS = [
+    ("bf16", 1, 2, 128, 700, 64, 704, 0, 1.0, False),      # whole blocks, several workgroups per key block
+    ("bf16", 1, 2, 128, 515, 97, 517, 0, 1.0, False),      # tail and rows of no whole piece
+    ("bf16", 2, 1, 128, 640, 200, 672, 32, 1.0, False),    # positions shifted by a word
+    ("bf16", 4, 2, 64, 600, 130, 640, 3, 1.0, False),      # positions shifted by no piece
+    ("bf16", 8, 1, 64, 300, 48, 320, 0, 1.0, True),        # keys missing: general blocks next to fast ones
+    ("f32", 1, 2, 64, 520, 80, 576, 0, 1.0, False),
+    ("f32", 2, 2, 128, 333, 100, 352, 0, 1.0, True),       # 32 keys per wave
+    ("f32", 8, 1, 128, 400, 33, 448, 32, 1.0, False),
+    ("bf16", 2, 2, 128, 512, 64, 512, 0, 0.0, False),      # threshold 0: everything is important
+    ("bf16", 2, 2, 128, 512, 64, 512, 0, 1e30, False),     # and one that nothing reaches
+    ("bf16", 1, 40, 128, 300, 32, 320, 0, 2.5, False),     # one workgroup per key block
+]
+
+
+@pytest.mark.parametrize("case", range(len(SEEDS)))
+def test_seed_decides_by_the_score_on_every_ring(case):
+    """Every ring type starts from the same fp32 score of a (query, key) pair and decides by one comparison, so with the
+    fp32 ring as the witness the others follow bit for bit: a bf16 ring holds its rounding to nearest even, the
+    boolean ring is "score >= c/t", and last_hit is the latest step whose stored score reaches c/t -- whatever way
+    (bands of raw logits, thresholds before rounding) the kernel takes to that decision."""
+    dtype, G, Hkv, d, P, m, Tcap, first, c, holes = SEEDS[case]
+    print("[case]", SEEDS[case], flush=True)
+    B, Hq = 2, G * Hkv
+    g = torch.Generator(device=DEV).manual_seed(case)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    K = torch.randn(B, Hkv, P, d, device=DEV, generator=g).to(tdt)
+    q = torch.randn(B, Hq, m, d, device=DEV, generator=g).to(tdt)
+    pos = torch.arange(P, device=DEV)
+    if holes:   # drop every 7th key of the first half
+        pos = pos[(pos >= P // 2) | (pos % 7 != 3)]
+    n = len(pos)
+    t_last = P + first
+    got = {}
+    for ring in ("f32", "bf16", "bit"):
+        st = corm.LayerState(B, Hq, Hkv, d, P, Tcap + first, m + 1, 8, dtype, thr_scale=c, device=DEV, score_dtype=ring)
+        st.K[:, :, :n] = K[:, :, pos]
+        st.pos[:, :, :n] = (pos + first).int()
+        st.lens.fill_(n)
+        t = torch.full((B,), t_last, dtype=torch.int32, device=DEV)
+        st.prefill_seed(q, t, torch.zeros_like(t))      # m < w: nothing is moved
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == 0
+        got[ring] = st
+    steps = torch.arange(t_last - m + 1, t_last + 1, device=DEV)
+    rows = (steps - 1) % (m + 1)
+    seen = (pos + first).view(1, -1) < steps.view(-1, 1)                                   # [m, n]
+    score = got["f32"].ring[:, :, rows][..., pos + first]                                  # [B, Hq, m, n]
+    # rows are normalized: fp32 sums of at most 700 terms
+    total = torch.where(seen, score, 0).double().sum(-1)
+    assert (total - 1).abs().max() < 1e-5
+    assert torch.equal(got["bf16"].ring[:, :, rows][..., pos + first][..., seen], score.bfloat16()[..., seen])
+    thr = torch.tensor(c, dtype=torch.float32, device=DEV) / steps.float()
+    for ring, stored in (("f32", score), ("bf16", score.bfloat16().float()), ("bit", score)):
+        hit = (stored >= thr.view(-1, 1)) & seen
+        want = torch.where(hit, steps.view(-1, 1).int(), 0).amax(2).view(B, Hkv, G, n).amax(2)
+        assert torch.equal(got[ring].last_hit[:, :, :n], want), ring
+    words = got["bit"].ring[:, :, rows].contiguous()
+    bits = (words.unsqueeze(-1) >> torch.arange(32, device=DEV)) & 1
+    bits = bits.flatten(-2)[..., pos + first].bool()
+    assert torch.equal(bits & seen, (score >= thr.view(-1, 1)) & seen)
+    if c == 0.0:
+        assert bool((bits | ~seen).all())
+    if c == 1.0:
+        assert bool(hit.any()) and not bool(hit.all())
