@@ -128,7 +128,7 @@ struct Attend {
 // above the unit's length read as dead.  Ends with a barrier.
 __device__ __forceinline__ void stage_live_masks(const Params& p, int unit, const UnitLen& ul, int first, int nwords,
                                                  bool owns_new_slot, unsigned long long* sh_live) {
-  unsigned long long* bitsb = p.keepbits + (size_t)unit * p.kb_stride;
+  unsigned long long* bitsb = p.live + (size_t)unit * p.kb_stride;
   for (int wd = threadIdx.x; wd < nwords; wd += blockDim.x) {
     const int lo = first + wd * 64;   // first slot of this word
     unsigned long long w = 0ull;
@@ -156,6 +156,7 @@ __global__ __launch_bounds__(WG) void corm_attend_kernel(const Params p) {
   const int L = ul.L;
   // (boolean message) the row of this step is cleared here, one launch before the record kernel sets bits
   if (split == 0) clear_bit_rows(p, unit / p.Hkv, (unit % p.Hkv) * G, G, WG);
+  if (split == 0 && threadIdx.x == 0 && p.do_evict) p.unit_state[unit] = make_int2(L, 0);   // (the record launch counts)
   if (split * p.part_keys >= L) return;   // no live key in this part
 
   const int b = unit / p.Hkv;
@@ -436,6 +437,7 @@ void corm_attend_gqa_kernel(const Params p) {
   const UnitLen ul = unit_len(p, unit);
   const int L = ul.L;
   if (split == 0) clear_bit_rows(p, unit / p.Hkv, (unit % p.Hkv) * G, G, WG);
+  if (split == 0 && threadIdx.x == 0 && p.do_evict) p.unit_state[unit] = make_int2(L, 0);   // (the record launch counts)
   if (split * p.part_keys >= L) return;
 
   const int b = unit / p.Hkv;

@@ -7,24 +7,28 @@ namespace {
 
 // ---------------------------------------------------------------- stable in-place compaction
 //
-// Survivor number rho of a unit (in slot order) must end in slot rho.  Two launches, no
-// cross-workgroup synchronization inside either:
+// Survivor number rho of a unit (in slot order) must end in slot rho.  No cross-workgroup synchronization inside a
+// launch; the unit's length is handed over through the workspace by the launch before (lens is written here).
 //
+// Units of up to SLAB_MAX_SLOTS slots, one launch: a workgroup owns a slab of columns of K or V over the whole
+// unit (one more the metadata), so nobody else reads or writes what it moves: it walks the survivors behind the first
+// hole in ascending batches (every destination <= its source; all loads of a batch complete before any of its
+// stores).
+//
+// Longer units, two launches, where a slab would be one long serial walk:
 //   local     grid (splits, units).  R_c = survivors before chunk c (from the per-split counts).
 //             The workgroup of chunk c = slots [a_c, a_c + CHUNK) moves its survivors with rho >= a_c
 //             to slot rho -- inside its own chunk, so it reads and writes only its own slots -- in
-//             ascending batches (every destination <= its source; inside a batch all loads complete
-//             before any store).  Its first survivors, those with rho < a_c ("boundary rows", at most
+//             ascending batches.  Its first survivors, those with rho < a_c ("boundary rows", at most
 //             as many as slots were freed before the chunk), belong in earlier chunks, whose owners
 //             may not have read those slots yet: they go to the chunk's staging area instead.
 //   boundary  grid (splits, units).  Workgroup c copies its staged rows to slots
 //             [R_c, min(a_c, R_{c+1})): slots no local workgroup writes, and whose old contents were
 //             consumed in the previous launch.  Workgroup 0 writes lens, the live count and, in lazy
-//             mode, the reset live masks.  The unit's length is handed over through the workspace so
-//             that no workgroup of this launch reads lens.
+//             mode, the reset live masks.
 //
 // Policy (lazy mode): a unit is compacted only when its dead slots reach dead_num/dead_den of its
-// slots (or its slots are about to run out); otherwise both launches leave it alone, its dead rows
+// slots (or its slots are about to run out); otherwise the launches leave it alone, its dead rows
 // stay in place and the attend kernels skip them by their live masks.  Exact mode: dead_num = 0.
 
 // The local launch runs one thread per slot of a chunk: a chunk is scanned in one step and its rows are requested
@@ -46,25 +50,19 @@ struct CompactArgs {
   int32_t* last_hit;
   int32_t* lens;
   const uint8_t* keep;           // caller's byte mask (corm_compact only)
-  unsigned long long* keepbits;  // [units, kb_stride] wave ballots: workspace, or the caller's live masks (lazy mode)
+  unsigned long long* keepbits;  // [units, kb_stride] wave ballots (workspace)
+  unsigned long long* live;      // lazy mode: the caller's live masks, reset where a unit is compacted
   int32_t* kept_idx;             // optional
   const int32_t* counts;         // [units, nsplit]
-  int32_t* unit_len;             // [units] slots of the unit in this step (written by local, read by boundary)
+  int2* unit_state;              // [units] (slots, survivors) of the unit in this step, written by the launch before
   int32_t* nlive;                // optional [units]: live keys after the step
   char* stage_k;                 // [units, nsplit, CHUNK, ROWB]
   char* stage_v;
   int32_t* stage_meta;           // [units, nsplit, CHUNK, 2] (pos, last_hit)
-  int32_t nsplit, Lcap, do_append, kb_stride;
+  int32_t units, nsplit, Lcap, kb_stride;
+  int32_t sum_counts;            // the launch before left the survivors in counts alone
   int32_t lazy, dead_num, dead_den;
-  const int32_t* unit_dirty;     // optional (with t) [units]: a value other than dirty_tag(t, K) means the unit is not compacted
-  const int32_t* t;
 };
-
-// The unit does not have to be compacted (told by the step launch before, in one word): only its first
-// workgroup still has the bookkeeping to do (the unit's length, lens, the live count).
-__device__ __forceinline__ bool nothing_to_compact(const CompactArgs& a, int unit) {
-  return a.unit_dirty != nullptr && a.unit_dirty[unit] != dirty_tag(a.t, a.K);
-}
 
 __device__ __forceinline__ bool compact_now(const CompactArgs& a, int L, int T) {
   return compact_policy(a.lazy, a.dead_num, a.dead_den, a.Lcap, L, T);
@@ -137,13 +135,6 @@ __device__ __forceinline__ int chunk_scan(bool keep, CompactShared& sh, int* kep
   return before + rank;
 }
 
-__device__ __forceinline__ int compact_unit_len(const CompactArgs& a, int unit) {
-  int L = a.lens[unit];
-  L = L < 0 ? 0 : (L > a.Lcap ? a.Lcap : L);
-  if (a.do_append && L < a.Lcap) L += 1;
-  return L;
-}
-
 // survivors before chunk `split` (R) and of the whole unit (T), by one wave-wide pass over the counts
 __device__ __forceinline__ void unit_counts(const int32_t* cnt, int nlive, int split, int* R, int* T) {
   int r = 0, t = 0;
@@ -161,12 +152,23 @@ __device__ __forceinline__ void unit_counts(const int32_t* cnt, int nlive, int s
   *T = t;
 }
 
+// slots and survivors of a unit: one load (what a workgroup of a unit with nothing to compact costs), or the counts
+__device__ __forceinline__ void unit_totals(const CompactArgs& a, int unit, int* L, int* T) {
+  const int2 st = a.unit_state[unit];
+  int R;
+  *L = st.x;
+  *T = st.y;
+  if (a.sum_counts) unit_counts(a.counts + (size_t)unit * a.nsplit, (st.x + CHUNK - 1) / CHUNK, 0, &R, T);
+}
+
 // a caller's byte mask (corm_compact) -> wave ballots and survivors per split
 __global__ __launch_bounds__(WG) void corm_count_kernel(const CompactArgs a, int32_t* counts) {
   __shared__ int sh_cnt[WAVES];
   const int split = blockIdx.x, unit = blockIdx.y;
-  const int L = compact_unit_len(a, unit);
+  int L = a.lens[unit];
+  L = L < 0 ? 0 : (L > a.Lcap ? a.Lcap : L);
   const int cbeg = split * CHUNK;
+  if (split == 0 && threadIdx.x == 0) a.unit_state[unit].x = L;
   if (cbeg >= L) return;
   const int cend = min(cbeg + CHUNK, L);
   const uint8_t* keepb = a.keep + (size_t)unit * a.Lcap;
@@ -194,17 +196,10 @@ __global__ __launch_bounds__(CWG) void corm_compact_local_kernel(const CompactAr
   __shared__ CompactShared sh_c;
   const int split = blockIdx.x, unit = blockIdx.y;
   const int tid = threadIdx.x;
-  if (split != 0 && nothing_to_compact(a, unit)) return;
-  const int L = compact_unit_len(a, unit);
-  if (split == 0 && tid == 0) a.unit_len[unit] = L;
-  // (a unit that is not compacted: handing its length on was all its first workgroup had to do; lens and the unit's
-  // word are loaded together, nothing waits for the counts)
-  if (split == 0 && nothing_to_compact(a, unit)) return;
+  int L, T;
+  unit_totals(a, unit, &L, &T);
   const int nlive = (L + CHUNK - 1) / CHUNK;
   if (split >= nlive) return;
-  const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
-  int R, T;   // survivors before this chunk, survivors of the unit
-  unit_counts(cnt, nlive, split, &R, &T);
   int32_t* idxb = a.kept_idx ? a.kept_idx + (size_t)unit * a.Lcap : nullptr;
   const int cbeg = split * CHUNK;
   const int cend = min(cbeg + CHUNK, L);
@@ -213,6 +208,9 @@ __global__ __launch_bounds__(CWG) void corm_compact_local_kernel(const CompactAr
     if (idxb && T == L && i < cend) idxb[i] = i;
     return;
   }
+  const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
+  int R;   // survivors before this chunk
+  unit_counts(cnt, nlive, split, &R, &T);
   const int my_cnt = cnt[split];
   if (R == cbeg && my_cnt == cend - cbeg) {   // no hole before or inside this chunk
     if (idxb && i < cend) idxb[i] = i;
@@ -262,24 +260,35 @@ __global__ __launch_bounds__(CWG) void corm_compact_local_kernel(const CompactAr
   move_rows<ROWB>(Kb, Vb, sk, sv, sh_c.src_of + fixed, kept - fixed, R + fixed, cbeg, R);
 }
 
+// by one workgroup of a unit: lens, the live count and, in lazy mode, the live masks of a unit that was compacted
+__device__ __forceinline__ void unit_bookkeeping(const CompactArgs& a, int unit, int L, int T, bool compacted) {
+  if (threadIdx.x == 0) {
+    a.lens[unit] = compacted ? T : L;
+    if (a.nlive) a.nlive[unit] = T;
+  }
+  if (a.lazy && compacted) {   // every slot below T is live again
+    unsigned long long* liveb = a.live + (size_t)unit * a.kb_stride;
+    for (int wd = threadIdx.x; wd < a.kb_stride; wd += blockDim.x) {
+      const int lo = wd * 64;
+      liveb[wd] = T >= lo + 64 ? ~0ull : (T > lo ? ((1ull << (T - lo)) - 1ull) : 0ull);
+    }
+  }
+}
+
 template <int ROWB>
 __global__ __launch_bounds__(WG) void corm_compact_boundary_kernel(const CompactArgs a) {
   constexpr int LPR = ROWB / 16;
   const int split = blockIdx.x, unit = blockIdx.y;
   const int tid = threadIdx.x;
-  if (split != 0 && nothing_to_compact(a, unit)) return;
-  const int L = a.unit_len[unit];
-  if (split == 0 && !a.nlive && nothing_to_compact(a, unit)) {   // not compacted and nobody asks for the live count
-    if (tid == 0) a.lens[unit] = L;
-    return;
-  }
+  int L, T;
+  unit_totals(a, unit, &L, &T);
   const int nlive = (L + CHUNK - 1) / CHUNK;
   if (split >= nlive && split != 0) return;
-  const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
-  int R, T;
-  unit_counts(cnt, nlive, split, &R, &T);
   const bool compacted = compact_now(a, L, T);
   if (compacted && split > 0) {
+    const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
+    int R;
+    unit_counts(cnt, nlive, split, &R, &T);
     const int nb = min(split * CHUNK, R + cnt[split]) - R;   // boundary rows of this chunk: survivors [R, R + nb)
     if (nb > 0) {
       char* Kb = a.K + (size_t)unit * a.Lcap * ROWB;
@@ -300,19 +309,156 @@ __global__ __launch_bounds__(WG) void corm_compact_boundary_kernel(const Compact
       }
     }
   }
-  if (split == 0) {
-    const int Lnew = compacted ? T : L;
-    if (tid == 0) {
-      a.lens[unit] = Lnew;
-      if (a.nlive) a.nlive[unit] = T;
-    }
-    if (a.lazy && compacted) {   // every slot below T is live again
-      unsigned long long* bitsb = a.keepbits + (size_t)unit * a.kb_stride;
-      for (int wd = tid; wd < a.kb_stride; wd += WG) {
-        const int lo = wd * 64;
-        bitsb[wd] = T >= lo + 64 ? ~0ull : (T > lo ? ((1ull << (T - lo)) - 1ull) : 0ull);
+  if (split == 0) unit_bookkeeping(a, unit, L, T, compacted);
+}
+
+// ---------------------------------------------------------------- one launch, a slab of columns per workgroup
+//
+// A slab is 128 bytes of a row, one cache line: 5 workgroups make a unit of 256-byte rows.  Bound by the bytes it has
+// to move where many units evict (512 units of 1100 to 4300 keys, a hole each: 0.42 GB read and written in 82 us,
+// 5.1 TB/s, what a plain copy reaches here; the two chunk launches 101 + 6 us), by the walk of one unit where a single
+// one does (4000 rows 27 us at worst, 9.5 us a step on average over the dense 512 units against 13.4), by the launch
+// itself where none does (4.9 us against 4.9 + 4.8).  Measured beside it on the same launches: slabs of 64 bytes 102
+// us and 7.4 us for the launch that finds nothing, whole rows 89 us; 256 threads 89 us, 1024 threads 83 us but 7.2 us
+// idle; four passes in flight 87 us.
+constexpr int SLAB_WG = 512;
+constexpr int SLAB_WAVES = SLAB_WG / 64;
+constexpr int SLAB_MAX_SLOTS = 16384;          // a 64-slot word per thread and a 16-bit source slot per survivor in LDS
+static_assert(SLAB_MAX_SLOTS <= SLAB_WG * 64 && SLAB_MAX_SLOTS <= 65536, "words of a unit, source slots");
+constexpr int SLAB_XCDS = 8;                   // accelerator dies of the device
+constexpr int slab_bytes(int rowb) { return rowb < 128 ? rowb : 128; }
+
+template <int ROWB>
+__global__ __launch_bounds__(SLAB_WG) void corm_compact_slab_kernel(const CompactArgs a) {
+  constexpr int SLAB_BYTES = slab_bytes(ROWB);
+  constexpr int SLABS = 2 * ROWB / SLAB_BYTES;   // of K, then of V; one more workgroup: metadata
+  constexpr int LPR = SLAB_BYTES / 16;           // lanes per piece of a row
+  constexpr int RPP = SLAB_WG / LPR;             // rows per pass of the workgroup
+  constexpr int NP = 8;                          // passes in flight together, two such batches
+  extern __shared__ uint16_t sh_src[];           // [Lcap] old slots of the survivors behind the first hole
+  __shared__ int sh_wave[SLAB_WAVES], sh_first[SLAB_WAVES];
+  __shared__ unsigned long long sh_word[SLAB_WG];
+  __shared__ int sh_before[SLAB_WG];
+
+  // XCD id % 8 takes the same contiguous range of units as the unit kernel
+  const int per_xcd = (a.units + SLAB_XCDS - 1) / SLAB_XCDS;
+  const int li = (int)(blockIdx.x / SLAB_XCDS);
+  const int slab = li % (SLABS + 1);
+  const int unit = (int)(blockIdx.x % SLAB_XCDS) * per_xcd + li / (SLABS + 1);
+  if (li / (SLABS + 1) >= per_xcd || unit >= a.units) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  int L, T;
+  unit_totals(a, unit, &L, &T);
+  const bool compacted = compact_now(a, L, T);
+  int32_t* idxb = a.kept_idx ? a.kept_idx + (size_t)unit * a.Lcap : nullptr;
+  if (slab == SLABS) unit_bookkeeping(a, unit, L, T, compacted);
+  if (!compacted) {   // nothing evicted, or (lazy mode) not enough dead slots yet
+    if (slab == SLABS && idxb && T == L)
+      for (int i = tid; i < L; i += SLAB_WG) idxb[i] = i;
+    return;
+  }
+
+  // survivors before every 64-slot word and the first hole: a word per thread, scanned over the workgroup
+  const unsigned long long* bitsb = a.keepbits + (size_t)unit * a.kb_stride;
+  const int nword = (L + 63) / 64;
+  unsigned long long word = 0ull;
+  int hole = 0x7fffffff;
+  if (tid < nword) {
+    word = bitsb[tid];
+    const int valid = L - tid * 64;   // slots of this word that are in use
+    if (valid < 64) word &= (1ull << valid) - 1ull;
+    if (~word != 0ull) hole = tid * 64 + __ffsll((long long)~word) - 1;   // (>= L: no hole)
+  }
+  int before = __popcll(word);
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int x = __shfl_up(before, off);
+    if (lane >= off) before += x;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) hole = min(hole, __shfl_xor(hole, off));
+  if (lane == 63) sh_wave[wv] = before;
+  if (lane == 0) sh_first[wv] = hole;
+  before -= __popcll(word);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < SLAB_WAVES; ++i) {
+    if (i < wv) before += sh_wave[i];
+    hole = min(hole, sh_first[i]);
+  }
+  sh_word[tid] = word;
+  sh_before[tid] = before;
+  __syncthreads();
+  const int fixed = min(hole, L);   // the survivors in front of the first hole lie where they belong
+  // the list of old slots: a slot per lane, the words dealt to the waves
+#pragma unroll 4
+  for (int w = (fixed >> 6) + wv; w < nword; w += SLAB_WAVES) {
+    const unsigned long long bw = sh_word[w];
+    const int r = sh_before[w] + __popcll(bw & ((1ull << lane) - 1ull));
+    if (((bw >> lane) & 1ull) && r >= fixed) sh_src[r - fixed] = (uint16_t)(w * 64 + lane);
+  }
+  __syncthreads();
+  const int n = T - fixed;   // rows to move, to slots fixed, fixed + 1, ...
+
+  if (slab == SLABS) {   // metadata: a slot per thread and step
+    int32_t* posb = a.pos + (size_t)unit * a.Lcap;
+    int32_t* lhb = a.last_hit + (size_t)unit * a.Lcap;
+    if (idxb)
+      for (int i = tid; i < fixed; i += SLAB_WG) idxb[i] = i;
+    constexpr int MP = 4;   // in flight together
+    for (int base = 0; base < n; base += SLAB_WG * MP) {
+      int p[MP], h[MP], src[MP];
+#pragma unroll
+      for (int u = 0; u < MP; ++u) {
+        src[u] = sh_src[min(base + u * SLAB_WG + tid, n - 1)];
+        p[u] = posb[src[u]];
+        h[u] = lhb[src[u]];
+      }
+      wait_vm_loads();
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < MP; ++u) {
+        const int j = base + u * SLAB_WG + tid;
+        if (j < n) {
+          posb[fixed + j] = p[u];
+          lhb[fixed + j] = h[u];
+          if (idxb) idxb[fixed + j] = src[u];
+        }
       }
     }
+    return;
+  }
+  if (n <= 0) return;   // what went lay behind every survivor
+
+  constexpr int HALF = SLABS / 2;
+  char* base = (slab < HALF ? a.K : a.V) + (size_t)unit * a.Lcap * ROWB + (slab % HALF) * SLAB_BYTES + (tid % LPR) * 16;
+  const int sub = tid / LPR;
+  // Two batches of NP passes: the next one's loads are in flight while this one waits and is stored (its sources lie
+  // behind every destination of this batch).  A batch is stored once all of its loads, of every wave, are in.
+  u32x4_t ra[NP], rb[NP];
+  auto load = [&](int j0, u32x4_t (&r)[NP]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NP; ++u)   // (clamped: every load reads a valid row)
+      r[u] = *reinterpret_cast<const u32x4_t*>(base + (size_t)sh_src[min(j0 + u * RPP + sub, n - 1)] * ROWB);
+  };
+  auto store = [&](int j0, const u32x4_t (&r)[NP]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NP; ++u) asm volatile("" ::"v"(r[u]));   // this wave's loads of the batch are in ...
+    __syncthreads();                                             // ... and everybody's
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int j = j0 + u * RPP + sub;
+      if (j < n) *reinterpret_cast<u32x4_t*>(base + (size_t)(fixed + j) * ROWB) = r[u];
+    }
+  };
+  constexpr int BATCH = RPP * NP;
+  load(0, ra);
+  for (int j0 = 0; j0 < n; j0 += 2 * BATCH) {
+    if (j0 + BATCH < n) load(j0 + BATCH, rb);
+    store(j0, ra);
+    if (j0 + BATCH >= n) break;
+    if (j0 + 2 * BATCH < n) load(j0 + 2 * BATCH, ra);
+    store(j0 + BATCH, rb);
   }
 }
 

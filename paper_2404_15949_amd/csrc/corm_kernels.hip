@@ -225,7 +225,8 @@ int corm_compact(const corm_desc* desc, void* K, void* V, int32_t* pos, int32_t*
   WorkspaceLayout wl;
   rc = check_workspace(desc, workspace, workspace_bytes, &wl);
   if (rc) return rc;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, keep, kept_idx, 0, true, CompactPolicy(),
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, keep, kept_idx, true, true,
+                        CompactPolicy(),
                         (hipStream_t)stream);
 }
 
@@ -252,10 +253,8 @@ int corm_step_attend(const corm_desc* desc, const void* q, const void* k_new, co
   return launch_attend_record(desc, p, ctx, (hipStream_t)stream);
 }
 
-// t: the step's t array when the attend launch of the same step maintained the workspace's dirty word (the
-// compaction launches then leave at once where nothing is to be compacted); NULL: no such shortcut
-static int step_evict_impl(const corm_desc* desc, void* K, void* V, int32_t* lens, int32_t* pos, int32_t* last_hit,
-                           int32_t* kept_idx, void* workspace, size_t workspace_bytes, const int32_t* t, void* stream) {
+int corm_step_evict(const corm_desc* desc, void* K, void* V, int32_t* lens, int32_t* pos, int32_t* last_hit,
+                    int32_t* kept_idx, void* workspace, size_t workspace_bytes, void* stream) {
   int rc = validate_desc(desc);
   if (rc) return rc;
   if (!K || !V || !pos || !last_hit || !lens) return CORM_EINVAL;
@@ -265,15 +264,8 @@ static int step_evict_impl(const corm_desc* desc, void* K, void* V, int32_t* len
   WorkspaceLayout wl;
   rc = check_workspace(desc, workspace, workspace_bytes, &wl);
   if (rc) return rc;
-  CompactPolicy pol;
-  pol.t = t;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, 1, false, pol,
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, false, CompactPolicy(),
                         (hipStream_t)stream);
-}
-
-int corm_step_evict(const corm_desc* desc, void* K, void* V, int32_t* lens, int32_t* pos, int32_t* last_hit,
-                    int32_t* kept_idx, void* workspace, size_t workspace_bytes, void* stream) {
-  return step_evict_impl(desc, K, V, lens, pos, last_hit, kept_idx, workspace, workspace_bytes, nullptr, stream);
 }
 
 int corm_decode_step(const corm_desc* desc, const void* q, const void* k_new, const void* v_new, void* K, void* V,
@@ -286,7 +278,7 @@ int corm_decode_step(const corm_desc* desc, const void* q, const void* k_new, co
   rc = corm_step_attend(desc, q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, keep,
                         workspace, workspace_bytes, status, opts, stream);
   if (rc) return rc;
-  return step_evict_impl(desc, K, V, lens, pos, last_hit, kept_idx, workspace, workspace_bytes, t, stream);
+  return corm_step_evict(desc, K, V, lens, pos, last_hit, kept_idx, workspace, workspace_bytes, stream);
 }
 
 int corm_decode_step_lazy(const corm_desc* desc, const void* q, const void* k_new, const void* v_new, void* K, void* V,
@@ -313,16 +305,14 @@ int corm_decode_step_lazy(const corm_desc* desc, const void* q, const void* k_ne
   p.do_append = 1; p.do_evict = 1;
   bind_params(desc, wl, workspace, p);
   p.lazy = 1;
-  p.dead_num = dead_num; p.dead_den = dead_den;
-  p.keepbits = reinterpret_cast<unsigned long long*>(live);   // the live masks are read, then replaced by the new ones
+  p.live = reinterpret_cast<unsigned long long*>(live);
   rc = launch_attend_record(desc, p, ctx, (hipStream_t)stream);
   if (rc) return rc;
   CompactPolicy pol;
   pol.lazy = 1; pol.dead_num = dead_num; pol.dead_den = dead_den;
   pol.live = reinterpret_cast<unsigned long long*>(live);
   pol.nlive = nlive;
-  pol.t = use_unit_path(desc, ctx) ? t : nullptr;   // (the unit kernel evaluates the policy per unit; the split kernels cannot)
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, nullptr, 1, false, pol,
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, nullptr, false, false, pol,
                         (hipStream_t)stream);
 }
 
@@ -374,10 +364,12 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
   if (rc) return rc;
   hipLaunchKernelGGL(corm_decide_kernel, dim3(wl.nsplit, units), dim3(WG), 0, s, lens, last_hit, t, t_first,
                      reinterpret_cast<unsigned long long*>(ws + wl.keepbits_off),
-                     reinterpret_cast<int32_t*>(ws + wl.counts_off), keep, desc->Hkv, desc->Lcap, wl.nsplit,
+                     reinterpret_cast<int32_t*>(ws + wl.counts_off),
+                     reinterpret_cast<int2*>(ws + wl.unit_state_off), keep, desc->Hkv, desc->Lcap, wl.nsplit,
                      wl.kb_stride, desc->w, desc->r, m);
   if (launch_status()) return CORM_EHIP;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, 0, false, CompactPolicy(), s);
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, true,
+                        CompactPolicy(), s);
 }
 
 int corm_selected_path(const corm_desc* desc, const corm_launch_opts* opts) {

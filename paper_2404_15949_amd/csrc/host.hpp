@@ -8,7 +8,7 @@ namespace {
 // ---------------------------------------------------------------- host side
 
 struct WorkspaceLayout {
-  size_t counts_off, unit_len_off, dirty_off, keepbits_off, partials_off, logits_off, stage_meta_off, stage_k_off, stage_v_off;
+  size_t counts_off, unit_state_off, keepbits_off, partials_off, logits_off, stage_meta_off, stage_k_off, stage_v_off;
   size_t seed_part_off, seed_stats_off, total;
   int nsplit, kb_stride;
   int seed_kb, seed_nkb;   // prompt seeding: keys per workgroup, key blocks per unit
@@ -25,9 +25,8 @@ WorkspaceLayout workspace_layout(const corm_desc& d) {
   const size_t stage_rows = units * w.nsplit * CHUNK;   // every survivor of a chunk may be a boundary row
   w.counts_off = 0;
   w.kb_stride = (d.Lcap + 63) / 64;
-  w.unit_len_off = align_up(units * w.nsplit * sizeof(int32_t), 256);
-  w.dirty_off = w.unit_len_off + units * sizeof(int32_t);   // one word per unit: see Params::unit_dirty
-  w.keepbits_off = align_up(w.dirty_off + units * sizeof(int32_t), 256);
+  w.unit_state_off = align_up(units * w.nsplit * sizeof(int32_t), 256);
+  w.keepbits_off = align_up(w.unit_state_off + units * sizeof(int2), 256);
   w.partials_off = align_up(w.keepbits_off + units * w.kb_stride * sizeof(unsigned long long), 256);
   w.logits_off = align_up(w.partials_off + heads * w.nsplit * MAX_PARTS_PER_CHUNK * (d.d + 2) * sizeof(float), 256);
   w.stage_meta_off = align_up(w.logits_off + heads * d.Lcap * sizeof(float), 256);
@@ -114,7 +113,7 @@ int check_workspace(const corm_desc* d, void* workspace, size_t workspace_bytes,
 void bind_params(const corm_desc* d, const WorkspaceLayout& wl, void* workspace, Params& p) {
   char* ws = reinterpret_cast<char*>(workspace);
   p.counts = reinterpret_cast<int32_t*>(ws + wl.counts_off);
-  p.unit_dirty = reinterpret_cast<int32_t*>(ws + wl.dirty_off);
+  p.unit_state = reinterpret_cast<int2*>(ws + wl.unit_state_off);
   p.keepbits = reinterpret_cast<unsigned long long*>(ws + wl.keepbits_off);
   p.kb_stride = wl.kb_stride;
   p.partials = reinterpret_cast<float*>(ws + wl.partials_off);
@@ -289,52 +288,55 @@ int launch_attend_record(const corm_desc* d, const Params& p0, const LaunchCtx& 
 // units whose dead slots reach dead_num / dead_den of their slots.
 struct CompactPolicy {
   int lazy = 0, dead_num = 0, dead_den = 1;
-  unsigned long long* live = nullptr;   // lazy mode: the caller's live masks take the place of the keep masks
+  unsigned long long* live = nullptr;   // lazy mode: the caller's live masks
   int32_t* nlive = nullptr;             // optional output: live keys per unit
-  const int32_t* t = nullptr;           // the step's t array, if the launch before maintains the workspace's dirty words
 };
 
-// local + boundary launches of the compaction; count_first: derive the per-split counts from the mask
+template <int ROWB>
+void launch_compact_rows(const CompactArgs& a, hipStream_t s) {
+  // One launch of column slabs up to SLAB_MAX_SLOTS, beyond it chunks in two launches.
+  if (a.Lcap <= SLAB_MAX_SLOTS) {
+    const int groups = (a.units + SLAB_XCDS - 1) / SLAB_XCDS * SLAB_XCDS;
+    hipLaunchKernelGGL((corm_compact_slab_kernel<ROWB>), dim3(groups * (2 * ROWB / slab_bytes(ROWB) + 1)), dim3(SLAB_WG),
+                       (size_t)a.Lcap * sizeof(uint16_t), s, a);
+    return;
+  }
+  const dim3 grid(a.nsplit, a.units);
+  hipLaunchKernelGGL((corm_compact_local_kernel<ROWB>), grid, dim3(CWG), 0, s, a);
+  hipLaunchKernelGGL((corm_compact_boundary_kernel<ROWB>), grid, dim3(WG), 0, s, a);
+}
+
+// count_first: derive the per-split counts from the caller's mask; sum_counts: the launch before left no unit totals
 int launch_compact(const corm_desc* d, const WorkspaceLayout& wl, void* workspace, void* K, void* V, int32_t* pos,
-                   int32_t* last_hit, int32_t* lens, const uint8_t* keep, int32_t* kept_idx, int do_append,
-                   bool count_first, const CompactPolicy& pol, hipStream_t s) {
+                   int32_t* last_hit, int32_t* lens, const uint8_t* keep, int32_t* kept_idx, bool count_first,
+                   bool sum_counts, const CompactPolicy& pol, hipStream_t s) {
   char* ws = reinterpret_cast<char*>(workspace);
   CompactArgs a;
   a.K = reinterpret_cast<char*>(K);
   a.V = reinterpret_cast<char*>(V);
   a.pos = pos; a.last_hit = last_hit; a.lens = lens; a.keep = keep; a.kept_idx = kept_idx;
-  a.keepbits = pol.live ? pol.live : reinterpret_cast<unsigned long long*>(ws + wl.keepbits_off);
+  a.keepbits = reinterpret_cast<unsigned long long*>(ws + wl.keepbits_off);
+  a.live = pol.live;
   a.kb_stride = wl.kb_stride;
   int32_t* counts = reinterpret_cast<int32_t*>(ws + wl.counts_off);
   a.counts = counts;
-  a.unit_len = reinterpret_cast<int32_t*>(ws + wl.unit_len_off);
+  a.unit_state = reinterpret_cast<int2*>(ws + wl.unit_state_off);
+  a.sum_counts = sum_counts;
   a.nlive = pol.nlive;
   a.stage_k = ws + wl.stage_k_off;
   a.stage_v = ws + wl.stage_v_off;
   a.stage_meta = reinterpret_cast<int32_t*>(ws + wl.stage_meta_off);
-  a.nsplit = wl.nsplit; a.Lcap = d->Lcap; a.do_append = do_append;
+  a.units = d->B * d->Hkv; a.nsplit = wl.nsplit; a.Lcap = d->Lcap;
   a.lazy = pol.lazy; a.dead_num = pol.dead_num; a.dead_den = pol.dead_den;
-  // (a caller who wants kept_idx gets the identity written for untouched units: every workgroup has work then)
-  a.unit_dirty = pol.t && !kept_idx ? reinterpret_cast<const int32_t*>(ws + wl.dirty_off) : nullptr;
-  a.t = pol.t;
   const dim3 grid(wl.nsplit, d->B * d->Hkv);
   if (count_first) {
     hipLaunchKernelGGL(corm_count_kernel, grid, dim3(WG), 0, s, a, counts);
     if (launch_status()) return CORM_EHIP;
   }
   switch (row_bytes(d)) {
-    case 128:
-      hipLaunchKernelGGL((corm_compact_local_kernel<128>), grid, dim3(CWG), 0, s, a);
-      hipLaunchKernelGGL((corm_compact_boundary_kernel<128>), grid, dim3(WG), 0, s, a);
-      break;
-    case 256:
-      hipLaunchKernelGGL((corm_compact_local_kernel<256>), grid, dim3(CWG), 0, s, a);
-      hipLaunchKernelGGL((corm_compact_boundary_kernel<256>), grid, dim3(WG), 0, s, a);
-      break;
-    case 512:
-      hipLaunchKernelGGL((corm_compact_local_kernel<512>), grid, dim3(CWG), 0, s, a);
-      hipLaunchKernelGGL((corm_compact_boundary_kernel<512>), grid, dim3(WG), 0, s, a);
-      break;
+    case 128: launch_compact_rows<128>(a, s); break;
+    case 256: launch_compact_rows<256>(a, s); break;
+    case 512: launch_compact_rows<512>(a, s); break;
     default: return CORM_EUNSUPPORTED;
   }
   return launch_status();

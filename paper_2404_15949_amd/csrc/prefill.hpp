@@ -641,8 +641,8 @@ __global__ __launch_bounds__(256) void corm_prefill_merge_kernel(const PrefillAr
 // for the compaction launches, optionally one byte per slot; writes t_first.
 __global__ __launch_bounds__(WG) void corm_decide_kernel(const int32_t* lens, const int32_t* last_hit, const int32_t* t,
                                                          int32_t* t_first, unsigned long long* keepbits,
-                                                         int32_t* counts, uint8_t* keep, int Hkv, int Lcap, int nsplit,
-                                                         int kb_stride, int w, int r, int m) {
+                                                         int32_t* counts, int2* unit_state, uint8_t* keep, int Hkv,
+                                                         int Lcap, int nsplit, int kb_stride, int w, int r, int m) {
   __shared__ int sh_cnt[WAVES];
   const int split = blockIdx.x, unit = blockIdx.y;
   const int b = unit / Hkv;
@@ -651,6 +651,7 @@ __global__ __launch_bounds__(WG) void corm_decide_kernel(const int32_t* lens, co
   if (split == 0 && unit % Hkv == 0 && tid == 0) t_first[b] = tcur - m + 1;
   int L = lens[unit];
   L = L < 0 ? 0 : (L > Lcap ? Lcap : L);
+  if (split == 0 && tid == 0) unit_state[unit].x = L;
   const int cbeg = split * CHUNK;
   if (cbeg >= L) return;
   const int cend = min(cbeg + CHUNK, L);

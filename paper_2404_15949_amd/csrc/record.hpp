@@ -42,6 +42,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   int32_t* lhb = p.last_hit + (size_t)unit * p.Lcap;
   const float* logit_u = p.logits + (size_t)(b * p.Hq + hq0) * p.Lcap;
   unsigned long long* bitsb = p.keepbits + (size_t)unit * p.kb_stride;
+  unsigned long long* liveb = p.lazy ? p.live + (size_t)unit * p.kb_stride : nullptr;
   int my_pos[KPT], my_lh[KPT];
   bool my_live[KPT];   // lazy mode: the slot holds a key that was not evicted earlier
   float lg[KPT][G];
@@ -50,7 +51,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
     const int i = min(rbeg + k * WG + tid, max(rend - 1, 0));   // clamped: a live slot (or 0 in an empty unit)
     my_pos[k] = posb[i];
     my_lh[k] = lhb[i];
-    my_live[k] = p.lazy ? ((bitsb[i >> 6] >> (i & 63)) & 1ull) != 0 : true;
+    my_live[k] = p.lazy ? ((liveb[i >> 6] >> (i & 63)) & 1ull) != 0 : true;
 #pragma unroll
     for (int g = 0; g < G; ++g) lg[k][g] = logit_u[(size_t)g * p.Lcap + i];
   }
@@ -174,7 +175,10 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
     }
     if (p.do_evict && keepb && i < rend) keepb[i] = keep ? 1 : 0;
     const unsigned long long bal = __ballot(keep);
-    if (p.do_evict && lane == 0 && rbeg + k * WG + wv * 64 < rend) bitsb[((rbeg + k * WG) >> 6) + wv] = bal;
+    if (p.do_evict && lane == 0 && rbeg + k * WG + wv * 64 < rend) {
+      bitsb[((rbeg + k * WG) >> 6) + wv] = bal;
+      if (p.lazy) liveb[((rbeg + k * WG) >> 6) + wv] = bal;
+    }
     kept[k / KPC] += __popcll(bal);
   }
   if (p.do_evict) {
@@ -189,8 +193,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
       for (int i = 0; i < WAVES; ++i) tot += sh_cnt[tid][i];
       const int chunk = rsplit * RECORD_CHUNKS + tid;
       p.counts[(size_t)unit * p.nsplit + chunk] = tot;
-      // exact mode: a chunk that lost a key means the compaction launches have work (see Params::unit_dirty)
-      if (!p.lazy && tot != min(CHUNK, L - chunk * CHUNK)) p.unit_dirty[unit] = dirty_tag(p.t, p.K);
+      atomicAdd(&p.unit_state[unit].y, tot);
     }
   }
 }

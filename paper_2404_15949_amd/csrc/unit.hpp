@@ -112,6 +112,7 @@ __global__ __launch_bounds__(UNIT_WG) void corm_unit_kernel(const Params p, cons
   clear_bit_rows(p, b, hq0, G, UNIT_WG);   // (ordered before the record phase by the barriers of the merge)
   if (L == 0) {   // empty unit: out = 0, nothing to record
     for (int idx = tid; idx < G * D; idx += UNIT_WG) p.out[(size_t)(b * p.Hq + hq0) * D + idx] = 0.f;
+    if (tid == 0 && p.do_evict) p.unit_state[unit] = make_int2(0, 0);
     return;
   }
 
@@ -258,6 +259,7 @@ __global__ __launch_bounds__(UNIT_WG) void corm_unit_kernel(const Params p, cons
   const bool full = p.do_evict && step_ok && (tcur - tfirst + 1 >= p.w);
   uint8_t* keepb = p.keep ? p.keep + (size_t)unit * p.Lcap : nullptr;
   unsigned long long* bitsb = p.keepbits + (size_t)unit * p.kb_stride;
+  unsigned long long* liveb = LAZY ? p.live + (size_t)unit * p.kb_stride : nullptr;
   // Boolean message (score_dtype CORM_BIT): a plain loop of its own, so that the unrolled loop below
   // keeps its register budget.  The fp32 score itself is compared; bits are set wave by wave.
   if (p.ring_bits) {
@@ -300,6 +302,7 @@ __global__ __launch_bounds__(UNIT_WG) void corm_unit_kernel(const Params p, cons
         const unsigned long long bal = __ballot(keep);
         if (lane == 0 && tile + wv * 64 < L) {
           bitsb[(tile >> 6) + wv] = bal;
+          if (LAZY) liveb[(tile >> 6) + wv] = bal;
           atomicAdd(&sh_tilecnt[tile / CHUNK], __popcll(bal));
         }
       }
@@ -349,6 +352,7 @@ __global__ __launch_bounds__(UNIT_WG) void corm_unit_kernel(const Params p, cons
       const unsigned long long bal = __ballot(keep);
       if (lane == 0 && tile + wv * 64 < L) {
         bitsb[(tile >> 6) + wv] = bal;
+        if (LAZY) liveb[(tile >> 6) + wv] = bal;
         atomicAdd(&sh_tilecnt[tile / CHUNK], __popcll(bal));
       }
     }
@@ -357,10 +361,10 @@ __global__ __launch_bounds__(UNIT_WG) void corm_unit_kernel(const Params p, cons
     __syncthreads();
     const int ntile = (L + CHUNK - 1) / CHUNK;
     if (tid < ntile) p.counts[(size_t)unit * p.nsplit + tid] = sh_tilecnt[tid];
-    if (tid == 0) {   // tell the compaction launches, in one word, whether this unit needs them
+    if (tid == 0) {
       int T = 0;
       for (int k = 0; k < ntile; ++k) T += sh_tilecnt[k];
-      if (compact_policy(LAZY, p.dead_num, p.dead_den, p.Lcap, L, T)) p.unit_dirty[unit] = dirty_tag(p.t, p.K);
+      p.unit_state[unit] = make_int2(L, T);
     }
   }
 }

@@ -74,3 +74,41 @@ def test_seed_decides_by_the_score_on_every_ring(case):
         assert bool((bits | ~seen).all())
     if c == 1.0:
         assert bool(hit.any()) and not bool(hit.all())
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 128)])
+@pytest.mark.parametrize("Lcap", [1, 64, 513, 4097, 16384, 16385])
+def test_compact_on_both_sides_of_the_slab_limit(dtype, d, Lcap):
+    """A unit per kind of mask, at the edges of 64-slot words, of a batch of rows and of the longest unit that is compacted
+    in one launch; the survivors, their metadata and kept_idx against an index operation of torch, exactly."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(Lcap)
+    kinds = ["all", "first", "last", "none", "third", "half", "tail", "one"]
+    U = len(kinds)
+    st = corm.LayerState(1, U, U, d, Lcap, Lcap, 1, 1, dtype, device=DEV, want_masks=True, want_ring=False)
+    st.K.copy_(torch.randn(1, U, Lcap, d, device=DEV, generator=g).to(tdt))
+    st.V.copy_(torch.randn(1, U, Lcap, d, device=DEV, generator=g).to(tdt))
+    st.pos.copy_(torch.arange(Lcap, device=DEV, dtype=torch.int32))
+    st.last_hit.copy_(torch.randint(0, 99, (1, U, Lcap), device=DEV, generator=g, dtype=torch.int32))
+    lens = [Lcap, Lcap, Lcap, Lcap, Lcap, max(Lcap - 5, 0), Lcap, Lcap // 2]
+    st.lens.copy_(torch.tensor([lens], dtype=torch.int32))
+    keep = torch.ones(U, Lcap, dtype=torch.bool, device=DEV)
+    keep[1, 0] = False
+    keep[2, -1] = False
+    keep[3] = False
+    keep[4] = torch.rand(Lcap, device=DEV, generator=g) < 0.33
+    keep[5] = torch.rand(Lcap, device=DEV, generator=g) < 0.5
+    keep[6, Lcap - Lcap // 3:] = False
+    keep[7, Lcap // 4] = False
+    st.keep.copy_(keep.unsqueeze(0))
+    before = {k: getattr(st, k).clone() for k in ("K", "V", "pos", "last_hit")}
+    print("[case]", dtype, d, Lcap, flush=True)
+    corm.corm_compact(st.desc, st.K, st.V, st.pos, st.last_hit, st.lens, st.keep, st.kept_idx, st.workspace)
+    torch.cuda.synchronize()
+    for u, kind in enumerate(kinds):
+        idx = torch.nonzero(keep[u, :lens[u]]).squeeze(1)
+        n = len(idx)
+        assert int(st.lens[0, u]) == n, kind
+        assert torch.equal(st.kept_idx[0, u, :n].long(), idx), kind
+        for name, old in before.items():
+            assert torch.equal(getattr(st, name)[0, u, :n], old[0, u, idx]), (kind, name)
