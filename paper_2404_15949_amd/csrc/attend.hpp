@@ -145,22 +145,27 @@ __device__ __forceinline__ void stage_live_masks(const Params& p, int unit, cons
   __syncthreads();
 }
 
+// G: query heads this workgroup serves.  A launch that would leave the chip idle shares a unit's query heads among
+// p.head_groups workgroups (each then streams the part's rows, out of the L2 from the second on).
 template <typename DT, int D, int G, bool LAZY>
 __global__ __launch_bounds__(WG) void corm_attend_kernel(const Params p) {
   using A = Attend<DT, D, G, WAVES>;
   constexpr int EPL = A::EPL, ROWB = A::ROWB, LPR = A::LPR, RPL = A::RPL;
 
   const int split = blockIdx.x;
-  const int unit = blockIdx.y;
+  const int unit = p.head_groups == 1 ? blockIdx.y : blockIdx.y / p.head_groups;
+  const int hgroup = blockIdx.y - unit * p.head_groups;
   const UnitLen ul = unit_len(p, unit);
   const int L = ul.L;
-  // (boolean message) the row of this step is cleared here, one launch before the record kernel sets bits
-  if (split == 0) clear_bit_rows(p, unit / p.Hkv, (unit % p.Hkv) * G, G, WG);
-  if (split == 0 && threadIdx.x == 0 && p.do_evict) p.unit_state[unit] = make_int2(L, 0);   // (the record launch counts)
-  if (split * p.part_keys >= L) return;   // no live key in this part
-
   const int b = unit / p.Hkv;
   const int hkv = unit - b * p.Hkv;
+  const int hq0 = (hkv * p.head_groups + hgroup) * G;   // first query head of this workgroup
+  // (boolean message) the row of this step is cleared here, one launch before the record kernel sets bits
+  if (split == 0) clear_bit_rows(p, b, hq0, G, WG);
+  if (split == 0 && hgroup == 0 && threadIdx.x == 0 && p.do_evict)
+    p.unit_state[unit] = make_int2(L, 0);   // (the record launch counts)
+  if (split * p.part_keys >= L) return;   // no live key in this part
+
   const int tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
   const int sub = lane / LPR, cl = lane % LPR;
@@ -173,14 +178,14 @@ __global__ __launch_bounds__(WG) void corm_attend_kernel(const Params p) {
 
   char* Kb = reinterpret_cast<char*>(p.K) + (size_t)unit * p.Lcap * ROWB;
   char* Vb = reinterpret_cast<char*>(p.V) + (size_t)unit * p.Lcap * ROWB;
-  const int hq0 = hkv * G;
   // this workgroup's keys: a whole 512-key chunk, or (launches with few units) a fraction of one; the
   // unrolled pipeline below simply ends early
   const int cbeg = split * p.part_keys;
   const int cend = min(cbeg + p.part_keys, L);
 
   // The append: the owner of the chunk that holds the new slot writes the row and its metadata into the
-  // cache first; after the barrier every wave of this workgroup reads it back like any other row.
+  // cache first; after the barrier every wave of this workgroup reads it back like any other row.  (Workgroups
+  // that share the unit's heads all write the same bytes, each for itself.)
   if (ul.appended && ul.L0 >= cbeg && ul.L0 < cend) {   // this workgroup owns the new slot
     if (wv == 0) {
       if (lane < LPR) {

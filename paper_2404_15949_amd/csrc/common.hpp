@@ -40,6 +40,7 @@ struct Params {
   int32_t ring_bits;    // the ring holds the boolean message: one bit per (row, position), 32 positions per word
   int32_t ring_words;   // words per ring row in that case: ceil(Tcap / 32)
   int32_t part_keys;    // split path: keys per attend workgroup (CHUNK, or a fraction of it when the launch has few units)
+  int32_t head_groups;  // split path, vector-ALU kernel: workgroups that share the query heads of a unit's part
   int32_t npart;        // partials per head in the workspace: nsplit * (CHUNK / smallest part)
   int32_t kb_stride;    // 64-bit words per unit in keepbits
   int32_t lazy;         // lazy mode: dead slots are skipped
@@ -216,26 +217,36 @@ __device__ __forceinline__ void clear_bit_rows(const Params& p, int b, int hq0, 
   }
 }
 
-// Sets the bits of the keys this wave found important for one head.  pos: this lane's key position
-// (any value where !valid); hit implies valid.  When the valid lanes hold consecutive positions
-// (lane l: base + l) the wave's ballot is shifted into at most three words and three lanes issue one
-// atomic each; otherwise every hit lane sets its own bit.
-__device__ __forceinline__ void record_bits(uint32_t* row, int ring_words, int pos, bool valid, bool hit) {
+// How a wave's valid lanes lie: `run` if they hold consecutive positions (lane l: base + l).  The same for every
+// head, so it is found once per key.
+struct BitRun {
+  bool run;
+  int base;
+};
+__device__ __forceinline__ BitRun bit_run(int pos, bool valid) {
   const int lane = threadIdx.x & 63;
   const unsigned long long vmask = __ballot(valid);
-  if (vmask == 0ull) return;
-  const int first = __ffsll((long long)vmask) - 1;
-  const int base = __shfl(pos, first) - first;
-  const bool run = __all(!valid || pos == base + lane) && base >= 0;
+  const int first = vmask ? __ffsll((long long)vmask) - 1 : 0;
+  BitRun r;
+  r.base = __builtin_amdgcn_readlane(pos, first) - first;
+  r.run = __all(!valid || pos == r.base + lane) && r.base >= 0;
+  return r;
+}
+
+// Sets the bits of the keys this wave found important for one head.  pos: this lane's key position; hit implies a
+// valid lane.  A run: the wave's ballot is shifted into at most three words and three lanes issue one atomic each;
+// otherwise every hit lane sets its own bit.
+__device__ __forceinline__ void record_bits(uint32_t* row, int ring_words, const BitRun& r, int pos, bool hit) {
+  const int lane = threadIdx.x & 63;
   const unsigned long long hmask = __ballot(hit);
   if (hmask == 0ull) return;
-  if (run) {
-    const int sh = base & 31;
+  if (r.run) {
+    const int sh = r.base & 31;
     const unsigned long long lo = hmask << sh;                        // bits 0..63 of the shifted mask
     const uint32_t hi = sh ? (uint32_t)(hmask >> (64 - sh)) : 0u;     // bits 64..95
     if (lane < 3) {
       const uint32_t part = lane == 0 ? (uint32_t)lo : (lane == 1 ? (uint32_t)(lo >> 32) : hi);
-      const int w = (base >> 5) + lane;
+      const int w = (r.base >> 5) + lane;
       if (part && w < ring_words) atomicOr(&row[w], part);
     }
   } else if (hit) {

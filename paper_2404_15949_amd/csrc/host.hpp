@@ -122,6 +122,7 @@ void bind_params(const corm_desc* d, const WorkspaceLayout& wl, void* workspace,
   p.nsplit = wl.nsplit;
   p.npart = wl.nsplit * MAX_PARTS_PER_CHUNK;
   p.part_keys = CHUNK;
+  p.head_groups = 1;
   p.thr_scale = d->thr_scale;
   const float sm = d->sm_scale > 0.f ? d->sm_scale : 1.0f / sqrtf((float)d->d);
   p.scale_log2 = sm * LOG2E;
@@ -153,18 +154,22 @@ int launch_attend_gqa(const Params& p, int G, dim3 grid, hipStream_t s) {
   return launch_status();
 }
 
+// grouped queries, bf16, d = 128: q.K^T on the matrix cores
+bool attend_on_mfma(const corm_desc* d, const LaunchCtx& c) {
+  return d->kv_dtype == CORM_BF16 && d->d == 128 && d->Hq > d->Hkv && c.path != 3;
+}
+
 template <bool LAZY>
 int launch_attend_dt(const corm_desc* d, const Params& p, const LaunchCtx& c, int G, dim3 grid, hipStream_t s) {
   if (d->kv_dtype == CORM_F32)
     return d->d == 64 ? launch_attend_g<F32, 64, LAZY>(p, G, grid, s) : launch_attend_g<F32, 128, LAZY>(p, G, grid, s);
-  // grouped queries, bf16, d = 128: q.K^T on the matrix cores
-  if (d->d == 128 && G > 1 && c.path != 3) return launch_attend_gqa<LAZY>(p, G, grid, s);
+  if (attend_on_mfma(d, c)) return launch_attend_gqa<LAZY>(p, G, grid, s);
   return d->d == 64 ? launch_attend_g<BF16, 64, LAZY>(p, G, grid, s) : launch_attend_g<BF16, 128, LAZY>(p, G, grid, s);
 }
 
 int launch_attend(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStream_t s) {
-  const int G = d->Hq / d->Hkv;
-  const dim3 grid((d->Lcap + p.part_keys - 1) / p.part_keys, d->B * d->Hkv);
+  const int G = d->Hq / d->Hkv / p.head_groups;
+  const dim3 grid((d->Lcap + p.part_keys - 1) / p.part_keys, d->B * d->Hkv * p.head_groups);
   if (c.ev0 && hipEventRecord(c.ev0, s) != hipSuccess) return CORM_EHIP;
   const int rc = p.lazy ? launch_attend_dt<true>(d, p, c, G, grid, s) : launch_attend_dt<false>(d, p, c, G, grid, s);
   if (rc) return rc;
@@ -265,9 +270,7 @@ int launch_record(const corm_desc* d, const Params& p, const LaunchCtx& c, hipSt
 // launch would otherwise have fewer than about two workgroups per compute unit.  A part must hold whole
 // pairs of pipeline stages of the kernel that runs.
 int attend_part_keys(const corm_desc* d, const LaunchCtx& c) {
-  const int G = d->Hq / d->Hkv;
-  const bool mfma = d->kv_dtype == CORM_BF16 && d->d == 128 && G > 1 && c.path != 3;
-  const int stage_rows = mfma ? WAVES * 16 : WAVES * (64 / (row_bytes(d) / 16)) * UNROLL;
+  const int stage_rows = attend_on_mfma(d, c) ? WAVES * 16 : WAVES * (64 / (row_bytes(d) / 16)) * UNROLL;
   const long want = 2L * c.cus;
   const long wgs = (long)d->B * d->Hkv * ((d->Lcap + CHUNK - 1) / CHUNK);
   int part = CHUNK;
@@ -275,10 +278,23 @@ int attend_part_keys(const corm_desc* d, const LaunchCtx& c) {
   return part;
 }
 
+// Workgroups that share a unit's query heads on the split path (vector-ALU kernel): while the launch would have fewer
+// than two workgroups per compute unit, so that a part's dots and products of G heads do not run one after the
+// other on a few of them (9 units of 8 heads, d 64, 840 keys: 63 workgroups 13.9 us, 504 of one head each 7.3 us).
+int attend_head_groups(const corm_desc* d, const LaunchCtx& c, int part_keys) {
+  if (attend_on_mfma(d, c)) return 1;
+  const int G = d->Hq / d->Hkv;
+  const long wgs = (long)d->B * d->Hkv * ((d->Lcap + part_keys - 1) / part_keys);
+  int n = 1;
+  while (n < G && wgs * n * 2 <= 2L * c.cus && (long)d->B * d->Hkv * n * 2 <= 65535) n *= 2;
+  return n;
+}
+
 int launch_attend_record(const corm_desc* d, const Params& p0, const LaunchCtx& c, hipStream_t s) {
   if (use_unit_path(d, c)) return launch_unit(d, p0, c, s);
   Params p = p0;
   p.part_keys = attend_part_keys(d, c);
+  p.head_groups = attend_head_groups(d, c, p.part_keys);
   const int rc = launch_attend(d, p, c, s);
   if (rc) return rc;
   return launch_record(d, p, c, s);

@@ -9,6 +9,8 @@ namespace {
 
 // RECORD_CHUNKS: 512-slot chunks per workgroup (more keys per workgroup amortize its fixed chain of
 // dependent loads; fewer keep the chip full when the launch has few units)
+constexpr int OUT_WAVE_PARTS = 16;   // up to here one wave folds the partial rows of an item alone
+
 template <int G, int RECORD_CHUNKS>
 __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const int D) {
   constexpr int RECORD_ROWS = RECORD_CHUNKS * CHUNK;  // keys per workgroup
@@ -58,16 +60,19 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   const int tcur = p.t[b];
   const int tfirst = p.do_evict ? p.t_first[b] : tcur;
 
-  // global max and sum of Eq. 2 from the split partials (wave g handles head g, g + WAVES, ...)
+  // global max and sum of Eq. 2 from the split partials (wave g handles head g, g + WAVES, ...); the first 64 partials
+  // stay in registers between the max and the sum
   for (int g = wv; g < G; g += WAVES) {
     const float* part0 = p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE;
-    float mx = neg_inf();
-    for (int s = lane; s < nparts; s += 64) mx = fmaxf(mx, part0[(size_t)s * PSTRIDE]);
+    float2 first = make_float2(neg_inf(), 0.f);
+    if (lane < nparts) first = *reinterpret_cast<const float2*>(part0 + (size_t)lane * PSTRIDE);
+    float mx = first.x;
+    for (int s = lane + 64; s < nparts; s += 64) mx = fmaxf(mx, part0[(size_t)s * PSTRIDE]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     const float ms = mx == neg_inf() ? 0.f : mx;
-    float zt = 0.f;
-    for (int s = lane; s < nparts; s += 64) {
+    float zt = first.y * exp2f(first.x - ms);
+    for (int s = lane + 64; s < nparts; s += 64) {
       const float* ps = part0 + (size_t)s * PSTRIDE;
       zt = fmaf(ps[1], exp2f(ps[0] - ms), zt);
     }
@@ -80,30 +85,46 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   }
   __syncthreads();
 
-  // out (Eq. 1): (head, block of 64 columns) items of the unit are dealt round-robin to its
-  // workgroups; lane = column, so every split's partial row is read as one contiguous 256-byte piece
-  // and the loads of all splits are independent (no cross-lane reduction, one memory latency per item)
-  // An item belongs to one workgroup; its waves take the splits round-robin and meet in LDS.
+  // out (Eq. 1): (head, block of 64 columns) items of the unit are dealt round-robin; lane = column, so every split's
+  // partial row is read as one contiguous 256-byte piece and the loads of all splits are independent (no cross-lane
+  // reduction, one memory latency per item).  Few splits: an item belongs to one wave, many items in flight and no
+  // barrier.  Many splits: to one workgroup, whose waves take the splits
+  // round-robin and meet in LDS.
   const int cblocks = D / 64;
-  for (int item = rsplit; item < G * cblocks; item += nwg) {   // (uniform over the workgroup)
-    const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
-    const float* part0 = p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE;
-    const float ms = sh_M[g];
-    float at = 0.f;
+  if (nparts <= OUT_WAVE_PARTS) {
+    for (int item = rsplit * WAVES + wv; item < G * cblocks; item += nwg * WAVES) {
+      const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
+      const float* part0 = p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE;
+      const float ms = sh_M[g];
+      float at = 0.f;
+#pragma unroll 8
+      for (int s = 0; s < nparts; ++s) {
+        const float* ps = part0 + (size_t)s * PSTRIDE;
+        at = fmaf(ps[2 + c], exp2f(ps[0] - ms), at);
+      }
+      p.out[(size_t)(b * p.Hq + hq0 + g) * D + c] = L > 0 ? at / sh_Z[g] : 0.f;
+    }
+  } else {
+    for (int item = rsplit; item < G * cblocks; item += nwg) {   // (uniform over the workgroup)
+      const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
+      const float* part0 = p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE;
+      const float ms = sh_M[g];
+      float at = 0.f;
 #pragma unroll 4
-    for (int s = wv; s < nparts; s += WAVES) {
-      const float* ps = part0 + (size_t)s * PSTRIDE;
-      at = fmaf(ps[2 + c], exp2f(ps[0] - ms), at);
-    }
-    sh_out[wv][lane] = at;
-    __syncthreads();
-    if (wv == 0) {
-      float tot = 0.f;
+      for (int s = wv; s < nparts; s += WAVES) {
+        const float* ps = part0 + (size_t)s * PSTRIDE;
+        at = fmaf(ps[2 + c], exp2f(ps[0] - ms), at);
+      }
+      sh_out[wv][lane] = at;
+      __syncthreads();
+      if (wv == 0) {
+        float tot = 0.f;
 #pragma unroll
-      for (int i = 0; i < WAVES; ++i) tot += sh_out[i][lane];
-      p.out[(size_t)(b * p.Hq + hq0 + g) * D + c] = L > 0 ? tot / sh_Z[g] : 0.f;
+        for (int i = 0; i < WAVES; ++i) tot += sh_out[i][lane];
+        p.out[(size_t)(b * p.Hq + hq0 + g) * D + c] = L > 0 ? tot / sh_Z[g] : 0.f;
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
   if (L == 0) return;  // an empty unit: nothing to record
 
@@ -127,6 +148,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
       const bool pos_ok = live && my_pos[k] >= 0 && my_pos[k] < p.Tcap;
       if (live && !pos_ok && p.status) atomicOr(p.status, CORM_DEV_BAD_STEP);
       bool hit = false;
+      const BitRun run = bit_run(my_pos[k], pos_ok);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const float sc = live ? exp2f(lg[k][g] - sh_M[g]) / sh_Z[g] : 0.f;
@@ -134,7 +156,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
         hit |= hg;
         if (p.ring && step_ok)
           record_bits(reinterpret_cast<uint32_t*>(p.ring) + ((size_t)(b * p.Hq + hq0 + g) * p.w + slot) * p.ring_words,
-                      p.ring_words, my_pos[k], pos_ok, hg && pos_ok);
+                      p.ring_words, run, my_pos[k], hg && pos_ok);
       }
       if (live) {
         int lh = my_lh[k];

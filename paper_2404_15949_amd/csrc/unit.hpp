@@ -279,6 +279,7 @@ __global__ __launch_bounds__(UNIT_WG) void corm_unit_kernel(const Params p, cons
       const bool pos_ok = live && my_pos >= 0 && my_pos < p.Tcap;
       if (live && !pos_ok && p.status) atomicOr(p.status, CORM_DEV_BAD_STEP);
       bool hit = false;
+      const BitRun run = bit_run(my_pos, pos_ok);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const float sc = live ? fast_exp2(sh_logit[g * lstride + i] - sh_M[g]) / sh_Z[g] : 0.f;
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(UNIT_WG) void corm_unit_kernel(const Params p, cons
         hit |= hg;
         if (p.ring && step_ok)
           record_bits(reinterpret_cast<uint32_t*>(p.ring) + ((size_t)(b * p.Hq + hq0 + g) * p.w + slot) * p.ring_words,
-                      p.ring_words, my_pos, pos_ok, hg && pos_ok);
+                      p.ring_words, run, my_pos, hg && pos_ok);
       }
       bool keep = false;
       if (live) {

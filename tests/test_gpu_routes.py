@@ -112,3 +112,57 @@ def test_compact_on_both_sides_of_the_slab_limit(dtype, d, Lcap):
         assert torch.equal(st.kept_idx[0, u, :n].long(), idx), kind
         for name, old in before.items():
             assert torch.equal(getattr(st, name)[0, u, :n], old[0, u, idx]), (kind, name)
+
+
+# kv dtype, G, Hkv, d, Lcap: few units whose heads are shared by workgroups (1, 2, 4, 8 of them), lengths on both sides
+# of a part, and the largest small units that one workgroup takes whole
+ROUTES = [("bf16", 8, 1, 64, 1000), ("f32", 8, 2, 64, 520), ("f32", 4, 3, 128, 700), ("bf16", 4, 40, 64, 900),
+          ("f32", 2, 30, 128, 515), ("bf16", 1, 4, 64, 1600), ("bf16", 1, 4, 64, 1601), ("f32", 2, 1, 64, 400)]
+
+
+@pytest.mark.parametrize("ring", ["f32", "bit", None])
+@pytest.mark.parametrize("case", range(len(ROUTES)))
+def test_default_route_of_a_small_launch_equals_torch(case, ring):
+    """One step by the route the rules choose against a softmax in float64 on the same stored bits: out, the recorded row and
+    last_hit.  out: fp32 sums of at most 1600 terms and a 2^x of about 1 ulp: 1e-5 of the largest element.  A score
+    within that of c/t may fall on either side."""
+    dtype, G, Hkv, d, Lcap = ROUTES[case]
+    print("[case]", ROUTES[case], ring, flush=True)
+    B, Hq, tdt = 1, G * Hkv, torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(case)
+    st = corm.LayerState(B, Hq, Hkv, d, Lcap, Lcap, 4, 4, dtype, device=DEV, want_ring=ring is not None, score_dtype=ring)
+    lens = torch.randint(1, Lcap, (B, Hkv), device=DEV, generator=g, dtype=torch.int32)
+    lens.view(-1)[0] = Lcap - 1
+    st.K.copy_(torch.randn(B, Hkv, Lcap, d, device=DEV, generator=g).to(tdt))
+    st.V.copy_(torch.randn(B, Hkv, Lcap, d, device=DEV, generator=g).to(tdt))
+    st.pos.copy_(torch.arange(Lcap, device=DEV, dtype=torch.int32))
+    st.lens.copy_(lens)
+    q = torch.randn(B, Hq, d, device=DEV, generator=g).to(tdt)
+    k, v = (torch.randn(B, Hkv, d, device=DEV, generator=g).to(tdt) for _ in range(2))
+    t = torch.full((B,), Lcap, dtype=torch.int32, device=DEV)
+    st.step_attend(q, k, v, t, t)                       # the window is not full: nothing goes
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == 0
+    for h in range(Hkv):
+        n = int(lens[0, h])
+        K = torch.cat([st.K[0, h, :n], k[0, h][None]]).double()
+        V = torch.cat([st.V[0, h, :n], v[0, h][None]]).double()
+        a = torch.softmax(q[0, h * G:(h + 1) * G].double() @ K.t().contiguous() / d ** 0.5, dim=-1)
+        want = a @ V
+        got = st.out[0, h * G:(h + 1) * G].double()
+        assert ((got - want).abs().amax(1) <= 1e-5 * want.abs().amax(1)).all()
+        assert torch.equal(st.K[0, h, n], k[0, h]) and torch.equal(st.V[0, h, n], v[0, h])
+        # (without a ring on a bf16 cache the score is compared as a bf16 ring would hold it: half an ulp, 2^-8 at most)
+        clear = (a * Lcap - 1).abs() > (2.0 ** -8 if ring is None and dtype == "bf16" else 0) + 1e-4
+        hits = a * Lcap >= 1
+        pos = torch.cat([torch.arange(n, device=DEV), torch.tensor([Lcap - 1], device=DEV)])
+        assert torch.equal(st.pos[0, h, :n + 1].long(), pos)
+        sure = clear.all(0)
+        assert torch.equal((st.last_hit[0, h, :n + 1] == Lcap)[sure], hits.any(0)[sure])
+        if ring == "f32":
+            row = st.ring[0, h * G:(h + 1) * G, (Lcap - 1) % 4][:, pos].double()
+            assert ((row - a).abs() <= 1e-5 * a + 1e-9).all()
+        if ring == "bit":
+            words = st.ring[0, h * G:(h + 1) * G, (Lcap - 1) % 4]
+            bits = ((words[:, pos // 32] >> (pos % 32)) & 1).bool()
+            assert torch.equal(bits[clear], hits[clear])
