@@ -105,6 +105,8 @@ def _ptr(x) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if torch.cuda.is_initialized():   # the handle alone: building a Stream object takes longer than a launch
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
