@@ -595,22 +595,33 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void
   prefill_pass<DT, D, 2, MODE>(a);
 }
 
-// boolean message: zero the words of the rows of steps tau_0 .. tau_{m-1} that pass 2 may set bits in
-// (positions < tau); workgroup = 16 rows of one head
+// boolean message: zero the words of the rows of steps tau_0 .. tau_{m-1} that pass 2 may set single bits in
+// (positions < tau); workgroup = 16 rows of one head.  Words that pass 2 stores whole are left to it: slot and position
+// agree over the 64 slots that hold the word and its neighbour (positions ascend, so the first and the last tell), and
+// every query whose step lies behind the word's first position sees a key there.  A prompt without holes leaves
+// next to nothing to clear: 512 heads x 1024 rows x 8192 positions 132 -> CLEAR_US us.
 __global__ __launch_bounds__(256) void corm_prefill_clear_bits_kernel(const PrefillArgs a) {
   const int head = blockIdx.x;   // (heads in x: B * Hq may exceed the 65535 rows a grid has in y)
-  const int tcur = a.t[head / a.Hq];
+  const int b = head / a.Hq;
+  const int tcur = a.t[b];
   const int tau0 = tcur - a.m + 1;
   if (tau0 < 1 || tcur > a.Tcap) return;
+  const int unit = b * a.Hkv + (head - b * a.Hq) / (a.Hq / a.Hkv);
+  int L = a.lens[unit];
+  L = L < 0 ? 0 : (L > a.Lcap ? a.Lcap : L);
+  const int32_t* posb = a.pos + (size_t)unit * a.Lcap;
   const int s0 = (tau0 - 1) % a.w;
-  for (int jr = 0; jr < 16; ++jr) {
-    const int j = blockIdx.y * 16 + jr;
-    if (j >= a.m) break;
-    int slot = s0 + j;
-    if (slot >= a.w) slot -= a.w;
-    uint32_t* row = reinterpret_cast<uint32_t*>(a.ring) + ((size_t)head * a.w + slot) * a.ring_words;
-    const int nw = min((tau0 + j + 31) >> 5, a.ring_words);
-    for (int i = threadIdx.x; i < nw; i += 256) row[i] = 0u;
+  const int j0 = blockIdx.y * 16, j1 = min(j0 + 16, a.m);
+  const int nw_max = min((tau0 + j1 - 1 + 31) >> 5, a.ring_words);
+  for (int i = threadIdx.x; i < nw_max; i += 256) {
+    const int k0 = (i >> 1) * 64;
+    if (k0 + 64 <= L && posb[k0] == k0 && posb[k0 + 63] == k0 + 63) continue;
+    for (int j = j0; j < j1; ++j) {
+      int slot = s0 + j;
+      if (slot >= a.w) slot -= a.w;
+      if (i < (tau0 + j + 31) >> 5)
+        reinterpret_cast<uint32_t*>(a.ring)[((size_t)head * a.w + slot) * a.ring_words + i] = 0u;
+    }
   }
 }
 
