@@ -599,7 +599,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void
 // (positions < tau); workgroup = 16 rows of one head.  Words that pass 2 stores whole are left to it: slot and position
 // agree over the 64 slots that hold the word and its neighbour (positions ascend, so the first and the last tell), and
 // every query whose step lies behind the word's first position sees a key there.  A prompt without holes leaves
-// next to nothing to clear: 512 heads x 1024 rows x 8192 positions 132 -> CLEAR_US us.
+// next to nothing to clear: 512 heads x 1024 rows x 8192 positions 132 -> 37 us.
 __global__ __launch_bounds__(256) void corm_prefill_clear_bits_kernel(const PrefillArgs a) {
   const int head = blockIdx.x;   // (heads in x: B * Hq may exceed the 65535 rows a grid has in y)
   const int b = head / a.Hq;
