@@ -328,6 +328,9 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
       misaligned4(kept_idx) || misaligned4(status))
     return CORM_EINVAL;
   if (m < 1 || m > desc->w) return CORM_EINVAL;
+  LaunchCtx ctx;
+  rc = make_ctx(nullptr, &ctx);
+  if (rc) return rc;
   if ((m + 15) / 16 > 65535) return CORM_EUNSUPPORTED;   // grid rows of the clear / merge launches
   WorkspaceLayout wl;
   rc = check_workspace(desc, workspace, workspace_bytes, &wl);
@@ -348,7 +351,7 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
   a.units = units;
   const long long key_blocks = (long long)PREFILL_XCDS * ((units + PREFILL_XCDS - 1) / PREFILL_XCDS) * wl.seed_nkb;
   if (key_blocks > 2147483647LL) return CORM_EUNSUPPORTED;
-  seed_segments(desc, m, key_blocks, &a.nseg, &a.seg_blocks);
+  seed_segments(desc, ctx, m, key_blocks, &a.nseg, &a.seg_blocks);
   const dim3 grid((unsigned)(key_blocks * a.nseg));
   const dim3 mgrid(desc->B * desc->Hq, (m + 255) / 256);
   if (a.ring_bits && score_ring) {

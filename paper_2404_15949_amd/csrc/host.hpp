@@ -362,16 +362,32 @@ int launch_compact(const corm_desc* d, const WorkspaceLayout& wl, void* workspac
   return launch_status();
 }
 
-// How many workgroups share the query blocks of a key block (prompt seeding): one while the key blocks alone
-// fill the chip, else enough for about SEED_WGS workgroups, of at least SEED_MIN_BLOCKS query blocks each (a
-// workgroup loads its keys once, whatever the number of blocks).  16 units x 2000 fp32 keys, 8 blocks of queries:
-// one workgroup per key block 48 + 74 us for the two passes, four 30 + 39 us.
-constexpr int SEED_WGS = 1024, SEED_MIN_BLOCKS = 2;
-void seed_segments(const corm_desc* d, int m, long long key_blocks, int32_t* nseg, int32_t* seg_blocks) {
+// How many workgroups share the query blocks of a key block (prompt seeding).
+// bf16, where the latency of a block bounds the passes: a workgroup's time is its blocks and about one more (it loads its
+// keys once, whatever the number of blocks), the launch takes that times the workgroups that each of two slots per
+// compute unit gets, at least one; a split that gains less than a twentieth by this count is not made (4 units x 900
+// keys, w 256: 49.6 us unsplit, 28.1; 8 units x 5000, w 700: 86.8, 60.3).
+// fp32, where the matrix cores bound them: about SEED_WGS workgroups of at least two blocks, and no split in two, after
+// which some compute units have two workgroups and others one (16 units x 2000 keys, 8 blocks: one workgroup 48 + 74
+// us for the two passes, four 30 + 39 (two workgroups 45 us more than four); 16 units x 3000, 5 blocks: one 32 + 40, two 37 + 42).
+constexpr int SEED_WGS = 1024;
+void seed_segments(const corm_desc* d, const LaunchCtx& c, int m, long long key_blocks, int32_t* nseg,
+                   int32_t* seg_blocks) {
   const int qt = (row_bytes(d) <= 256 ? PrefillGeom<256>::QT : PrefillGeom<512>::QT);
   const int blocks = ((m + 15) / 16 * (d->Hq / d->Hkv) + qt - 1) / qt;
-  const long long want = (SEED_WGS + key_blocks - 1) / key_blocks;
-  const int n = (int)std::max(1LL, std::min(want, (long long)(blocks / SEED_MIN_BLOCKS)));
+  int n = 1;
+  if (d->kv_dtype == CORM_F32) {
+    n = (int)std::min((SEED_WGS + key_blocks - 1) / key_blocks, (long long)(blocks / 2));
+    if (n < 3) n = 1;
+  } else {
+    double best = 0.;
+    for (int i = 1; i <= std::min(blocks, 64); ++i) {
+      const double cost = std::max(1., (double)key_blocks * i / (2. * c.cus)) * ((blocks + i - 1) / i + 1);
+      if (i > 1 && cost > 0.95 * best) continue;
+      best = cost;
+      n = i;
+    }
+  }
   *seg_blocks = (blocks + n - 1) / n;
   *nseg = (blocks + *seg_blocks - 1) / *seg_blocks;
 }

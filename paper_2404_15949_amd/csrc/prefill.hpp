@@ -79,11 +79,10 @@ __device__ __forceinline__ float prefill_score(float d, float scale_log2, float 
   return fast_exp2(fmaf(d, scale_log2, -ms)) * inv;
 }
 
-// (x << 1) | this lane's bit of the mask, in one instruction
-__device__ __forceinline__ uint32_t shift_in(uint32_t x, unsigned long long mask) {
-  unsigned long long carry_out;
-  asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(x), "=s"(carry_out) : "s"(mask));
-  return x;
+// (x << 1) | the sign of t, in one instruction that touches no scalar register: a compare would put its result there,
+// and every reader of it waits
+__device__ __forceinline__ uint32_t shift_in_sign(uint32_t x, float t) {
+  return __builtin_amdgcn_alignbit(x, __float_as_uint(t), 31);
 }
 
 // What the ring holds: which form of Def. 3.1 pass 2 evaluates (an instance each).
@@ -94,7 +93,7 @@ enum { SEED_BF16 = 0, SEED_F32 = 1, SEED_BITS = 2 };
 //   score rings   z = the smallest fp32 score whose stored value reaches thr.  bf16: rounding to nearest even is
 //                 monotone, so "stored >= thr" is "score >= z" with z the midpoint below the smallest bf16 >= thr
 //                 (or the next fp32, where that midpoint rounds down).  fp32: z = thr.
-//   boolean ring  [z, w): raw logits at or above w are important, those below z are not, and only those between
+//   boolean ring  (z, w]: raw logits above w are important, those up to z are not, and only those between
 //                 need the score itself.  The band is the threshold in the logit domain -+ a bound on every
 //                 rounding between a logit and its score (products, fma, exp2, 1/sum, the logarithms here: together
 //                 below 2e-6 of the terms), so the decisions are bit for bit those of the score.
@@ -307,6 +306,28 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
   for (int tl = 0; tl < T; ++tl)
 #pragma unroll
     for (int r = 0; r < 4; ++r) hm[tl][r] = 0;
+  // Boolean ring: fast blocks only shift a bit per key and tile into a history; every 32 tiles, or where their run ends,
+  // the newest set bit of each becomes a step.  (With score rings, whose tail is longer, the registers cost more than
+  // the compares: 1.22 -> 1.24 ms.)
+  constexpr bool HIST = PASS == 2 && MODE == SEED_BITS;
+  uint32_t hist[T][4];
+#pragma unroll
+  for (int tl = 0; tl < T; ++tl)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) hist[tl][r] = 0u;
+  int hist_n = 0, hist_tt = 0;   // tiles in it, the newest one
+  auto settle = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int tl = 0; tl < T; ++tl)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int back = __ffs((int)hist[tl][r]) - 1;
+        const int tau = tau0 + ((hist_tt - back) >> lgG) * 16 + n;
+        if (hist[tl][r]) hm[tl][r] = max(hm[tl][r], tau);
+        hist[tl][r] = 0u;
+      }
+    hist_n = 0;
+  };
 
   auto stage = [&](int buf, const u32x4_t (&qr)[QLOADS], const float4& str) __attribute__((always_inline)) {
 #pragma unroll
@@ -337,6 +358,11 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
       const bool fast = tt0 + QT <= ntt && ((tt0 + QT - 1) >> lgG) * 16 + 15 < a.m &&
                         pos_wmax <= tau0 + (tt0 >> lgG) * 16 - 1 && (PASS == 1 || (rows_ok && offsets32));
       if (fast) {
+        if (HIST) {
+          if (hist_n + QT > 32 || (hist_n && hist_tt + 1 != tt0)) settle();
+          hist_n += QT;
+          hist_tt = tt0 + QT - 1;
+        }
         f32x4_t dn[T];
         mma_tile(cur, 0, dn);
 #pragma unroll
@@ -352,18 +378,15 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
             if (lg == 0) sh_part[wv][(blk - grp) * QBLK + ti * 16 + n] = make_float2(mx, z);
           } else if (MODE == SEED_BITS) {
             const float4 st = sh_st[cur][ti * 16 + n];
-            unsigned long long unsure = 0ull;
-            uint32_t hbits = 0u;
+            uint32_t unsure = 0u, hbits = 0u;
 #pragma unroll
             for (int i = 4 * T - 1; i >= 0; --i) {   // key i of the lane's run: row i % 4 of key tile i / 4
-              const float x = d[i >> 2][i & 3];
-              const bool hit = x >= st.w;
-              const unsigned long long hits = __ballot(hit);
-              hm[i >> 2][i & 3] = hit ? tau : hm[i >> 2][i & 3];
-              hbits = shift_in(hbits, hits);
-              unsure |= __ballot(x >= st.z) ^ hits;
+              const float above = st.w - d[i >> 2][i & 3], below = st.z - d[i >> 2][i & 3];
+              hist[i >> 2][i & 3] = shift_in_sign(hist[i >> 2][i & 3], above);
+              hbits = shift_in_sign(hbits, above);
+              unsure |= __float_as_uint(above) ^ __float_as_uint(below);
             }
-            if (unsure) {   // (uniform, rare) what lies in the band is decided by the score; the rest stays
+            if (__any((int)unsure < 0)) {   // (uniform, rare) what lies in the band is decided by the score
               const float thr = importance_threshold(a.thr_scale, tau);
 #pragma unroll 1
               for (int tl = 0; tl < T; ++tl) {
@@ -373,7 +396,7 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
                   hbits |= (prefill_score(x[r], a.scale_log2, st.x, st.y) >= thr ? 1u : 0u) << (4 * tl + r);
               }
 #pragma unroll
-              for (int i = 0; i < 4 * T; ++i) hm[i >> 2][i & 3] = (hbits >> i) & 1u ? tau : hm[i >> 2][i & 3];
+              for (int i = 0; i < 4 * T; ++i) hist[i >> 2][i & 3] |= (hbits >> i) & 1u;
             }
             // the wave owns whole words of every query's row: plain stores
             const __amdgpu_buffer_rsrc_t rr = head_ring(g);
@@ -547,6 +570,7 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
   }
 
   if (PASS == 2) {
+    if (HIST) settle();
     // the latest hit of every key over the 16 queries of a tile, one key per lane (through LDS: a lane's 4*T keys
     // read and written one after the other cost as many memory latencies)
     __syncthreads();   // sh_pos of this wave is free
@@ -581,8 +605,8 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
 // and LDS of three (0.91 -> 0.64 ms for 512 heads x 1024 queries x 4096 keys).  Pass 2 needs the registers of two
 // (205; held to three it spills: 1.27 -> 1.76 ms).  Both are bound by vector instructions: per tile of 16 queries x
 // 64 keys 16 MFMAs and about 90 (pass 1), 102 (bf16 scores), 80 (bits) others.  Measured: bf16 scores 1.39 -> 1.27 ms
-// (ring written at 3.4 TB/s); bits, 512 heads x 1024 x 8192, 3.22 -> 2.07 ms (one wave per SIMD and a score per pair
-// before); fp32, 16 units of 2000 keys, 74 -> 39 us (the queries of a key block shared by several workgroups).
+// (ring written at 3.4 TB/s); bits, 512 heads x 1024 x 8192, 3.22 -> 1.62 ms (one wave per SIMD and a score per pair
+// before; 2.04 with compares whose results went through scalar registers); fp32, 16 units of 2000 keys, 74 -> 39 us (the queries of a key block shared by several workgroups).
 template <typename DT, int D>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void corm_prefill_stats_kernel(
     const PrefillArgs a) {
