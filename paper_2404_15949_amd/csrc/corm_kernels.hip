@@ -3,8 +3,8 @@
 // One decode step of one layer, on one stream, with kernel boundaries as the only cross-workgroup
 // synchronization (no device-wide fences, no spinning inside the kernels):
 //
-//   many units (>= compute units, logits fit LDS):   unit kernel | compact local | compact boundary
-//   few units:                       attend | record | compact local | compact boundary
+//   many units (>= compute units, logits fit LDS), or small ones:   unit kernel | compact
+//   few units:                                                       attend | record | compact
 //
 //   unit     one workgroup per unit streams its K and V once, keeps the logits in LDS, writes the new
 //            row (append), out (Eq. 1), the ring row and last_hit (Eq. 2, Def. 3.1), the keep masks
@@ -12,8 +12,9 @@
 //   attend   grid (parts, units): online-softmax partials and raw logits per part of a unit; the
 //            owner of slot lens[u] writes the new row.                                     attend.hpp
 //   record   merges the partials -> out; scores, ring row, last_hit, keep masks, counts.   record.hpp
-//   compact  stable in-place gather of Algorithm 1, chunk-parallel, in two launches; skipped per unit
-//            when nothing was evicted, or deferred by policy (lazy mode).                 compact.hpp
+//   compact  stable in-place gather of Algorithm 1, a workgroup per slab of columns (units beyond 16384 slots:
+//            chunk-parallel in two launches); skipped per unit when nothing was evicted, or deferred by policy
+//            (lazy mode).                                                                 compact.hpp
 //   prefill  the prompt's last w queries in one dense call (MFMA), then the bulk eviction. prefill.hpp
 //
 // Row geometry: a K/V row is d*sizeof(T) bytes (256 B for bf16 d=128 and fp32 d=64); each lane

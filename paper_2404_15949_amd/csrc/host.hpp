@@ -304,7 +304,7 @@ int launch_attend_record(const corm_desc* d, const Params& p0, const LaunchCtx& 
   return launch_record(d, p, c, s);
 }
 
-// Policy of the compaction launches: exact mode compacts every unit that lost a key; lazy mode only
+// Policy of the compaction: exact mode compacts every unit that lost a key; lazy mode only
 // units whose dead slots reach dead_num / dead_den of their slots.
 struct CompactPolicy {
   int lazy = 0, dead_num = 0, dead_den = 1;

@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256) void corm_prefill_merge_kernel(const PrefillAr
 }
 
 // Def. 4.1 + recent r from last_hit for whole units (no append): wave ballots and survivors per chunk
-// for the compaction launches, optionally one byte per slot; writes t_first.
+// for the compaction, optionally one byte per slot; writes t_first.
 __global__ __launch_bounds__(WG) void corm_decide_kernel(const int32_t* lens, const int32_t* last_hit, const int32_t* t,
                                                          int32_t* t_first, unsigned long long* keepbits,
                                                          int32_t* counts, int2* unit_state, uint8_t* keep, int Hkv,

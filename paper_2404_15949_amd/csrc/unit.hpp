@@ -11,7 +11,7 @@ namespace {
 // nothing: one workgroup of 512 threads streams a whole unit, keeps the raw logits in LDS, and,
 // knowing the unit's max and sum itself, writes out, the ring row, last_hit and the keep flags in
 // the same launch.  No partials, no logits round trip through memory, no second kernel.  Only the
-// (rare) compaction remains for the two compaction launches.
+// (rare) compaction remains for the launch after it.
 
 constexpr int UNIT_WG = 512;
 constexpr int UNIT_WAVES = UNIT_WG / 64;
