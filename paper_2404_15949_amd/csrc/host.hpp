@@ -187,16 +187,12 @@ size_t unit_lds_bytes(const corm_desc* d, int* lstride) {
 
 // The unit kernel needs the unit's logits in LDS (48 KiB of dynamic LDS at most here, so that two
 // workgroups fit a compute unit) and pays off once there are at least as many units as compute units.
-// It also takes units so small that one workgroup is through with them before a second launch would have begun.
-// Rows x bytes x heads of a unit, us per step split / unit: 144 KiB (4 units, fp32 d 64) 17.1 / 13.3, 192 KiB (32
-// units, 2 heads, bf16 d 128) 17.2 / 15.3; on the other side 352 KiB (the same, twice as long) 14.7 / 16.6.
-constexpr long SMALL_UNIT_BYTES = 200 * 1024;
 bool use_unit_path(const corm_desc* d, const LaunchCtx& c) {
   int lstride;
   const bool fits = unit_lds_bytes(d, &lstride) <= 48 * 1024 && d->Hq / d->Hkv <= 4;  // G = 8 exceeds the register file
   if (c.path == 1 || c.path == 3 || !fits) return false;
   if (c.path == 2) return true;
-  return d->B * d->Hkv >= c.cus || (long)d->Lcap * row_bytes(d) * (d->Hq / d->Hkv) <= SMALL_UNIT_BYTES;
+  return d->B * d->Hkv >= c.cus;
 }
 
 template <typename DT, int D, bool LAZY>
