@@ -3,8 +3,8 @@
 // One decode step of one layer, on one stream, with kernel boundaries as the only cross-workgroup
 // synchronization (no device-wide fences, no spinning inside the kernels):
 //
-//   many units (>= compute units, logits fit LDS), or small ones:   unit kernel | compact
-//   few units:                                                       attend | record | compact
+//   many units (>= compute units, logits fit LDS):   unit kernel | compact
+//   few units:                                       attend | record | compact
 //
 //   unit     one workgroup per unit streams its K and V once, keeps the logits in LDS, writes the new
 //            row (append), out (Eq. 1), the ring row and last_hit (Eq. 2, Def. 3.1), the keep masks

@@ -115,7 +115,7 @@ def test_compact_on_both_sides_of_the_slab_limit(dtype, d, Lcap):
 
 
 # kv dtype, G, Hkv, d, Lcap: few units whose heads are shared by workgroups (1, 2, 4, 8 of them), lengths on both sides
-# of a part, and the largest small units that one workgroup takes whole
+# of a part and of the number of parts one wave folds
 ROUTES = [("bf16", 8, 1, 64, 1000), ("f32", 8, 2, 64, 520), ("f32", 4, 3, 128, 700), ("bf16", 4, 40, 64, 900),
           ("f32", 2, 30, 128, 515), ("bf16", 1, 4, 64, 1600), ("bf16", 1, 4, 64, 1601), ("f32", 2, 1, 64, 400)]
 
