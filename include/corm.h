@@ -129,8 +129,9 @@ const char* corm_strerror(int status);
 /* Bytes of workspace the attend/step calls need for this descriptor (host call). */
 int corm_workspace_bytes(const corm_desc* desc, size_t* bytes);
 
-/* Prepare a freshly allocated workspace (clears its per-split survivor counts).  Optional: every
- * call writes what it later reads. */
+/* Prepare a freshly allocated workspace (clears its survivor counts and unit states).  Optional: every
+ * call writes what it later reads, corm_step_evict what the corm_step_attend before it wrote; on a workspace that
+ * none filled it touches nothing outside the units. */
 int corm_workspace_init(const corm_desc* desc, void* workspace, size_t workspace_bytes, void* stream);
 
 /* Append (shapes of Algorithm 1): K[b,h,lens] = k_new, V likewise, pos = t-1, last_hit = 0, lens += 1.

@@ -139,7 +139,7 @@ __device__ __forceinline__ int chunk_scan(bool keep, CompactShared& sh, int* kep
 __device__ __forceinline__ void unit_counts(const int32_t* cnt, int nlive, int split, int* R, int* T) {
   int r = 0, t = 0;
   for (int s = (threadIdx.x & 63); s < nlive; s += 64) {
-    const int c = cnt[s];
+    const int c = min(max(cnt[s], 0), CHUNK);   // (whatever the workspace holds, rows stay inside the unit)
     if (s < split) r += c;
     t += c;
   }
@@ -152,13 +152,15 @@ __device__ __forceinline__ void unit_counts(const int32_t* cnt, int nlive, int s
   *T = t;
 }
 
-// slots and survivors of a unit: one load (what a workgroup of a unit with nothing to compact costs), or the counts
+// slots and survivors of a unit: one load (what a workgroup of a unit with nothing to compact costs), or the counts.
+// Within [0, Lcap] and [0, L] whatever the workspace holds (corm_step_evict may be called on one that no
+// corm_step_attend filled): nothing outside the unit is touched.
 __device__ __forceinline__ void unit_totals(const CompactArgs& a, int unit, int* L, int* T) {
   const int2 st = a.unit_state[unit];
-  int R;
-  *L = st.x;
-  *T = st.y;
-  if (a.sum_counts) unit_counts(a.counts + (size_t)unit * a.nsplit, (st.x + CHUNK - 1) / CHUNK, 0, &R, T);
+  int R, total = st.y;
+  *L = min(max(st.x, 0), a.Lcap);
+  if (a.sum_counts) unit_counts(a.counts + (size_t)unit * a.nsplit, (*L + CHUNK - 1) / CHUNK, 0, &R, &total);
+  *T = min(max(total, 0), *L);
 }
 
 // a caller's byte mask (corm_compact) -> wave ballots and survivors per split
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(CWG) void corm_compact_local_kernel(const CompactAr
   const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
   int R;   // survivors before this chunk
   unit_counts(cnt, nlive, split, &R, &T);
-  const int my_cnt = cnt[split];
+  const int my_cnt = min(max(cnt[split], 0), CHUNK);
   if (R == cbeg && my_cnt == cend - cbeg) {   // no hole before or inside this chunk
     if (idxb && i < cend) idxb[i] = i;
     return;
@@ -289,7 +291,7 @@ __global__ __launch_bounds__(WG) void corm_compact_boundary_kernel(const Compact
     const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
     int R;
     unit_counts(cnt, nlive, split, &R, &T);
-    const int nb = min(split * CHUNK, R + cnt[split]) - R;   // boundary rows of this chunk: survivors [R, R + nb)
+    const int nb = min(split * CHUNK, R + min(max(cnt[split], 0), CHUNK)) - R;   // boundary rows of this chunk: survivors [R, R + nb)
     if (nb > 0) {
       char* Kb = a.K + (size_t)unit * a.Lcap * ROWB;
       char* Vb = a.V + (size_t)unit * a.Lcap * ROWB;
@@ -381,9 +383,11 @@ __global__ __launch_bounds__(SLAB_WG) void corm_compact_slab_kernel(const Compac
   if (lane == 0) sh_first[wv] = hole;
   before -= __popcll(word);
   __syncthreads();
+  int listed = 0;   // survivors by the masks: T, unless the workspace holds something else
 #pragma unroll
   for (int i = 0; i < SLAB_WAVES; ++i) {
     if (i < wv) before += sh_wave[i];
+    listed += sh_wave[i];
     hole = min(hole, sh_first[i]);
   }
   sh_word[tid] = word;
@@ -398,7 +402,7 @@ __global__ __launch_bounds__(SLAB_WG) void corm_compact_slab_kernel(const Compac
     if (((bw >> lane) & 1ull) && r >= fixed) sh_src[r - fixed] = (uint16_t)(w * 64 + lane);
   }
   __syncthreads();
-  const int n = T - fixed;   // rows to move, to slots fixed, fixed + 1, ...
+  const int n = min(T, listed) - fixed;   // rows to move, to slots fixed, fixed + 1, ...
 
   if (slab == SLABS) {   // metadata: a slot per thread and step
     int32_t* posb = a.pos + (size_t)unit * a.Lcap;

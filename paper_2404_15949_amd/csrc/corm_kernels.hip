@@ -98,7 +98,7 @@ int corm_workspace_init(const corm_desc* desc, void* workspace, size_t workspace
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return CORM_EINVAL;
   const WorkspaceLayout wl = workspace_layout(*desc);
   if (workspace_bytes < wl.total) return CORM_ECAPACITY;
-  const size_t n = (size_t)desc->B * desc->Hkv * wl.nsplit;
+  const size_t n = (wl.keepbits_off - wl.counts_off) / sizeof(int32_t);   // counts and unit states
   hipLaunchKernelGGL(corm_fill_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                      reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + wl.counts_off), n, 0);
   return launch_status();

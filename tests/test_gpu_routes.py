@@ -166,3 +166,35 @@ def test_default_route_of_a_small_launch_equals_torch(case, ring):
             words = st.ring[0, h * G:(h + 1) * G, (Lcap - 1) % 4]
             bits = ((words[:, pos // 32] >> (pos % 32)) & 1).bool()
             assert torch.equal(bits[clear], hits[clear])
+
+
+@pytest.mark.parametrize("Lcap", [600, 16500])
+@pytest.mark.parametrize("poison", ["init", 0x7f, 0xff, "random"])
+def test_evict_on_a_workspace_that_no_attend_filled(Lcap, poison):
+    """corm_step_evict reads a unit's slots and survivors from the workspace.  After corm_workspace_init there are none;
+    whatever else the workspace holds, only the call's own units are written (units in front of and behind them are
+    the witnesses) and lens stays within its range."""
+    print("[case]", Lcap, poison, flush=True)
+    U, d = 3, 64
+    st = corm.LayerState(1, U, U, d, Lcap, Lcap, 4, 4, "f32", device=DEV, want_ring=False)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    K, V = (torch.randn(U + 2, Lcap, d, device=DEV, generator=g) for _ in range(2))
+    pos, hit, idx = (torch.randint(0, 99, (U + 2, Lcap), device=DEV, generator=g, dtype=torch.int32) for _ in range(3))
+    lens = torch.full((U + 2,), Lcap // 2, dtype=torch.int32, device=DEV)
+    arrays = [K, V, pos, hit, lens, idx]
+    before = [a.clone() for a in arrays]
+    if poison == "init":
+        st.workspace.fill_(0x7f)
+        corm.corm_workspace_init(st.desc, st.workspace)
+    elif poison == "random":
+        st.workspace.copy_(torch.randint(0, 256, st.workspace.shape, device=DEV, generator=g, dtype=torch.uint8))
+    else:
+        st.workspace.fill_(poison)
+    corm.corm_step_evict(st.desc, K[1:], V[1:], lens[1:], pos[1:], hit[1:], idx[1:], st.workspace)
+    torch.cuda.synchronize()
+    for a, b in zip(arrays, before):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[-1], b[-1])
+    assert ((lens[1:-1] >= 0) & (lens[1:-1] <= Lcap)).all()
+    if poison == "init":
+        assert (lens[1:-1] == 0).all()
+        assert torch.equal(K, before[0]) and torch.equal(V, before[1])
