@@ -76,7 +76,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 // the score of a raw logit: the one formula every ring type starts from
 __device__ __forceinline__ float prefill_score(float d, float scale_log2, float ms, float inv) {
-  return fast_exp2(fmaf(d, scale_log2, -ms)) * inv;
+  return fast_exp2(fmaf(d, scale_log2, -ms)) * fabsf(inv);   // (its sign: see prefill_query_stats)
 }
 
 // (x << 1) | the sign of t, in one instruction that touches no scalar register: a compare would put its result there,
@@ -97,6 +97,9 @@ enum { SEED_BF16 = 0, SEED_F32 = 1, SEED_BITS = 2 };
 //                 need the score itself.  The band is the threshold in the logit domain -+ a bound on every
 //                 rounding between a logit and its score (products, fma, exp2, 1/sum, the logarithms here: together
 //                 below 2e-6 of the terms), so the decisions are bit for bit those of the score.
+//                 A query without such a band has the sign of y set instead and is decided by the score
+//                 throughout: thresholds 0 or near the ends of the fp32 range, and rows with a logit that is not finite
+//                 (their max or sum is not a finite number either).  There the sign of a difference may be that of a NaN.
 __device__ __forceinline__ float4 prefill_query_stats(const PrefillArgs& a, float ms, float z, float thr) {
   float4 s = make_float4(ms, z > 0.f ? 1.0f / z : 0.f, thr, 0.f);
   if (a.ring_bits) {
@@ -104,11 +107,7 @@ __device__ __forceinline__ float4 prefill_query_stats(const PrefillArgs& a, floa
     const float at = ms + lt + lz, pad = 1e-5f + 2e-6f * (fabsf(ms) + fabsf(lt) + fabsf(lz));
     s.z = (at - pad) / a.scale_log2;
     s.w = (at + pad) / a.scale_log2;
-    // thresholds 0, infinite or near the end of the fp32 range: decide by the score throughout
-    if (!(lt + lz > -100.f) || !(fabsf(s.z) < 1e30f) || !(fabsf(s.w) < 1e30f)) {
-      s.z = neg_inf();
-      s.w = -neg_inf();
-    }
+    if (!(lt + lz > -100.f) || !(fabsf(s.z) < 1e30f) || !(fabsf(s.w) < 1e30f)) s.y = -s.y;
   } else if (a.ring_bf16) {
     const uint32_t up = (__float_as_uint(thr) + 0xffffu) >> 16;   // the smallest bf16 >= thr (thr >= 0)
     s.z = up ? __uint_as_float(((up - 1u) << 16) + 0x8000u + (up & 1u)) : 0.f;
@@ -378,7 +377,7 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
             if (lg == 0) sh_part[wv][(blk - grp) * QBLK + ti * 16 + n] = make_float2(mx, z);
           } else if (MODE == SEED_BITS) {
             const float4 st = sh_st[cur][ti * 16 + n];
-            uint32_t unsure = 0u, hbits = 0u;
+            uint32_t unsure = __float_as_uint(st.y), hbits = 0u;   // (the sign: this query has no band)
 #pragma unroll
             for (int i = 4 * T - 1; i >= 0; --i) {   // key i of the lane's run: row i % 4 of key tile i / 4
               const float above = st.w - d[i >> 2][i & 3], below = st.z - d[i >> 2][i & 3];
@@ -388,6 +387,7 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
             }
             if (__any((int)unsure < 0)) {   // (uniform, rare) what lies in the band is decided by the score
               const float thr = importance_threshold(a.thr_scale, tau);
+              if (__float_as_int(st.y) < 0) hbits = 0u;
 #pragma unroll 1
               for (int tl = 0; tl < T; ++tl) {
                 const f32x4_t x = tl == 0 ? d[0] : tl == 1 ? d[1] : tl == 2 ? d[T > 2 ? 2 : 0] : d[T > 2 ? 3 : 0];
@@ -396,7 +396,8 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
                   hbits |= (prefill_score(x[r], a.scale_log2, st.x, st.y) >= thr ? 1u : 0u) << (4 * tl + r);
               }
 #pragma unroll
-              for (int i = 0; i < 4 * T; ++i) hist[i >> 2][i & 3] |= (hbits >> i) & 1u;
+              for (int i = 0; i < 4 * T; ++i)   // (an instruction each: the low bit replaced)
+                hist[i >> 2][i & 3] = (hist[i >> 2][i & 3] & ~1u) | ((hbits >> i) & 1u);
             }
             // the wave owns whole words of every query's row: plain stores
             const __amdgpu_buffer_rsrc_t rr = head_ring(g);

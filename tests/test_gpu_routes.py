@@ -198,3 +198,55 @@ def test_evict_on_a_workspace_that_no_attend_filled(Lcap, poison):
     if poison == "init":
         assert (lens[1:-1] == 0).all()
         assert torch.equal(K, before[0]) and torch.equal(V, before[1])
+
+
+def _bit_hits(ring, rows, pos):
+    """Recorded booleans [B, Hq, len(rows), len(pos)] of a boolean ring."""
+    words = ring[:, :, rows].contiguous()
+    bits = (words.unsqueeze(-1) >> torch.arange(32, device=DEV)) & 1
+    return bits.flatten(-2)[..., pos].bool()
+
+
+POISON = {"nan": (0x7fc0, 0x7fc00000), "-nan": (0xffc0, 0xffc00000), "inf": (0x7f80, 0x7f800000), "-inf": (0xff80, 0xff800000)}
+
+
+@pytest.mark.parametrize("c", [0.0, 1.0])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_seed_with_logits_that_are_not_finite(dtype, d, c):
+    """A key with NaN of either sign, or an infinity of either sign, in one element: Def. 3.1 compares scores, so a score
+    that is not a number is minor and one that is 0 reaches the threshold 0, on every ring type and whichever way the
+    kernel decides.  The scores an fp32 ring holds are the witness; comparisons of them are exact.  Keys in front of the
+    first tail query take the kernel's fast blocks, those among the tail its general ones: both get a poisoned key."""
+    print("[case]", dtype, d, c, flush=True)
+    P, m, Hkv = 600, 80, len(POISON)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(d)
+    K = torch.randn(1, Hkv, P, d, device=DEV, generator=g).to(tdt)
+    q = torch.randn(1, Hkv, m, d, device=DEV, generator=g).to(tdt)
+    for h, (bf16, f32) in enumerate(POISON.values()):
+        raw = K.view(torch.int32 if dtype == "f32" else torch.int16)
+        value = f32 if dtype == "f32" else bf16
+        raw[0, h, 5, 0] = raw[0, h, P - 9, 0] = value - (1 << (32 if dtype == "f32" else 16)) if value >> (31 if dtype == "f32" else 15) else value
+    steps = torch.arange(P - m + 1, P + 1, device=DEV)
+    rows, pos = (steps - 1) % (m + 1), torch.arange(P, device=DEV)
+    seen = pos.view(1, -1) < steps.view(-1, 1)
+    got = {}
+    for ring in ("f32", "bf16", "bit"):
+        st = corm.LayerState(1, Hkv, Hkv, d, P, P, m + 1, 8, dtype, thr_scale=c, device=DEV, score_dtype=ring)
+        st.preload(K, torch.zeros_like(K))
+        t = torch.full((1,), P, dtype=torch.int32, device=DEV)
+        st.prefill_seed(q, t, torch.zeros_like(t))
+        torch.cuda.synchronize()
+        got[ring] = st
+    score = got["f32"].ring[:, :, rows][..., pos]
+    thr = torch.tensor(c, dtype=torch.float32, device=DEV) / steps.float()
+    wrong = []
+    for ring, stored in (("f32", score), ("bf16", score.bfloat16().float()), ("bit", score)):
+        hit = (stored >= thr.view(-1, 1)) & seen
+        want = torch.where(hit, steps.view(-1, 1).int(), 0).amax(2)
+        for h, kind in enumerate(POISON):
+            if not torch.equal(got[ring].last_hit[:, h], want[:, h]):
+                wrong.append((ring, kind, "last_hit"))
+            if ring == "bit" and not torch.equal(_bit_hits(got[ring].ring, rows, pos)[:, h] & seen, hit[:, h]):
+                wrong.append((ring, kind, "bits"))
+    assert not wrong, wrong
