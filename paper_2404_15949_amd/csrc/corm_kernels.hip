@@ -346,7 +346,7 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
   a.Hq = desc->Hq; a.Hkv = desc->Hkv; a.Lcap = desc->Lcap; a.Tcap = desc->Tcap; a.w = desc->w; a.m = m;
   a.nkb = wl.seed_nkb; a.ring_bf16 = desc->score_dtype == CORM_BF16;
   a.ring_bits = desc->score_dtype == CORM_BIT; a.ring_words = (desc->Tcap + 31) / 32;
-  a.thr_scale = desc->thr_scale;
+  a.thr_scale = fabsf(desc->thr_scale);   // (-0.0 is accepted: its bits are no threshold before rounding)
   a.scale_log2 = (desc->sm_scale > 0.f ? desc->sm_scale : 1.0f / sqrtf((float)desc->d)) * LOG2E;
   const int units = desc->B * desc->Hkv;
   a.units = units;

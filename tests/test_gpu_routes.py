@@ -250,3 +250,18 @@ def test_seed_with_logits_that_are_not_finite(dtype, d, c):
             if ring == "bit" and not torch.equal(_bit_hits(got[ring].ring, rows, pos)[:, h] & seen, hit[:, h]):
                 wrong.append((ring, kind, "bits"))
     assert not wrong, wrong
+
+
+@pytest.mark.parametrize("ring", ["f32", "bf16", "bit"])
+def test_seed_with_a_threshold_of_minus_zero(ring):
+    """thr_scale = -0.0 passes the descriptor's check (it is not below 0) and is the threshold 0: every key is important to
+    every query that sees it."""
+    P, m = 300, 32
+    g = torch.Generator(device=DEV).manual_seed(3)
+    K, q = (torch.randn(1, 2, n, 64, device=DEV, generator=g).bfloat16() for n in (P, m))
+    st = corm.LayerState(1, 2, 2, 64, P, P, m + 1, 8, "bf16", thr_scale=-0.0, device=DEV, score_dtype=ring)
+    st.preload(K, K)
+    t = torch.full((1,), P, dtype=torch.int32, device=DEV)
+    st.prefill_seed(q, t, torch.zeros_like(t))
+    torch.cuda.synchronize()
+    assert (st.last_hit == P).all()
