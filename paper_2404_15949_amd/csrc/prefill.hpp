@@ -622,8 +622,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void
 
 // boolean message: zero the words of the rows of steps tau_0 .. tau_{m-1} that pass 2 may set single bits in
 // (positions < tau); workgroup = 16 rows of one head.  Words that pass 2 stores whole are left to it: slot and position
-// agree over the 64 slots that hold the word and its neighbour (positions ascend, so the first and the last tell), and
-// every query whose step lies behind the word's first position sees a key there.  A prompt without holes leaves
+// agree over the 64 slots that hold the word and its neighbour (positions ascend, so the first and the last tell), all
+// of them have a column, and every query whose step lies behind the word's first position sees a key there.  A prompt without holes leaves
 // next to nothing to clear: 512 heads x 1024 rows x 8192 positions 132 -> 37 us.
 __global__ __launch_bounds__(256) void corm_prefill_clear_bits_kernel(const PrefillArgs a) {
   const int head = blockIdx.x;   // (heads in x: B * Hq may exceed the 65535 rows a grid has in y)
@@ -640,7 +640,7 @@ __global__ __launch_bounds__(256) void corm_prefill_clear_bits_kernel(const Pref
   const int nw_max = min((tau0 + j1 - 1 + 31) >> 5, a.ring_words);
   for (int i = threadIdx.x; i < nw_max; i += 256) {
     const int k0 = (i >> 1) * 64;
-    if (k0 + 64 <= L && posb[k0] == k0 && posb[k0 + 63] == k0 + 63) continue;
+    if (k0 + 64 <= min(L, a.Tcap) && posb[k0] == k0 && posb[k0 + 63] == k0 + 63) continue;
     for (int j = j0; j < j1; ++j) {
       int slot = s0 + j;
       if (slot >= a.w) slot -= a.w;

@@ -265,3 +265,28 @@ def test_seed_with_a_threshold_of_minus_zero(ring):
     st.prefill_seed(q, t, torch.zeros_like(t))
     torch.cuda.synchronize()
     assert (st.last_hit == P).all()
+
+
+@pytest.mark.parametrize("P", [256, 300])
+def test_seed_bits_next_to_positions_without_a_column(P):
+    """Keys at positions the ring has no column for are skipped and flagged; the words that hold the valid positions of the same
+    64 slots are those of a ring that was clear before."""
+    Tcap, m, d = 225, 16, 64
+    g = torch.Generator(device=DEV).manual_seed(P)
+    K, q = (torch.randn(1, 2, n, d, device=DEV, generator=g).bfloat16() for n in (P, m))
+    got = []
+    for before in (0, -1):
+        st = corm.LayerState(1, 2, 2, d, P, Tcap, m + 1, 8, "bf16", device=DEV, score_dtype="bit")
+        st.preload(K, K)
+        st.ring.fill_(before)
+        t = torch.full((1,), Tcap, dtype=torch.int32, device=DEV)
+        st.prefill_seed(q, t, torch.zeros_like(t))
+        torch.cuda.synchronize()
+        assert int(st.status.item()) == corm.CORM_DEV_BAD_STEP
+        got.append(st)
+    steps = torch.arange(Tcap - m + 1, Tcap + 1, device=DEV)
+    pos = torch.arange(Tcap, device=DEV)
+    seen = pos.view(1, -1) < steps.view(-1, 1)
+    a, b = (_bit_hits(st.ring, (steps - 1) % (m + 1), pos) & seen for st in got)
+    assert bool(a.any()) and torch.equal(a, b)
+    assert torch.equal(got[0].last_hit, got[1].last_hit)
