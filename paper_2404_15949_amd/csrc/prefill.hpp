@@ -283,10 +283,11 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
       for (int tl = 0; tl < T; ++tl) d[tl] = PrefillMma<DT>::mma(ka[tl][c], qb[c], d[tl]);
   };
   // Fast blocks store through a buffer descriptor of one head's ring: 32-bit offsets, and without a ring a
-  // descriptor of length 0, which drops the stores (no branch around them).
+  // descriptor of length 0, which drops the stores (no branch around them).  So are those at DEAD_OFFSET, as long as the
+  // ring ends in front of it.
   const uint64_t head_bytes = (uint64_t)a.w * (MODE == SEED_BITS ? (uint64_t)a.ring_words * 4 : (uint64_t)a.Tcap * (MODE == SEED_BF16 ? 2 : 4));
   const uint32_t row_bytes = (uint32_t)(head_bytes / a.w);
-  const bool offsets32 = head_bytes < (1ull << 31);
+  const bool offsets32 = head_bytes <= DEAD_OFFSET;
   auto head_ring = [&](int g) __attribute__((always_inline)) {
     char* p = reinterpret_cast<char*>(a.ring);
     return make_rsrc(p ? p + (uint64_t)(b * a.Hq + hkv * G + g) * head_bytes : p, a.ring ? (uint32_t)head_bytes : 0u);

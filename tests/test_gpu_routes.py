@@ -290,3 +290,27 @@ def test_seed_bits_next_to_positions_without_a_column(P):
     a, b = (_bit_hits(st.ring, (steps - 1) % (m + 1), pos) & seen for st in got)
     assert bool(a.any()) and torch.equal(a, b)
     assert torch.equal(got[0].last_hit, got[1].last_hit)
+
+
+@pytest.mark.parametrize("w,words", [(2044, 262657), (16383, 32770)])
+def test_seed_bits_in_a_ring_of_two_gigabytes(w, words):
+    """Stores that a lane has no part in go to an offset behind the head's ring, 0x7ffffff0 at most: a ring of just that
+    many bytes, and one whose last words lie behind that offset.  Only the tail's rows may change."""
+    P, m, t_last, d = 64, 64, 300, 64
+    print("[case]", w, words, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    K, q = (torch.randn(1, 1, n, d, device=DEV, generator=g).bfloat16() for n in (P, m))
+    st = corm.LayerState(1, 1, 1, d, P, words * 32, w, 8, "bf16", device=DEV, score_dtype="bit")
+    st.preload(K, K)
+    st.ring.fill_(-1)
+    t = torch.full((1,), t_last, dtype=torch.int32, device=DEV)
+    st.prefill_seed(q, t, torch.zeros_like(t))
+    torch.cuda.synchronize()
+    flat = st.ring.view(w, words)
+    steps = torch.arange(t_last - m + 1, t_last + 1, device=DEV)
+    rows = (steps - 1) % w
+    hits = _bit_hits(st.ring, rows, torch.arange(P, device=DEV))[0, 0]
+    assert bool(hits.any()) and not bool(hits.all())
+    assert torch.equal(torch.where(hits, steps.view(-1, 1).int(), 0).amax(0), st.last_hit[0, 0])
+    flat[rows] = -1
+    assert bool((flat == -1).all())
