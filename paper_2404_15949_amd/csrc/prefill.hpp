@@ -155,7 +155,8 @@ struct PrefillGeom {
   static_assert(QBLK * ROWB % (WG * 16) == 0 && QBLK <= WG, "a block is loaded in whole passes of the workgroup");
 };
 
-template <typename DT, int D, int PASS, int MODE>
+// FAR: a head's ring reaches beyond the 32-bit offsets of a buffer descriptor (pass 2).
+template <typename DT, int D, int PASS, int MODE, bool FAR>
 __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
   constexpr int ROWB = D * DT::ESZ;
   using Geo = PrefillGeom<ROWB>;
@@ -282,20 +283,26 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
 #pragma unroll
       for (int tl = 0; tl < T; ++tl) d[tl] = PrefillMma<DT>::mma(ka[tl][c], qb[c], d[tl]);
   };
-  // Fast blocks store through a buffer descriptor of one head's ring: 32-bit offsets, and without a ring a
-  // descriptor of length 0, which drops the stores (no branch around them).  So are those at DEAD_OFFSET, as long as the
-  // ring ends in front of it.
-  const uint64_t head_bytes = (uint64_t)a.w * (MODE == SEED_BITS ? (uint64_t)a.ring_words * 4 : (uint64_t)a.Tcap * (MODE == SEED_BF16 ? 2 : 4));
-  const uint32_t row_bytes = (uint32_t)(head_bytes / a.w);
-  const bool offsets32 = head_bytes <= DEAD_OFFSET;
-  auto head_ring = [&](int g) __attribute__((always_inline)) {
-    char* p = reinterpret_cast<char*>(a.ring);
-    return make_rsrc(p ? p + (uint64_t)(b * a.Hq + hkv * G + g) * head_bytes : p, a.ring ? (uint32_t)head_bytes : 0u);
-  };
+  // Fast blocks store through a buffer descriptor with 32-bit offsets: of one head's ring, or (FAR; as an instance of its
+  // own, since the few scalar instructions per tile cost the others 1 to 3 %) of the rows of a tile's 16 queries, which lie
+  // in a row unless the ring wraps among them.  Without a ring its length is 0, which drops the stores (no branch
+  // around them); so are those at DEAD_OFFSET, as long as the descriptor ends in front of it.
+  const uint64_t row_bytes64 = MODE == SEED_BITS ? (uint64_t)a.ring_words * 4 : (uint64_t)a.Tcap * (MODE == SEED_BF16 ? 2 : 4);
+  const uint64_t head_bytes = a.w * row_bytes64;
+  const uint32_t row_bytes = (uint32_t)row_bytes64;
   // ring slot of query j; row of the ring that query j of head g is recorded in
   auto slot_of = [&](int j) __attribute__((always_inline)) -> uint32_t {
     const int slot = s0 + j;
     return (uint32_t)(slot >= a.w ? slot - a.w : slot);
+  };
+  auto rows_rsrc = [&](int tt) __attribute__((always_inline)) {
+    char* p = reinterpret_cast<char*>(a.ring);
+    const uint64_t at = (uint64_t)(b * a.Hq + hkv * G + (tt & (G - 1))) * head_bytes +
+                        (FAR ? slot_of((tt >> lgG) * 16) * row_bytes64 : 0);
+    return make_rsrc(p ? p + at : p, a.ring ? (FAR ? 16 * row_bytes : (uint32_t)head_bytes) : 0u);
+  };
+  auto row_of = [&](int tt, int j) __attribute__((always_inline)) -> uint32_t {   // row of the descriptor for query j
+    return FAR ? (uint32_t)(j - (tt >> lgG) * 16) : slot_of(j);
   };
   auto ring_row = [&](int g, int j) __attribute__((always_inline)) -> size_t {
     return (size_t)(b * a.Hq + hkv * G + g) * a.w + slot_of(j);
@@ -356,7 +363,9 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
       // (uniform over the wave) every query of the block exists and sees every key of the wave, and pass 2 can
       // store whole pieces: straight-line code, the next tile's MFMAs under this tile's tail
       const bool fast = tt0 + QT <= ntt && ((tt0 + QT - 1) >> lgG) * 16 + 15 < a.m &&
-                        pos_wmax <= tau0 + (tt0 >> lgG) * 16 - 1 && (PASS == 1 || (rows_ok && offsets32));
+                        pos_wmax <= tau0 + (tt0 >> lgG) * 16 - 1 && (PASS == 1 || rows_ok) &&
+                        (!FAR || (16 * row_bytes64 <= DEAD_OFFSET &&
+                                  slot_of((tt0 >> lgG) * 16) <= slot_of(((tt0 + QT - 1) >> lgG) * 16 + 15)));
       if (fast) {
         if (HIST) {
           if (hist_n + QT > 32 || (hist_n && hist_tt + 1 != tt0)) settle();
@@ -371,7 +380,7 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
 #pragma unroll
           for (int tl = 0; tl < T; ++tl) d[tl] = dn[tl];
           if (ti + 1 < QT) mma_tile(cur, ti + 1, dn);
-          const int tt = tt0 + ti, g = tt & (G - 1), j = (tt >> lgG) * 16 + n, tau = tau0 + j;
+          const int tt = tt0 + ti, j = (tt >> lgG) * 16 + n, tau = tau0 + j;
           if (PASS == 1) {
             float mx, z;
             prefill_stats_tile<false, T>(d, 0u, a.scale_log2, mx, z);
@@ -401,8 +410,8 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
                 hist[i >> 2][i & 3] = (hist[i >> 2][i & 3] & ~1u) | ((hbits >> i) & 1u);
             }
             // the wave owns whole words of every query's row: plain stores
-            const __amdgpu_buffer_rsrc_t rr = head_ring(g);
-            const uint32_t at = slot_of(j) * row_bytes + (uint32_t)(pos_w0 >> 5) * 4;
+            const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
+            const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 >> 5) * 4;
             if (T == 4) {   // 16 keys per lane: two lane groups to a word
               const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
               __builtin_amdgcn_raw_buffer_store_b32(sw[0] | (sw[1] << 16), rr, (lg & 1) ? DEAD_OFFSET : at + (lg >> 1) * 4, 0, 0);
@@ -423,9 +432,9 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
                 // scalar registers, spills those, and selects at the end)
                 asm volatile("" : "+v"(hm[tl][r]));
               }
-            const __amdgpu_buffer_rsrc_t rr = head_ring(g);
+            const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
             if (MODE == SEED_F32) {
-              const uint32_t at = slot_of(j) * row_bytes + (uint32_t)(pos_w0 + 4 * lg) * 4;
+              const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 + 4 * lg) * 4;
 #pragma unroll
               for (int tl = 0; tl < T; ++tl) {
                 const u32x4_t v = {__float_as_uint(pv[tl][0]), __float_as_uint(pv[tl][1]), __float_as_uint(pv[tl][2]),
@@ -448,7 +457,7 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
                 const int qi = h * RPS + lane / PIECES, ch = lane % PIECES;
                 const u32x4_t v = *reinterpret_cast<const u32x4_t*>(&sh_t[wv][qi][ch * 8]);
                 __builtin_amdgcn_raw_buffer_store_b128(
-                    v, rr, slot_of((tt >> lgG) * 16 + qi) * row_bytes + (uint32_t)(pos_w0 + ch * 8) * 2, 0, 2);
+                    v, rr, row_of(tt, (tt >> lgG) * 16 + qi) * row_bytes + (uint32_t)(pos_w0 + ch * 8) * 2, 0, 2);
               }
               __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
@@ -612,13 +621,13 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
 template <typename DT, int D>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void corm_prefill_stats_kernel(
     const PrefillArgs a) {
-  prefill_pass<DT, D, 1, SEED_F32>(a);
+  prefill_pass<DT, D, 1, SEED_F32, false>(a);
 }
 
-template <typename DT, int D, int MODE>
+template <typename DT, int D, int MODE, bool FAR>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void corm_prefill_scores_kernel(
     const PrefillArgs a) {
-  prefill_pass<DT, D, 2, MODE>(a);
+  prefill_pass<DT, D, 2, MODE, FAR>(a);
 }
 
 // boolean message: zero the words of the rows of steps tau_0 .. tau_{m-1} that pass 2 may set single bits in

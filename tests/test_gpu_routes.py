@@ -314,3 +314,25 @@ def test_seed_bits_in_a_ring_of_two_gigabytes(w, words):
     assert torch.equal(torch.where(hits, steps.view(-1, 1).int(), 0).amax(0), st.last_hit[0, 0])
     flat[rows] = -1
     assert bool((flat == -1).all())
+
+
+@pytest.mark.parametrize("t_last", [300, 330])   # the ring wraps in the second and in the first block of queries
+@pytest.mark.parametrize("ring,Tcap", [("bf16", 12000000), ("f32", 6000000), ("bit", 180000000)])
+def test_seed_in_a_ring_beyond_32_bit_offsets(ring, Tcap, t_last):
+    """A head's ring of more than 2 GiB, whose fast blocks address the rows of a tile: the same bits as in a short one."""
+    P, m, w, d = 160, 90, 97, 128
+    print("[case]", ring, t_last, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(7)
+    K, q = (torch.randn(1, 1, n, d, device=DEV, generator=g).bfloat16() for n in (P, m))
+    got = []
+    for columns in (Tcap, 512):
+        st = corm.LayerState(1, 1, 1, d, P, columns, w, 8, "bf16", device=DEV, score_dtype=ring)
+        st.preload(K, K)
+        t = torch.full((1,), t_last, dtype=torch.int32, device=DEV)
+        st.prefill_seed(q, t, torch.zeros_like(t))
+        torch.cuda.synchronize()
+        n = P // 32 if ring == "bit" else P
+        got.append((st.ring[..., :n].clone(), st.last_hit))
+        assert not bool(st.ring[..., n:].any())
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert bool(got[0][1].any())
