@@ -1,4 +1,4 @@
-// stable in-place compaction: count, local and boundary launches.
+// stable in-place compaction: column slabs in one launch, or chunks in two (local and boundary).
 // Part of one translation unit: included by corm_kernels.hip, in this order, after <hip/hip_runtime.h> and corm.h.
 #ifndef CORM_COMPACT_HPP
 #define CORM_COMPACT_HPP
@@ -10,12 +10,12 @@ namespace {
 // Survivor number rho of a unit (in slot order) must end in slot rho.  No cross-workgroup synchronization inside a
 // launch; the unit's length is handed over through the workspace by the launch before (lens is written here).
 //
-// Units of up to SLAB_MAX_SLOTS slots, one launch: a workgroup owns a slab of columns of K or V over the whole
+// Many units, or short ones (compact_by_slabs), one launch: a workgroup owns a slab of columns of K or V over the whole
 // unit (one more the metadata), so nobody else reads or writes what it moves: it walks the survivors behind the first
 // hole in ascending batches (every destination <= its source; all loads of a batch complete before any of its
 // stores).
 //
-// Longer units, two launches, where a slab would be one long serial walk:
+// Few long units, two launches, where slabs would be a few long serial walks:
 //   local     grid (splits, units).  R_c = survivors before chunk c (from the per-split counts).
 //             The workgroup of chunk c = slots [a_c, a_c + CHUNK) moves its survivors with rho >= a_c
 //             to slot rho -- inside its own chunk, so it reads and writes only its own slots -- in

@@ -12,7 +12,7 @@
 //   attend   grid (parts, units): online-softmax partials and raw logits per part of a unit; the
 //            owner of slot lens[u] writes the new row.                                     attend.hpp
 //   record   merges the partials -> out; scores, ring row, last_hit, keep masks, counts.   record.hpp
-//   compact  stable in-place gather of Algorithm 1, a workgroup per slab of columns (units beyond 16384 slots:
+//   compact  stable in-place gather of Algorithm 1, a workgroup per slab of columns (few long units:
 //            chunk-parallel in two launches); skipped per unit when nothing was evicted, or deferred by policy
 //            (lazy mode).                                                                 compact.hpp
 //   prefill  the prompt's last w queries in one dense call (MFMA), then the bulk eviction. prefill.hpp

@@ -94,6 +94,21 @@ def test_lazy_trajectory(name):
         assert rep["compactions"] > 0, "no unit was ever compacted: the policy branch is not exercised"
 
 
+@pytest.mark.parametrize("deferred", [False, True])
+@pytest.mark.parametrize("name", ["structured", "f32_d128", "bf16_d64", "bf16_gqa8"])
+def test_trajectory_with_chunk_compaction(name, deferred):
+    """Slots beyond those the one-launch compaction takes: units of ragged length over several chunks, evictions at nearly every
+    step, compacted at once (with keep and kept_idx) or by the dead fraction, the live masks, nlive and lens with them."""
+    wl, every = TRAJ[name]
+    lazy = (1, 16) if deferred else None
+    say("chunk compaction", name, lazy, wl)
+    rep = harness.run_slaved_trajectory(wl, DEV, check_state_every=every, lazy=lazy, Lcap=16500)
+    say("report", name, {k: v for k, v in rep.items() if k != "final_lens"})
+    assert rep["evicted_total"] > 0
+    if lazy:
+        assert 0 < rep["compactions"] < rep["steps"] * rep["units"], "one side of the policy is not exercised"
+
+
 def test_lazy_with_zero_fraction_is_the_exact_step():
     """dead_num = 0 compacts at every eviction: slot for slot the state corm_decode_step leaves."""
     wl, _ = TRAJ["bf16_mha"]
