@@ -163,7 +163,7 @@ __global__ __launch_bounds__(WG) void corm_attend_kernel(const Params p) {
   // (boolean message) the row of this step is cleared here, one launch before the record kernel sets bits
   if (split == 0) clear_bit_rows(p, b, hq0, G, WG);
   if (split == 0 && hgroup == 0 && threadIdx.x == 0 && p.do_evict)
-    p.unit_state[unit] = make_int2(L, 0);   // (the record launch counts)
+    p.unit_state[unit] = make_int2(L, L);   // (the record launch says where keys went)
   if (split * p.part_keys >= L) return;   // no live key in this part
 
   const int tid = threadIdx.x;
@@ -442,7 +442,8 @@ void corm_attend_gqa_kernel(const Params p) {
   const UnitLen ul = unit_len(p, unit);
   const int L = ul.L;
   if (split == 0) clear_bit_rows(p, unit / p.Hkv, (unit % p.Hkv) * G, G, WG);
-  if (split == 0 && threadIdx.x == 0 && p.do_evict) p.unit_state[unit] = make_int2(L, 0);   // (the record launch counts)
+  if (split == 0 && threadIdx.x == 0 && p.do_evict)
+    p.unit_state[unit] = make_int2(L, L);   // (the record launch says where keys went)
   if (split * p.part_keys >= L) return;
 
   const int b = unit / p.Hkv;

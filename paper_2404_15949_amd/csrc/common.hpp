@@ -10,6 +10,7 @@ constexpr int WAVES = WG / 64;   // waves per workgroup
 constexpr int CHUNK = 512;       // keys per split
 constexpr int UNROLL = 4;        // 16-byte K loads (and V loads) per lane and pipeline stage
 constexpr int MAX_PARTS_PER_CHUNK = 4;   // split path: a chunk may be shared by up to 4 attend workgroups
+constexpr int SUM_COUNTS = -1;   // unit_state: the survivors are the sum of the unit's counts
 constexpr float LOG2E = 1.4426950408889634f;
 
 struct Params {
@@ -30,7 +31,8 @@ struct Params {
   unsigned long long* live;      // lazy mode: the caller's live masks, same layout: read, then replaced by the keep flags
   int32_t* kept_idx;   // optional
   int32_t* counts;     // survivors per (unit, split)
-  int2* unit_state;    // [units] of the workspace: (slots, survivors) of the unit in this step, for the compaction
+  int2* unit_state;    // [units] of the workspace: (slots, survivors or SUM_COUNTS) of the unit in this step, for the
+                       // compaction
   float* partials;     // [B*Hq, nsplit, d+2]
   float* logits;       // [B*Hq, Lcap], log2 domain
   int32_t* status;

@@ -54,13 +54,12 @@ struct CompactArgs {
   unsigned long long* live;      // lazy mode: the caller's live masks, reset where a unit is compacted
   int32_t* kept_idx;             // optional
   const int32_t* counts;         // [units, nsplit]
-  int2* unit_state;              // [units] (slots, survivors) of the unit in this step, written by the launch before
+  int2* unit_state;              // [units] (slots, survivors or SUM_COUNTS) of the unit in this step, by the launch before
   int32_t* nlive;                // optional [units]: live keys after the step
   char* stage_k;                 // [units, nsplit, CHUNK, ROWB]
   char* stage_v;
   int32_t* stage_meta;           // [units, nsplit, CHUNK, 2] (pos, last_hit)
   int32_t units, nsplit, Lcap, kb_stride;
-  int32_t sum_counts;            // the launch before left the survivors in counts alone
   int32_t lazy, dead_num, dead_den;
 };
 
@@ -152,14 +151,27 @@ __device__ __forceinline__ void unit_counts(const int32_t* cnt, int nlive, int s
   *T = t;
 }
 
-// slots and survivors of a unit: one load (what a workgroup of a unit with nothing to compact costs), or the counts.
-// Within [0, Lcap] and [0, L] whatever the workspace holds (corm_step_evict may be called on one that no
-// corm_step_attend filled): nothing outside the unit is touched.
+// What the launch before left in a unit's state: its slots, and its survivors or, where several workgroups counted and a
+// key went, SUM_COUNTS.  (Adding up in the record launch, by atomics on one word of the unit, cost that launch 0.6 to
+// 1.5 us.)  A unit that lost nothing is known by this one load: the chunk launches, which have a workgroup per 512
+// slots, leave then (128 units x 33000 slots with nothing to move, local launch: 5.1 us, 7.0 with the counts read as well).
+// Slots are held to [0, Lcap] and survivors to [0, slots] whatever the workspace holds (corm_step_evict may be called on
+// one that no corm_step_attend filled): nothing outside the unit is touched.
+__device__ __forceinline__ int unit_slots(const CompactArgs& a, int2 state) { return min(max(state.x, 0), a.Lcap); }
+
+// The slab launch: slots L and survivors T.  The counts are requested with the state and cost no further latency.
 __device__ __forceinline__ void unit_totals(const CompactArgs& a, int unit, int* L, int* T) {
-  const int2 st = a.unit_state[unit];
-  int R, total = st.y;
-  *L = min(max(st.x, 0), a.Lcap);
-  if (a.sum_counts) unit_counts(a.counts + (size_t)unit * a.nsplit, (*L + CHUNK - 1) / CHUNK, 0, &R, &total);
+  const int lane = threadIdx.x & 63;
+  const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;   // (at most 32: SLAB_MAX_SLOTS / CHUNK)
+  const int2 state = a.unit_state[unit];
+  const int c = lane < a.nsplit ? cnt[lane] : 0;
+  *L = unit_slots(a, state);
+  int total = state.y;
+  if (total == SUM_COUNTS) {   // (uniform)
+    total = lane * CHUNK < *L ? min(max(c, 0), CHUNK) : 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
+  }
   *T = min(max(total, 0), *L);
 }
 
@@ -170,7 +182,7 @@ __global__ __launch_bounds__(WG) void corm_count_kernel(const CompactArgs a, int
   int L = a.lens[unit];
   L = L < 0 ? 0 : (L > a.Lcap ? a.Lcap : L);
   const int cbeg = split * CHUNK;
-  if (split == 0 && threadIdx.x == 0) a.unit_state[unit].x = L;
+  if (split == 0 && threadIdx.x == 0) a.unit_state[unit] = make_int2(L, SUM_COUNTS);
   if (cbeg >= L) return;
   const int cend = min(cbeg + CHUNK, L);
   const uint8_t* keepb = a.keep + (size_t)unit * a.Lcap;
@@ -198,10 +210,15 @@ __global__ __launch_bounds__(CWG) void corm_compact_local_kernel(const CompactAr
   __shared__ CompactShared sh_c;
   const int split = blockIdx.x, unit = blockIdx.y;
   const int tid = threadIdx.x;
-  int L, T;
-  unit_totals(a, unit, &L, &T);
+  const int2 state = a.unit_state[unit];
+  if (state.x == state.y && !a.kept_idx) return;   // nothing went
+  const int L = unit_slots(a, state);
   const int nlive = (L + CHUNK - 1) / CHUNK;
   if (split >= nlive) return;
+  const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
+  int R, T;   // survivors before this chunk, survivors of the unit
+  unit_counts(cnt, nlive, split, &R, &T);
+  T = min(T, L);
   int32_t* idxb = a.kept_idx ? a.kept_idx + (size_t)unit * a.Lcap : nullptr;
   const int cbeg = split * CHUNK;
   const int cend = min(cbeg + CHUNK, L);
@@ -210,9 +227,6 @@ __global__ __launch_bounds__(CWG) void corm_compact_local_kernel(const CompactAr
     if (idxb && T == L && i < cend) idxb[i] = i;
     return;
   }
-  const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
-  int R;   // survivors before this chunk
-  unit_counts(cnt, nlive, split, &R, &T);
   const int my_cnt = min(max(cnt[split], 0), CHUNK);
   if (R == cbeg && my_cnt == cend - cbeg) {   // no hole before or inside this chunk
     if (idxb && i < cend) idxb[i] = i;
@@ -282,15 +296,17 @@ __global__ __launch_bounds__(WG) void corm_compact_boundary_kernel(const Compact
   constexpr int LPR = ROWB / 16;
   const int split = blockIdx.x, unit = blockIdx.y;
   const int tid = threadIdx.x;
-  int L, T;
-  unit_totals(a, unit, &L, &T);
+  const int2 state = a.unit_state[unit];
+  if (state.x == state.y && split != 0) return;   // nothing went
+  const int L = unit_slots(a, state);
   const int nlive = (L + CHUNK - 1) / CHUNK;
   if (split >= nlive && split != 0) return;
+  const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
+  int R, T;
+  unit_counts(cnt, nlive, split, &R, &T);
+  T = min(T, L);
   const bool compacted = compact_now(a, L, T);
   if (compacted && split > 0) {
-    const int32_t* cnt = a.counts + (size_t)unit * a.nsplit;
-    int R;
-    unit_counts(cnt, nlive, split, &R, &T);
     const int nb = min(split * CHUNK, R + min(max(cnt[split], 0), CHUNK)) - R;   // boundary rows of this chunk: survivors [R, R + nb)
     if (nb > 0) {
       char* Kb = a.K + (size_t)unit * a.Lcap * ROWB;

@@ -226,8 +226,7 @@ int corm_compact(const corm_desc* desc, void* K, void* V, int32_t* pos, int32_t*
   WorkspaceLayout wl;
   rc = check_workspace(desc, workspace, workspace_bytes, &wl);
   if (rc) return rc;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, keep, kept_idx, true, true,
-                        CompactPolicy(),
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, keep, kept_idx, true, CompactPolicy(),
                         (hipStream_t)stream);
 }
 
@@ -265,7 +264,7 @@ int corm_step_evict(const corm_desc* desc, void* K, void* V, int32_t* lens, int3
   WorkspaceLayout wl;
   rc = check_workspace(desc, workspace, workspace_bytes, &wl);
   if (rc) return rc;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, false, CompactPolicy(),
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, CompactPolicy(),
                         (hipStream_t)stream);
 }
 
@@ -313,7 +312,7 @@ int corm_decode_step_lazy(const corm_desc* desc, const void* q, const void* k_ne
   pol.lazy = 1; pol.dead_num = dead_num; pol.dead_den = dead_den;
   pol.live = reinterpret_cast<unsigned long long*>(live);
   pol.nlive = nlive;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, nullptr, false, false, pol,
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, nullptr, false, pol,
                         (hipStream_t)stream);
 }
 
@@ -372,8 +371,7 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
                      reinterpret_cast<int2*>(ws + wl.unit_state_off), keep, desc->Hkv, desc->Lcap, wl.nsplit,
                      wl.kb_stride, desc->w, desc->r, m);
   if (launch_status()) return CORM_EHIP;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, true,
-                        CompactPolicy(), s);
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, CompactPolicy(), s);
 }
 
 int corm_selected_path(const corm_desc* desc, const corm_launch_opts* opts) {

@@ -338,10 +338,10 @@ void launch_compact_rows(const CompactArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((corm_compact_boundary_kernel<ROWB>), grid, dim3(WG), 0, s, a);
 }
 
-// count_first: derive the per-split counts from the caller's mask; sum_counts: the launch before left no unit totals
+// count_first: derive the per-split counts from the caller's mask
 int launch_compact(const corm_desc* d, const WorkspaceLayout& wl, void* workspace, void* K, void* V, int32_t* pos,
                    int32_t* last_hit, int32_t* lens, const uint8_t* keep, int32_t* kept_idx, bool count_first,
-                   bool sum_counts, const CompactPolicy& pol, hipStream_t s) {
+                   const CompactPolicy& pol, hipStream_t s) {
   char* ws = reinterpret_cast<char*>(workspace);
   CompactArgs a;
   a.K = reinterpret_cast<char*>(K);
@@ -353,7 +353,6 @@ int launch_compact(const corm_desc* d, const WorkspaceLayout& wl, void* workspac
   int32_t* counts = reinterpret_cast<int32_t*>(ws + wl.counts_off);
   a.counts = counts;
   a.unit_state = reinterpret_cast<int2*>(ws + wl.unit_state_off);
-  a.sum_counts = sum_counts;
   a.nlive = pol.nlive;
   a.stage_k = ws + wl.stage_k_off;
   a.stage_v = ws + wl.stage_v_off;

@@ -697,7 +697,7 @@ __global__ __launch_bounds__(WG) void corm_decide_kernel(const int32_t* lens, co
   if (split == 0 && unit % Hkv == 0 && tid == 0) t_first[b] = tcur - m + 1;
   int L = lens[unit];
   L = L < 0 ? 0 : (L > Lcap ? Lcap : L);
-  if (split == 0 && tid == 0) unit_state[unit].x = L;
+  if (split == 0 && tid == 0) unit_state[unit] = make_int2(L, SUM_COUNTS);
   const int cbeg = split * CHUNK;
   if (cbeg >= L) return;
   const int cend = min(cbeg + CHUNK, L);

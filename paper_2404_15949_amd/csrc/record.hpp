@@ -215,7 +215,8 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
       for (int i = 0; i < WAVES; ++i) tot += sh_cnt[tid][i];
       const int chunk = rsplit * RECORD_CHUNKS + tid;
       p.counts[(size_t)unit * p.nsplit + chunk] = tot;
-      atomicAdd(&p.unit_state[unit].y, tot);
+      // (a plain store: whoever lost a key stores the same)
+      if (tot != min(CHUNK, L - chunk * CHUNK)) p.unit_state[unit].y = SUM_COUNTS;
     }
   }
 }
