@@ -146,7 +146,8 @@ __device__ __forceinline__ void stage_live_masks(const Params& p, int unit, cons
 }
 
 // G: query heads this workgroup serves.  A launch that would leave the chip idle shares a unit's query heads among
-// p.head_groups workgroups (each then streams the part's rows, out of the L2 from the second on).
+// p.head_groups workgroups (each then streams the part's rows: they are gridDim.x workgroups apart, so in general on
+// dies with an L2 of their own).
 template <typename DT, int D, int G, bool LAZY>
 __global__ __launch_bounds__(WG) void corm_attend_kernel(const Params p) {
   using A = Attend<DT, D, G, WAVES>;

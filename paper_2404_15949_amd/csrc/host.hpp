@@ -281,12 +281,19 @@ int attend_part_keys(const corm_desc* d, const LaunchCtx& c) {
 // Workgroups that share a unit's query heads on the split path (vector-ALU kernel): while the launch would have fewer
 // than two workgroups per compute unit, so that a part's dots and products of G heads do not run one after the
 // other on a few of them (9 units of 8 heads, d 64, 840 keys: 63 workgroups 13.9 us, 504 of one head each 7.3 us).
+// Each of them streams the part's rows.  With few heads left to each, a second workgroup per compute unit costs more in
+// rows than it saves in products, with fp32 (more bytes a product) earlier than with bf16: about 200 -> 400 workgroups,
+// fp32 d 128 of 2 heads 12.7 -> 16.2 us, of 4 heads 16.0 -> 17.6, of 8 heads 25.9 -> 22.6; fp32 d 64 of 2 heads 10.4 -> 11.8, of 4 12.6 ->
+// 13.1; bf16 of 2 heads 11.4 -> 12.0 (d 64) and 11.8 -> 12.8 (d 128), of 4 heads 14.9 -> 14.2.
 int attend_head_groups(const corm_desc* d, const LaunchCtx& c, int part_keys) {
   if (attend_on_mfma(d, c)) return 1;
   const int G = d->Hq / d->Hkv;
   const long wgs = (long)d->B * d->Hkv * ((d->Lcap + part_keys - 1) / part_keys);
   int n = 1;
-  while (n < G && wgs * n * 2 <= 2L * c.cus && (long)d->B * d->Hkv * n * 2 <= 65535) n *= 2;
+  while (n < G && wgs * n * 2 <= 2L * c.cus && (long)d->B * d->Hkv * n * 2 <= 65535) {
+    if (wgs * n * 2 > c.cus && G / (n * 2) < (d->kv_dtype == CORM_F32 ? 4 : 2)) break;
+    n *= 2;
+  }
   return n;
 }
 
