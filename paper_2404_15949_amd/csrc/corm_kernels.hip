@@ -371,7 +371,9 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
                      reinterpret_cast<int2*>(ws + wl.unit_state_off), keep, desc->Hkv, desc->Lcap, wl.nsplit,
                      wl.kb_stride, desc->w, desc->r, m);
   if (launch_status()) return CORM_EHIP;
-  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, CompactPolicy(), s);
+  CompactPolicy pol;
+  pol.bulk = true;
+  return launch_compact(desc, wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, pol, s);
 }
 
 int corm_selected_path(const corm_desc* desc, const corm_launch_opts* opts) {

@@ -313,28 +313,34 @@ struct CompactPolicy {
   int lazy = 0, dead_num = 0, dead_den = 1;
   unsigned long long* live = nullptr;   // lazy mode: the caller's live masks
   int32_t* nlive = nullptr;             // optional output: live keys per unit
+  bool bulk = false;                    // prompt seeding: most of a unit may go at once
 };
 
 // One launch of column slabs, or two of chunks?  A slab is one serial walk over its unit: where units * slabs leave compute
 // units idle, the chunks of a long unit share the work better (a hole at slot 0 of every unit, slabs | chunks, us, with
 // the 2-3 us of the count launch; rows of 256 bytes): 1 unit x 2048 slots 11 | 13, 4096: 16 | 13, 16384: 53 | 14;
-// 8 x 4096: 18 | 16, 16384: 56 | 30; 32 x 4096: 27 | 31, 16384: 136 | 94; 128 x 2048: 47 | 49, 4096: 103 | 94, 8192: 241 |
-// 232; 512 x 4096: 441 | 443, 8192: 873 | 886.  Where nothing is to be moved the slabs are a launch less (32 units x 4096
-// 4.8 | 6.3), unless many units of few slots pay for more workgroups (slabs + 1 each) than they have chunks (768 units x
-// 512 slots 11.2 | 7.6, 512-byte rows 16.4 | 7.5; 1024 slots 12.3 | 8.8 and 17.6 | 9.2).  The limits lie where the slabs were no
-// slower than the chunks in both regimes (1 to 768 units x 256 to 16384 slots, rows of 128, 256 and 512 bytes).
-bool compact_by_slabs(int units, int Lcap, int rowb) {
+// 8 x 4096: 18 | 16, 16384: 56 | 30; 32 x 4096: 27 | 31, 16384: 136 | 94; 128 x 4096: 103 | 94; 512 x 4096: 441 | 443.  Where
+// nothing is to be moved, and where a unit of many slots has few left, the slabs are a launch less (32 x 4096: 4.8 | 6.3),
+// unless very many units pay for more workgroups (slabs + 1 each) than they have chunks (768 units x 512 slots of 512
+// bytes 16.4 | 7.5).
+// The limits are those of whole decode steps that evict at every step, now and then, and never (2 to 768 units, 300 to
+// 16000 slots, 900 shapes): within them slabs are at worst 4 % slower than chunks and up to 45 % faster, beyond them up to 45 % slower
+// (8 units x 11700 slots: 59 us a step by slabs, 34 by chunks).
+// bulk: prompt seeding, whose eviction leaves few rows to walk (measured like that: 3 to 20 % faster by slabs).
+bool compact_by_slabs(int units, int Lcap, int rowb, bool bulk) {
   if (Lcap > SLAB_MAX_SLOTS) return false;
   const long slabs = 2 * rowb / slab_bytes(rowb), walks = units * slabs;
   const int nsplit = (Lcap + CHUNK - 1) / CHUNK;
-  if (units * (slabs + 1) > 1024 && 2 * (slabs + 1) > 3 * nsplit) return false;
-  if (Lcap <= (rowb <= 128 ? 2048 : rowb <= 256 ? 2816 : 3584)) return true;
-  return walks >= 1536 || (rowb >= 256 && walks >= 96 && walks <= 384 && Lcap <= 4608);
+  if (bulk) return Lcap <= 5632 || walks >= 64;
+  if (walks + units > 8192 && 2 * (slabs + 1) > 3 * nsplit) return false;
+  if (walks >= 1536) return true;
+  if (rowb <= 128) return Lcap <= (walks > 128 && walks < 512 ? 2304 : 2816);
+  return Lcap <= (rowb <= 256 && walks > 192 && walks < 320 ? 3072 : 4352);
 }
 
 template <int ROWB>
-void launch_compact_rows(const CompactArgs& a, hipStream_t s) {
-  if (compact_by_slabs(a.units, a.Lcap, ROWB)) {
+void launch_compact_rows(const CompactArgs& a, bool bulk, hipStream_t s) {
+  if (compact_by_slabs(a.units, a.Lcap, ROWB, bulk)) {
     const int groups = (a.units + SLAB_XCDS - 1) / SLAB_XCDS * SLAB_XCDS;
     hipLaunchKernelGGL((corm_compact_slab_kernel<ROWB>), dim3(groups * (2 * ROWB / slab_bytes(ROWB) + 1)), dim3(SLAB_WG),
                        (size_t)a.Lcap * sizeof(uint16_t), s, a);
@@ -372,9 +378,9 @@ int launch_compact(const corm_desc* d, const WorkspaceLayout& wl, void* workspac
     if (launch_status()) return CORM_EHIP;
   }
   switch (row_bytes(d)) {
-    case 128: launch_compact_rows<128>(a, s); break;
-    case 256: launch_compact_rows<256>(a, s); break;
-    case 512: launch_compact_rows<512>(a, s); break;
+    case 128: launch_compact_rows<128>(a, pol.bulk, s); break;
+    case 256: launch_compact_rows<256>(a, pol.bulk, s); break;
+    case 512: launch_compact_rows<512>(a, pol.bulk, s); break;
     default: return CORM_EUNSUPPORTED;
   }
   return launch_status();

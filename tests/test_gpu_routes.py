@@ -114,13 +114,12 @@ def test_compact_on_both_sides_of_the_slab_limit(dtype, d, Lcap):
             assert torch.equal(getattr(st, name)[0, u, :n], old[0, u, idx]), (kind, name)
 
 
-# kv dtype, d, units, Lcap: both sides of the limits between one launch of slabs and two of chunks (slots of few units; walks
-# of slabs, and slots, of more; workgroups of many short units)
-COMPACTS = [("bf16", 64, 5, 2048), ("bf16", 64, 5, 2049), ("bf16", 128, 5, 2816), ("bf16", 128, 5, 2817),
-            ("f32", 128, 5, 3584), ("f32", 128, 5, 3585), ("bf16", 128, 23, 4608), ("bf16", 128, 24, 4608),
-            ("f32", 64, 96, 4608), ("f32", 64, 97, 4608), ("bf16", 128, 24, 4609), ("bf16", 128, 383, 3000),
-            ("bf16", 128, 384, 3000), ("bf16", 64, 768, 16384), ("bf16", 64, 8, 16384), ("f32", 128, 113, 512),
-            ("f32", 128, 114, 512), ("bf16", 128, 204, 1536), ("bf16", 128, 205, 1536), ("bf16", 128, 205, 1537)]
+# kv dtype, d, units, Lcap: both sides of the limits between one launch of slabs and two of chunks (slots of a unit, by
+# the walks of the launch; walks; workgroups of very many short units)
+COMPACTS = [("bf16", 64, 5, 2816), ("bf16", 64, 5, 2817), ("bf16", 64, 70, 2304), ("bf16", 64, 70, 2305),
+            ("bf16", 128, 5, 4352), ("bf16", 128, 5, 4353), ("f32", 64, 64, 3072), ("f32", 64, 64, 3073),
+            ("f32", 128, 5, 4352), ("f32", 128, 5, 4353), ("bf16", 128, 383, 4360), ("bf16", 128, 384, 4360),
+            ("bf16", 64, 768, 16384), ("bf16", 64, 8, 16384), ("f32", 128, 910, 512), ("f32", 128, 911, 512)]
 
 
 @pytest.mark.parametrize("case", range(len(COMPACTS)))
