@@ -103,10 +103,15 @@ def _ptr(x) -> Optional[int]:
     return int(x)
 
 
+# The current stream's handle alone: building a Stream object takes longer than a launch.  Not a documented entry of
+# torch, so a build without it takes the documented one.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        if torch.cuda.is_initialized():   # the handle alone: building a Stream object takes longer than a launch
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream

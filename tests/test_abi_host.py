@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2404_15949_amd import corm
 
@@ -220,3 +221,19 @@ def test_product_code_never_touches_the_oracle():
     nxt = re.search(r"^(def |class |if __name__)", body[1:], flags=re.M)     # the next top-level statement
     body = body[:nxt.start() + 1] if nxt else body
     assert all(ln.strip() in body for ln in uses), "the oracle is imported outside the cpu_baseline leg"
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """torch's raw-stream entry is not a documented one: a build without it takes the documented Stream object."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    monkeypatch.setattr(corm, "_raw_stream", None)
+    assert corm._stream(None) == 0x1234
+    monkeypatch.setattr(corm, "_raw_stream", lambda device: 100 + device)
+    assert corm._stream(None) == 103
+    assert corm._stream(7) == 7
