@@ -10,9 +10,11 @@ DEV = "cuda:0"
 
 # kv dtype, G, Hkv, d, P, m, Tcap, position of the first key, thr_scale, holes
 SEEDS = [
-    ("bf16", 1, 2, 128, 700, 64, 704, 0, 1.0, False),      # whole blocks, several workgroups per key block
+    ("bf16", 1, 2, 128, 700, 64, 704, 0, 1.0, False),      # one whole block of queries
     ("bf16", 1, 2, 128, 515, 97, 517, 0, 1.0, False),      # tail and rows of no whole piece
-    ("bf16", 2, 1, 128, 640, 200, 672, 32, 1.0, False),    # positions shifted by a word
+    ("bf16", 2, 1, 128, 640, 200, 672, 32, 1.0, False),    # positions shifted by a word; seven workgroups per key block
+    ("bf16", 1, 128, 64, 700, 600, 704, 0, 1.0, False),    # one workgroup per key block over 38 tiles: more than the
+                                                           # 32 that the boolean ring's histories hold
     ("bf16", 4, 2, 64, 600, 130, 640, 3, 1.0, False),      # positions shifted by no piece
     ("bf16", 8, 1, 64, 300, 48, 320, 0, 1.0, True),        # keys missing: general blocks next to fast ones
     ("f32", 1, 2, 64, 520, 80, 576, 0, 1.0, False),
@@ -20,7 +22,7 @@ SEEDS = [
     ("f32", 8, 1, 128, 400, 33, 448, 32, 1.0, False),
     ("bf16", 2, 2, 128, 512, 64, 512, 0, 0.0, False),      # threshold 0: everything is important
     ("bf16", 2, 2, 128, 512, 64, 512, 0, 1e30, False),     # and one that nothing reaches
-    ("bf16", 1, 40, 128, 300, 32, 320, 0, 2.5, False),     # one workgroup per key block
+    ("bf16", 1, 40, 128, 300, 32, 320, 0, 2.5, False),     # many units with a block that is not whole
 ]
 
 
@@ -79,8 +81,9 @@ def test_seed_decides_by_the_score_on_every_ring(case):
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 128)])
 @pytest.mark.parametrize("Lcap", [1, 64, 513, 4097, 16384, 16385])
 def test_compact_on_both_sides_of_the_slab_limit(dtype, d, Lcap):
-    """A unit per kind of mask, at the edges of 64-slot words, of a batch of rows and of the longest unit that is compacted
-    in one launch; the survivors, their metadata and kept_idx against an index operation of torch, exactly."""
+    """A unit per kind of mask, at the edges of 64-slot words, of a batch of rows and of the longest unit that one launch could
+    hold (by slabs up to 513 slots here, the longer ones by chunks; the rule's own limits and long slabs are the next test);
+    the survivors, their metadata and kept_idx against an index operation of torch, exactly."""
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator(device=DEV).manual_seed(Lcap)
     kinds = ["all", "first", "last", "none", "third", "half", "tail", "one"]
