@@ -189,7 +189,8 @@ int corm_evict_mask_summary(const corm_desc* desc, const int32_t* last_hit, cons
 
 /* Stable per-unit compaction (the gather of Algorithm 1), in place: survivors keep their order;
  * K, V, pos, last_hit rows move to slot (number of survivors before them); lens = survivors.
- * kept_idx (may be NULL) receives the old slot of each survivor.  Uses the workspace for staging. */
+ * kept_idx (may be NULL) receives the old slot of each survivor.  Uses the workspace for the keep words and
+ * counts and, where the rows are moved by chunks in two launches, for staging. */
 int corm_compact(const corm_desc* desc, void* K, void* V, int32_t* pos, int32_t* last_hit, int32_t* lens,
                  const uint8_t* keep, int32_t* kept_idx, void* workspace, size_t workspace_bytes, void* stream);
 

@@ -334,11 +334,11 @@ __global__ __launch_bounds__(WG) void corm_compact_boundary_kernel(const Compact
 //
 // A slab is 128 bytes of a row, one cache line: 5 workgroups make a unit of 256-byte rows.  Bound by the bytes it has
 // to move where many units evict (512 units of 1100 to 4300 keys, a hole each: 0.42 GB read and written in 82 us,
-// 5.1 TB/s, what a plain copy reaches here; the two chunk launches 101 + 6 us), by the walk of one unit where a single
-// one does (4000 rows 27 us at worst, 9.5 us a step on average over the dense 512 units against 13.4), by the launch
-// itself where none does (4.9 us against 4.9 + 4.8).  Measured beside it on the same launches: slabs of 64 bytes 102
-// us and 7.4 us for the launch that finds nothing, whole rows 89 us; 256 threads 89 us, 1024 threads 83 us but 7.2 us
-// idle; four passes in flight 87 us.
+// 5.1 TB/s, what a plain copy reaches here; the two chunk launches 101 + 6 us), by what one compute unit loads and stores
+// where few do (a batch of 512 pieces 1.5 us: 4000 rows 12 us and the list; compact_by_slabs says where chunks are the better
+// choice), by the launch itself where none does (4.9 us for 512 units, 2.4 for 32; the chunks 4.9 + 4.8 and 2.2 + 2.4).
+// Measured beside it on the 512 units: slabs of 64 bytes 102 us and 7.4 us for the launch that finds nothing, whole rows
+// 89 us; 256 threads 89 us, 1024 threads 83 us but 7.2 us idle; four passes in flight 87 us.
 constexpr int SLAB_WG = 512;
 constexpr int SLAB_WAVES = SLAB_WG / 64;
 constexpr int SLAB_MAX_SLOTS = 16384;          // a 64-slot word per thread and a 16-bit source slot per survivor in LDS
@@ -453,8 +453,10 @@ __global__ __launch_bounds__(SLAB_WG) void corm_compact_slab_kernel(const Compac
   constexpr int HALF = SLABS / 2;
   char* base = (slab < HALF ? a.K : a.V) + (size_t)unit * a.Lcap * ROWB + (slab % HALF) * SLAB_BYTES + (tid % LPR) * 16;
   const int sub = tid / LPR;
-  // Two batches of NP passes: the next one's loads are in flight while this one waits and is stored (its sources lie
-  // behind every destination of this batch).  A batch is stored once all of its loads, of every wave, are in.
+  // Two batches of NP passes, the next one's loads issued before this one is stored (its sources lie behind every
+  // destination of this batch).  A batch is stored once all of its loads, of every wave, are in.  (The stores are
+  // predicated, so the compiler waits for both batches together.  Straight-line stores through a buffer descriptor, with
+  // exact counts, measured 2 % faster on 512 units x 4096 rows and 0.5 to 0.8 us slower on units of 1000.)
   u32x4_t ra[NP], rb[NP];
   auto load = [&](int j0, u32x4_t (&r)[NP]) __attribute__((always_inline)) {
 #pragma unroll

@@ -326,13 +326,14 @@ struct CompactPolicy {
 // The limits are those of whole decode steps that evict at every step, now and then, and never (2 to 768 units, 300 to
 // 16000 slots, 900 shapes): within them slabs are at worst 4 % slower than chunks and up to 45 % faster, beyond them up to 45 % slower
 // (8 units x 11700 slots: 59 us a step by slabs, 34 by chunks).
-// bulk: prompt seeding, whose eviction leaves few rows to walk (measured like that: 3 to 20 % faster by slabs).
+// bulk: prompt seeding, whose eviction leaves few rows to walk (measured like that: 3 to 20 % faster by slabs); very many
+// workgroups with nothing to walk cost the same there.
 bool compact_by_slabs(int units, int Lcap, int rowb, bool bulk) {
   if (Lcap > SLAB_MAX_SLOTS) return false;
   const long slabs = 2 * rowb / slab_bytes(rowb), walks = units * slabs;
   const int nsplit = (Lcap + CHUNK - 1) / CHUNK;
-  if (bulk) return Lcap <= 5632 || walks >= 64;
   if (walks + units > 8192 && 2 * (slabs + 1) > 3 * nsplit) return false;
+  if (bulk) return Lcap <= 5632 || walks >= 64;
   if (walks >= 1536) return true;
   if (rowb <= 128) return Lcap <= (walks > 128 && walks < 512 ? 2304 : 2816);
   return Lcap <= (rowb <= 256 && walks > 192 && walks < 320 ? 3072 : 4352);

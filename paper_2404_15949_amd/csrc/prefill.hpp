@@ -613,11 +613,15 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
 }
 
 // Pass 1 has a light tail (max, exp, sum) and is latency-bound at two waves per SIMD: held to the registers
-// and LDS of three (0.91 -> 0.64 ms for 512 heads x 1024 queries x 4096 keys).  Pass 2 needs the registers of two
-// (205; held to three it spills: 1.27 -> 1.76 ms).  Both are bound by vector instructions: per tile of 16 queries x
-// 64 keys 16 MFMAs and about 90 (pass 1), 102 (bf16 scores), 80 (bits) others.  Measured: bf16 scores 1.39 -> 1.27 ms
-// (ring written at 3.4 TB/s); bits, 512 heads x 1024 x 8192, 3.22 -> 1.62 ms (one wave per SIMD and a score per pair
-// before; 2.04 with compares whose results went through scalar registers); fp32, 16 units of 2000 keys, 74 -> 39 us (the queries of a key block shared by several workgroups).
+// and LDS of three (0.91 -> 0.64 ms for 512 heads x 1024 queries x 4096 keys; 166 registers now).  Pass 2 on 256-byte rows
+// takes the registers of two: four key tiles per wave hold 16 accumulators, 16 of the next tile, 16 latest hits and, by
+// the ring, 16 scores or histories beside the 64 of the keys (205 for bf16 scores, 253 for bits; held to three waves it
+// spills: 1.27 -> 1.76 ms).  fp32 rows of 512 bytes, two key tiles per wave, fit three (153 and 157 with score rings).
+// Both passes are bound by vector instructions: per tile of 16 queries x 64 keys 16 MFMAs and about 83 (pass 1), 102 (bf16
+// scores), 108 to 114 (bits) others.  Kernel times: bf16 scores 1.39 -> 1.20 ms (ring written at 3.5 TB/s);
+// bits, 512 heads x 1024 x 8192, 3.22 -> 1.62 ms (one wave per SIMD and a score per pair before; 2.04 with compares
+// whose results went through scalar registers); fp32, 16 units of 2000 keys, 74 -> 39 us (the queries of a key block shared by
+// several workgroups).
 template <typename DT, int D>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void corm_prefill_stats_kernel(
     const PrefillArgs a) {
