@@ -359,11 +359,11 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
     if (launch_status()) return CORM_EHIP;
   }
   if (desc->kv_dtype == CORM_F32)
-    rc = desc->d == 64 ? launch_prefill_dt<F32, 64>(a, grid, mgrid, wl.seed_kb, s)
-                       : launch_prefill_dt<F32, 128>(a, grid, mgrid, wl.seed_kb, s);
+    rc = desc->d == 64 ? launch_prefill_dt<F32, 64>(desc, ctx, wl, a, grid, mgrid, s)
+                       : launch_prefill_dt<F32, 128>(desc, ctx, wl, a, grid, mgrid, s);
   else
-    rc = desc->d == 64 ? launch_prefill_dt<BF16, 64>(a, grid, mgrid, wl.seed_kb, s)
-                       : launch_prefill_dt<BF16, 128>(a, grid, mgrid, wl.seed_kb, s);
+    rc = desc->d == 64 ? launch_prefill_dt<BF16, 64>(desc, ctx, wl, a, grid, mgrid, s)
+                       : launch_prefill_dt<BF16, 128>(desc, ctx, wl, a, grid, mgrid, s);
   if (rc) return rc;
   hipLaunchKernelGGL(corm_decide_kernel, dim3(wl.nsplit, units), dim3(WG), 0, s, lens, last_hit, t, t_first,
                      reinterpret_cast<unsigned long long*>(ws + wl.keepbits_off),

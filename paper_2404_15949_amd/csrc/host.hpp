@@ -417,10 +417,45 @@ void seed_segments(const corm_desc* d, const LaunchCtx& c, int m, long long key_
   *nseg = (blocks + *seg_blocks - 1) / *seg_blocks;
 }
 
+// Pass 1: query tiles per wave (max_qw, or 1) and how many workgroups share the keys of a query block (segments of whole
+// key blocks; the partials have room for one per key block).  A launch takes its rounds over the chip (three workgroups per
+// compute unit by registers, of the small ones four by LDS, which share it badly) times a segment's key tiles by the wave's query tiles and a fixed part
+// (queries, first keys, the end).  Whole calls, us, one query tile and four per wave, each with its best number of segments: 512 heads x
+// 1024 queries x 4096 keys 1841, 1600; 32 heads 134, 122; 8 heads x 700 x 5000 59, 59; 4 heads x 256 x 900 27, 31; 64 heads x 48 x
+// 20000 213, 232.  Unsplit the last three take 94, 33 and 407.
+constexpr double STATS_FIXED = 24., STATS_TILE = 1.5;
+template <int ROWB>
+int stats_segments(const corm_desc* d, const LaunchCtx& c, const WorkspaceLayout& wl, int max_qw, PrefillArgs& a) {
+  const int ntt = (a.m + 15) / 16 * (d->Hq / d->Hkv);
+  const long long units = d->B * d->Hkv;
+  double best = 0.;
+  int qw = max_qw, n = 0;
+  for (int w = max_qw; w >= 1; w -= w > 1 ? w - 1 : 1)
+    for (int i = 1; i <= std::min(wl.seed_nkb, 64); ++i) {
+      const long long wgs = units * ((ntt + WAVES * w - 1) / (WAVES * w)) * i, slots = (w > 1 ? 6LL : 7LL) * c.cus / 2;
+      const int tiles = (wl.seed_nkb + i - 1) / i * (wl.seed_kb / 16);
+      const double cost = (double)((wgs + slots - 1) / slots) * (tiles * (w + STATS_TILE) + STATS_FIXED);
+      if (n > 0 && cost > 0.95 * best) continue;
+      best = cost;
+      qw = w;
+      n = i;
+    }
+  a.nqb = (ntt + WAVES * qw - 1) / (WAVES * qw);
+  a.kseg = (wl.seed_nkb + n - 1) / n * wl.seed_kb;
+  a.nks = (d->Lcap + a.kseg - 1) / a.kseg;
+  return qw;
+}
+
 template <typename DT, int D>
-int launch_prefill_dt(const PrefillArgs& a, dim3 grid, dim3 mgrid, int KB, hipStream_t s) {
-  hipLaunchKernelGGL((corm_prefill_stats_kernel<DT, D>), grid, dim3(WG), 0, s, a);
-  hipLaunchKernelGGL(corm_prefill_merge_kernel, mgrid, dim3(256), 0, s, a, KB);
+int launch_prefill_dt(const corm_desc* d, const LaunchCtx& c, const WorkspaceLayout& wl, PrefillArgs& a, dim3 grid,
+                      dim3 mgrid, hipStream_t s) {
+  constexpr int MAX_QW = std::is_same<DT, F32>::value ? 1 : stats_qw<D * DT::ESZ>();
+  const int qw = stats_segments<D * DT::ESZ>(d, c, wl, MAX_QW, a);
+  const long long wgs = (long long)PREFILL_XCDS * ((a.units + PREFILL_XCDS - 1) / PREFILL_XCDS) * a.nqb * a.nks;
+  if (wgs > 2147483647LL) return CORM_EUNSUPPORTED;
+  if (qw == MAX_QW) hipLaunchKernelGGL((corm_prefill_stats_kernel<DT, D, MAX_QW>), dim3((unsigned)wgs), dim3(WG), 0, s, a);
+  else hipLaunchKernelGGL((corm_prefill_stats_kernel<DT, D, 1>), dim3((unsigned)wgs), dim3(WG), 0, s, a);
+  hipLaunchKernelGGL(corm_prefill_merge_kernel, mgrid, dim3(256), 0, s, a);
   // (a head's ring of more than DEAD_OFFSET bytes, 8 heads x 4096 rows x 270336 bf16 positions: 1269 us by the general
   // blocks, 927 by the rows of a tile)
   const uint64_t row = a.ring_bits ? (uint64_t)a.ring_words * 4 : (uint64_t)a.Tcap * (a.ring_bf16 ? 2 : 4);

@@ -12,13 +12,14 @@ namespace {
 // have put them.  [m x L] logits per head are a dense contraction, so q.K^T runs on the MFMA units; the
 // elementwise tail (exp, rounding, compare) and the ring store bound the rest.
 //
-// Key-major decomposition, the same inner loop twice:
-//   pass 1   workgroup = 256 (128) keys of a unit, loops over all query tiles: per query the max and the
-//            sum of exp over its keys -> partials [head, key block, query]
-//   merge    per query: max and 1/sum over the key blocks, and what pass 2 compares with
-//   pass 2   same loop; p = exp2(s - max) / sum, stored to the ring row of the query's step at the key's
-//            position, and per key the latest step whose stored score reaches the threshold
-// The workgroup keeps its keys in registers as the A operand (lane l: row l%16 of a 16-key tile, the
+// Two passes over the same products:
+//   pass 1   query-major, workgroup = up to 16 tiles of 16 queries, loops over the keys of its segment: per query the sum of
+//            exp relative to a reference -> partials [head, key segment, query]
+//   merge    per query: reference and 1/sum over the segments, and what pass 2 compares with
+//   pass 2   key-major, workgroup = 256 (128) keys of a unit, loops over all query tiles; p = exp2(s - reference) / sum,
+//            stored to the ring row of the query's step at the key's position, and per key the latest step whose
+//            stored score reaches the threshold
+// In pass 2 the workgroup keeps its keys in registers as the A operand (lane l: row l%16 of a 16-key tile, the
 // 16 bytes 64*c + 16*(l/16) .. of each 64-byte chunk c of the row); a tile of 16 queries is the B
 // operand in the same layout, read from LDS, where the workgroup stages the queries in double-buffered
 // blocks.  D: lane l holds query l%16 and rows 4*(l/16) .. +3 of each key tile.
@@ -38,12 +39,13 @@ struct PrefillArgs {
   int32_t* last_hit;
   const int32_t* t;
   void* ring;
-  float2* part;    // [B*Hq, nkb, w]  (max, sum) per key block
+  float2* part;    // [B*Hq, nkb, w]  (reference, sum) per key segment (nks <= nkb of them)
   float4* stats;   // [B*Hq, w]       per query: see prefill_query_stats
   int32_t* status;
   int32_t Hq, Hkv, Lcap, Tcap, w, m, nkb, ring_bf16;
   int32_t units;                   // B * Hkv
-  int32_t nseg, seg_blocks;        // workgroups that share the query blocks of a key block, blocks each
+  int32_t nqb, nks, kseg;          // pass 1: query blocks of a unit, key segments of a unit, keys per segment
+  int32_t nseg, seg_blocks;        // pass 2: workgroups that share the query blocks of a key block, blocks each
   int32_t ring_bits, ring_words;   // boolean message: one bit per (row, position), words per row
   float thr_scale, scale_log2;
 };
@@ -115,32 +117,6 @@ __device__ __forceinline__ float4 prefill_query_stats(const PrefillArgs& a, floa
   return s;
 }
 
-// Pass 1 on one wave tile (16 queries x 16*T keys): per query, max of the scaled logits and the sum of
-// exp2 relative to it, over the keys the query sees.  seen: bit 4*tl + r of this lane (MASKED only).
-template <bool MASKED, int T>
-__device__ __forceinline__ void prefill_stats_tile(const f32x4_t (&d)[T], uint32_t seen, float scale_log2,
-                                                   float& mx_out, float& z_out) {
-  float mx = neg_inf();   // of the raw logits: the scale is positive and keeps their order
-#pragma unroll
-  for (int tl = 0; tl < T; ++tl)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      mx = fmaxf(mx, (!MASKED || ((seen >> (4 * tl + r)) & 1u)) ? d[tl][r] : neg_inf());
-  mx = rows_allreduce_max(mx);
-  const float ms = mx == neg_inf() ? 0.f : mx * scale_log2;
-  float z = 0.f;
-#pragma unroll
-  for (int tl = 0; tl < T; ++tl)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float e = fast_exp2(fmaf(d[tl][r], scale_log2, -ms));
-      z += (!MASKED || ((seen >> (4 * tl + r)) & 1u)) ? e : 0.f;
-    }
-  z = rows_allreduce_sum(z);
-  mx_out = mx == neg_inf() ? mx : ms;
-  z_out = z;
-}
-
 template <int ROWB>
 struct PrefillGeom {
   static constexpr int NCH = ROWB / 64;            // 64-byte chunks of a row
@@ -149,24 +125,293 @@ struct PrefillGeom {
   static constexpr int KB = WAVES * WKEYS;         // keys per workgroup
   static constexpr int QBLK = ROWB <= 256 ? 64 : 32;   // queries staged in LDS at a time
   static constexpr int QT = QBLK / 16;             // query tiles of a block
-  static constexpr int FLUSH = 512 / QBLK;         // blocks whose pass-1 partials a workgroup holds in LDS at a time
   static constexpr int QROW = ROWB + 16;           // LDS row pitch (padded against bank conflicts)
   static constexpr int QLOADS = QBLK * ROWB / (WG * 16);   // 16-byte loads per thread and block
   static_assert(QBLK * ROWB % (WG * 16) == 0 && QBLK <= WG, "a block is loaded in whole passes of the workgroup");
 };
 
+// ---------------------------------------------------------------- pass 1: the sum of exp per query
+//
+// Query-major, the other way round than pass 2: a wave keeps QW tiles of 16 queries in registers (B operand) and all keys of
+// its segment pass by through LDS (A operand, double-buffered blocks).  A lane then holds four keys of ONE query per tile,
+// so its sum stays in a register from the first key to the last: nothing crosses lanes, and nothing is flushed,
+// inside the loop.  The elementwise tail is little more than fma, exp2, add per pair: the reference of a sum (a power of two,
+// each lane its own) is not the running maximum but follows it: where a tile's four terms add up to more than STATS_JUMP, the
+// reference is moved to their maximum and they are formed again, which is rare after the first block.  So, as with the maximum,
+// the terms that make up a sum come from small differences.  A workgroup with a sum that is 0 or not
+// finite in the end does the loop again, first for the maxima and then for the sums against them.
+// Bound by the products, at the rate the card's power leaves (with the tail dropped 480 us for 512 heads x 1024 queries x 4096 keys:
+// 1.0 PFLOP/s; a large library product 1.15), and by what of the tail does not fit beside them.  Key-major with a maximum per
+// tile, as before, 768 us in a row of runs, now 697 (bf16), 1291 -> 1094 for 512 x 1024 x 8192; the merge 22 -> 7 us, since a
+// row has a partial per segment and no longer one per 256 keys.  A sum against the fixed reference 0 takes 640, but its
+// terms carry the rounding of whole logits (fp32 ring 8.3e-7 from 64 bits, 5.6e-7 as it is); a whole block done again in
+// place of a tile 729; 32 x 32 tiles at two waves per SIMD 686 and 702, 128 queries per wave 709 to 764 (all against the reference 0).
+
+constexpr float STATS_JUMP = 16.f;
+
+// QW query tiles per wave: as many as the registers of three waves per SIMD hold, so that a key tile read from LDS serves as many
+// products as it can; one where the launch is short of workgroups, and with fp32, whose products take long enough for any
+// LDS traffic (stats_segments).
+template <int ROWB>
+constexpr int stats_qw() { return ROWB <= 256 ? 4 : 2; }
+
+template <int ROWB, int QW>
+struct StatsGeom {
+  static constexpr int NCH = ROWB / 64;
+  static constexpr int QTWG = WAVES * QW;          // query tiles per workgroup
+  static constexpr int KBLK = ROWB <= 256 ? 64 : 32;   // keys staged in LDS at a time
+  static constexpr int KT = KBLK / 16;
+  static constexpr int NT = QW >= KT ? 1 : KT / QW;    // key tiles worked on together: independent chains of products
+  static constexpr int KROW = ROWB + 16;           // LDS row pitch (padded against bank conflicts)
+  static constexpr int KLOADS = KBLK * ROWB / (WG * 16);
+  static_assert(KBLK * ROWB % (WG * 16) == 0 && KBLK <= 64, "a block is loaded in whole passes of the workgroup");
+};
+
+template <typename DT, int D, int QW>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void corm_prefill_stats_kernel(
+    const PrefillArgs a) {
+  constexpr int ROWB = D * DT::ESZ;
+  using Geo = StatsGeom<ROWB, QW>;
+  constexpr int NCH = Geo::NCH, KBLK = Geo::KBLK, KT = Geo::KT, KROW = Geo::KROW, KLOADS = Geo::KLOADS;
+  constexpr int NT = Geo::NT;
+  constexpr int NEVER = 0x7fffffff;   // position of a slot that holds no key: visible to no query
+
+  // workgroup id % 8 names the XCD; the workgroups of a unit (its query blocks first, they read the same keys) follow one
+  // another on it
+  const int per_xcd = (a.units + PREFILL_XCDS - 1) / PREFILL_XCDS;
+  const int li = (int)(blockIdx.x / PREFILL_XCDS);
+  const int qblk = li % a.nqb, lk = li / a.nqb;
+  const int ks = lk % a.nks;
+  const int unit = (int)(blockIdx.x % PREFILL_XCDS) * per_xcd + lk / a.nks;
+  if (lk / a.nks >= per_xcd || unit >= a.units) return;
+  const int b = unit / a.Hkv, hkv = unit - b * a.Hkv;
+  const int G = a.Hq / a.Hkv;
+  const int lgG = 31 - __clz(G);   // G is a power of two
+  int L = a.lens[unit];
+  L = L < 0 ? 0 : (L > a.Lcap ? a.Lcap : L);
+  const int key_beg = ks * a.kseg, key_end = min(key_beg + a.kseg, L);
+  if (key_beg >= L) return;
+  const int tcur = a.t[b];
+  const int tau0 = tcur - a.m + 1;   // step of tail query 0
+  if (tau0 < 1 || tcur > a.Tcap) return;   // (pass 2 reports it)
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n = lane & 15, lg = lane >> 4;
+
+  __shared__ __attribute__((aligned(16))) char sh_k[2][KBLK * KROW];
+  __shared__ __attribute__((aligned(16))) int32_t sh_pos[2][KBLK];
+
+  const int ntt = ((a.m + 15) / 16) << lgG;                    // query tiles of the group
+  const int wtt = (qblk * WAVES + wv) * QW;                    // this wave's first
+  const int tt_end = min((qblk + 1) * WAVES * QW, ntt);        // end of the workgroup's
+  const int nqt = min(max(ntt - wtt, 0), QW);                  // tiles of this wave
+  // the last position the workgroup sees, the last and the first query of the wave: positions they see
+  const int wg_last = tau0 + min(((tt_end - 1) >> lgG) * 16 + 15, a.m - 1) - 1;
+  const int vis_last = tau0 + min(((wtt + nqt - 1) >> lgG) * 16 + 15, a.m - 1) - 1;
+  const int vis_first = tau0 + (wtt >> lgG) * 16 - 1;
+
+  uint4 qb[QW][NCH];
+  int vis[QW];   // this lane's query of the tile sees positions <= vis
+#pragma unroll
+  for (int qt = 0; qt < QW; ++qt) {
+    const int tt = min(wtt + qt, ntt - 1), j = (tt >> lgG) * 16 + n;
+    const char* q = reinterpret_cast<const char*>(a.q_tail) +
+                    ((size_t)(b * a.Hq + hkv * G + (tt & (G - 1))) * a.m + min(j, a.m - 1)) * ROWB;
+    vis[qt] = wtt + qt < ntt && j < a.m ? tau0 + j - 1 : -1;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) qb[qt][c] = *reinterpret_cast<const uint4*>(q + c * 64 + 16 * lg);
+  }
+
+  const __amdgpu_buffer_rsrc_t rk = make_rsrc(
+      reinterpret_cast<const char*>(a.K) + (size_t)unit * a.Lcap * ROWB, (uint32_t)key_end * ROWB);
+  const __amdgpu_buffer_rsrc_t rp = make_rsrc(a.pos + (size_t)unit * a.Lcap, (uint32_t)key_end * 4);
+  u32x4_t kr[KLOADS];
+  int pr;
+  auto fetch = [&](int key0) __attribute__((always_inline)) {   // (past the end: zeros, no traffic)
+#pragma unroll
+    for (int i = 0; i < KLOADS; ++i)
+      kr[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, (int)((uint32_t)key0 * ROWB + (uint32_t)(i * WG + tid) * 16), 0, 0);
+    pr = __builtin_amdgcn_raw_buffer_load_b32(rp, (key0 + tid % KBLK) * 4, 0, 0);
+  };
+  auto stage = [&](int buf, int key0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < KLOADS; ++i) {
+      const int o = (i * WG + tid) * 16;   // row o / ROWB, column o % ROWB
+      *reinterpret_cast<u32x4_t*>(&sh_k[buf][(o / ROWB) * KROW + (o % ROWB)]) = kr[i];
+    }
+    const bool held = key0 + tid % KBLK < key_end && pr >= 0 && pr < a.Tcap;
+    sh_pos[buf][tid % KBLK] = held ? pr : NEVER;
+  };
+  auto mma_tile = [&](int cur, int kt, f32x4_t (&d)[QW]) __attribute__((always_inline)) {
+    uint4 ka[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      ka[c] = *reinterpret_cast<const uint4*>(&sh_k[cur][(kt * 16 + n) * KROW + c * 64 + 16 * lg]);
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) d[qt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int qt = 0; qt < QW; ++qt) d[qt] = PrefillMma<DT>::mma(ka[c], qb[qt][c], d[qt]);
+  };
+
+  float ms[QW], mx[QW], z[QW];   // reference of the sum, maximum (raw logits), sum: of this lane's keys of a query
+  uint32_t any = 0u;             // bit qt: the query saw a key
+#pragma unroll
+  for (int qt = 0; qt < QW; ++qt) {
+    ms[qt] = 0.f;
+    mx[qt] = neg_inf();
+  }
+  float unset = 2.f * STATS_JUMP * NT;   // (0 from the first block on) the wave's references are to be set
+  // moves a reference to the maximum m of a tile's raw logits, if it is higher or the first
+  auto follow = [&](int qt, float m) __attribute__((always_inline)) {
+    const float to = rintf(m * a.scale_log2);
+    if (fabsf(to) < 1e6f && (to > ms[qt] || z[qt] == 0.f)) {
+      z[qt] = ldexpf(z[qt], (int)(ms[qt] - to));
+      ms[qt] = to;
+    }
+  };
+  enum { FOLLOW, MAXIMA, FIXED };   // the reference follows the sum; the maxima instead; the sum against the maxima
+  auto walk = [&](int mode) __attribute__((always_inline)) {
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) z[qt] = 0.f;
+    fetch(key_beg);
+    stage(0, key_beg);
+    int cur = 0;
+    for (int key0 = key_beg; key0 < key_end; key0 += KBLK, cur ^= 1) {
+      __syncthreads();   // the block is staged; nobody reads the other buffer any more
+      const int first = sh_pos[cur][0];
+      if (first > wg_last && first != NEVER) break;   // (uniform) positions ascend: nothing more to be seen
+      fetch(key0 + KBLK);
+      const int p = sh_pos[cur][lane % KBLK];
+      if (__all(p <= vis_first) && nqt == QW && mode != MAXIMA) {
+        // (uniform over the wave) every query sees every key: straight-line code, the next tile's products under this tile's tail
+        any = (1u << QW) - 1u;
+        f32x4_t dn[NT][QW];
+#pragma unroll
+        for (int x = 0; x < NT; ++x) mma_tile(cur, x, dn[x]);
+#pragma unroll
+        for (int kt = 0; kt < KT; kt += NT) {
+          f32x4_t d[NT][QW];
+#pragma unroll
+          for (int x = 0; x < NT; ++x)
+#pragma unroll
+            for (int qt = 0; qt < QW; ++qt) d[x][qt] = dn[x][qt];
+#pragma unroll
+          for (int x = 0; x < NT; ++x)
+            if (kt + NT < KT) mma_tile(cur, kt + NT + x, dn[x]);
+          float sum[QW], big = kt ? 0.f : unset;
+          auto terms = [&](int x, int qt) __attribute__((always_inline)) {
+            float e[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[r] = fast_exp2(fmaf(d[x][qt][r], a.scale_log2, -ms[qt]));
+            return (e[0] + e[1]) + (e[2] + e[3]);
+          };
+#pragma unroll
+          for (int qt = 0; qt < QW; ++qt) {
+            sum[qt] = 0.f;
+#pragma unroll
+            for (int x = 0; x < NT; ++x) sum[qt] += terms(x, qt);
+            big = fmaxf(big, sum[qt]);
+          }
+          if (__builtin_expect(__any(big > STATS_JUMP * NT) && mode == FOLLOW, 0)) {
+#pragma unroll
+            for (int qt = 0; qt < QW; ++qt) {
+              asm volatile("" : "+v"(ms[qt]));   // (nothing of this is to be done ahead of the branch)
+              float m = neg_inf();
+#pragma unroll
+              for (int x = 0; x < NT; ++x)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) m = fmaxf(m, d[x][qt][r]);
+              follow(qt, m);
+              sum[qt] = 0.f;
+#pragma unroll
+              for (int x = 0; x < NT; ++x) sum[qt] += terms(x, qt);
+            }
+          }
+#pragma unroll
+          for (int qt = 0; qt < QW; ++qt) z[qt] += sum[qt];
+        }
+        unset = 0.f;
+      } else if (__any(p <= vis_last) && nqt > 0) {
+        unset = 0.f;
+#pragma unroll 1
+        for (int kt = 0; kt < KT; ++kt) {
+          f32x4_t d[QW];
+          mma_tile(cur, kt, d);
+          const int4 kp = *reinterpret_cast<const int4*>(&sh_pos[cur][kt * 16 + 4 * lg]);
+#pragma unroll
+          for (int qt = 0; qt < QW; ++qt) {
+            const bool s[4] = {kp.x <= vis[qt], kp.y <= vis[qt], kp.z <= vis[qt], kp.w <= vis[qt]};
+            any |= (s[0] || s[1] || s[2] || s[3]) ? 1u << qt : 0u;
+            float m = neg_inf();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m = fmaxf(m, s[r] ? d[qt][r] : neg_inf());
+            if (mode == MAXIMA) {
+              mx[qt] = fmaxf(mx[qt], m);
+            } else {
+              if (mode == FOLLOW) follow(qt, m);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float e = fast_exp2(fmaf(d[qt][r], a.scale_log2, -ms[qt]));
+                z[qt] += s[r] ? e : 0.f;
+              }
+            }
+          }
+        }
+      }
+      stage(cur ^ 1, key0 + KBLK);
+    }
+    __syncthreads();
+  };
+
+  walk(FOLLOW);
+  bool out_of_range = false;
+#pragma unroll
+  for (int qt = 0; qt < QW; ++qt) {   // the four lane groups of a query, each with a reference of its own
+    const float m = z[qt] > 0.f ? ms[qt] : neg_inf();
+    ms[qt] = rows_allreduce_max(m);
+    z[qt] = rows_allreduce_sum(z[qt] > 0.f ? ldexpf(z[qt], (int)(m - ms[qt])) : z[qt]);
+    if (ms[qt] == neg_inf()) ms[qt] = 0.f;
+    out_of_range |= ((rows_allreduce_or(any) >> qt) & 1u) && !(z[qt] > 0.f && z[qt] < __builtin_inff());
+  }
+  if (__syncthreads_or(out_of_range)) {   // (rare)
+    walk(MAXIMA);
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) {
+      mx[qt] = rows_allreduce_max(mx[qt]);
+      ms[qt] = mx[qt] == neg_inf() ? 0.f : mx[qt] * a.scale_log2;
+    }
+    walk(FIXED);
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) {
+      z[qt] = rows_allreduce_sum(z[qt]);
+      if (mx[qt] == neg_inf()) ms[qt] = neg_inf();
+    }
+  }
+  any = rows_allreduce_or(any);
+#pragma unroll
+  for (int qt = 0; qt < QW; ++qt) {
+    const int tt = wtt + qt, j = (tt >> lgG) * 16 + n;
+    if (lg == 0 && tt < ntt && j < a.m)
+      a.part[((size_t)(b * a.Hq + hkv * G + (tt & (G - 1))) * a.nkb + ks) * a.w + j] =
+          make_float2((any >> qt) & 1u ? ms[qt] : neg_inf(), z[qt]);
+  }
+}
+
+// ---------------------------------------------------------------- pass 2: scores, ring rows, last hits
+
 // FAR: a head's ring reaches beyond the 32-bit offsets of a buffer descriptor (pass 2).
-template <typename DT, int D, int PASS, int MODE, bool FAR>
-__device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
+template <typename DT, int D, int MODE, bool FAR>
+__device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   constexpr int ROWB = D * DT::ESZ;
   using Geo = PrefillGeom<ROWB>;
   constexpr int NCH = Geo::NCH, T = Geo::T, KB = Geo::KB, WKEYS = Geo::WKEYS, QT = Geo::QT;
-  constexpr int QBLK = Geo::QBLK, QROW = Geo::QROW, QLOADS = Geo::QLOADS, FLUSH = Geo::FLUSH;
+  constexpr int QBLK = Geo::QBLK, QROW = Geo::QROW, QLOADS = Geo::QLOADS;
   constexpr int NEVER = 0x7fffffff;   // position of a slot that holds no key: visible to no query
   // Which key of the wave sits in row 4*lg + r of key tile tl: where a lane's 4*T values leave as bf16 or as bits,
   // 4*T consecutive keys (they pack into whole words of the lane); fp32 scores leave per key tile, 64
   // consecutive bytes per query.
-  constexpr bool RUN = PASS == 2 && MODE != SEED_F32;
+  constexpr bool RUN = MODE != SEED_F32;
 
   // One-dimensional grid of 8 * ceil(units / 8) * nkb * nseg workgroups.  Workgroups are dealt round-robin to the 8
   // XCDs, so id % 8 names the XCD; each XCD takes a contiguous range of units and runs the key blocks of a unit
@@ -195,13 +440,12 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
   const int s0 = (tau0 - 1) % a.w;   // ring slot of tail query 0
 
   __shared__ __attribute__((aligned(16))) char sh_q[2][QBLK * QROW];     // query blocks, double buffered
-  __shared__ __attribute__((aligned(16))) float4 sh_st[2][PASS == 2 ? QBLK : 1];   // prefill_query_stats per query
+  __shared__ __attribute__((aligned(16))) float4 sh_st[2][QBLK];   // prefill_query_stats per query
   __shared__ __attribute__((aligned(16))) int32_t sh_pos[KB];            // positions of the workgroup's keys
-  __shared__ float2 sh_part[PASS == 1 ? WAVES : 1][PASS == 1 ? FLUSH * QBLK : 1];
   // Pass 2, bf16 ring: a wave's tile of stored scores is turned through LDS so that every query's consecutive
   // positions leave as one piece of its ring row (16 bytes per lane).  Rows are padded by 16 bytes.
   constexpr int TROW = WKEYS + 8;
-  constexpr bool TURN = PASS == 2 && MODE == SEED_BF16;
+  constexpr bool TURN = MODE == SEED_BF16;
   __shared__ __attribute__((aligned(16))) uint16_t sh_t[TURN ? WAVES : 1][TURN ? 16 : 1][TURN ? TROW : 1];
 
   const char* Kb = reinterpret_cast<const char*>(a.K) + (size_t)unit * a.Lcap * ROWB;
@@ -265,11 +509,10 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
       const char* q = qg + (size_t)(tt & (G - 1)) * a.m * ROWB;
       qr[i] = *reinterpret_cast<const u32x4_t*>(q + (uint32_t)j * ROWB + (tid * 16) % ROWB);
     }
-    if (PASS == 2) {   // (every wave the same QBLK queries: no branch, whose join would cost the exact wait count)
-      const int tt = min(blk * QT + (tid % QBLK) / 16, ntt - 1);
-      const int j = min((tt >> lgG) * 16 + (tid & 15), a.m - 1);
-      str = stats[(size_t)(tt & (G - 1)) * a.w + j];
-    }
+    // (every wave the same QBLK queries: no branch, whose join would cost the exact wait count)
+    const int tt = min(blk * QT + (tid % QBLK) / 16, ntt - 1);
+    const int j = min((tt >> lgG) * 16 + (tid & 15), a.m - 1);
+    str = stats[(size_t)(tt & (G - 1)) * a.w + j];
   };
   auto mma_tile = [&](int cur, int ti, f32x4_t (&d)[T]) __attribute__((always_inline)) {
     uint4 qb[NCH];
@@ -316,7 +559,7 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
   // Boolean ring: fast blocks only shift a bit per key and tile into a history; every 32 tiles, or where their run ends,
   // the newest set bit of each becomes a step.  (With score rings, whose tail is longer, the registers cost more than
   // the compares: 1.22 -> 1.24 ms.)
-  constexpr bool HIST = PASS == 2 && MODE == SEED_BITS;
+  constexpr bool HIST = MODE == SEED_BITS;
   uint32_t hist[T][4];
 #pragma unroll
   for (int tl = 0; tl < T; ++tl)
@@ -342,296 +585,252 @@ __device__ __forceinline__ void prefill_pass(const PrefillArgs& a) {
       const int o = (i * WG + tid) * 16;   // row o / ROWB, column o % ROWB
       *reinterpret_cast<u32x4_t*>(&sh_q[buf][(o / ROWB) * QROW + (o % ROWB)]) = qr[i];
     }
-    if (PASS == 2) sh_st[buf][tid % QBLK] = str;
+    sh_st[buf][tid % QBLK] = str;
   };
   if (blk_beg < blk_end) {
     fetch(blk_beg, qr, str);
     stage(blk_beg & 1, qr, str);
   }
-  // pass 1 empties its partials every FLUSH blocks; pass 2 has one stretch
-  for (int grp = PASS == 1 ? blk_seg : blk_beg; grp < blk_end; grp += PASS == 1 ? FLUSH : blk_end) {
-    const int grp_end = PASS == 1 ? min(grp + FLUSH, blk_end) : blk_end;
-    if (PASS == 1) {
-      for (int i = tid; i < WAVES * FLUSH * QBLK; i += WG) (&sh_part[0][0])[i] = make_float2(neg_inf(), 0.f);
-    }
-    for (int blk = max(grp, blk_beg); blk < grp_end; ++blk) {
-      const int cur = blk & 1;
-      __syncthreads();   // block blk is staged; nobody reads the other buffer any more
-      fetch(min(blk + 1, blk_end - 1), qr, str);
-      const int tt0 = blk * QT;
+  for (int blk = blk_beg; blk < blk_end; ++blk) {
+    const int cur = blk & 1;
+    __syncthreads();   // block blk is staged; nobody reads the other buffer any more
+    fetch(min(blk + 1, blk_end - 1), qr, str);
+    const int tt0 = blk * QT;
 
-      // (uniform over the wave) every query of the block exists and sees every key of the wave, and pass 2 can
-      // store whole pieces: straight-line code, the next tile's MFMAs under this tile's tail
-      const bool fast = tt0 + QT <= ntt && ((tt0 + QT - 1) >> lgG) * 16 + 15 < a.m &&
-                        pos_wmax <= tau0 + (tt0 >> lgG) * 16 - 1 && (PASS == 1 || rows_ok) &&
-                        (!FAR || (16 * row_bytes64 <= DEAD_OFFSET &&
-                                  slot_of((tt0 >> lgG) * 16) <= slot_of(((tt0 + QT - 1) >> lgG) * 16 + 15)));
-      if (fast) {
-        if (HIST) {
-          if (hist_n + QT > 32 || (hist_n && hist_tt + 1 != tt0)) settle();
-          hist_n += QT;
-          hist_tt = tt0 + QT - 1;
-        }
-        f32x4_t dn[T];
-        mma_tile(cur, 0, dn);
-#pragma unroll
-        for (int ti = 0; ti < QT; ++ti) {
-          f32x4_t d[T];
-#pragma unroll
-          for (int tl = 0; tl < T; ++tl) d[tl] = dn[tl];
-          if (ti + 1 < QT) mma_tile(cur, ti + 1, dn);
-          const int tt = tt0 + ti, j = (tt >> lgG) * 16 + n, tau = tau0 + j;
-          if (PASS == 1) {
-            float mx, z;
-            prefill_stats_tile<false, T>(d, 0u, a.scale_log2, mx, z);
-            if (lg == 0) sh_part[wv][(blk - grp) * QBLK + ti * 16 + n] = make_float2(mx, z);
-          } else if (MODE == SEED_BITS) {
-            const float4 st = sh_st[cur][ti * 16 + n];
-            uint32_t unsure = __float_as_uint(st.y), hbits = 0u;   // (the sign: this query has no band)
-#pragma unroll
-            for (int i = 4 * T - 1; i >= 0; --i) {   // key i of the lane's run: row i % 4 of key tile i / 4
-              const float above = st.w - d[i >> 2][i & 3], below = st.z - d[i >> 2][i & 3];
-              hist[i >> 2][i & 3] = shift_in_sign(hist[i >> 2][i & 3], above);
-              hbits = shift_in_sign(hbits, above);
-              unsure |= __float_as_uint(above) ^ __float_as_uint(below);
-            }
-            if (__any((int)unsure < 0)) {   // (uniform, rare) what lies in the band is decided by the score
-              const float thr = importance_threshold(a.thr_scale, tau);
-              if (__float_as_int(st.y) < 0) hbits = 0u;
-#pragma unroll 1
-              for (int tl = 0; tl < T; ++tl) {
-                const f32x4_t x = tl == 0 ? d[0] : tl == 1 ? d[1] : tl == 2 ? d[T > 2 ? 2 : 0] : d[T > 2 ? 3 : 0];
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  hbits |= (prefill_score(x[r], a.scale_log2, st.x, st.y) >= thr ? 1u : 0u) << (4 * tl + r);
-              }
-#pragma unroll
-              for (int i = 0; i < 4 * T; ++i)   // (an instruction each: the low bit replaced)
-                hist[i >> 2][i & 3] = (hist[i >> 2][i & 3] & ~1u) | ((hbits >> i) & 1u);
-            }
-            // the wave owns whole words of every query's row: plain stores
-            const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
-            const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 >> 5) * 4;
-            if (T == 4) {   // 16 keys per lane: two lane groups to a word
-              const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
-              __builtin_amdgcn_raw_buffer_store_b32(sw[0] | (sw[1] << 16), rr, (lg & 1) ? DEAD_OFFSET : at + (lg >> 1) * 4, 0, 0);
-            } else {        // 8 keys per lane: four lane groups to a word
-              const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
-              __builtin_amdgcn_raw_buffer_store_b32(w, rr, lg ? DEAD_OFFSET : at, 0, 0);
-            }
-          } else {
-            const float4 st = sh_st[cur][ti * 16 + n];
-            float pv[T][4];
-#pragma unroll
-            for (int tl = 0; tl < T; ++tl)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                pv[tl][r] = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
-                hm[tl][r] = pv[tl][r] >= st.z ? tau : hm[tl][r];
-                // (said to be read here: left alone, the compiler keeps the compares of all tiles of the block in
-                // scalar registers, spills those, and selects at the end)
-                asm volatile("" : "+v"(hm[tl][r]));
-              }
-            const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
-            if (MODE == SEED_F32) {
-              const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 + 4 * lg) * 4;
-#pragma unroll
-              for (int tl = 0; tl < T; ++tl) {
-                const u32x4_t v = {__float_as_uint(pv[tl][0]), __float_as_uint(pv[tl][1]), __float_as_uint(pv[tl][2]),
-                                   __float_as_uint(pv[tl][3])};
-                __builtin_amdgcn_raw_buffer_store_b128(v, rr, at + tl * 64, 0, 0);
-              }
-            } else {
-              constexpr int PIECES = WKEYS / 8;        // 16-byte pieces of a query's row
-              constexpr int RPS = 64 / PIECES;         // rows per store of the wave
-              uint32_t pk[2 * T];
-#pragma unroll
-              for (int i = 0; i < 2 * T; ++i) pk[i] = pack_bf16x2(pv[i >> 1][2 * (i & 1)], pv[i >> 1][2 * (i & 1) + 1]);
-#pragma unroll
-              for (int h = 0; h < T / 2; ++h)
-                *reinterpret_cast<uint4*>(&sh_t[wv][n][lg * (4 * T) + h * 8]) =
-                    make_uint4(pk[4 * h], pk[4 * h + 1], pk[4 * h + 2], pk[4 * h + 3]);
-              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
-#pragma unroll
-              for (int h = 0; h < 16 / RPS; ++h) {
-                const int qi = h * RPS + lane / PIECES, ch = lane % PIECES;
-                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(&sh_t[wv][qi][ch * 8]);
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    v, rr, row_of(tt, (tt >> lgG) * 16 + qi) * row_bytes + (uint32_t)(pos_w0 + ch * 8) * 2, 0, 2);
-              }
-              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            }
-          }
-        }
-        stage(cur ^ 1, qr, str);
-        asm volatile("; (keeps the two paths' staging from being merged behind the join)");
-        continue;
+    // (uniform over the wave) every query of the block exists and sees every key of the wave, and pass 2 can
+    // store whole pieces: straight-line code, the next tile's MFMAs under this tile's tail
+    const bool fast = tt0 + QT <= ntt && ((tt0 + QT - 1) >> lgG) * 16 + 15 < a.m &&
+                      pos_wmax <= tau0 + (tt0 >> lgG) * 16 - 1 && rows_ok &&
+                      (!FAR || (16 * row_bytes64 <= DEAD_OFFSET &&
+                                slot_of((tt0 >> lgG) * 16) <= slot_of(((tt0 + QT - 1) >> lgG) * 16 + 15)));
+    if (fast) {
+      if (HIST) {
+        if (hist_n + QT > 32 || (hist_n && hist_tt + 1 != tt0)) settle();
+        hist_n += QT;
+        hist_tt = tt0 + QT - 1;
       }
-
-      // the general block: queries that see a part of the keys, units with holes, the ends of tails and units
-#pragma unroll 1
+      f32x4_t dn[T];
+      mma_tile(cur, 0, dn);
+#pragma unroll
       for (int ti = 0; ti < QT; ++ti) {
-        const int tt = tt0 + ti, jt = tt >> lgG, g = tt & (G - 1);
-        if (tt >= ntt || jt < jt_first || wkey0 >= L) continue;   // (uniform) past the end / no key to be seen
         f32x4_t d[T];
-        mma_tile(cur, ti, d);
-        const int j = jt * 16 + n;                 // this lane's query
-        const int tau = tau0 + j;
-        const int vis = j < a.m ? tau - 1 : -1;    // the query sees positions <= vis
-        int kp[T][4];                              // positions of this lane's keys
-        uint32_t seen = 0u;
 #pragma unroll
-        for (int tl = 0; tl < T; ++tl) {
-          const int4 v = *reinterpret_cast<const int4*>(
-              &sh_pos[wv * WKEYS + (RUN ? lg * (4 * T) + tl * 4 : tl * 16 + 4 * lg)]);
-          kp[tl][0] = v.x; kp[tl][1] = v.y; kp[tl][2] = v.z; kp[tl][3] = v.w;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) seen |= (kp[tl][r] <= vis ? 1u : 0u) << (4 * tl + r);
-        }
-        if (PASS == 1) {
-          float mx, z;
-          prefill_stats_tile<true, T>(d, seen, a.scale_log2, mx, z);
-          if (lg == 0) sh_part[wv][(blk - grp) * QBLK + ti * 16 + n] = make_float2(mx, z);
-          continue;
-        }
-        const float4 st = sh_st[cur][ti * 16 + n];
-        const float thr = MODE == SEED_BITS ? importance_threshold(a.thr_scale, tau) : st.z;
-        float pv[T][4];
-        uint32_t hbits = 0u;
-#pragma unroll
-        for (int tl = 0; tl < T; ++tl)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const bool s = (seen >> (4 * tl + r)) & 1u;
-            const float e = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
-            pv[tl][r] = s ? e : 0.f;
-            const bool hit = s && e >= thr;
-            hm[tl][r] = hit ? tau : hm[tl][r];
-            hbits |= (hit ? 1u : 0u) << (4 * tl + r);
-          }
-        if (!a.ring) continue;   // summary-only state: nothing is recorded but last_hit
-        const size_t row = ring_row(g, min(j, a.m - 1));   // (no lane stores for a query past the last)
+        for (int tl = 0; tl < T; ++tl) d[tl] = dn[tl];
+        if (ti + 1 < QT) mma_tile(cur, ti + 1, dn);
+        const int tt = tt0 + ti, j = (tt >> lgG) * 16 + n, tau = tau0 + j;
         if (MODE == SEED_BITS) {
-          uint32_t* roww = reinterpret_cast<uint32_t*>(a.ring) + row * a.ring_words;
-          if (rows_ok) {        // (uniform) whole words
-            if (T == 4) {
-              const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
-              if (!(lg & 1) && j < a.m) roww[(pos_w0 >> 5) + (lg >> 1)] = sw[0] | (sw[1] << 16);
-            } else {
-              const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
-              if (lg == 0 && j < a.m) roww[pos_w0 >> 5] = w;
-            }
-          } else {              // rows were cleared by the launch before: set single bits
+          const float4 st = sh_st[cur][ti * 16 + n];
+          uint32_t unsure = __float_as_uint(st.y), hbits = 0u;   // (the sign: this query has no band)
 #pragma unroll
-            for (int tl = 0; tl < T; ++tl)
+          for (int i = 4 * T - 1; i >= 0; --i) {   // key i of the lane's run: row i % 4 of key tile i / 4
+            const float above = st.w - d[i >> 2][i & 3], below = st.z - d[i >> 2][i & 3];
+            hist[i >> 2][i & 3] = shift_in_sign(hist[i >> 2][i & 3], above);
+            hbits = shift_in_sign(hbits, above);
+            unsure |= __float_as_uint(above) ^ __float_as_uint(below);
+          }
+          if (__any((int)unsure < 0)) {   // (uniform, rare) what lies in the band is decided by the score
+            const float thr = importance_threshold(a.thr_scale, tau);
+            if (__float_as_int(st.y) < 0) hbits = 0u;
+#pragma unroll 1
+            for (int tl = 0; tl < T; ++tl) {
+              const f32x4_t x = tl == 0 ? d[0] : tl == 1 ? d[1] : tl == 2 ? d[T > 2 ? 2 : 0] : d[T > 2 ? 3 : 0];
 #pragma unroll
               for (int r = 0; r < 4; ++r)
-                if ((hbits >> (4 * tl + r)) & 1u) atomicOr(&roww[kp[tl][r] >> 5], 1u << (kp[tl][r] & 31));
+                hbits |= (prefill_score(x[r], a.scale_log2, st.x, st.y) >= thr ? 1u : 0u) << (4 * tl + r);
+            }
+#pragma unroll
+            for (int i = 0; i < 4 * T; ++i)   // (an instruction each: the low bit replaced)
+              hist[i >> 2][i & 3] = (hist[i >> 2][i & 3] & ~1u) | ((hbits >> i) & 1u);
+          }
+          // the wave owns whole words of every query's row: plain stores
+          const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
+          const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 >> 5) * 4;
+          if (T == 4) {   // 16 keys per lane: two lane groups to a word
+            const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
+            __builtin_amdgcn_raw_buffer_store_b32(sw[0] | (sw[1] << 16), rr, (lg & 1) ? DEAD_OFFSET : at + (lg >> 1) * 4, 0, 0);
+          } else {        // 8 keys per lane: four lane groups to a word
+            const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
+            __builtin_amdgcn_raw_buffer_store_b32(w, rr, lg ? DEAD_OFFSET : at, 0, 0);
           }
         } else {
+          const float4 st = sh_st[cur][ti * 16 + n];
+          float pv[T][4];
 #pragma unroll
-          for (int tl = 0; tl < T; ++tl) {
-            // four consecutive positions, all seen, whole and aligned: one store
-            const bool quad = ((seen >> (4 * tl)) & 15u) == 15u && kp[tl][1] == kp[tl][0] + 1 &&
-                              kp[tl][2] == kp[tl][0] + 2 && kp[tl][3] == kp[tl][0] + 3 &&
-                              ((row * a.Tcap + (size_t)kp[tl][0]) & 3) == 0;
-            if (MODE == SEED_BF16) {
-              uint16_t* dst = reinterpret_cast<uint16_t*>(a.ring) + row * a.Tcap;
-              const uint32_t p0 = pack_bf16x2(pv[tl][0], pv[tl][1]), p1 = pack_bf16x2(pv[tl][2], pv[tl][3]);
-              if (quad) {
-                *reinterpret_cast<uint2*>(dst + kp[tl][0]) = make_uint2(p0, p1);
-              } else {
+          for (int tl = 0; tl < T; ++tl)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  if ((seen >> (4 * tl + r)) & 1u)
-                    dst[kp[tl][r]] = (uint16_t)((r & 2 ? p1 : p0) >> (16 * (r & 1)));
-              }
-            } else {
-              float* dst = reinterpret_cast<float*>(a.ring) + row * a.Tcap;
-              if (quad) {
-                *reinterpret_cast<float4*>(dst + kp[tl][0]) = make_float4(pv[tl][0], pv[tl][1], pv[tl][2], pv[tl][3]);
-              } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  if ((seen >> (4 * tl + r)) & 1u) dst[kp[tl][r]] = pv[tl][r];
-              }
+            for (int r = 0; r < 4; ++r) {
+              pv[tl][r] = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
+              hm[tl][r] = pv[tl][r] >= st.z ? tau : hm[tl][r];
+              // (said to be read here: left alone, the compiler keeps the compares of all tiles of the block in
+              // scalar registers, spills those, and selects at the end)
+              asm volatile("" : "+v"(hm[tl][r]));
             }
+          const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
+          if (MODE == SEED_F32) {
+            const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 + 4 * lg) * 4;
+#pragma unroll
+            for (int tl = 0; tl < T; ++tl) {
+              const u32x4_t v = {__float_as_uint(pv[tl][0]), __float_as_uint(pv[tl][1]), __float_as_uint(pv[tl][2]),
+                                 __float_as_uint(pv[tl][3])};
+              __builtin_amdgcn_raw_buffer_store_b128(v, rr, at + tl * 64, 0, 0);
+            }
+          } else {
+            constexpr int PIECES = WKEYS / 8;        // 16-byte pieces of a query's row
+            constexpr int RPS = 64 / PIECES;         // rows per store of the wave
+            uint32_t pk[2 * T];
+#pragma unroll
+            for (int i = 0; i < 2 * T; ++i) pk[i] = pack_bf16x2(pv[i >> 1][2 * (i & 1)], pv[i >> 1][2 * (i & 1) + 1]);
+#pragma unroll
+            for (int h = 0; h < T / 2; ++h)
+              *reinterpret_cast<uint4*>(&sh_t[wv][n][lg * (4 * T) + h * 8]) =
+                  make_uint4(pk[4 * h], pk[4 * h + 1], pk[4 * h + 2], pk[4 * h + 3]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
+#pragma unroll
+            for (int h = 0; h < 16 / RPS; ++h) {
+              const int qi = h * RPS + lane / PIECES, ch = lane % PIECES;
+              const u32x4_t v = *reinterpret_cast<const u32x4_t*>(&sh_t[wv][qi][ch * 8]);
+              __builtin_amdgcn_raw_buffer_store_b128(
+                  v, rr, row_of(tt, (tt >> lgG) * 16 + qi) * row_bytes + (uint32_t)(pos_w0 + ch * 8) * 2, 0, 2);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           }
         }
       }
       stage(cur ^ 1, qr, str);
+      asm volatile("; (keeps the two paths' staging from being merged behind the join)");
+      continue;
     }
-    if (PASS == 1) {
-      __syncthreads();
-      for (int e = tid; e < (grp_end - grp) * QBLK; e += WG) {
-        const int tt = grp * QT + e / 16, j = (tt >> lgG) * 16 + (e & 15);
-        if (tt >= ntt || j >= a.m) continue;
-        float mx = neg_inf();
+
+    // the general block: queries that see a part of the keys, units with holes, the ends of tails and units
+#pragma unroll 1
+    for (int ti = 0; ti < QT; ++ti) {
+      const int tt = tt0 + ti, jt = tt >> lgG, g = tt & (G - 1);
+      if (tt >= ntt || jt < jt_first || wkey0 >= L) continue;   // (uniform) past the end / no key to be seen
+      f32x4_t d[T];
+      mma_tile(cur, ti, d);
+      const int j = jt * 16 + n;                 // this lane's query
+      const int tau = tau0 + j;
+      const int vis = j < a.m ? tau - 1 : -1;    // the query sees positions <= vis
+      int kp[T][4];                              // positions of this lane's keys
+      uint32_t seen = 0u;
 #pragma unroll
-        for (int i = 0; i < WAVES; ++i) mx = fmaxf(mx, sh_part[i][e].x);
-        const float ms = mx == neg_inf() ? 0.f : mx;
-        float z = 0.f;
+      for (int tl = 0; tl < T; ++tl) {
+        const int4 v = *reinterpret_cast<const int4*>(
+            &sh_pos[wv * WKEYS + (RUN ? lg * (4 * T) + tl * 4 : tl * 16 + 4 * lg)]);
+        kp[tl][0] = v.x; kp[tl][1] = v.y; kp[tl][2] = v.z; kp[tl][3] = v.w;
 #pragma unroll
-        for (int i = 0; i < WAVES; ++i) z = fmaf(sh_part[i][e].y, fast_exp2(sh_part[i][e].x - ms), z);
-        const int head = b * a.Hq + hkv * G + (tt & (G - 1));
-        a.part[((size_t)head * a.nkb + kb) * a.w + j] = make_float2(mx, z);
+        for (int r = 0; r < 4; ++r) seen |= (kp[tl][r] <= vis ? 1u : 0u) << (4 * tl + r);
       }
-      __syncthreads();
+      const float4 st = sh_st[cur][ti * 16 + n];
+      const float thr = MODE == SEED_BITS ? importance_threshold(a.thr_scale, tau) : st.z;
+      float pv[T][4];
+      uint32_t hbits = 0u;
+#pragma unroll
+      for (int tl = 0; tl < T; ++tl)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool s = (seen >> (4 * tl + r)) & 1u;
+          const float e = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
+          pv[tl][r] = s ? e : 0.f;
+          const bool hit = s && e >= thr;
+          hm[tl][r] = hit ? tau : hm[tl][r];
+          hbits |= (hit ? 1u : 0u) << (4 * tl + r);
+        }
+      if (!a.ring) continue;   // summary-only state: nothing is recorded but last_hit
+      const size_t row = ring_row(g, min(j, a.m - 1));   // (no lane stores for a query past the last)
+      if (MODE == SEED_BITS) {
+        uint32_t* roww = reinterpret_cast<uint32_t*>(a.ring) + row * a.ring_words;
+        if (rows_ok) {        // (uniform) whole words
+          if (T == 4) {
+            const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
+            if (!(lg & 1) && j < a.m) roww[(pos_w0 >> 5) + (lg >> 1)] = sw[0] | (sw[1] << 16);
+          } else {
+            const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
+            if (lg == 0 && j < a.m) roww[pos_w0 >> 5] = w;
+          }
+        } else {              // rows were cleared by the launch before: set single bits
+#pragma unroll
+          for (int tl = 0; tl < T; ++tl)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if ((hbits >> (4 * tl + r)) & 1u) atomicOr(&roww[kp[tl][r] >> 5], 1u << (kp[tl][r] & 31));
+        }
+      } else {
+#pragma unroll
+        for (int tl = 0; tl < T; ++tl) {
+          // four consecutive positions, all seen, whole and aligned: one store
+          const bool quad = ((seen >> (4 * tl)) & 15u) == 15u && kp[tl][1] == kp[tl][0] + 1 &&
+                            kp[tl][2] == kp[tl][0] + 2 && kp[tl][3] == kp[tl][0] + 3 &&
+                            ((row * a.Tcap + (size_t)kp[tl][0]) & 3) == 0;
+          if (MODE == SEED_BF16) {
+            uint16_t* dst = reinterpret_cast<uint16_t*>(a.ring) + row * a.Tcap;
+            const uint32_t p0 = pack_bf16x2(pv[tl][0], pv[tl][1]), p1 = pack_bf16x2(pv[tl][2], pv[tl][3]);
+            if (quad) {
+              *reinterpret_cast<uint2*>(dst + kp[tl][0]) = make_uint2(p0, p1);
+            } else {
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if ((seen >> (4 * tl + r)) & 1u)
+                  dst[kp[tl][r]] = (uint16_t)((r & 2 ? p1 : p0) >> (16 * (r & 1)));
+            }
+          } else {
+            float* dst = reinterpret_cast<float*>(a.ring) + row * a.Tcap;
+            if (quad) {
+              *reinterpret_cast<float4*>(dst + kp[tl][0]) = make_float4(pv[tl][0], pv[tl][1], pv[tl][2], pv[tl][3]);
+            } else {
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if ((seen >> (4 * tl + r)) & 1u) dst[kp[tl][r]] = pv[tl][r];
+            }
+          }
+        }
+      }
     }
+    stage(cur ^ 1, qr, str);
   }
 
-  if (PASS == 2) {
-    if (HIST) settle();
-    // the latest hit of every key over the 16 queries of a tile, one key per lane (through LDS: a lane's 4*T keys
-    // read and written one after the other cost as many memory latencies)
-    __syncthreads();   // sh_pos of this wave is free
+  if (HIST) settle();
+  // the latest hit of every key over the 16 queries of a tile, one key per lane (through LDS: a lane's 4*T keys
+  // read and written one after the other cost as many memory latencies)
+  __syncthreads();   // sh_pos of this wave is free
 #pragma unroll
-    for (int tl = 0; tl < T; ++tl) {
+  for (int tl = 0; tl < T; ++tl) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int v = hm[tl][r];
-        v = max(v, __shfl_xor(v, 1));
-        v = max(v, __shfl_xor(v, 2));
-        v = max(v, __shfl_xor(v, 4));
-        hm[tl][r] = max(v, __shfl_xor(v, 8));
-      }
-      if (n == 0)
-        *reinterpret_cast<int4*>(&sh_pos[wv * WKEYS + (RUN ? lg * (4 * T) + tl * 4 : tl * 16 + 4 * lg)]) =
-            make_int4(hm[tl][0], hm[tl][1], hm[tl][2], hm[tl][3]);
+    for (int r = 0; r < 4; ++r) {
+      int v = hm[tl][r];
+      v = max(v, __shfl_xor(v, 1));
+      v = max(v, __shfl_xor(v, 2));
+      v = max(v, __shfl_xor(v, 4));
+      hm[tl][r] = max(v, __shfl_xor(v, 8));
     }
-    __syncthreads();
-    const int key = wkey0 + lane;
-    if (lane < WKEYS && key < L) {
-      int32_t* lh = a.last_hit + (size_t)unit * a.Lcap + key;
-      const int v = sh_pos[wv * WKEYS + lane];
-      if (v > *lh) {
-        if (a.nseg == 1) *lh = v;
-        else atomicMax(lh, v);
-      }
+    if (n == 0)
+      *reinterpret_cast<int4*>(&sh_pos[wv * WKEYS + (RUN ? lg * (4 * T) + tl * 4 : tl * 16 + 4 * lg)]) =
+          make_int4(hm[tl][0], hm[tl][1], hm[tl][2], hm[tl][3]);
+  }
+  __syncthreads();
+  const int key = wkey0 + lane;
+  if (lane < WKEYS && key < L) {
+    int32_t* lh = a.last_hit + (size_t)unit * a.Lcap + key;
+    const int v = sh_pos[wv * WKEYS + lane];
+    if (v > *lh) {
+      if (a.nseg == 1) *lh = v;
+      else atomicMax(lh, v);
     }
   }
 }
 
-// Pass 1 has a light tail (max, exp, sum) and is latency-bound at two waves per SIMD: held to the registers
-// and LDS of three (0.91 -> 0.64 ms for 512 heads x 1024 queries x 4096 keys; 166 registers now).  Pass 2 on 256-byte rows
-// takes the registers of two: four key tiles per wave hold 16 accumulators, 16 of the next tile, 16 latest hits and, by
-// the ring, 16 scores or histories beside the 64 of the keys (205 for bf16 scores, 253 for bits; held to three waves it
-// spills: 1.27 -> 1.76 ms).  fp32 rows of 512 bytes, two key tiles per wave, fit three (153 and 157 with score rings).
-// Both passes are bound by vector instructions: per tile of 16 queries x 64 keys 16 MFMAs and about 83 (pass 1), 102 (bf16
+// Pass 2 on 256-byte rows takes the registers of two waves per SIMD: four key tiles per wave hold 16 accumulators, 16 of the
+// next tile, 16 latest hits and, by the ring, 16 scores or histories beside the 64 of the keys (205 for bf16 scores, 253 for bits;
+// held to three waves it spills: 1.27 -> 1.76 ms).  fp32 rows of 512 bytes, two key tiles per wave, fit three (153 and 157 with
+// score rings).  It is bound by vector instructions: per tile of 16 queries x 64 keys 16 MFMAs and about 102 (bf16
 // scores), 108 to 114 (bits) others.  Kernel times: bf16 scores 1.39 -> 1.20 ms (ring written at 3.5 TB/s);
 // bits, 512 heads x 1024 x 8192, 3.22 -> 1.62 ms (one wave per SIMD and a score per pair before; 2.04 with compares
 // whose results went through scalar registers); fp32, 16 units of 2000 keys, 74 -> 39 us (the queries of a key block shared by
 // several workgroups).
-template <typename DT, int D>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void corm_prefill_stats_kernel(
-    const PrefillArgs a) {
-  prefill_pass<DT, D, 1, SEED_F32, false>(a);
-}
-
 template <typename DT, int D, int MODE, bool FAR>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void corm_prefill_scores_kernel(
     const PrefillArgs a) {
-  prefill_pass<DT, D, 2, MODE, FAR>(a);
+  prefill_scores<DT, D, MODE, FAR>(a);
 }
 
 // boolean message: zero the words of the rows of steps tau_0 .. tau_{m-1} that pass 2 may set single bits in
@@ -664,15 +863,15 @@ __global__ __launch_bounds__(256) void corm_prefill_clear_bits_kernel(const Pref
   }
 }
 
-// per query: max and 1/sum over the key blocks of its unit
-__global__ __launch_bounds__(256) void corm_prefill_merge_kernel(const PrefillArgs a, const int KB) {
+// per query: reference (the largest of them) and 1/sum over the key segments of its unit
+__global__ __launch_bounds__(256) void corm_prefill_merge_kernel(const PrefillArgs a) {
   const int head = blockIdx.x;   // (heads in x: B * Hq may exceed the 65535 rows a grid has in y)
   const int j = blockIdx.y * 256 + threadIdx.x;
   if (j >= a.m) return;
   const int unit = (head / a.Hq) * a.Hkv + (head % a.Hq) / (a.Hq / a.Hkv);
   int L = a.lens[unit];
   L = L < 0 ? 0 : (L > a.Lcap ? a.Lcap : L);
-  const int nblk = (L + KB - 1) / KB;
+  const int nblk = (L + a.kseg - 1) / a.kseg;
   const float2* part = a.part + (size_t)head * a.nkb * a.w + j;
   float mx = neg_inf();
   for (int k = 0; k < nblk; ++k) mx = fmaxf(mx, part[(size_t)k * a.w].x);

@@ -415,3 +415,48 @@ def test_seed_in_a_ring_beyond_32_bit_offsets(ring, Tcap, t_last):
         assert not bool(st.ring[..., n:].any())
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
     assert bool(got[0][1].any())
+
+
+# kv dtype, G, Hkv, d, P, m, scaled logit of the keys (log2) in the first and in the second half of the prompt
+SUM_RANGES = [
+    ("bf16", 1, 2, 128, 700, 64, 0, 0),          # few workgroups: a query tile per wave, the keys in segments
+    ("bf16", 1, 2, 128, 700, 64, 150, 150),      # sums beyond 2^100,
+    ("bf16", 1, 2, 64, 700, 64, -150, -150),     # below 2^-60,
+    ("bf16", 2, 2, 128, 1300, 40, -150, 150),    # and both in different segments
+    ("bf16", 4, 2, 64, 1300, 33, 150, 3),
+    ("bf16", 1, 300, 128, 530, 130, -90, 0),     # many units: four query tiles per wave, one segment
+    ("bf16", 1, 300, 64, 530, 70, 0, 0),
+    ("f32", 2, 2, 64, 1300, 50, -150, 0),
+    ("f32", 1, 2, 128, 700, 90, 150, 150),       # key blocks of 128
+    ("f32", 1, 300, 128, 300, 70, 0, 120),
+]
+
+
+@pytest.mark.parametrize("case", range(len(SUM_RANGES)))
+def test_seed_sums_over_the_range_of_the_logits(case):
+    """The sum of a row is taken against a fixed reference where it stays in range and against the row's maximum where it does not:
+    scores against softmax in 64 bits.  Keys and queries are nearly constant vectors, so the d products of a logit x all have
+    its sign: summed in fp32 in any order they carry at most d 2^-24 |x|, the few operations after them 8 2^-24 |x|, and a
+    score is e to that."""
+    dtype, G, Hkv, d, P, m, lo, hi = SUM_RANGES[case]
+    print("[case]", SUM_RANGES[case], flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(case)
+    unit = (d ** 0.5 / 1.4426950408889634) / d            # a key of this constant has a scaled logit of 1 with the query 1
+    level = torch.where(torch.arange(P, device=DEV) < P // 2, lo, hi).view(1, 1, P, 1)
+    K = ((level + torch.randn(1, Hkv, P, 1, device=DEV, generator=g)) * unit +
+         0.05 * torch.randn(1, Hkv, P, d, device=DEV, generator=g)).to(tdt)
+    q = (1 + 0.05 * torch.randn(1, Hkv * G, m, d, device=DEV, generator=g)).to(tdt)
+    st = corm.LayerState(1, Hkv * G, Hkv, d, P, P, m + 1, 8, dtype, device=DEV, score_dtype="f32")
+    st.preload(K, torch.zeros_like(K))
+    t = torch.full((1,), P, dtype=torch.int32, device=DEV)
+    st.prefill_seed(q, t, torch.zeros_like(t))
+    torch.cuda.synchronize()
+    steps = torch.arange(P - m + 1, P + 1, device=DEV)
+    seen = torch.arange(P, device=DEV).view(1, -1) < steps.view(-1, 1)
+    got = st.ring[0][:, (steps - 1) % (m + 1)][..., :P].double()
+    for h in range(0, Hkv * G, 7 if Hkv > 8 else 1):
+        s = (q[0, h].double() @ K[0, h // G].double().t().contiguous() / d ** 0.5).masked_fill(~seen, float("-inf"))
+        want = torch.softmax(s, dim=-1)
+        tol = 0.7 * (d + 8) * 2.0 ** -24 * (max(abs(lo), abs(hi)) + 16)   # (log2 units; 16: the spread within a level)
+        assert ((got[h] - want).abs() <= tol * want + 1e-30)[seen].all(), h
