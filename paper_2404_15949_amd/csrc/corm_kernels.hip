@@ -5,10 +5,12 @@
 //
 //   many units (>= compute units, logits fit LDS):   unit kernel | compact
 //   few units:                                       attend | record | compact
+//   few small units (corm_decode_step):              small kernel
 //
 //   unit     one workgroup per unit streams its K and V once, keeps the logits in LDS, writes the new
 //            row (append), out (Eq. 1), the ring row and last_hit (Eq. 2, Def. 3.1), the keep masks
 //            (Def. 4.1 + recent r) and the survivors per 512-slot chunk.                     unit.hpp
+//   small    one workgroup per unit does the whole step, compaction included.              small.hpp
 //   attend   grid (parts, units): online-softmax partials and raw logits per part of a unit; the
 //            owner of slot lens[u] writes the new row.                                     attend.hpp
 //   record   merges the partials -> out; scores, ring row, last_hit, keep masks, counts.   record.hpp
@@ -33,6 +35,7 @@
 #include "common.hpp"
 #include "attend.hpp"
 #include "unit.hpp"
+#include "small.hpp"
 #include "record.hpp"
 #include "compact.hpp"
 #include "prefill.hpp"
@@ -275,6 +278,21 @@ int corm_decode_step(const corm_desc* desc, const void* q, const void* k_new, co
   int rc = validate_desc(desc);
   if (rc) return rc;
   if (misaligned4(kept_idx)) return CORM_EINVAL;
+  LaunchCtx ctx;
+  if (make_ctx(opts, &ctx) == CORM_OK && small_step(desc, ctx)) {
+    rc = check_step_pointers(q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, kept_idx, status);
+    if (rc) return rc;
+    WorkspaceLayout wl;
+    rc = check_workspace(desc, workspace, workspace_bytes, &wl);
+    if (rc) return rc;
+    Params p = {};
+    p.q = q; p.k_new = k_new; p.v_new = v_new; p.K = K; p.V = V; p.lens = lens; p.pos = pos;
+    p.last_hit = last_hit; p.t = t; p.t_first = t_first; p.ring = score_ring; p.out = out; p.keep = keep;
+    p.kept_idx = kept_idx; p.status = status;
+    p.do_append = 1; p.do_evict = 1;
+    bind_params(desc, wl, workspace, p);
+    return launch_small(desc, p, ctx, (hipStream_t)stream);
+  }
   rc = corm_step_attend(desc, q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, keep,
                         workspace, workspace_bytes, status, opts, stream);
   if (rc) return rc;

@@ -307,6 +307,44 @@ int launch_attend_record(const corm_desc* d, const Params& p0, const LaunchCtx& 
   return launch_record(d, p, c, s);
 }
 
+// A whole step in one launch (small.hpp)?  A unit is then one workgroup's alone, so only while its rows are few: kernel times with
+// every slot in use, us, split launches | one: 32 units x 640 rows of 256 bytes 12.5 | 12.9, of 1024 12.5 | 16.5; two heads a unit,
+// 320 rows 13.7 | 12.0, 512 13.6 | 13.5; four heads, 320 rows 16.4 | 15.8 (the launches' own cost, two saved, comes on top); half-full
+// units take less.  Where the units alone fill half the chip the split launches share out less: 100 units x 640 rows 15.4 | 14.0,
+// 200 units 20.9 | 15.4, 200 units x 1024 rows of 128 bytes 23.0 | 14.4.
+bool small_step(const corm_desc* d, const LaunchCtx& c) {
+  const int G = d->Hq / d->Hkv;
+  if (c.path != 0 || G > 4 || d->Lcap > SMALL_MAX_SLOTS || use_unit_path(d, c)) return false;
+  const long limit = (2L * d->B * d->Hkv >= c.cus ? 256L : 160L) * 1024;
+  return (long)d->Lcap * row_bytes(d) <= (G == 1 ? limit : G == 2 ? limit * 4 / 5 : limit / 2);
+}
+
+template <typename DT, int D>
+int launch_small_dt(const Params& p, int G, int units, hipStream_t s) {
+  auto go = [&](auto kernel, int stage_rows) {
+    const int lstride = (p.Lcap + 2 * stage_rows - 1) / (2 * stage_rows) * (2 * stage_rows) + stage_rows;
+    hipLaunchKernelGGL(kernel, dim3(units), dim3(SMALL_WG), (size_t)G * lstride * sizeof(float), s, p, lstride);
+    return launch_status();
+  };
+  switch (G) {
+    case 1: return go(corm_small_kernel<DT, D, 1>, small_stage_rows<DT, D, 1>());
+    case 2: return go(corm_small_kernel<DT, D, 2>, small_stage_rows<DT, D, 2>());
+    case 4: return go(corm_small_kernel<DT, D, 4>, small_stage_rows<DT, D, 4>());
+    default: return CORM_EUNSUPPORTED;
+  }
+}
+
+int launch_small(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStream_t s) {
+  const int G = d->Hq / d->Hkv, units = d->B * d->Hkv;
+  if (c.ev0 && hipEventRecord(c.ev0, s) != hipSuccess) return CORM_EHIP;
+  const int rc = d->kv_dtype == CORM_F32
+                     ? (d->d == 64 ? launch_small_dt<F32, 64>(p, G, units, s) : launch_small_dt<F32, 128>(p, G, units, s))
+                     : (d->d == 64 ? launch_small_dt<BF16, 64>(p, G, units, s) : launch_small_dt<BF16, 128>(p, G, units, s));
+  if (rc) return rc;
+  if (c.ev1 && hipEventRecord(c.ev1, s) != hipSuccess) return CORM_EHIP;
+  return CORM_OK;
+}
+
 // Policy of the compaction: exact mode compacts every unit that lost a key; lazy mode only
 // units whose dead slots reach dead_num / dead_den of their slots.
 struct CompactPolicy {

@@ -460,3 +460,63 @@ def test_seed_sums_over_the_range_of_the_logits(case):
         want = torch.softmax(s, dim=-1)
         tol = 0.7 * (d + 8) * 2.0 ** -24 * (max(abs(lo), abs(hi)) + 16)   # (log2 units; 16: the spread within a level)
         assert ((got[h] - want).abs() <= tol * want + 1e-30)[seen].all(), h
+
+
+# kv dtype, G, Hkv, d, Lcap, ring, w
+SMALL = [
+    ("f32", 1, 4, 64, 640, "f32", 8), ("f32", 1, 3, 64, 576, "bit", 8), ("f32", 2, 2, 128, 256, None, 4), ("f32", 4, 1, 128, 160, "bf16", 4),
+    ("bf16", 1, 2, 128, 640, "bf16", 8), ("bf16", 1, 5, 64, 1024, "bit", 6), ("bf16", 2, 2, 64, 1023, "bf16", 8), ("bf16", 4, 2, 128, 320, "f32", 5),
+    ("bf16", 4, 3, 64, 513, "bit", 8), ("bf16", 1, 100, 128, 1024, None, 8), ("bf16", 2, 1, 128, 65, "bf16", 3), ("bf16", 1, 1, 128, 1, "bit", 2),
+    ("f32", 1, 2, 64, 64, "f32", 3),
+]
+
+
+@pytest.mark.parametrize("case", range(len(SMALL)))
+def test_small_units_in_one_launch_equal_the_split_launches(case):
+    """A step of small units in one launch against attend, record and compact: the same cache, decisions and survivors, steps at
+    which keys go and at which none does, units that are empty, full or hold an invalid length, positions and steps without a
+    column; out and the scores within the rounding of fp32 sums (both paths are compared with the oracle elsewhere)."""
+    dtype, G, Hkv, d, Lcap, ring, w = SMALL[case]
+    print("[case]", SMALL[case], flush=True)
+    B, Hq, Tcap = 2, G * Hkv, Lcap + 40
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(case)
+    lens = torch.randint(0, Lcap + 1, (B, Hkv), device=DEV, generator=g, dtype=torch.int32)
+    edge = [0, Lcap, max(Lcap - 1, 0), min(Lcap, 512), min(Lcap, 511), Lcap + 7, -3]
+    for i, n in enumerate(edge):
+        if i < B * Hkv:
+            lens.view(-1)[(i + case) % (B * Hkv)] = n
+    rows = [torch.randn(B, Hkv, Lcap, d, device=DEV, generator=g).to(tdt) for _ in range(2)]
+    pos = torch.arange(Lcap, device=DEV, dtype=torch.int32).expand(B, Hkv, Lcap).clone()
+    pos[0, 0, Lcap // 2] = Tcap + 5                       # a position without a column
+    hit = torch.randint(0, Lcap + 4, (B, Hkv, Lcap), device=DEV, generator=g, dtype=torch.int32)
+    states = []
+    for path in (0, 1):
+        st = corm.LayerState(B, Hq, Hkv, d, Lcap, Tcap, w, 3, dtype, device=DEV, want_ring=ring is not None, want_masks=True,
+                             score_dtype=ring)
+        st.K.copy_(rows[0]), st.V.copy_(rows[1]), st.pos.copy_(pos), st.last_hit.copy_(hit), st.lens.copy_(lens)
+        states.append(st)
+    t = torch.tensor([Lcap + 1, Lcap + 3], dtype=torch.int32, device=DEV)
+    for step in range(10):
+        q = torch.randn(B, Hq, d, device=DEV, generator=g).to(tdt)
+        k, v = (torch.randn(B, Hkv, d, device=DEV, generator=g).to(tdt) for _ in range(2))
+        ts = t.clone()
+        if step == 7:
+            ts[1] = Tcap + 1                               # a step without a column
+        t_first = ts - (0 if step % 4 == 3 else w)         # the window is full, or (every fourth step) not
+        for st, path in zip(states, (0, 1)):
+            assert corm.corm_selected_path(st.desc) == 1
+            st.keep.zero_(), st.kept_idx.zero_()
+            st.step(q, k, v, ts, t_first, opts=corm.corm_launch_opts(path, 0, None, None))
+        torch.cuda.synchronize()
+        a, b = states
+        for name in ("lens", "pos", "last_hit", "K", "V", "keep", "kept_idx", "status"):
+            assert torch.equal(getattr(a, name), getattr(b, name)), (name, step)
+        scale = b.out.abs().amax(-1, keepdim=True)
+        assert ((a.out - b.out).abs() <= 2e-6 * scale).all(), step
+        if ring == "bit":
+            assert torch.equal(a.ring, b.ring), step
+        elif ring:
+            x, y = a.ring.double(), b.ring.double()
+            assert ((x - y).abs() <= (2.0 ** -7 if ring == "bf16" else 4e-6) * y + 1e-12).all(), step
+        t += 1
