@@ -12,8 +12,8 @@ namespace {
 // a unit: the logits stay in LDS as in the unit kernel, the new row is attended to from k_new and v_new directly (nothing is
 // written to be read back), pos and last_hit are read once and stored once, at the slot the key ends in, and the
 // survivors' list never leaves LDS.  Bound by that chain, and with hundreds of rows by what one workgroup streams: 4 units of 52 keys
-// that evict at every step (fp32, d 64) 4.1 + 4.8 + 2.1 us in three launches, 6.9 in one (a step of the program, with what the
-// launches cost the host, 14.0 -> 11.3).  small_step says where that pays.
+// that evict at every step (fp32, d 64) 4.1 + 4.8 + 2.1 us in three launches, 6.9 in one with the inputs in the caches; with new
+// inputs at every step 4.4 + 5.2 + 5.0 and 11.0 (a step of the program 13.8 -> 11.4).  small_step says where that pays.
 
 constexpr int SMALL_WG = 512;
 constexpr int SMALL_WAVES = SMALL_WG / 64;
