@@ -138,8 +138,8 @@ struct PrefillGeom {
 // inside the loop.  The elementwise tail is little more than fma, exp2, add per pair: the reference of a sum (a power of two,
 // each lane its own) is not the running maximum but follows it: where a tile's four terms add up to more than STATS_JUMP, the
 // reference is moved to their maximum and they are formed again, which is rare after the first block.  So, as with the maximum,
-// the terms that make up a sum come from small differences.  A workgroup with a sum that is 0 or not
-// finite in the end does the loop again, first for the maxima and then for the sums against them.
+// the terms that make up a sum come from small differences.  A workgroup with a lane whose reference could not be set, or whose
+// sum is not finite, does the loop again, first for the maxima and then for the sums against them.
 // Bound by the products, at the rate the card's power leaves (with the tail dropped 480 us for 512 heads x 1024 queries x 4096 keys:
 // 1.0 PFLOP/s; a large library product 1.15), and by what of the tail does not fit beside them.  Key-major with a maximum per
 // tile, as before, 768 us in a row of runs, now 697 (bf16), 1291 -> 1094 for 512 x 1024 x 8192; the merge 22 -> 7 us, since a
@@ -262,11 +262,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     mx[qt] = neg_inf();
   }
   float unset = 2.f * STATS_JUMP * NT;   // (0 from the first block on) the wave's references are to be set
-  // moves a reference to the maximum m of a tile's raw logits, if it is higher or the first
+  // moves a reference to the maximum m of a tile's raw logits, if it is higher or the first.  A lower one after keys whose terms
+  // vanished (against the reference 0 of a lane that could not set one) comes too late for those: the sum is not a number from then on.
   auto follow = [&](int qt, float m) __attribute__((always_inline)) {
     const float to = rintf(m * a.scale_log2);
     if (fabsf(to) < 1e6f && (to > ms[qt] || z[qt] == 0.f)) {
-      z[qt] = ldexpf(z[qt], (int)(ms[qt] - to));
+      z[qt] = to > ms[qt] || !((any >> qt) & 1u) ? ldexpf(z[qt], (int)(ms[qt] - to)) : __builtin_nanf("");
       ms[qt] = to;
     }
   };
@@ -285,7 +286,6 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
       const int p = sh_pos[cur][lane % KBLK];
       if (__all(p <= vis_first) && nqt == QW && mode != MAXIMA) {
         // (uniform over the wave) every query sees every key: straight-line code, the next tile's products under this tile's tail
-        any = (1u << QW) - 1u;
         f32x4_t dn[NT][QW];
 #pragma unroll
         for (int x = 0; x < NT; ++x) mma_tile(cur, x, dn[x]);
@@ -330,6 +330,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
           }
 #pragma unroll
           for (int qt = 0; qt < QW; ++qt) z[qt] += sum[qt];
+          any = (1u << QW) - 1u;
         }
         unset = 0.f;
       } else if (__any(p <= vis_last) && nqt > 0) {
@@ -342,7 +343,6 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 #pragma unroll
           for (int qt = 0; qt < QW; ++qt) {
             const bool s[4] = {kp.x <= vis[qt], kp.y <= vis[qt], kp.z <= vis[qt], kp.w <= vis[qt]};
-            any |= (s[0] || s[1] || s[2] || s[3]) ? 1u << qt : 0u;
             float m = neg_inf();
 #pragma unroll
             for (int r = 0; r < 4; ++r) m = fmaxf(m, s[r] ? d[qt][r] : neg_inf());
@@ -356,6 +356,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
                 z[qt] += s[r] ? e : 0.f;
               }
             }
+            any |= (s[0] || s[1] || s[2] || s[3]) ? 1u << qt : 0u;
           }
         }
       }
@@ -365,14 +366,17 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   };
 
   walk(FOLLOW);
+  // A lane whose reference was set in time holds a sum of at least 2^-1/2, its largest term.  Any other that saw a key summed
+  // against the reference 0, which a sum below 1/2 does not fit (terms may have vanished), or set one too late: asked per lane,
+  // since the other lane groups of the query hide it.
   bool out_of_range = false;
 #pragma unroll
   for (int qt = 0; qt < QW; ++qt) {   // the four lane groups of a query, each with a reference of its own
+    out_of_range |= ((any >> qt) & 1u) && !(z[qt] >= 0.5f && z[qt] < __builtin_inff());
     const float m = z[qt] > 0.f ? ms[qt] : neg_inf();
     ms[qt] = rows_allreduce_max(m);
     z[qt] = rows_allreduce_sum(z[qt] > 0.f ? ldexpf(z[qt], (int)(m - ms[qt])) : z[qt]);
     if (ms[qt] == neg_inf()) ms[qt] = 0.f;
-    out_of_range |= ((rows_allreduce_or(any) >> qt) & 1u) && !(z[qt] > 0.f && z[qt] < __builtin_inff());
   }
   if (__syncthreads_or(out_of_range)) {   // (rare)
     walk(MAXIMA);

@@ -462,6 +462,91 @@ def test_seed_sums_over_the_range_of_the_logits(case):
         assert ((got[h] - want).abs() <= tol * want + 1e-30)[seen].all(), h
 
 
+# kv dtype, G, Hkv, d, P, m, (lane groups, in the first n keys) that differ, their scaled logit (log2), scaled logit of the others, the
+# query that is 2^13 times the others, slots without a column.  Key i is lane group i % 16 // 4's.  Few units have one query
+# tile per wave, which looks at 64 keys at a time, 600 of them with 9 or more tiles four, which look at 16.
+INF = float("inf")
+FAR_SUMS = [
+    ("bf16", 1, 2, 128, 700, 64, ((0,), 64), -1.2e6, -300, None, 0),       # a lane group's first keys; the keys in segments
+    ("bf16", 1, 2, 128, 700, 64, ((1,), 64), -INF, -300, None, 0),
+    ("bf16", 2, 2, 64, 1300, 40, ((2, 3), 64), -1.2e6, -300, None, 0),
+    ("bf16", 1, 600, 128, 530, 130, ((1,), 16), -1.2e6, -300, None, 0),    # one segment
+    ("bf16", 1, 600, 64, 530, 130, ((3,), 16), -INF, -300, None, 0),
+    ("bf16", 4, 150, 128, 300, 64, ((0, 2), 16), -INF, -300, None, 0),
+    ("f32", 2, 2, 64, 1300, 50, ((0,), 64), -1.2e6, -300, None, 0),
+    ("f32", 1, 2, 128, 700, 90, ((1, 2, 3), 64), -INF, -300, None, 0),
+    ("bf16", 1, 600, 128, 530, 130, ((0,), 16), -1.2e6, -126, None, 0),    # the group's sum is positive, and not whole
+    ("bf16", 1, 2, 128, 700, 64, ((0,), 64), 2e6, -300, None, 0),
+    ("bf16", 4, 2, 64, 600, 33, ((0, 1, 2, 3), 64), -INF, 150, None, 0),   # all groups, and more than one block
+    ("bf16", 1, 600, 128, 530, 130, ((0, 1, 2, 3), 96), -INF, -300, None, 0),
+    ("bf16", 1, 2, 128, 700, 64, ((), 0), 0, 1.5e6, None, 0),              # every row beyond 10^6
+    ("f32", 1, 2, 64, 700, 64, ((), 0), 0, -1.5e6, None, 0),
+    ("bf16", 1, 600, 128, 530, 130, ((), 0), 0, 300, 21, 0),               # one query of the workgroup beyond it
+    ("bf16", 1, 2, 128, 700, 64, ((), 0), 0, -300, 5, 0),
+    ("bf16", 1, 2, 128, 700, 64, ((), 0), 0, -300, None, 4),               # the first block is seen in part, and one group
+    ("bf16", 1, 600, 64, 530, 130, ((), 0), 0, -300, None, 52),            # sees none of it
+    ("f32", 1, 2, 128, 700, 64, ((), 0), 0, -300, None, 61),
+]
+
+
+@pytest.mark.parametrize("ring", ["f32", "bf16", "bit"])
+@pytest.mark.parametrize("case", range(len(FAR_SUMS)))
+def test_seed_sums_that_the_reference_cannot_follow(case, ring):
+    """Rows whose sum cannot be taken in the first walk over the keys, wholly or in one lane group, are walked again against their
+    maximum: scores against softmax in 64 bits, rows that sum to 1.  A logit is the sum of two products, exact in fp32 in any
+    order; scaling, the difference to the reference and exp2 round once each, at up to 32 + |log2 score| after the difference, and
+    the sums of up to 1300 positive terms add less than 100 roundings: together (132 + |log2 score|) 2^-24, in exp2 times ln 2."""
+    dtype, G, Hkv, d, P, m, (groups, n), special, others, big, gone = FAR_SUMS[case]
+    print("[case]", FAR_SUMS[case], ring, flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(case)
+    scale = float(1 / torch.tensor(float(d)).sqrt() * torch.tensor(1.4426950408889634))      # (in fp32, as the library does)
+    K = torch.zeros(1, Hkv, P, d, device=DEV)
+    K[..., 0] = others / scale
+    step = 5 if abs(others) > 1e5 else 0.5
+    K[..., 1] = torch.randint(-4, 5, (1, Hkv, P), device=DEV, generator=g) * step
+    slots = [i for i in range(n) if i % 16 // 4 in groups]
+    K[:, :, slots, 0] = special / scale
+    K[:, :, slots, 1] = 0
+    K = K.to(torch.bfloat16).to(tdt)                     # (both elements exact in bf16, their sum in fp32)
+    q = torch.zeros(1, Hkv * G, m, d, device=DEV)
+    q[..., :2] = 1
+    if big is not None:
+        q[:, :, big] *= 2 ** 13
+    q = q.to(tdt)
+    st = corm.LayerState(1, Hkv * G, Hkv, d, P, P, m + 1, 8, dtype, device=DEV, score_dtype=ring)
+    st.preload(K, torch.zeros_like(K))
+    pos = torch.arange(P, device=DEV) - gone             # the first `gone` lie in front of the ring's columns
+    st.pos[:] = pos.int()
+    t_last = P - gone
+    t = torch.full((1,), t_last, dtype=torch.int32, device=DEV)
+    st.prefill_seed(q, t, torch.zeros_like(t))
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == (corm.CORM_DEV_BAD_STEP if gone else 0)
+    steps = torch.arange(t_last - m + 1, t_last + 1, device=DEV)
+    rows = (steps - 1) % (m + 1)
+    seen = (pos.view(1, -1) < steps.view(-1, 1)) & (pos >= 0)
+    for h in range(0, Hkv * G, 37 if Hkv > 8 else 1):
+        raw = K[0, h // G, :, 0].double() + K[0, h // G, :, 1].double()
+        x = (q[0, h, :, :1].double() * raw * scale).masked_fill(~seen, -INF)
+        z = torch.exp2(x - x.amax(-1, keepdim=True))
+        want = z / z.sum(-1, keepdim=True)
+        tol = 0.7 * 2.0 ** -24 * (132 - torch.log2(want.clamp(min=1e-36))) * want
+        thr = 1.0 / steps.double().view(-1, 1)
+        if ring == "bit":
+            hits = _bit_hits(st.ring, rows, pos.clamp(min=0))[0, h]
+            sure = seen & ((want - thr).abs() > tol)
+            assert torch.equal(hits[sure], (want >= thr)[sure]), h
+            continue
+        got = st.ring[0, h][rows][:, :P - gone].double()
+        want, tol, seen_h = (a[:, gone:] for a in (want, tol, seen))
+        if ring == "bf16":
+            tol = tol * 1.01 + 2.0 ** -8 * want
+        else:
+            assert ((torch.where(seen_h, got, 0.0).sum(-1) - 1).abs() <= 200 * 2.0 ** -24).all(), h
+        assert ((got - want).abs() <= tol + 2e-36)[seen_h].all(), h
+
+
 # kv dtype, G, Hkv, d, Lcap, ring, w
 SMALL = [
     ("f32", 1, 4, 64, 640, "f32", 8), ("f32", 1, 3, 64, 576, "bit", 8), ("f32", 2, 2, 128, 256, None, 4), ("f32", 4, 1, 128, 160, "bf16", 4),
