@@ -134,8 +134,8 @@ struct PrefillGeom {
 //
 // Query-major, the other way round than pass 2: a wave keeps QW tiles of 16 queries in registers (B operand) and all keys of
 // its segment pass by through LDS (A operand, double-buffered blocks).  A lane then holds four keys of ONE query per tile,
-// so its sum stays in a register from the first key to the last: nothing crosses lanes, and nothing is flushed,
-// inside the loop.  The elementwise tail is little more than fma, exp2, add per pair: the reference of a sum (a power of two,
+// so its sum stays in a register: nothing crosses lanes inside the loop, and every 256 keys the register is added to a word
+// of LDS.  The elementwise tail is little more than fma, exp2, add per pair: the reference of a sum (a power of two,
 // each lane its own) is not the running maximum but follows it: where a tile's four terms add up to more than STATS_JUMP, the
 // reference is moved to their maximum and they are formed again, which is rare after the first block.  So, as with the maximum,
 // the terms that make up a sum come from small differences.  A workgroup with a lane whose reference could not be set, or whose
@@ -148,6 +148,13 @@ struct PrefillGeom {
 // place of a tile 729; 32 x 32 tiles at two waves per SIMD 686 and 702, 128 queries per wave 709 to 764 (all against the reference 0).
 
 constexpr float STATS_JUMP = 16.f;
+
+// Blocks of keys (the first is one for itself) whose sums are added up by themselves before they join the sum of all: with one register
+// from the first key to the last, a few large terms at a prompt's start swallow the low bits of the thousands of tiles after them.
+// Error of the row sum on the CPU (rms), in this order | one register | partials of 256 keys against their maximum (as pass 1 was when it
+// went key-major), the first 16 keys 2^24 above the others: 8192 keys 1.0e-7 | 3.6e-6 | 1.6e-7, 32768 keys 1.8e-7 | 1.4e-5 | 3.1e-7; without
+// such keys, 32768: 0.9e-7 | 3.3e-7 | 1.6e-7.
+constexpr int STATS_FOLD = 4;
 
 // QW query tiles per wave: as many as the registers of three waves per SIMD hold, so that a key tile read from LDS serves as many
 // products as it can; one where the launch is short of workgroups, and with fp32, whose products take long enough for any
@@ -194,7 +201,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const int tcur = a.t[b];
   const int tau0 = tcur - a.m + 1;   // step of tail query 0
   if (tau0 < 1 || tcur > a.Tcap) return;   // (pass 2 reports it)
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // (uniform: what hangs on it
+  // takes scalar registers; in vector registers it had them spilled, and a reload in the loop waits for the keys in flight)
   const int n = lane & 15, lg = lane >> 4;
 
   __shared__ __attribute__((aligned(16))) char sh_k[2][KBLK * KROW];
@@ -210,13 +218,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const int vis_first = tau0 + (wtt >> lgG) * 16 - 1;
 
   uint4 qb[QW][NCH];
-  int vis[QW];   // this lane's query of the tile sees positions <= vis
 #pragma unroll
   for (int qt = 0; qt < QW; ++qt) {
     const int tt = min(wtt + qt, ntt - 1), j = (tt >> lgG) * 16 + n;
     const char* q = reinterpret_cast<const char*>(a.q_tail) +
                     ((size_t)(b * a.Hq + hkv * G + (tt & (G - 1))) * a.m + min(j, a.m - 1)) * ROWB;
-    vis[qt] = wtt + qt < ntt && j < a.m ? tau0 + j - 1 : -1;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) qb[qt][c] = *reinterpret_cast<const uint4*>(q + c * 64 + 16 * lg);
   }
@@ -254,27 +260,49 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
       for (int qt = 0; qt < QW; ++qt) d[qt] = PrefillMma<DT>::mma(ka[c], qb[qt][c], d[qt]);
   };
 
-  float ms[QW], mx[QW], z[QW];   // reference of the sum, maximum (raw logits), sum: of this lane's keys of a query
-  uint32_t any = 0u;             // bit qt: the query saw a key
+  // of this lane's keys of a query: reference of the sum, maximum (raw logits), sum of up to STATS_FOLD blocks; in LDS (the
+  // registers are full) the sum of the blocks before them and its reference, a thread's own words
+  float ms[QW], mx[QW], z[QW];
+  __shared__ __attribute__((aligned(16))) float sh_z[WG][QW], sh_zref[WG][QW];
+  uint32_t any = 0u;             // bit qt: the query saw a key; bit 16 + qt: its reference is set
 #pragma unroll
   for (int qt = 0; qt < QW; ++qt) {
     ms[qt] = 0.f;
     mx[qt] = neg_inf();
   }
   float unset = 2.f * STATS_JUMP * NT;   // (0 from the first block on) the wave's references are to be set
-  // moves a reference to the maximum m of a tile's raw logits, if it is higher or the first.  A lower one after keys whose terms
-  // vanished (against the reference 0 of a lane that could not set one) comes too late for those: the sum is not a number from then on.
+  // Moves a reference to the maximum m of a tile's raw logits, if it is higher or the first.  A first one that is lower than the 0 it
+  // replaces comes too late for keys seen before (their terms may have vanished): the sum is not a number from then on.
   auto follow = [&](int qt, float m) __attribute__((always_inline)) {
     const float to = rintf(m * a.scale_log2);
-    if (fabsf(to) < 1e6f && (to > ms[qt] || z[qt] == 0.f)) {
-      z[qt] = to > ms[qt] || !((any >> qt) & 1u) ? ldexpf(z[qt], (int)(ms[qt] - to)) : __builtin_nanf("");
+    if (fabsf(to) < 1e6f && (to > ms[qt] || !((any >> (16 + qt)) & 1u))) {
+      z[qt] = to >= ms[qt] || !((any >> qt) & 1u) ? ldexpf(z[qt], (int)(ms[qt] - to)) : __builtin_nanf("");
       ms[qt] = to;
+      any |= 0x10000u << qt;
     }
   };
   enum { FOLLOW, MAXIMA, FIXED };   // the reference follows the sum; the maxima instead; the sum against the maxima
+  auto fold = [&](int mode) __attribute__((always_inline)) {
+    int th = tid;
+    asm volatile("" : "+v"(th));   // (its addresses are formed here, not kept in registers through the loop)
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) {
+      float before = sh_z[th][qt];
+      if (mode == FOLLOW) {   // (the reference rose, or was set before anything was summed)
+        before = ldexpf(before, (int)(sh_zref[th][qt] - ms[qt]));
+        sh_zref[th][qt] = ms[qt];
+      }
+      sh_z[th][qt] = before + z[qt];
+      z[qt] = 0.f;
+    }
+  };
   auto walk = [&](int mode) __attribute__((always_inline)) {
 #pragma unroll
-    for (int qt = 0; qt < QW; ++qt) z[qt] = 0.f;
+    for (int qt = 0; qt < QW; ++qt) {
+      z[qt] = 0.f;
+      sh_z[tid][qt] = 0.f;
+      sh_zref[tid][qt] = ms[qt];
+    }
     fetch(key_beg);
     stage(0, key_beg);
     int cur = 0;
@@ -330,11 +358,18 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
           }
 #pragma unroll
           for (int qt = 0; qt < QW; ++qt) z[qt] += sum[qt];
-          any = (1u << QW) - 1u;
+          any |= (1u << QW) - 1u;
         }
         unset = 0.f;
       } else if (__any(p <= vis_last) && nqt > 0) {
         unset = 0.f;
+        int vis[QW], nl = lane;   // this lane's query of the tile sees positions <= vis
+        asm volatile("" : "+v"(nl));   // (formed here, not kept in registers through the other blocks)
+#pragma unroll
+        for (int qt = 0; qt < QW; ++qt) {
+          const int j = ((wtt + qt) >> lgG) * 16 + (nl & 15);
+          vis[qt] = wtt + qt < ntt && j < a.m ? tau0 + j - 1 : -1;
+        }
 #pragma unroll 1
         for (int kt = 0; kt < KT; ++kt) {
           f32x4_t d[QW];
@@ -350,18 +385,24 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void
               mx[qt] = fmaxf(mx[qt], m);
             } else {
               if (mode == FOLLOW) follow(qt, m);
+              float e[4];
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
-                const float e = fast_exp2(fmaf(d[qt][r], a.scale_log2, -ms[qt]));
-                z[qt] += s[r] ? e : 0.f;
+                e[r] = fast_exp2(fmaf(d[qt][r], a.scale_log2, -ms[qt]));
+                e[r] = s[r] ? e[r] : 0.f;
               }
+              z[qt] += (e[0] + e[1]) + (e[2] + e[3]);
             }
             any |= (s[0] || s[1] || s[2] || s[3]) ? 1u << qt : 0u;
           }
         }
       }
+      if (mode != MAXIMA && (key0 - key_beg) / KBLK % STATS_FOLD == 0) fold(mode);   // (uniform)
       stage(cur ^ 1, key0 + KBLK);
     }
+    fold(mode);
+#pragma unroll
+    for (int qt = 0; qt < QW; ++qt) z[qt] = sh_z[tid][qt];
     __syncthreads();
   };
 

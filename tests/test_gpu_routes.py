@@ -547,6 +547,40 @@ def test_seed_sums_that_the_reference_cannot_follow(case, ring):
         assert ((got - want).abs() <= tol + 2e-36)[seen_h].all(), h
 
 
+# kv dtype, G, units, d, P, m: so many that the keys of a query block stay in one segment
+LONG_SUMS = [("bf16", 4, 768, 64, 8192, 64), ("bf16", 4, 768, 64, 16300, 64), ("bf16", 4, 768, 128, 2048, 64), ("f32", 4, 224, 64, 32768, 64)]
+
+
+@pytest.mark.parametrize("sink", [0, 24])
+@pytest.mark.parametrize("case", range(len(LONG_SUMS)))
+def test_seed_sums_of_long_rows(case, sink):
+    """The sum of a long row behind a few keys that hold nearly all of it: every score is its term over that sum, so the row
+    sums to 1 within the sum's roundings.  A lane adds up the tiles of 256 keys and then those sums, a chain of 16 + P / 256
+    roundings at most; 20 more for terms, quotient and the four lane groups."""
+    dtype, G, units, d, P, m = LONG_SUMS[case]
+    print("[case]", LONG_SUMS[case], sink, flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(case)
+    K = torch.randn(1, units, P, d, device=DEV, generator=g, dtype=tdt) * 0.9
+    K[..., 0] = 0
+    K[:, :, :16, 0] = sink / (1.4426950408889634 / d ** 0.5)
+    q = torch.randn(1, units * G, m, d, device=DEV, generator=g).to(tdt)
+    q[..., 0] = 1
+    st = corm.LayerState(1, units * G, units, d, P, P, m + 1, 8, dtype, device=DEV, score_dtype="f32")
+    st.preload(K, K)
+    t = torch.full((1,), P, dtype=torch.int32, device=DEV)
+    st.prefill_seed(q, t, torch.zeros_like(t))
+    torch.cuda.synchronize()
+    steps = torch.arange(P - m + 1, P + 1, device=DEV)
+    seen = torch.arange(P, device=DEV).view(1, -1) < steps.view(-1, 1)
+    worst = 0.0
+    for h in range(0, units * G, 97):
+        row = torch.where(seen, st.ring[0, h][(steps - 1) % (m + 1)], 0.0)
+        worst = max(worst, float((row.double().sum(-1) - 1).abs().max()))
+    print("[worst]", worst, flush=True)
+    assert worst <= (36 + P / 256) * 2.0 ** -24
+
+
 # kv dtype, G, Hkv, d, Lcap, ring, w
 SMALL = [
     ("f32", 1, 4, 64, 640, "f32", 8), ("f32", 1, 3, 64, 576, "bit", 8), ("f32", 2, 2, 128, 256, None, 4), ("f32", 4, 1, 128, 160, "bf16", 4),
