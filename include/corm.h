@@ -109,8 +109,8 @@ typedef struct corm_desc {
  *   path   how attend + record are launched: 0 = chosen by shape (default); 1 = split kernels (several
  *          workgroups per unit, partials merged by a second launch; grouped bf16 d=128 queries take q.K^T on
  *          the matrix cores); 2 = one workgroup per unit with the logits in LDS (taken only if they fit);
- *          3 = as 1 but q.K^T always on the vector ALU.  (With 0, corm_decode_step does a step of small units in
- *          one launch where it would otherwise take 1; corm_selected_path then still says 1.)  Every path produces the same keep mask, indices
+ *          3 = as 1 but q.K^T always on the vector ALU.  (With 0, and without events, corm_decode_step does a step of
+ *          small units in one launch, with the bits of 1.)  Every path produces the same keep mask, indices
  *          and cache; out and the recorded scores agree within fp32 rounding.  A tuning and test knob.
  *   attend_start_event, attend_stop_event   hipEvent_t handles (as void*), both or neither: recorded on the
  *          call's stream immediately before and after the launch that streams K and V (the split attend
@@ -287,7 +287,7 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
  * message is w x l booleans; this keeps one int32 per key instead). */
 
 /* The path (1 or 2, see corm_launch_opts) the attend / step calls take for this descriptor and these options
- * (NULL = defaults) on the current device; a negative corm_status for a bad descriptor or bad options. */
+ * (NULL = defaults) on the current device (1 also where corm_decode_step does what 1 does in one launch); a negative corm_status for a bad descriptor or bad options. */
 int corm_selected_path(const corm_desc* desc, const corm_launch_opts* opts);
 
 /* Diagnostic: thr[i] = fp32(c) / fp32(t[i]) exactly as the kernels compute it (Def. 3.1). */

@@ -121,6 +121,26 @@ struct Attend {
       m_run[g] = mnew;
     }
   }
+
+  // The row groups of a wave (lanes differing in bits >= log2(LPR)) meet: every lane gets the sums over all of them.  (Which
+  // product is fused is said: every kernel that sums a part has the same bits.)
+  __device__ static __forceinline__ void merge_rows(float& m, float& z, float (&acc)[EPL]) {
+#pragma unroll
+    for (int o = LPR; o < 64; o <<= 1) {
+      const float mo = __shfl_xor(m, o);
+      const float zo = __shfl_xor(z, o);
+      const float mn = fmaxf(m, mo);
+      const float ms = mn == neg_inf() ? 0.f : mn;
+      const float a0 = fast_exp2(m - ms), a1 = fast_exp2(mo - ms);
+      z = fmaf(z, a0, zo * a1);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        const float ao = __shfl_xor(acc[e], o);
+        acc[e] = fmaf(acc[e], a0, ao * a1);
+      }
+      m = mn;
+    }
+  }
 };
 
 // Lazy mode, shared by the attend kernels: the live masks of slots [first, first + 64*nwords) go to
@@ -257,21 +277,7 @@ __global__ __launch_bounds__(WG) void corm_attend_kernel(const Params p) {
   // merge the row groups of the wave (lanes differing in bits >= log2(LPR)), then the waves
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-#pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) {
-      const float mo = __shfl_xor(m_run[g], o);
-      const float zo = __shfl_xor(z_run[g], o);
-      const float mn = fmaxf(m_run[g], mo);
-      const float ms = mn == neg_inf() ? 0.f : mn;
-      const float a0 = fast_exp2(m_run[g] - ms), a1 = fast_exp2(mo - ms);
-      z_run[g] = z_run[g] * a0 + zo * a1;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const float ao = __shfl_xor(acc[g][e], o);
-        acc[g][e] = acc[g][e] * a0 + ao * a1;
-      }
-      m_run[g] = mn;
-    }
+    A::merge_rows(m_run[g], z_run[g], acc[g]);
     if (sub == 0) {
 #pragma unroll
       for (int e = 0; e < EPL; ++e) sh_acc[g][wv][cl * EPL + e] = acc[g][e];

@@ -70,6 +70,37 @@ int static_scratch(void** ptr) {
 }
 }  // namespace
 
+// What a step call needs, from its checked arguments.
+namespace {
+struct StepCall {
+  Params p;
+  WorkspaceLayout wl;
+  LaunchCtx ctx;
+};
+
+int step_call(const corm_desc* desc, const void* q, const void* k_new, const void* v_new, void* K, void* V, int32_t* lens,
+              int32_t* pos, int32_t* last_hit, const int32_t* t, const int32_t* t_first, void* score_ring, float* out,
+              uint8_t* keep, int32_t* kept_idx, void* workspace, size_t workspace_bytes, int32_t* status,
+              const corm_launch_opts* opts, StepCall* c) {
+  int rc = validate_desc(desc);
+  if (rc) return rc;
+  rc = check_step_pointers(q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, kept_idx, status);
+  if (rc) return rc;
+  rc = check_workspace(desc, workspace, workspace_bytes, &c->wl);
+  if (rc) return rc;
+  rc = make_ctx(opts, &c->ctx);
+  if (rc) return rc;
+  Params& p = c->p;
+  p = {};
+  p.q = q; p.k_new = k_new; p.v_new = v_new; p.K = K; p.V = V; p.lens = lens; p.pos = pos;
+  p.last_hit = last_hit; p.t = t; p.t_first = t_first; p.ring = score_ring; p.out = out; p.keep = keep;
+  p.kept_idx = kept_idx; p.status = status;
+  p.do_append = 1; p.do_evict = 1;
+  bind_params(desc, c->wl, workspace, p);
+  return CORM_OK;
+}
+}  // namespace
+
 // ---------------------------------------------------------------- C ABI
 
 extern "C" {
@@ -237,23 +268,10 @@ int corm_step_attend(const corm_desc* desc, const void* q, const void* k_new, co
                      const int32_t* lens, int32_t* pos, int32_t* last_hit, const int32_t* t, const int32_t* t_first,
                      void* score_ring, float* out, uint8_t* keep, void* workspace, size_t workspace_bytes,
                      int32_t* status, const corm_launch_opts* opts, void* stream) {
-  int rc = validate_desc(desc);
-  if (rc) return rc;
-  rc = check_step_pointers(q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, nullptr, status);
-  if (rc) return rc;
-  WorkspaceLayout wl;
-  rc = check_workspace(desc, workspace, workspace_bytes, &wl);
-  if (rc) return rc;
-  LaunchCtx ctx;
-  rc = make_ctx(opts, &ctx);
-  if (rc) return rc;
-  Params p = {};
-  p.q = q; p.k_new = k_new; p.v_new = v_new; p.K = K; p.V = V; p.lens = const_cast<int32_t*>(lens); p.pos = pos;
-  p.last_hit = last_hit; p.t = t; p.t_first = t_first; p.ring = score_ring; p.out = out; p.keep = keep;
-  p.status = status;
-  p.do_append = 1; p.do_evict = 1;
-  bind_params(desc, wl, workspace, p);
-  return launch_attend_record(desc, p, ctx, (hipStream_t)stream);
+  StepCall c;
+  const int rc = step_call(desc, q, k_new, v_new, K, V, const_cast<int32_t*>(lens), pos, last_hit, t, t_first, score_ring, out,
+                           keep, nullptr, workspace, workspace_bytes, status, opts, &c);
+  return rc ? rc : launch_attend_record(desc, c.p, c.ctx, (hipStream_t)stream);
 }
 
 int corm_step_evict(const corm_desc* desc, void* K, void* V, int32_t* lens, int32_t* pos, int32_t* last_hit,
@@ -275,28 +293,15 @@ int corm_decode_step(const corm_desc* desc, const void* q, const void* k_new, co
                      int32_t* lens, int32_t* pos, int32_t* last_hit, const int32_t* t, const int32_t* t_first,
                      void* score_ring, float* out, uint8_t* keep, int32_t* kept_idx, void* workspace,
                      size_t workspace_bytes, int32_t* status, const corm_launch_opts* opts, void* stream) {
-  int rc = validate_desc(desc);
+  StepCall c;
+  int rc = step_call(desc, q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, keep, kept_idx, workspace,
+                     workspace_bytes, status, opts, &c);
   if (rc) return rc;
-  if (misaligned4(kept_idx)) return CORM_EINVAL;
-  LaunchCtx ctx;
-  if (make_ctx(opts, &ctx) == CORM_OK && small_step(desc, ctx)) {
-    rc = check_step_pointers(q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, kept_idx, status);
-    if (rc) return rc;
-    WorkspaceLayout wl;
-    rc = check_workspace(desc, workspace, workspace_bytes, &wl);
-    if (rc) return rc;
-    Params p = {};
-    p.q = q; p.k_new = k_new; p.v_new = v_new; p.K = K; p.V = V; p.lens = lens; p.pos = pos;
-    p.last_hit = last_hit; p.t = t; p.t_first = t_first; p.ring = score_ring; p.out = out; p.keep = keep;
-    p.kept_idx = kept_idx; p.status = status;
-    p.do_append = 1; p.do_evict = 1;
-    bind_params(desc, wl, workspace, p);
-    return launch_small(desc, p, ctx, (hipStream_t)stream);
-  }
-  rc = corm_step_attend(desc, q, k_new, v_new, K, V, lens, pos, last_hit, t, t_first, score_ring, out, keep,
-                        workspace, workspace_bytes, status, opts, stream);
+  if (small_step(desc, c.ctx)) return launch_small(desc, c.p, c.ctx, (hipStream_t)stream);
+  rc = launch_attend_record(desc, c.p, c.ctx, (hipStream_t)stream);
   if (rc) return rc;
-  return corm_step_evict(desc, K, V, lens, pos, last_hit, kept_idx, workspace, workspace_bytes, stream);
+  return launch_compact(desc, c.wl, workspace, K, V, pos, last_hit, lens, nullptr, kept_idx, false, CompactPolicy(),
+                        (hipStream_t)stream);
 }
 
 int corm_decode_step_lazy(const corm_desc* desc, const void* q, const void* k_new, const void* v_new, void* K, void* V,

@@ -307,42 +307,50 @@ int launch_attend_record(const corm_desc* d, const Params& p0, const LaunchCtx& 
   return launch_record(d, p, c, s);
 }
 
-// A whole step in one launch (small.hpp)?  A unit is then one workgroup's alone, so only while its rows are few: kernel times with
-// every slot in use, us, split launches | one: 32 units x 640 rows of 256 bytes 12.5 | 12.9, of 1024 12.5 | 16.5; two heads a unit,
-// 320 rows 13.7 | 12.0, 512 13.6 | 13.5; four heads, 320 rows 16.4 | 15.8 (the launches' own cost, two saved, comes on top); half-full
-// units take less.  Where the units alone fill half the chip the split launches share out less: 100 units x 640 rows 15.4 | 14.0,
-// 200 units 20.9 | 15.4, 200 units x 1024 rows of 128 bytes 23.0 | 14.4.
+// A whole step in one launch (small.hpp)?  A unit is then one workgroup's alone, so only while its rows are few.  Whole steps in a
+// captured graph, us, split launches | one, every slot in use, at which no key goes (in brackets: one does, at slot 0, so that every
+// row moves).  fp32, rows of 256 bytes, 8 units: 64 slots 9.6 | 6.4 (12.3 | 7.4), 320 slots 9.9 | 7.7 (13.5 | 11.0), 640 slots
+// 10.0 | 9.7 (14.9 | 15.1), 832 slots 10.0 | 11.6 (15.3 | 18.1); one unit of 640 slots 9.2 | 8.5 (13.3 | 14.5).  Two heads a
+// unit, rows of 128 bytes: 640 slots 1.07 times as fast, 832 0.93; four heads: 256 slots 1.04, 320 0.97, 640 0.83.  From half the
+// chip on the split launches share out less: 160 units of 1024 slots of 256 bytes 23.3 | 19.2, two heads 24.7 | 20.5, four
+// 28.7 | 23.7.  What decides is the capacity, which the host knows: at the limits one launch is up to 8 % slower where every slot
+// is in use, and with 52 keys in 576 slots (4 units that evict at every step) 14.0 | 11.2 as called from a program.  (Eight heads
+// a unit, the deferred step and the two phases have no such kernel.)
 bool small_step(const corm_desc* d, const LaunchCtx& c) {
   const int G = d->Hq / d->Hkv;
-  if (c.path != 0 || G > 4 || d->Lcap > SMALL_MAX_SLOTS || use_unit_path(d, c)) return false;
-  const long limit = (2L * d->B * d->Hkv >= c.cus ? 256L : 160L) * 1024;
-  return (long)d->Lcap * row_bytes(d) <= (G == 1 ? limit : G == 2 ? limit * 4 / 5 : limit / 2);
+  if (c.path != 0 || c.ev0 || G > 4 || d->Lcap > SMALL_MAX_SLOTS || use_unit_path(d, c)) return false;
+  if (attend_on_mfma(d, c)) return false;   // (the split launches form these logits on the matrix cores)
+  const long kb = 2L * d->B * d->Hkv >= c.cus ? (G == 1 ? 256 : G == 2 ? 204 : 128) : (G == 1 ? 160 : G == 2 ? 104 : 40);
+  return (long)d->Lcap * row_bytes(d) <= kb * 1024;
+}
+
+template <typename DT, int D, int G>
+int launch_small_g(const Params& p, int units, hipStream_t s) {
+  constexpr int stage_rows = Attend<DT, D, G, WAVES>::STAGE_ROWS;
+  const int lstride = (p.Lcap + stage_rows - 1) / stage_rows * stage_rows, parts = (p.Lcap + p.part_keys - 1) / p.part_keys;
+  hipLaunchKernelGGL((corm_small_kernel<DT, D, G>), dim3(units), dim3(SMALL_WG),
+                     small_lds_floats(G, D, lstride, parts) * sizeof(float), s, p, lstride, parts);
+  return launch_status();
 }
 
 template <typename DT, int D>
 int launch_small_dt(const Params& p, int G, int units, hipStream_t s) {
-  auto go = [&](auto kernel, int stage_rows) {
-    const int lstride = (p.Lcap + 2 * stage_rows - 1) / (2 * stage_rows) * (2 * stage_rows) + stage_rows;
-    hipLaunchKernelGGL(kernel, dim3(units), dim3(SMALL_WG), (size_t)G * lstride * sizeof(float), s, p, lstride);
-    return launch_status();
-  };
   switch (G) {
-    case 1: return go(corm_small_kernel<DT, D, 1>, small_stage_rows<DT, D, 1>());
-    case 2: return go(corm_small_kernel<DT, D, 2>, small_stage_rows<DT, D, 2>());
-    case 4: return go(corm_small_kernel<DT, D, 4>, small_stage_rows<DT, D, 4>());
+    case 1: return launch_small_g<DT, D, 1>(p, units, s);
+    case 2: return launch_small_g<DT, D, 2>(p, units, s);
+    case 4: return launch_small_g<DT, D, 4>(p, units, s);
     default: return CORM_EUNSUPPORTED;
   }
 }
 
-int launch_small(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStream_t s) {
+int launch_small(const corm_desc* d, const Params& p0, const LaunchCtx& c, hipStream_t s) {
   const int G = d->Hq / d->Hkv, units = d->B * d->Hkv;
-  if (c.ev0 && hipEventRecord(c.ev0, s) != hipSuccess) return CORM_EHIP;
-  const int rc = d->kv_dtype == CORM_F32
-                     ? (d->d == 64 ? launch_small_dt<F32, 64>(p, G, units, s) : launch_small_dt<F32, 128>(p, G, units, s))
-                     : (d->d == 64 ? launch_small_dt<BF16, 64>(p, G, units, s) : launch_small_dt<BF16, 128>(p, G, units, s));
-  if (rc) return rc;
-  if (c.ev1 && hipEventRecord(c.ev1, s) != hipSuccess) return CORM_EHIP;
-  return CORM_OK;
+  Params p = p0;
+  p.part_keys = attend_part_keys(d, c);
+  if (d->kv_dtype == CORM_F32)
+    return d->d == 64 ? launch_small_dt<F32, 64>(p, G, units, s) : launch_small_dt<F32, 128>(p, G, units, s);
+  if (d->d == 64) return launch_small_dt<BF16, 64>(p, G, units, s);
+  return G == 1 ? launch_small_g<BF16, 128, 1>(p, units, s) : CORM_EUNSUPPORTED;
 }
 
 // Policy of the compaction: exact mode compacts every unit that lost a key; lazy mode only

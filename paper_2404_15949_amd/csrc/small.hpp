@@ -9,40 +9,66 @@ namespace {
 //
 // A few units of a few hundred slots leave nothing to share out: what a step costs is its launches and, in each, a chain of
 // memory latencies (lengths, then rows or partials, then masks, then rows again).  Here a workgroup does the whole step of
-// a unit: the logits stay in LDS as in the unit kernel, the new row is attended to from k_new and v_new directly (nothing is
+// a unit: logits and partials stay in LDS, the new row is attended to from k_new and v_new directly (nothing is
 // written to be read back), pos and last_hit are read once and stored once, at the slot the key ends in, and the
-// survivors' list never leaves LDS.  Bound by that chain, and with hundreds of rows by what one workgroup streams: 4 units of 52 keys
-// that evict at every step (fp32, d 64) 4.1 + 4.8 + 2.1 us in three launches, 6.9 in one with the inputs in the caches; with new
-// inputs at every step 4.4 + 5.2 + 5.0 and 11.0 (a step of the program 13.8 -> 11.4).  small_step says where that pays.
+// survivors' list never leaves LDS.  Bound by that chain, and with hundreds of rows by what one workgroup streams: small_step says
+// where that pays.
+//
+// The bits are those of the split launches, which the calls that do a part of a step keep to (corm_decode_attend, the two
+// phases, the deferred step): the same parts of p.part_keys keys, each walked by four waves in the order of
+// corm_attend_kernel and merged as there (two groups of four waves take the parts in turn), the partials folded as in
+// corm_record_kernel.
 
 constexpr int SMALL_WG = 512;
 constexpr int SMALL_WAVES = SMALL_WG / 64;
+constexpr int SMALL_GROUPS = SMALL_WAVES / WAVES;        // groups of waves that walk a part each
 constexpr int SMALL_TILES = 2;                           // slots per thread
 constexpr int SMALL_MAX_SLOTS = SMALL_TILES * SMALL_WG;
+constexpr int SMALL_MAX_PARTS = SMALL_MAX_SLOTS / (CHUNK / MAX_PARTS_PER_CHUNK);
 
-// LDS for logits: whole stage pairs, and the stage of the new row behind the last slot
-template <typename DT, int D, int G>
-constexpr int small_stage_rows() { return SMALL_WAVES * (64 / (D * DT::ESZ / 16)) * (G == 1 ? UNROLL : UNROLL / 2); }
+// (max, sum, products) of one column over the four waves of a part, as corm_attend_kernel merges them
+struct SmallPart {
+  float m, z, at;
+};
+__device__ __forceinline__ SmallPart small_part(const float* m, const float* z, const float* acc, int stride) {
+  SmallPart r = {neg_inf(), 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) r.m = fmaxf(r.m, m[i]);
+  const float ms = r.m == neg_inf() ? 0.f : r.m;
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) {
+    const float a = fast_exp2(m[i] - ms);
+    r.z = fmaf(z[i], a, r.z);
+    r.at = fmaf(acc[i * stride], a, r.at);
+  }
+  return r;
+}
+
+// floats of dynamic LDS: logits [G][lstride], partials of the waves: max and sum [parts][G][WAVES], products [parts][G][WAVES][D]
+inline size_t small_lds_floats(int G, int D, int lstride, int parts) {
+  return (size_t)G * lstride + (size_t)parts * G * WAVES * (D + 2);
+}
 
 template <typename DT, int D, int G>
-__global__ __launch_bounds__(SMALL_WG) void corm_small_kernel(const Params p, const int lstride) {
-  using A = Attend<DT, D, G, SMALL_WAVES, (G == 1 ? UNROLL : UNROLL / 2)>;
+__global__ __launch_bounds__(SMALL_WG) void corm_small_kernel(const Params p, const int lstride, const int max_parts) {
+  using A = Attend<DT, D, G, WAVES>;
   constexpr int EPL = A::EPL, ROWB = A::ROWB, LPR = A::LPR, RPL = A::RPL;
-  static_assert(A::STAGE_ROWS == small_stage_rows<DT, D, G>(), "the host sizes the LDS by it");
 
-  extern __shared__ float sh_logit[];   // [G][lstride] raw logits of the unit (log2 domain)
-  __shared__ float sh_m[G][SMALL_WAVES];
-  __shared__ float sh_z[G][SMALL_WAVES];
-  __shared__ float sh_acc[G][SMALL_WAVES][D];
+  extern __shared__ float sh_dyn[];     // see small_lds_floats
+  float* sh_logit = sh_dyn;             // raw logits of the unit (log2 domain)
+  float* sh_m = sh_logit + G * lstride;
+  float* sh_z = sh_m + max_parts * G * WAVES;
+  float* sh_acc = sh_z + max_parts * G * WAVES;
   __shared__ float sh_M[G], sh_Z[G];
   __shared__ unsigned long long sh_keep[SMALL_TILES * SMALL_WAVES];   // ballots, 64 slots each
   __shared__ uint16_t sh_src[SMALL_MAX_SLOTS];                        // old slots of the survivors
 
   const int unit = blockIdx.x;
   const int b = unit / p.Hkv, hkv = unit - b * p.Hkv, hq0 = hkv * G;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wv / WAVES, gwv = wv % WAVES;
   const int sub = lane / LPR, cl = lane % LPR;
-  const int lane_row = wv * RPL + sub;
+  const int lane_row = gwv * RPL + sub;   // this lane's row inside a load of its group
 
   // everything that does not hang on the unit's length is requested with it
   const int lens_value = p.lens[unit], tcur = p.t[b], tfirst = p.t_first[b];
@@ -51,26 +77,31 @@ __global__ __launch_bounds__(SMALL_WG) void corm_small_kernel(const Params p, co
   for (int g = 0; g < G; ++g)
     qreg[g] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.q) +
                                               ((size_t)(b * p.Hq + hq0 + g) * ROWB + (size_t)cl * 16));
-  const char* knew = reinterpret_cast<const char*>(p.k_new) + (size_t)unit * ROWB;
-  const char* vnew = reinterpret_cast<const char*>(p.v_new) + (size_t)unit * ROWB;
-  typename A::Stage sn;   // row 0 of the workgroup: the new one; the others are out of range
-  A::template load<false>(sn, make_rsrc(knew, ROWB), make_rsrc(vnew, ROWB), (uint32_t)lane_row * ROWB + (uint32_t)cl * 16,
-                          nullptr, 0);
+  const uint4 knew = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.k_new) + (size_t)unit * ROWB + (size_t)cl * 16);
+  const uint4 vnew = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.v_new) + (size_t)unit * ROWB + (size_t)cl * 16);
 
   const UnitLen ul = unit_len_of(p, __builtin_amdgcn_readfirstlane(lens_value));
-  const int L0 = ul.L0, L = ul.L;
+  const int L0 = ul.L0, L = ul.L;   // (L >= 1: there is room in an empty unit)
   if (tid == 0 && ul.flags && p.status) atomicOr(p.status, ul.flags);
   char* Kb = reinterpret_cast<char*>(p.K) + (size_t)unit * p.Lcap * ROWB;
   char* Vb = reinterpret_cast<char*>(p.V) + (size_t)unit * p.Lcap * ROWB;
   int32_t* posb = p.pos + (size_t)unit * p.Lcap;
   int32_t* lhb = p.last_hit + (size_t)unit * p.Lcap;
 
+  // The stages of a group: those of its parts (grp, grp + SMALL_GROUPS, ...) one after the other, the next one's loads always in
+  // flight.  The descriptors end at row L0; the new row is put in its place where a stage holds it.
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(Kb, (uint32_t)L0 * ROWB);
   const __amdgpu_buffer_rsrc_t rv = make_rsrc(Vb, (uint32_t)L0 * ROWB);
-  uint32_t off = (uint32_t)lane_row * ROWB + (uint32_t)cl * 16;
-  constexpr uint32_t STAGE_BYTES = (uint32_t)A::STAGE_ROWS * ROWB;
+  const int spp = p.part_keys / A::STAGE_ROWS, lg_spp = 31 - __clz(spp);   // stages per part: a power of two
+  auto stage_part = [&](int n) __attribute__((always_inline)) { return grp + (n >> lg_spp) * SMALL_GROUPS; };
+  auto stage_row = [&](int n) __attribute__((always_inline)) {   // first row of the group's stage n
+    return stage_part(n) * p.part_keys + (n & (spp - 1)) * A::STAGE_ROWS;
+  };
+  auto fetch = [&](typename A::Stage& st, int row) __attribute__((always_inline)) {
+    A::template load<false>(st, rk, rv, (uint32_t)(row + lane_row) * ROWB + (uint32_t)cl * 16, nullptr, 0);
+  };
   typename A::Stage s0, s1;
-  A::template load<false>(s0, rk, rv, off, nullptr, 0);
+  fetch(s0, stage_row(0));
   int my_pos[SMALL_TILES], my_lh[SMALL_TILES];   // of the slots tid, tid + SMALL_WG
   const __amdgpu_buffer_rsrc_t rp = make_rsrc(posb, (uint32_t)L0 * 4), rl = make_rsrc(lhb, (uint32_t)L0 * 4);
 #pragma unroll
@@ -82,75 +113,89 @@ __global__ __launch_bounds__(SMALL_WG) void corm_small_kernel(const Params p, co
   clear_bit_rows(p, b, hq0, G, SMALL_WG);   // (ordered before the record phase by the barriers of the merge)
 
   float m_run[G], z_run[G], acc[G][EPL];
+  auto begin_part = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m_run[g] = neg_inf();
-    z_run[g] = 0.f;
+    for (int g = 0; g < G; ++g) {
+      m_run[g] = neg_inf();
+      z_run[g] = 0.f;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
-  }
-  for (int it = 0; it < L0; it += 2 * A::STAGE_ROWS) {
-    A::template load<false>(s1, rk, rv, off + STAGE_BYTES, nullptr, 0);
-    A::compute(s0, it + lane_row, it + lane_row, L0, cl, qreg, p.scale_log2, sh_logit, lstride, m_run, z_run, acc);
-    off += 2 * STAGE_BYTES;
-    A::template load<false>(s0, rk, rv, off, nullptr, 0);
-    A::compute(s1, it + A::STAGE_ROWS + lane_row, it + A::STAGE_ROWS + lane_row, L0, cl, qreg, p.scale_log2, sh_logit,
-               lstride, m_run, z_run, acc);
-  }
-  __syncthreads();   // (the logits of the rows behind L0 that the last stages covered are in place)
-  if (ul.appended && wv == 0) {
-    A::compute(sn, L0 + lane_row, L0 + lane_row, L, cl, qreg, p.scale_log2, sh_logit, lstride, m_run, z_run, acc);
-    if (sub == 0) {
-      *reinterpret_cast<uint4*>(Kb + (size_t)L0 * ROWB + (size_t)cl * 16) = sn.k[0];
-      *reinterpret_cast<uint4*>(Vb + (size_t)L0 * ROWB + (size_t)cl * 16) = sn.v[0];
+      for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
     }
-  }
-
-  // merge the row groups of each wave (scaled once, to the wave's maximum), then the waves
+  };
+  auto work = [&](typename A::Stage& st, int n) __attribute__((always_inline)) {
+    const int row = stage_row(n);
+    if (row >= L) return;   // (uniform over the wave)
+    if (ul.appended && L0 >= row && L0 < row + A::STAGE_ROWS) {   // (uniform) the append
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    float mw = m_run[g];
-#pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
-    const float a = fast_exp2(m_run[g] - (mw == neg_inf() ? 0.f : mw));
-    m_run[g] = mw;
-    z_run[g] *= a;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[g][e] *= a;
-#pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) {
-      z_run[g] += __shfl_xor(z_run[g], o);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[g][e] += __shfl_xor(acc[g][e], o);
+      for (int j = 0; j < A::U; ++j)
+        if (row + lane_row + j * A::LOAD_ROWS == L0) {
+          st.k[j] = knew;
+          st.v[j] = vnew;
+          *reinterpret_cast<uint4*>(Kb + (size_t)L0 * ROWB + (size_t)cl * 16) = knew;
+          *reinterpret_cast<uint4*>(Vb + (size_t)L0 * ROWB + (size_t)cl * 16) = vnew;
+        }
     }
-    if (sub == 0) {
+    A::compute(st, row + lane_row, row + lane_row, L, cl, qreg, p.scale_log2, sh_logit, lstride, m_run, z_run, acc);
+    if (stage_part(n + 1) != stage_part(n) || stage_row(n + 1) >= L) {   // (uniform) the last of its part with a key
+      const int part = stage_part(n);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) sh_acc[g][wv][cl * EPL + e] = acc[g][e];
-      if (cl == 0) {
-        sh_m[g][wv] = m_run[g];
-        sh_z[g][wv] = z_run[g];
+      for (int g = 0; g < G; ++g) {
+        A::merge_rows(m_run[g], z_run[g], acc[g]);
+        const int at = (part * G + g) * WAVES + gwv;
+        if (sub == 0) {
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) sh_acc[at * D + cl * EPL + e] = acc[g][e];
+          if (cl == 0) {
+            sh_m[at] = m_run[g];
+            sh_z[at] = z_run[g];
+          }
+        }
       }
+      begin_part();
     }
+  };
+  begin_part();
+  for (int n = 0; stage_row(n) < L; n += 2) {
+    fetch(s1, stage_row(n + 1));
+    work(s0, n);
+    fetch(s0, stage_row(n + 2));
+    work(s1, n + 1);
   }
   __syncthreads();
 
   // out (Eq. 1) and the unit's max / sum (Eq. 2)
+  const int nparts = (L + p.part_keys - 1) / p.part_keys;
   for (int idx = tid; idx < G * D; idx += SMALL_WG) {
     const int g = idx / D, c = idx - g * D;
+    SmallPart part[SMALL_MAX_PARTS];
     float mx = neg_inf();
 #pragma unroll
-    for (int i = 0; i < SMALL_WAVES; ++i) mx = fmaxf(mx, sh_m[g][i]);
-    float zt = 0.f, at = 0.f;
-#pragma unroll
-    for (int i = 0; i < SMALL_WAVES; ++i) {
-      const float a = fast_exp2(sh_m[g][i] - mx);
-      zt = fmaf(sh_z[g][i], a, zt);
-      at = fmaf(sh_acc[g][i][c], a, at);
+    for (int s = 0; s < SMALL_MAX_PARTS; ++s) {
+      part[s] = SmallPart{neg_inf(), 0.f, 0.f};
+      if (s < nparts) {   // (uniform)
+        const int at = (s * G + g) * WAVES;
+        part[s] = small_part(sh_m + at, sh_z + at, sh_acc + at * D + c, D);
+      }
+      mx = fmaxf(mx, part[s].m);
     }
-    p.out[(size_t)(b * p.Hq + hq0 + g) * D + c] = at / zt;
+    const float ms = mx == neg_inf() ? 0.f : mx;
+    float zs[SMALL_MAX_PARTS], at = 0.f;
+#pragma unroll
+    for (int s = 0; s < SMALL_MAX_PARTS; ++s) {
+      const float a = exp2f(part[s].m - ms);
+      zs[s] = part[s].z * a;
+      asm volatile("" : "+v"(zs[s]));   // (rounded: not fused with the sums below)
+      at = fmaf(part[s].at, a, at);
+    }
+    // (the order of a wave that adds up a partial per lane)
+#pragma unroll
+    for (int o = SMALL_MAX_PARTS / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int s = 0; s < o; ++s) zs[s] += zs[s + o];
+    p.out[(size_t)(b * p.Hq + hq0 + g) * D + c] = at / zs[0];
     if (c == 0) {
-      sh_M[g] = mx;
-      sh_Z[g] = zt;
+      sh_M[g] = ms;
+      sh_Z[g] = zs[0];
     }
   }
   __syncthreads();

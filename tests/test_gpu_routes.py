@@ -581,61 +581,152 @@ def test_seed_sums_of_long_rows(case, sink):
     assert worst <= (36 + P / 256) * 2.0 ** -24
 
 
-# kv dtype, G, Hkv, d, Lcap, ring, w
+# kv dtype, G, Hkv, d, Lcap, ring, w (two sequences each): up to the limits of the one-launch step
 SMALL = [
-    ("f32", 1, 4, 64, 640, "f32", 8), ("f32", 1, 3, 64, 576, "bit", 8), ("f32", 2, 2, 128, 256, None, 4), ("f32", 4, 1, 128, 160, "bf16", 4),
-    ("bf16", 1, 2, 128, 640, "bf16", 8), ("bf16", 1, 5, 64, 1024, "bit", 6), ("bf16", 2, 2, 64, 1023, "bf16", 8), ("bf16", 4, 2, 128, 320, "f32", 5),
-    ("bf16", 4, 3, 64, 513, "bit", 8), ("bf16", 1, 100, 128, 1024, None, 8), ("bf16", 2, 1, 128, 65, "bf16", 3), ("bf16", 1, 1, 128, 1, "bit", 2),
-    ("f32", 1, 2, 64, 64, "f32", 3),
+    ("f32", 1, 4, 64, 640, "f32", 8), ("f32", 1, 3, 64, 576, "bit", 8), ("f32", 2, 2, 128, 208, None, 4), ("f32", 4, 1, 128, 80, "bf16", 4),
+    ("bf16", 1, 2, 128, 640, "bf16", 8), ("bf16", 1, 5, 64, 1024, "bit", 6), ("bf16", 2, 2, 64, 832, "bf16", 8), ("bf16", 4, 2, 64, 320, "f32", 5),
+    ("bf16", 4, 3, 64, 300, "bit", 8), ("bf16", 1, 100, 128, 1024, None, 8), ("f32", 2, 1, 64, 65, "bf16", 3), ("bf16", 1, 1, 128, 1, "bit", 2),
+    ("f32", 1, 2, 64, 64, "f32", 3), ("f32", 1, 2, 128, 320, "bit", 8), ("f32", 2, 3, 64, 416, "f32", 6), ("f32", 4, 2, 64, 160, "bf16", 6),
+    ("f32", 1, 100, 64, 1024, "bf16", 8), ("bf16", 2, 100, 64, 1023, "bit", 8), ("bf16", 4, 100, 64, 1024, "f32", 5), ("f32", 1, 100, 128, 512, "bf16", 6),
+    ("f32", 2, 100, 128, 408, "bit", 8), ("f32", 4, 100, 128, 256, "f32", 4),
+]
+
+# and beyond one of them
+NOT_SMALL = [
+    ("f32", 1, 4, 64, 641), ("f32", 2, 2, 128, 209), ("f32", 4, 1, 128, 81), ("bf16", 1, 2, 128, 641), ("bf16", 1, 5, 64, 1025),
+    ("bf16", 2, 2, 64, 833), ("bf16", 4, 2, 64, 321), ("f32", 1, 100, 64, 1025), ("f32", 1, 100, 128, 513), ("f32", 2, 100, 128, 409),
+    ("f32", 4, 100, 128, 257), ("f32", 8, 1, 64, 32), ("bf16", 8, 2, 64, 64), ("bf16", 2, 1, 128, 65), ("bf16", 4, 1, 128, 64),
+    ("f32", 1, 128, 64, 64),
 ]
 
 
-@pytest.mark.parametrize("case", range(len(SMALL)))
-def test_small_units_in_one_launch_equal_the_split_launches(case):
-    """A step of small units in one launch against attend, record and compact: the same cache, decisions and survivors, steps at
-    which keys go and at which none does, units that are empty, full or hold an invalid length, positions and steps without a
-    column; out and the scores within the rounding of fp32 sums (both paths are compared with the oracle elsewhere)."""
+def _in_one_launch(st):
+    """Whether a decode step of this layer is one launch: that writes nothing to the workspace, the launches of the split path do."""
+    other = corm.LayerState(st.B, st.Hq, st.Hkv, st.d, st.Lcap, st.Tcap, st.w, st.r, "f32" if st.dtype == torch.float32 else "bf16",
+                            device=DEV, want_ring=False)
+    other.workspace.fill_(0x5a)
+    q, k = (torch.zeros(st.B, h, st.d, dtype=st.dtype, device=DEV) for h in (st.Hq, st.Hkv))
+    one = torch.ones(st.B, dtype=torch.int32, device=DEV)
+    other.step(q, k, k, one, one)
+    torch.cuda.synchronize()
+    return bool((other.workspace == 0x5a).all())
+
+
+def _small_states(case, n):
+    """n layers in the same state (units that are empty, full or hold an invalid length, a position without a column), and a
+    generator of steps: (q, k, v, t, t_first), steps at which the window is full or not, one of them without a column."""
     dtype, G, Hkv, d, Lcap, ring, w = SMALL[case]
     print("[case]", SMALL[case], flush=True)
     B, Hq, Tcap = 2, G * Hkv, Lcap + 40
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator(device=DEV).manual_seed(case)
     lens = torch.randint(0, Lcap + 1, (B, Hkv), device=DEV, generator=g, dtype=torch.int32)
-    edge = [0, Lcap, max(Lcap - 1, 0), min(Lcap, 512), min(Lcap, 511), Lcap + 7, -3]
-    for i, n in enumerate(edge):
+    edge = [0, Lcap, max(Lcap - 1, 0), min(Lcap, 512), min(Lcap, 511), Lcap + 7, -3, min(Lcap, 128), min(Lcap, 127)]
+    for i, e in enumerate(edge):
         if i < B * Hkv:
-            lens.view(-1)[(i + case) % (B * Hkv)] = n
+            lens.view(-1)[(i + case) % (B * Hkv)] = e
     rows = [torch.randn(B, Hkv, Lcap, d, device=DEV, generator=g).to(tdt) for _ in range(2)]
     pos = torch.arange(Lcap, device=DEV, dtype=torch.int32).expand(B, Hkv, Lcap).clone()
-    pos[0, 0, Lcap // 2] = Tcap + 5                       # a position without a column
+    pos[0, 0, Lcap // 2] = Tcap + 5
     hit = torch.randint(0, Lcap + 4, (B, Hkv, Lcap), device=DEV, generator=g, dtype=torch.int32)
     states = []
-    for path in (0, 1):
+    for _ in range(n):
         st = corm.LayerState(B, Hq, Hkv, d, Lcap, Tcap, w, 3, dtype, device=DEV, want_ring=ring is not None, want_masks=True,
                              score_dtype=ring)
         st.K.copy_(rows[0]), st.V.copy_(rows[1]), st.pos.copy_(pos), st.last_hit.copy_(hit), st.lens.copy_(lens)
         states.append(st)
-    t = torch.tensor([Lcap + 1, Lcap + 3], dtype=torch.int32, device=DEV)
-    for step in range(10):
-        q = torch.randn(B, Hq, d, device=DEV, generator=g).to(tdt)
-        k, v = (torch.randn(B, Hkv, d, device=DEV, generator=g).to(tdt) for _ in range(2))
-        ts = t.clone()
-        if step == 7:
-            ts[1] = Tcap + 1                               # a step without a column
-        t_first = ts - (0 if step % 4 == 3 else w)         # the window is full, or (every fourth step) not
-        for st, path in zip(states, (0, 1)):
-            assert corm.corm_selected_path(st.desc) == 1
+
+    def steps():
+        t = torch.tensor([Lcap + 1, Lcap + 3], dtype=torch.int32, device=DEV)
+        for step in range(10):
+            q = torch.randn(B, Hq, d, device=DEV, generator=g).to(tdt)
+            k, v = (torch.randn(B, Hkv, d, device=DEV, generator=g).to(tdt) for _ in range(2))
+            ts = t + step
+            if step == 7:
+                ts[1] = Tcap + 1
+            yield step, q, k, v, ts, ts - (0 if step % 4 == 3 else w)
+    return states, steps()
+
+
+def _same(a, b, step, names):
+    for name in names:
+        x, y = getattr(a, name), getattr(b, name)
+        if x is None and y is None:
+            continue
+        if x.is_floating_point():        # (NaN in the same places)
+            assert torch.equal(x.isnan(), y.isnan()), (name, step)
+            x, y = x.nan_to_num(0, 1e38, -1e38), y.nan_to_num(0, 1e38, -1e38)
+        assert torch.equal(x, y), (name, step)
+
+
+@pytest.mark.parametrize("poison", [None, INF, -INF, float("nan")])
+@pytest.mark.parametrize("case", range(len(SMALL)))
+def test_small_units_in_one_launch_equal_the_split_launches(case, poison):
+    """A step of small units in one launch against attend, record and compact: the same bits in the cache, the decisions, the
+    survivors, out and the ring, with finite keys and with one that is not in every other unit."""
+    (a, b), steps = _small_states(case, 2)
+    assert _in_one_launch(a)
+    if poison is not None:
+        for st in (a, b):
+            st.K[0, ::2, st.Lcap // 3, 5] = poison
+    for step, q, k, v, t, t_first in steps:
+        for st, path in ((a, 0), (b, 1)):
             st.keep.zero_(), st.kept_idx.zero_()
-            st.step(q, k, v, ts, t_first, opts=corm.corm_launch_opts(path, 0, None, None))
+            st.step(q, k, v, t, t_first, opts=corm.corm_launch_opts(path, 0, None, None))
         torch.cuda.synchronize()
-        a, b = states
-        for name in ("lens", "pos", "last_hit", "K", "V", "keep", "kept_idx", "status"):
-            assert torch.equal(getattr(a, name), getattr(b, name)), (name, step)
-        scale = b.out.abs().amax(-1, keepdim=True)
-        assert ((a.out - b.out).abs() <= 2e-6 * scale).all(), step
-        if ring == "bit":
-            assert torch.equal(a.ring, b.ring), step
-        elif ring:
-            x, y = a.ring.double(), b.ring.double()
-            assert ((x - y).abs() <= (2.0 ** -7 if ring == "bf16" else 4e-6) * y + 1e-12).all(), step
-        t += 1
+        _same(a, b, step, ("out", "ring", "lens", "pos", "last_hit", "K", "V", "keep", "kept_idx", "status"))
+
+
+@pytest.mark.parametrize("case", range(len(SMALL)))
+def test_small_units_step_like_the_calls_that_do_a_part_of_it(case):
+    """What the header says of corm_decode_step, with default options: its bits are those of append, attend, mask and compact, and of
+    the two phases; the deferred step with dead_num = 0 reproduces it slot for slot (its recent-r rule goes by position: units with
+    room, and keys at the positions in front of the step's)."""
+    (a, two, lazy, single), steps = _small_states(case, 4)
+    room = max(a.Lcap - 8, 0)
+    n = a.lens.clamp(0, room)
+    before = torch.tensor([a.Lcap, a.Lcap + 2], device=DEV).view(2, 1, 1)
+    for st in (a, two, lazy, single):
+        st.lens.copy_(n)
+        st.pos.copy_(before - n.unsqueeze(-1) + torch.arange(a.Lcap, device=DEV))
+    for step, q, k, v, t, t_first in steps:
+        if step > min(room, 6):
+            break
+        a.step(q, k, v, t, t_first)
+        two.step_attend(q, k, v, t, t_first)
+        two.step_evict()
+        lazy.step_lazy(q, k, v, t, t_first, 0, 1)
+        s = single
+        corm.corm_append(s.desc, s.K, s.V, s.lens, s.pos, s.last_hit, k, v, t, s.status)
+        corm.corm_decode_attend(s.desc, q, s.K, s.V, s.lens, s.pos, t, s.ring, s.last_hit, s.out, s.workspace, status=s.status)
+        corm.corm_evict_mask_summary(s.desc, s.last_hit, s.lens, t, t_first, s.keep)
+        corm.corm_compact(s.desc, s.K, s.V, s.pos, s.last_hit, s.lens, s.keep, s.kept_idx, s.workspace)
+        torch.cuda.synchronize()
+        live = torch.arange(a.Lcap, device=DEV) < a.lens.unsqueeze(-1)
+        for other in (two, lazy, single):
+            _same(a, other, step, ("out", "ring", "lens", "status"))
+            for name in ("pos", "last_hit", "K", "V"):
+                assert torch.equal(getattr(a, name)[live], getattr(other, name)[live]), (name, step)
+
+
+@pytest.mark.parametrize("dtype,G,Hkv,d,Lcap", NOT_SMALL)
+def test_what_is_not_small_takes_the_launches_of_its_path(dtype, G, Hkv, d, Lcap):
+    assert not _in_one_launch(corm.LayerState(2, G * Hkv, Hkv, d, Lcap, Lcap + 8, 4, 3, dtype, device=DEV, want_ring=False))
+
+
+@pytest.mark.parametrize("case", [0, 4, 6])
+def test_a_step_of_small_units_with_events_brackets_the_launch_that_streams(case):
+    """The events of corm_launch_opts lie around the launch that streams K and V alone: a step with events takes the split launches."""
+    (a, b), steps = _small_states(case, 2)
+    a.workspace.fill_(0x5a)
+    for step, q, k, v, t, t_first in steps:
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        e0.record(), e1.record()      # (creates the handles)
+        a.step(q, k, v, t, t_first, opts=corm.make_opts(0, (e0.cuda_event, e1.cuda_event)))
+        b.step(q, k, v, t, t_first)
+        torch.cuda.synchronize()
+        assert e0.elapsed_time(e1) > 0
+        _same(a, b, step, ("out", "ring", "lens", "keep"))
+        if step == 0:
+            assert not bool((a.workspace == 0x5a).all())
+            break
