@@ -40,6 +40,19 @@ def make_state(wl: inputs.Workload, device, Lcap=None, Tcap=None, thr_scale=1.0,
                            device=device, workspace=workspace, want_masks=want_masks, score_dtype=score_dtype)
 
 
+def step_is_one_launch(st: corm.LayerState) -> bool:
+    """Whether a decode step of this layer, as called by default, is one launch: that writes nothing to the workspace, the
+    launches of the other paths do."""
+    other = corm.LayerState(st.B, st.Hq, st.Hkv, st.d, st.Lcap, st.Tcap, st.w, st.r, "f32" if st.dtype == torch.float32 else "bf16",
+                            device=st.K.device, want_ring=False)
+    other.workspace.fill_(0x5a)
+    q, k = (torch.zeros(st.B, h, st.d, dtype=st.dtype, device=st.K.device) for h in (st.Hq, st.Hkv))
+    one = torch.ones(st.B, dtype=torch.int32, device=st.K.device)
+    other.step(q, k, k, one, one)
+    torch.cuda.synchronize()
+    return bool((other.workspace == 0x5a).all())
+
+
 def ring_row(st: corm.LayerState, b: int, slot: int) -> np.ndarray:
     """Row `slot` of sequence b's ring as float32 [Hq, Tcap].  A bit ring (the boolean message) reads as
     1.0 / 0.0, which the oracle's threshold test maps back to the recorded boolean for any threshold in (0, 1]."""

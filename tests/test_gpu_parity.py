@@ -17,8 +17,9 @@ W = inputs.WORKLOADS
 @pytest.fixture(params=["split", "unit", "split_valu"], autouse=True)
 def launch_path(request):
     """Every test runs with both ways of launching attend + record: split kernels (several workgroups
-    per unit) and the fused one-workgroup-per-unit kernel."""
-    corm.set_default_path({"split": 1, "unit": 2, "split_valu": 3}[request.param])
+    per unit) and the fused one-workgroup-per-unit kernel.  (The tests at the end, of small units, take the default, by
+    which a whole step of theirs is one launch.)"""
+    corm.set_default_path({"split": 1, "unit": 2, "split_valu": 3, "default": 0}[request.param])
     yield request.param
     corm.set_default_path(0)
 
@@ -1081,3 +1082,82 @@ def test_bench_prints_one_json_line_with_the_required_fields(launch_path):
         assert eh[mode]["steps_per_s"] > 0 and 0.2 < eh[mode]["live_fraction_end"] < 0.9, (mode, eh[mode])   # (the first two layers are the dense ones)
         assert eh[mode]["live_fraction_per_head"]["min"] < eh[mode]["live_fraction_per_head"]["max"]
     assert eh["compaction_at_every_step"]["keys_evicted"] > 0 and eh["compaction_at_every_step"]["moved_bytes_per_step"] > 0
+
+
+# ------------------------------------------------------------------ small units: a whole step in one launch (default path)
+
+# every instance of the kernel: rows of fp32 and bf16, d 64 and 128, one, two and four heads a unit
+SMALL = {
+    "f32_d64": (W["tiny_f32"], 2),
+    "f32_d64_g2": (W["tiny_f32"].replace(Hq=4, Hkv=2, P=380, D=30, w=24, r=24), 2),
+    "f32_d64_g4": (W["tiny_f32"].replace(Hq=4, Hkv=1, P=128, D=30, w=16, r=16), 2),
+    "f32_d128": (W["tiny_f32"].replace(d=128, Hq=2, Hkv=2, P=280, D=30, w=24, r=24), 2),
+    "f32_d128_g2": (W["tiny_f32"].replace(d=128, Hq=4, Hkv=2, P=170, D=30, w=16, r=16), 2),
+    "f32_d128_g4": (W["tiny_f32"].replace(d=128, Hq=4, Hkv=1, P=60, D=20, w=8, r=8), 2),
+    "bf16_d64": (W["llama7b_1layer"].replace(B=2, Hq=3, Hkv=3, d=64, P=900, D=40, w=24, r=24), 4),
+    "bf16_d64_g2": (W["gqa_llama3"].replace(B=2, Hq=4, Hkv=2, d=64, P=700, D=40, w=24, r=24), 4),
+    "bf16_d64_g4": (W["gqa_llama3"].replace(B=2, Hq=8, Hkv=2, d=64, P=280, D=40, w=12, r=12), 4),
+    "bf16_d128": (W["llama7b_1layer"].replace(B=2, Hq=4, Hkv=4, P=560, D=40, w=40, r=40), 4),
+    "many_units": (W["tiny_f32"].replace(B=4, Hq=36, Hkv=36, P=260, D=12, w=8, r=8), 10),
+    "r_lt_w": (W["tiny_f32"].replace(P=128, D=40, w=24, r=3), 1),
+    "r_gt_w": (W["tiny_f32"].replace(P=128, D=40, w=8, r=40), 1),
+}
+small_units = pytest.mark.parametrize("launch_path", ["default"], indirect=True)
+
+
+def small_workload(name):
+    wl, every = SMALL[name]
+    assert harness.step_is_one_launch(harness.make_state(wl, DEV))
+    return wl, every
+
+
+@small_units
+@pytest.mark.parametrize("name,ring", [(n, r) for n in SMALL for r in (None, "bit")] +
+                         [("bf16_d64", "f32"), ("bf16_d64_g4", "f32"), ("bf16_d128", "f32")])
+def test_small_units_trajectory(name, ring, launch_path):
+    wl, every = small_workload(name)
+    say("small units", name, ring, wl)
+    rep = harness.run_slaved_trajectory(wl, DEV, check_state_every=every, score_dtype=ring)
+    say("report", name, {k: v for k, v in rep.items() if k != "final_lens"})
+    assert rep["evicted_total"] > 0 or name == "r_gt_w"
+
+
+@small_units
+def test_small_units_at_different_steps_and_thresholds(launch_path):
+    wl = W["tiny_f32"].replace(B=3, P=300, D=40, w=32, r=8)
+    harness.run_slaved_trajectory(wl, DEV, check_state_every=2, seq_offsets=[0, 7, 1000])
+    harness.run_slaved_trajectory(wl, DEV, check_state_every=2, seq_offsets=[0, 7, 1000], score_dtype="bit")
+    test_threshold_extremes(0.0, "none")
+    test_threshold_extremes(1e9, "window")
+    test_w1_r1()
+
+
+@small_units
+@pytest.mark.parametrize("name", ["f32_d64_g2", "bf16_d64_g4", "bf16_d128"])
+def test_small_units_after_a_seeded_prompt_in_dirty_memory(name, launch_path, monkeypatch):
+    """Slots at or above lens, the ring and the workspace start out full of NaN, hits and junk, as in the tests of the other paths."""
+    wl, every = small_workload(name)
+    make = harness.make_state
+
+    def dirty(*a, **kw):
+        st = make(*a, **kw)
+        for rows in (st.K, st.V):
+            rows.fill_(float("nan"))
+        st.pos.fill_(-7), st.last_hit.fill_(12345), st.workspace.fill_(0xAB), st.ring.fill_(1.0)
+        return st
+
+    monkeypatch.setattr(harness, "make_state", dirty)
+    for seed_kernel in (False, True):
+        rep = harness.run_slaved_trajectory(wl, DEV, check_state_every=every, seed_kernel=seed_kernel)
+        assert rep["evicted_total"] > 0
+
+
+@small_units
+@pytest.mark.parametrize("name", ["f32_d64", "f32_d64_g4", "bf16_d64_g2"])
+def test_small_units_without_ring_or_masks_and_under_capture(name, launch_path, monkeypatch):
+    """The tests of the other paths, on small units."""
+    wl, every = small_workload(name)
+    monkeypatch.setitem(TRAJ, "bf16_mha", (wl, every))
+    test_summary_only_state_equals_the_ring_state("bf16_mha", "exact")
+    test_step_without_mask_outputs_equals_the_step_with_them("bf16_mha", "exact")
+    test_decode_step_under_hip_graph_capture()

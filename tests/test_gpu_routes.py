@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2404_15949_amd import corm
+from tests import harness
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -600,18 +601,6 @@ NOT_SMALL = [
 ]
 
 
-def _in_one_launch(st):
-    """Whether a decode step of this layer is one launch: that writes nothing to the workspace, the launches of the split path do."""
-    other = corm.LayerState(st.B, st.Hq, st.Hkv, st.d, st.Lcap, st.Tcap, st.w, st.r, "f32" if st.dtype == torch.float32 else "bf16",
-                            device=DEV, want_ring=False)
-    other.workspace.fill_(0x5a)
-    q, k = (torch.zeros(st.B, h, st.d, dtype=st.dtype, device=DEV) for h in (st.Hq, st.Hkv))
-    one = torch.ones(st.B, dtype=torch.int32, device=DEV)
-    other.step(q, k, k, one, one)
-    torch.cuda.synchronize()
-    return bool((other.workspace == 0x5a).all())
-
-
 def _small_states(case, n):
     """n layers in the same state (units that are empty, full or hold an invalid length, a position without a column), and a
     generator of steps: (q, k, v, t, t_first), steps at which the window is full or not, one of them without a column."""
@@ -665,7 +654,7 @@ def test_small_units_in_one_launch_equal_the_split_launches(case, poison):
     """A step of small units in one launch against attend, record and compact: the same bits in the cache, the decisions, the
     survivors, out and the ring, with finite keys and with one that is not in every other unit."""
     (a, b), steps = _small_states(case, 2)
-    assert _in_one_launch(a)
+    assert harness.step_is_one_launch(a)
     if poison is not None:
         for st in (a, b):
             st.K[0, ::2, st.Lcap // 3, 5] = poison
@@ -711,7 +700,7 @@ def test_small_units_step_like_the_calls_that_do_a_part_of_it(case):
 
 @pytest.mark.parametrize("dtype,G,Hkv,d,Lcap", NOT_SMALL)
 def test_what_is_not_small_takes_the_launches_of_its_path(dtype, G, Hkv, d, Lcap):
-    assert not _in_one_launch(corm.LayerState(2, G * Hkv, Hkv, d, Lcap, Lcap + 8, 4, 3, dtype, device=DEV, want_ring=False))
+    assert not harness.step_is_one_launch(corm.LayerState(2, G * Hkv, Hkv, d, Lcap, Lcap + 8, 4, 3, dtype, device=DEV, want_ring=False))
 
 
 @pytest.mark.parametrize("case", [0, 4, 6])
