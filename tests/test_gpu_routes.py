@@ -420,23 +420,25 @@ def test_seed_in_a_ring_beyond_32_bit_offsets(ring, Tcap, t_last):
 
 # kv dtype, G, Hkv, d, P, m, scaled logit of the keys (log2) in the first and in the second half of the prompt
 SUM_RANGES = [
-    ("bf16", 1, 2, 128, 700, 64, 0, 0),          # few workgroups: a query tile per wave, the keys in segments
-    ("bf16", 1, 2, 128, 700, 64, 150, 150),      # sums beyond 2^100,
-    ("bf16", 1, 2, 64, 700, 64, -150, -150),     # below 2^-60,
-    ("bf16", 2, 2, 128, 1300, 40, -150, 150),    # and both in different segments
+    ("bf16", 1, 2, 128, 700, 64, 0, 0),          # few units: a query tile per wave, the keys in segments
+    ("bf16", 1, 2, 128, 700, 64, 150, 150),      # references far from 0,
+    ("bf16", 1, 2, 64, 700, 64, -150, -150),
+    ("bf16", 2, 2, 128, 1300, 40, -150, 150),    # different ones in different segments
     ("bf16", 4, 2, 64, 1300, 33, 150, 3),
-    ("bf16", 1, 300, 128, 530, 130, -90, 0),     # many units: four query tiles per wave, one segment
+    ("bf16", 1, 300, 128, 530, 130, -90, 0),     # more units: four query tiles per wave, two segments
     ("bf16", 1, 300, 64, 530, 70, 0, 0),
     ("f32", 2, 2, 64, 1300, 50, -150, 0),
     ("f32", 1, 2, 128, 700, 90, 150, 150),       # key blocks of 128
     ("f32", 1, 300, 128, 300, 70, 0, 120),
+    ("bf16", 1, 600, 128, 530, 130, -150, 150),  # four query tiles per wave, one segment: the reference rises within it,
+    ("bf16", 1, 600, 64, 530, 200, 150, -150),   # or stays while the terms vanish
 ]
 
 
 @pytest.mark.parametrize("case", range(len(SUM_RANGES)))
 def test_seed_sums_over_the_range_of_the_logits(case):
-    """The sum of a row is taken against a fixed reference where it stays in range and against the row's maximum where it does not:
-    scores against softmax in 64 bits.  Keys and queries are nearly constant vectors, so the d products of a logit x all have
+    """The sum of a row is taken against a reference that follows the logits (test_seed_sums_that_the_reference_cannot_follow has
+    the rows where it cannot): scores against softmax in 64 bits.  Keys and queries are nearly constant vectors, so the d products of a logit x all have
     its sign: summed in fp32 in any order they carry at most d 2^-24 |x|, the few operations after them 8 2^-24 |x|, and a
     score is e to that."""
     dtype, G, Hkv, d, P, m, lo, hi = SUM_RANGES[case]
