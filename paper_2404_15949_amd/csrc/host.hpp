@@ -466,11 +466,10 @@ void seed_segments(const corm_desc* d, const LaunchCtx& c, int m, long long key_
 // Pass 1: query tiles per wave (max_qw, or 1) and how many workgroups share the keys of a query block (segments of whole
 // key blocks; the partials have room for one per key block).  A launch takes its rounds over the chip (three workgroups per
 // compute unit by registers, of the small ones four by LDS, which share it badly) times a segment's key tiles by the wave's query tiles and a fixed part
-// (queries, first keys, the end).  Whole calls, us, one query tile and four per wave, each with its best number of segments: 512 heads x
-// 1024 queries x 4096 keys 1841, 1600; 32 heads 134, 122; 8 heads x 700 x 5000 59, 59; 4 heads x 256 x 900 27, 31; 64 heads x 48 x
-// 20000 213, 232.  Unsplit the last three take 94, 33 and 407.
+// (queries, first keys, the end).  Whole calls, us, one query tile and four per wave, each with its best number of segments, the rule's
+// choice last: 512 heads x 1024 queries x 4096 keys 1892, 1666: 1671; 32 heads 147, 139: 139; 8 heads x 700 x 5000 66, 70: 65; 4 heads x
+// 256 x 900 28, 36: 28; 64 heads x 48 x 20000 235, 252: 234.  Unsplit the last three take 103, 35 and 412.
 constexpr double STATS_FIXED = 24., STATS_TILE = 1.5;
-template <int ROWB>
 int stats_segments(const corm_desc* d, const LaunchCtx& c, const WorkspaceLayout& wl, int max_qw, PrefillArgs& a) {
   const int ntt = (a.m + 15) / 16 * (d->Hq / d->Hkv);
   const long long units = d->B * d->Hkv;
@@ -495,8 +494,8 @@ int stats_segments(const corm_desc* d, const LaunchCtx& c, const WorkspaceLayout
 template <typename DT, int D>
 int launch_prefill_dt(const corm_desc* d, const LaunchCtx& c, const WorkspaceLayout& wl, PrefillArgs& a, dim3 grid,
                       dim3 mgrid, hipStream_t s) {
-  constexpr int MAX_QW = std::is_same<DT, F32>::value ? 1 : stats_qw<D * DT::ESZ>();
-  const int qw = stats_segments<D * DT::ESZ>(d, c, wl, MAX_QW, a);
+  constexpr int MAX_QW = stats_qw<DT>();
+  const int qw = stats_segments(d, c, wl, MAX_QW, a);
   const long long wgs = (long long)PREFILL_XCDS * ((a.units + PREFILL_XCDS - 1) / PREFILL_XCDS) * a.nqb * a.nks;
   if (wgs > 2147483647LL) return CORM_EUNSUPPORTED;
   if (qw == MAX_QW) hipLaunchKernelGGL((corm_prefill_stats_kernel<DT, D, MAX_QW>), dim3((unsigned)wgs), dim3(WG), 0, s, a);

@@ -90,7 +90,7 @@ __device__ __forceinline__ uint32_t shift_in_sign(uint32_t x, float t) {
 // What the ring holds: which form of Def. 3.1 pass 2 evaluates (an instance each).
 enum { SEED_BF16 = 0, SEED_F32 = 1, SEED_BITS = 2 };
 
-// Per query, for pass 2: x = max, y = 1/sum and, so that pass 2 neither unpacks what it stores nor forms scores
+// Per query, for pass 2: x = reference, y = 1/sum (z, the sum of exp2(logit - reference)) and, so that pass 2 neither unpacks what it stores nor forms scores
 // that it does not store,
 //   score rings   z = the smallest fp32 score whose stored value reaches thr.  bf16: rounding to nearest even is
 //                 monotone, so "stored >= thr" is "score >= z" with z the midpoint below the smallest bf16 >= thr
@@ -101,7 +101,10 @@ enum { SEED_BF16 = 0, SEED_F32 = 1, SEED_BITS = 2 };
 //                 below 2e-6 of the terms), so the decisions are bit for bit those of the score.
 //                 A query without such a band has the sign of y set instead and is decided by the score
 //                 throughout: thresholds 0 or near the ends of the fp32 range, and rows with a logit that is not finite
-//                 (their max or sum is not a finite number either).  There the sign of a difference may be that of a NaN.
+//                 (their reference or sum is not a finite number either).  There the sign of a difference may be that of a NaN.
+// The reference is near the row's maximum, so that no term of the sum overflows and those that make it up do not vanish: at most
+// 1/2 above it, and at most log2(STATS_JUMP times the key tiles looked at together) below, in log2 units; it is the maximum where the
+// reference could not follow the logits.
 __device__ __forceinline__ float4 prefill_query_stats(const PrefillArgs& a, float ms, float z, float thr) {
   float4 s = make_float4(ms, z > 0.f ? 1.0f / z : 0.f, thr, 0.f);
   if (a.ring_bits) {
@@ -141,9 +144,11 @@ struct PrefillGeom {
 // the terms that make up a sum come from small differences.  A workgroup with a lane whose reference could not be set, or whose
 // sum is not finite, does the loop again, first for the maxima and then for the sums against them.
 // Bound by the products, at the rate the card's power leaves (with the tail dropped 480 us for 512 heads x 1024 queries x 4096 keys:
-// 1.0 PFLOP/s; a large library product 1.15), and by what of the tail does not fit beside them.  Key-major with a maximum per
-// tile, as before, 768 us in a row of runs, now 697 (bf16), 1291 -> 1094 for 512 x 1024 x 8192; the merge 22 -> 7 us, since a
-// row has a partial per segment and no longer one per 256 keys.  A sum against the fixed reference 0 takes 640, but its
+// 1.0 PFLOP/s; a large library product 1.15), and by what of the tail does not fit beside them.  Inside whole calls, key-major with
+// a maximum per tile, as before, and now, traced in turn: 600 to 616 us, 588 to 596 (bf16), 512 x 1024 x 8192 1170, 1041; the merge
+// 23 -> 6 and 40 -> 7 us, since a row has a partial per segment and no longer one per 256 keys.  (578 and 1025 us with one register for
+// the sum of a row and lanes that are not asked for themselves: wrong sums for logits of 10^6, low bits lost on long rows.)
+// Tried, as kernels alone in a row of runs, where key-major takes 768 and this one took 697: against the fixed reference 0 640, but its
 // terms carry the rounding of whole logits (fp32 ring 8.3e-7 from 64 bits, 5.6e-7 as it is); a whole block done again in
 // place of a tile 729; 32 x 32 tiles at two waves per SIMD 686 and 702, 128 queries per wave 709 to 764 (all against the reference 0).
 
@@ -156,16 +161,15 @@ constexpr float STATS_JUMP = 16.f;
 // such keys, 32768: 0.9e-7 | 3.3e-7 | 1.6e-7.
 constexpr int STATS_FOLD = 4;
 
-// QW query tiles per wave: as many as the registers of three waves per SIMD hold, so that a key tile read from LDS serves as many
-// products as it can; one where the launch is short of workgroups, and with fp32, whose products take long enough for any
-// LDS traffic (stats_segments).
-template <int ROWB>
-constexpr int stats_qw() { return ROWB <= 256 ? 4 : 2; }
+// QW query tiles per wave.  bf16: as many as the registers of three waves per SIMD hold, so that a key tile read from LDS serves as
+// many products as it can; one where the launch is short of workgroups (stats_segments).  fp32: one, its products take long
+// enough for any LDS traffic.
+template <typename DT>
+constexpr int stats_qw() { return std::is_same<DT, F32>::value ? 1 : 4; }
 
 template <int ROWB, int QW>
 struct StatsGeom {
   static constexpr int NCH = ROWB / 64;
-  static constexpr int QTWG = WAVES * QW;          // query tiles per workgroup
   static constexpr int KBLK = ROWB <= 256 ? 64 : 32;   // keys staged in LDS at a time
   static constexpr int KT = KBLK / 16;
   static constexpr int NT = QW >= KT ? 1 : KT / QW;    // key tiles worked on together: independent chains of products
