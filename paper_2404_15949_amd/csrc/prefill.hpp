@@ -81,6 +81,23 @@ __device__ __forceinline__ float prefill_score(float d, float scale_log2, float 
   return fast_exp2(fmaf(d, scale_log2, -ms)) * fabsf(inv);   // (its sign: see prefill_query_stats)
 }
 
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
+
+// Two 16-bit integers in a word: all ones in the half where x > limit.  (In assembly: as a
+// comparison of vectors the compiler takes it apart into two compares and two selects.)
+__device__ __forceinline__ uint32_t above16x2(uint32_t x, uint32_t limit) {
+  uint32_t m;
+  asm("v_pk_sub_i16 %0, %1, %2 clamp\n\tv_pk_ashrrev_i16 %0, 15, %0 op_sel_hi:[0,1]" : "=&v"(m) : "v"(limit), "v"(x));
+  return m;
+}
+
+// the least of near, |a| and |b| (those that are numbers)
+__device__ __forceinline__ float least_abs(float near, float a, float b) {
+  asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(near) : "v"(a), "v"(b));
+  return near;
+}
+
 // (x << 1) | the sign of t, in one instruction that touches no scalar register: a compare would put its result there,
 // and every reader of it waits
 __device__ __forceinline__ uint32_t shift_in_sign(uint32_t x, float t) {
@@ -94,14 +111,16 @@ enum { SEED_BF16 = 0, SEED_F32 = 1, SEED_BITS = 2 };
 // that it does not store,
 //   score rings   z = the smallest fp32 score whose stored value reaches thr.  bf16: rounding to nearest even is
 //                 monotone, so "stored >= thr" is "score >= z" with z the midpoint below the smallest bf16 >= thr
-//                 (or the next fp32, where that midpoint rounds down).  fp32: z = thr.
-//   boolean ring  (z, w]: raw logits above w are important, those up to z are not, and only those between
+//                 (or the next fp32, where that midpoint rounds down).  fp32: z = thr.  bf16, w: that smallest bf16 minus one
+//                 (as an integer: for scores that are numbers the order is the same) in both halves of a word, for whole blocks.
+//                 A row with a logit that is not finite (its reference or sum is not a finite number either), in which scores may
+//                 be no numbers, has the sign of y set and is decided by z throughout.
+//   boolean ring  raw logits above z + w are important, those below z - w are not, and only those between
 //                 need the score itself.  The band is the threshold in the logit domain -+ a bound on every
-//                 rounding between a logit and its score (products, fma, exp2, 1/sum, the logarithms here: together
+//                 rounding between a logit and its score (products, fma, exp2, 1/sum, the logarithms and z -+ w here: together
 //                 below 2e-6 of the terms), so the decisions are bit for bit those of the score.
-//                 A query without such a band has the sign of y set instead and is decided by the score
-//                 throughout: thresholds 0 or near the ends of the fp32 range, and rows with a logit that is not finite
-//                 (their reference or sum is not a finite number either).  There the sign of a difference may be that of a NaN.
+//                 A query without such a band has w = infinity and is decided by the score
+//                 throughout: thresholds 0 or near the ends of the fp32 range, and rows with a logit that is not finite.
 // The reference is near the row's maximum, so that no term of the sum overflows and those that make it up do not vanish: at most
 // 1/2 above it, and at most log2(STATS_JUMP times the key tiles looked at together) below, in log2 units; it is the maximum where the
 // reference could not follow the logits.
@@ -110,12 +129,17 @@ __device__ __forceinline__ float4 prefill_query_stats(const PrefillArgs& a, floa
   if (a.ring_bits) {
     const float lt = log2f(thr), lz = log2f(z);
     const float at = ms + lt + lz, pad = 1e-5f + 2e-6f * (fabsf(ms) + fabsf(lt) + fabsf(lz));
-    s.z = (at - pad) / a.scale_log2;
-    s.w = (at + pad) / a.scale_log2;
-    if (!(lt + lz > -100.f) || !(fabsf(s.z) < 1e30f) || !(fabsf(s.w) < 1e30f)) s.y = -s.y;
+    s.z = at / a.scale_log2;
+    s.w = 1.0001f * (pad / a.scale_log2);
+    if (!(lt + lz > -100.f) || !(fabsf(s.z) < 1e30f) || !(s.w < 1e30f)) s = make_float4(s.x, s.y, 0.f, __builtin_inff());
   } else if (a.ring_bf16) {
     const uint32_t up = (__float_as_uint(thr) + 0xffffu) >> 16;   // the smallest bf16 >= thr (thr >= 0)
     s.z = up ? __uint_as_float(((up - 1u) << 16) + 0x8000u + (up & 1u)) : 0.f;
+    s.w = __uint_as_float(((up - 1u) & 0xffffu) * 0x10001u);
+    if (!(fabsf(ms) < __builtin_inff()) || !(z < __builtin_inff())) {
+      s.y = -s.y;
+      s.w = __uint_as_float(0x7fff7fffu);   // (nothing is above)
+    }
   }
   return s;
 }
@@ -464,7 +488,8 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
 
   // One-dimensional grid of 8 * ceil(units / 8) * nkb * nseg workgroups.  Workgroups are dealt round-robin to the 8
   // XCDs, so id % 8 names the XCD; each XCD takes a contiguous range of units and runs the key blocks of a unit
-  // one after the other: they all read the same tail queries, which then stay in that XCD's L2.
+  // one after the other: they all read the same tail queries, which then stay in that XCD's L2.  (As many workgroups as the chip
+  // holds, which take the blocks from a queue per XCD and then from the others': 1843 -> 1824 us, not kept.)
   const int per_xcd = (a.units + PREFILL_XCDS - 1) / PREFILL_XCDS;
   const int li = (int)(blockIdx.x / PREFILL_XCDS);
   const int seg = li % a.nseg, lk = li / a.nseg;
@@ -488,11 +513,14 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   }
   const int s0 = (tau0 - 1) % a.w;   // ring slot of tail query 0
 
+  constexpr int STB = 4;   // (one behind is still read from when the next is staged)
   __shared__ __attribute__((aligned(16))) char sh_q[2][QBLK * QROW];     // query blocks, double buffered
-  __shared__ __attribute__((aligned(16))) float4 sh_st[2][QBLK];   // prefill_query_stats per query
+  __shared__ __attribute__((aligned(16))) float4 sh_st[STB][QBLK];   // prefill_query_stats per query
   __shared__ __attribute__((aligned(16))) int32_t sh_pos[KB];            // positions of the workgroup's keys
+
   // Pass 2, bf16 ring: a wave's tile of stored scores is turned through LDS so that every query's consecutive
   // positions leave as one piece of its ring row (16 bytes per lane).  Rows are padded by 16 bytes.
+  // (Stored straight from the lanes that hold them, a lane's 16 bytes in pieces of 64: the whole call 1890 -> 1950 to 2010 us.)
   constexpr int TROW = WKEYS + 8;
   constexpr bool TURN = MODE == SEED_BF16;
   __shared__ __attribute__((aligned(16))) uint16_t sh_t[TURN ? WAVES : 1][TURN ? 16 : 1][TURN ? TROW : 1];
@@ -520,7 +548,7 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   if (lane < WKEYS) sh_pos[wv * WKEYS + lane] = my_pos;
   // every slot of the wave holds a key; its positions are consecutive; the first and the last of them
   const bool wave_whole = __all(lane >= WKEYS || my_pos != NEVER);
-  const int pos_w0 = __builtin_amdgcn_readfirstlane(my_pos), pos_wlast = __shfl(my_pos, WKEYS - 1);
+  const int pos_w0 = __builtin_amdgcn_readfirstlane(my_pos), pos_wlast = __builtin_amdgcn_readlane(my_pos, WKEYS - 1);
   const bool wave_run = wave_whole && __all(lane >= WKEYS || my_pos == pos_w0 + lane);
   // Pass 2 stores whole pieces of a row where the wave's keys are consecutive and every piece is aligned (rows of
   // the ring then start at multiples of a piece as well).
@@ -533,6 +561,8 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   const int pfirst = posb[key_blk];
   const int jt_first = max(pfirst - tau0 + 1, 0) / 16;
 
+  const int jt_wave = pos_w0 == NEVER ? jt_first : max(pos_w0 - tau0 + 1, 0) / 16;   // the same of the wave's first key
+
   const int ntt = ((a.m + 15) / 16) << lgG;                    // query tiles of the group
   const int blk_end = min((seg + 1) * a.seg_blocks, (ntt + QT - 1) / QT);
   const int blk_vis = min((jt_first << lgG) / QT, blk_end);    // first block with a query that sees a key
@@ -544,36 +574,51 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   // Queries reach the waves through LDS, QBLK at a time: the block after the current one is in flight
   // (registers) while the current one is worked on, so the loop never waits on a load it has just
   // issued.  Two LDS buffers, one barrier per block.  Loads and stores share one in-order counter: the registers
-  // go to LDS at the end of each of the two paths through a block, where the number of ring stores issued
-  // behind the loads is known to the compiler -- after the join it would have to wait for all of them.
+  // go to LDS where the number of ring stores issued behind the loads is known to the compiler.
   u32x4_t qr[QLOADS];
   float4 str = make_float4(0.f, 0.f, 0.f, 0.f);
+  // A block's tiles start at a multiple of QT: tile x of the block is head h0 + x % G, 16 queries jt0 + x / G (G <= QT) or, for
+  // larger groups, head h0 + x.  What hangs on x alone is formed here, so that a block costs few scalar instructions.
+  constexpr int RPP = WG * 16 / ROWB;   // rows per pass of the workgroup
+  const int half = RPP == 32 ? __builtin_amdgcn_readfirstlane(tid >> 7) : 0;
+  uint32_t q_off[QLOADS], q_row[QLOADS];   // bytes from the block's first query, and of queries of its head before it
+#pragma unroll
+  for (int i = 0; i < QLOADS; ++i) {
+    const int x = i * RPP / 16 + half;
+    q_row[i] = (uint32_t)(x >> lgG) * 16u * ROWB;
+    q_off[i] = (uint32_t)(x & (G - 1)) * (uint32_t)a.m * ROWB + q_row[i];
+  }
+  const int st_x = (tid % QBLK) / 16;   // (every wave the same QBLK queries: no branch, whose join would cost the exact wait count)
+  const float4* stats_lane = stats + (size_t)(st_x & (G - 1)) * a.w + (st_x >> lgG) * 16 + (tid & 15);
   auto fetch = [&](int blk, u32x4_t (&qr)[QLOADS], float4& str) __attribute__((always_inline)) {
-    constexpr int RPP = WG * 16 / ROWB;   // rows per pass of the workgroup
-    const int half = __builtin_amdgcn_readfirstlane(tid >> 7);
+    const int h0 = (blk * QT) & (G - 1), j0 = ((blk * QT) >> lgG) * 16;
+    const char* q0 = qg + ((size_t)h0 * a.m + j0) * ROWB;
+    const uint32_t left = (uint32_t)(a.m - j0) * ROWB;
 #pragma unroll
     for (int i = 0; i < QLOADS; ++i) {
-      const int tt = min(blk * QT + (i * RPP) / 16 + (RPP == 32 ? half : 0), ntt - 1);   // (uniform over the wave)
-      const int j = min((tt >> lgG) * 16 + ((i * RPP + tid / (ROWB / 16)) & 15), a.m - 1);   // (past the last: masked)
-      const char* q = qg + (size_t)(tt & (G - 1)) * a.m * ROWB;
-      qr[i] = *reinterpret_cast<const u32x4_t*>(q + (uint32_t)j * ROWB + (tid * 16) % ROWB);
+      // (uniform over the wave) a descriptor that ends with the head's last query: zeros past it, which are masked
+      const __amdgpu_buffer_rsrc_t rq = make_rsrc(q0 + q_off[i], (uint32_t)max((int)(left - q_row[i]), 0));
+      qr[i] = __builtin_amdgcn_raw_buffer_load_b128(rq, (i * RPP * ROWB + tid * 16) % (16 * ROWB), 0, 0);
     }
-    // (every wave the same QBLK queries: no branch, whose join would cost the exact wait count)
-    const int tt = min(blk * QT + (tid % QBLK) / 16, ntt - 1);
-    const int j = min((tt >> lgG) * 16 + (tid & 15), a.m - 1);
-    str = stats[(size_t)(tt & (G - 1)) * a.w + j];
+    str = stats_lane[(size_t)h0 * a.w + j0];   // (past the last query: up to 63 more, which the workspace holds)
   };
-  auto mma_tile = [&](int cur, int ti, f32x4_t (&d)[T]) __attribute__((always_inline)) {
-    uint4 qb[NCH];
+  auto read_tile = [&](int cur, int ti, uint4 (&qb)[NCH]) __attribute__((always_inline)) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
       qb[c] = *reinterpret_cast<const uint4*>(&sh_q[cur][(ti * 16 + n) * QROW + c * 64 + 16 * lg]);
+  };
+  auto mma = [&](const uint4 (&qb)[NCH], f32x4_t (&d)[T]) __attribute__((always_inline)) {
 #pragma unroll
     for (int tl = 0; tl < T; ++tl) d[tl] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
 #pragma unroll
       for (int tl = 0; tl < T; ++tl) d[tl] = PrefillMma<DT>::mma(ka[tl][c], qb[c], d[tl]);
+  };
+  auto mma_tile = [&](int cur, int ti, f32x4_t (&d)[T]) __attribute__((always_inline)) {
+    uint4 qb[NCH];
+    read_tile(cur, ti, qb);
+    mma(qb, d);
   };
   // Fast blocks store through a buffer descriptor with 32-bit offsets: of one head's ring, or (FAR; as an instance of its
   // own, since the few scalar instructions per tile cost the others 1 to 3 %) of the rows of a tile's 16 queries, which lie
@@ -587,176 +632,241 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
     const int slot = s0 + j;
     return (uint32_t)(slot >= a.w ? slot - a.w : slot);
   };
-  auto rows_rsrc = [&](int tt) __attribute__((always_inline)) {
-    char* p = reinterpret_cast<char*>(a.ring);
-    const uint64_t at = (uint64_t)(b * a.Hq + hkv * G + (tt & (G - 1))) * head_bytes +
-                        (FAR ? slot_of((tt >> lgG) * 16) * row_bytes64 : 0);
-    return make_rsrc(p ? p + at : p, a.ring ? (FAR ? 16 * row_bytes : (uint32_t)head_bytes) : 0u);
-  };
-  auto row_of = [&](int tt, int j) __attribute__((always_inline)) -> uint32_t {   // row of the descriptor for query j
-    return FAR ? (uint32_t)(j - (tt >> lgG) * 16) : slot_of(j);
-  };
+  const uint64_t ring0 = reinterpret_cast<uint64_t>(a.ring) + (uint64_t)(b * a.Hq + hkv * G) * head_bytes;   // of the group's first head
+  const uint32_t ring_len = a.ring ? (FAR ? 16 * row_bytes : (uint32_t)head_bytes) : 0u;
   auto ring_row = [&](int g, int j) __attribute__((always_inline)) -> size_t {
     return (size_t)(b * a.Hq + hkv * G + g) * a.w + slot_of(j);
   };
 
-  int hm[T][4];   // pass 2: latest step at which one of the group's queries found the key important
+  // The latest hit of every key of the lane, over the queries n of every tile: fp32 ring, the step; else 1 + the number of the 16
+  // queries (0: none), two keys to a word, in the order of the lane's keys.
+  constexpr bool PACKED = MODE != SEED_F32;
+  int hm[PACKED ? 1 : T][4];
+  uint32_t hm2[PACKED ? 2 * T : 1];
 #pragma unroll
-  for (int tl = 0; tl < T; ++tl)
+  for (int tl = 0; tl < (PACKED ? 1 : T); ++tl)
 #pragma unroll
     for (int r = 0; r < 4; ++r) hm[tl][r] = 0;
-  // Boolean ring: fast blocks only shift a bit per key and tile into a history; every 32 tiles, or where their run ends,
-  // the newest set bit of each becomes a step.  (With score rings, whose tail is longer, the registers cost more than
-  // the compares: 1.22 -> 1.24 ms.)
+#pragma unroll
+  for (int i = 0; i < (PACKED ? 2 * T : 1); ++i) hm2[i] = 0u;
+  auto hit_at = [&](int i, int jt) __attribute__((always_inline)) {   // key i of the lane, 16 queries jt
+    hm2[PACKED ? i >> 1 : 0] = i & 1 ? (hm2[PACKED ? i >> 1 : 0] & 0xffffu) | ((uint32_t)(jt + 1) << 16)
+                                     : (hm2[PACKED ? i >> 1 : 0] & 0xffff0000u) | (uint32_t)(jt + 1);
+  };
+  auto raise = [&](int i, uint32_t at0, uint32_t at1) __attribute__((always_inline)) {   // word i, to at least these
+    uint32_t& h = hm2[PACKED ? i : 0];
+    h = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, h), __builtin_bit_cast(u16x2_t, at0 | (at1 << 16))));
+  };
+  // Boolean ring: fast blocks collect the latest hits of up to 32 tiles in bit slices: bit i of `seen` says that one found key i
+  // important, bit i of slice k is bit k of the latest such tile's number in the run.  A block adds its tiles together, 10
+  // instructions for four tiles of the lane's 16 keys (a history per key: 64).  After 32 tiles, or where their run ends, they join the above.
   constexpr bool HIST = MODE == SEED_BITS;
-  uint32_t hist[T][4];
-#pragma unroll
-  for (int tl = 0; tl < T; ++tl)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) hist[tl][r] = 0u;
-  int hist_n = 0, hist_tt = 0;   // tiles in it, the newest one
+  constexpr int SLICES = 5;
+  uint32_t seen_run = 0u, slice[SLICES] = {};
+  int run_n = 0, run_tt = 0;   // tiles in the run, its first
   auto settle = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int tl = 0; tl < T; ++tl)
+    for (int i = 0; i < 4 * T; i += 2) {
+      uint32_t at[2];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int back = __ffs((int)hist[tl][r]) - 1;
-        const int tau = tau0 + ((hist_tt - back) >> lgG) * 16 + n;
-        if (hist[tl][r]) hm[tl][r] = max(hm[tl][r], tau);
-        hist[tl][r] = 0u;
+      for (int x = 0; x < 2; ++x) {
+        int k = 0;
+#pragma unroll
+        for (int b = 0; b < SLICES; ++b) k |= (int)((slice[b] >> (i + x)) & 1u) << b;
+        at[x] = (seen_run >> (i + x)) & 1u ? (uint32_t)((run_tt + k) >> lgG) + 1u : 0u;
       }
-    hist_n = 0;
+      raise(i >> 1, at[0], at[1]);   // (a general block after the run may have found a later one)
+    }
+    seen_run = 0u;
+    run_n = 0;
   };
 
-  auto stage = [&](int buf, const u32x4_t (&qr)[QLOADS], const float4& str) __attribute__((always_inline)) {
+  auto stage = [&](int blk, const u32x4_t (&qr)[QLOADS], const float4& str) __attribute__((always_inline)) {
+    const int buf = blk & 1;
 #pragma unroll
     for (int i = 0; i < QLOADS; ++i) {
       const int o = (i * WG + tid) * 16;   // row o / ROWB, column o % ROWB
       *reinterpret_cast<u32x4_t*>(&sh_q[buf][(o / ROWB) * QROW + (o % ROWB)]) = qr[i];
     }
-    sh_st[buf][tid % QBLK] = str;
+    sh_st[blk % STB][tid % QBLK] = str;
   };
   if (blk_beg < blk_end) {
     fetch(blk_beg, qr, str);
-    stage(blk_beg & 1, qr, str);
+    stage(blk_beg, qr, str);
+    __syncthreads();
   }
-  for (int blk = blk_beg; blk < blk_end; ++blk) {
-    const int cur = blk & 1;
-    __syncthreads();   // block blk is staged; nobody reads the other buffer any more
-    fetch(min(blk + 1, blk_end - 1), qr, str);
+  // Fast blocks (uniform over the wave): every query of the block exists and sees every key of the wave, and whole pieces can be
+  // stored: straight-line code, the next tile's MFMAs under this tile's tail.  They follow one another; with FAR, but for a block
+  // whose rows go on at the ring's start.
+  const int fast_beg = !rows_ok || pos_wmax == NEVER || (FAR && 16 * row_bytes64 > DEAD_OFFSET)
+                           ? blk_end
+                           : ((((max(pos_wmax - tau0 + 1, 0) + 15) / 16) << lgG) + QT - 1) / QT;
+  const int fast_end = min(blk_end, ((a.m / 16) << lgG) / QT);
+  auto is_fast = [&](int blk) __attribute__((always_inline)) {
     const int tt0 = blk * QT;
-
-    // (uniform over the wave) every query of the block exists and sees every key of the wave, and pass 2 can
-    // store whole pieces: straight-line code, the next tile's MFMAs under this tile's tail
-    const bool fast = tt0 + QT <= ntt && ((tt0 + QT - 1) >> lgG) * 16 + 15 < a.m &&
-                      pos_wmax <= tau0 + (tt0 >> lgG) * 16 - 1 && rows_ok &&
-                      (!FAR || (16 * row_bytes64 <= DEAD_OFFSET &&
-                                slot_of((tt0 >> lgG) * 16) <= slot_of(((tt0 + QT - 1) >> lgG) * 16 + 15)));
-    if (fast) {
-      if (HIST) {
-        if (hist_n + QT > 32 || (hist_n && hist_tt + 1 != tt0)) settle();
-        hist_n += QT;
-        hist_tt = tt0 + QT - 1;
-      }
-      f32x4_t dn[T];
-      mma_tile(cur, 0, dn);
-#pragma unroll
-      for (int ti = 0; ti < QT; ++ti) {
-        f32x4_t d[T];
-#pragma unroll
-        for (int tl = 0; tl < T; ++tl) d[tl] = dn[tl];
-        if (ti + 1 < QT) mma_tile(cur, ti + 1, dn);
-        const int tt = tt0 + ti, j = (tt >> lgG) * 16 + n, tau = tau0 + j;
-        if (MODE == SEED_BITS) {
-          const float4 st = sh_st[cur][ti * 16 + n];
-          uint32_t unsure = __float_as_uint(st.y), hbits = 0u;   // (the sign: this query has no band)
-#pragma unroll
-          for (int i = 4 * T - 1; i >= 0; --i) {   // key i of the lane's run: row i % 4 of key tile i / 4
-            const float above = st.w - d[i >> 2][i & 3], below = st.z - d[i >> 2][i & 3];
-            hist[i >> 2][i & 3] = shift_in_sign(hist[i >> 2][i & 3], above);
-            hbits = shift_in_sign(hbits, above);
-            unsure |= __float_as_uint(above) ^ __float_as_uint(below);
-          }
-          if (__any((int)unsure < 0)) {   // (uniform, rare) what lies in the band is decided by the score
-            const float thr = importance_threshold(a.thr_scale, tau);
-            if (__float_as_int(st.y) < 0) hbits = 0u;
+    return blk >= fast_beg && blk < fast_end &&
+           (!FAR || slot_of((tt0 >> lgG) * 16) <= slot_of(((tt0 + QT - 1) >> lgG) * 16 + 15));
+  };
+  // bf16 ring, a block with rows whose scores may be no numbers (rare): their hits by the scores themselves
+  auto numberless = [&](int blk) __attribute__((always_inline)) {
 #pragma unroll 1
-            for (int tl = 0; tl < T; ++tl) {
-              const f32x4_t x = tl == 0 ? d[0] : tl == 1 ? d[1] : tl == 2 ? d[T > 2 ? 2 : 0] : d[T > 2 ? 3 : 0];
+    for (int ti = 0; ti < QT; ++ti) {
+      const float4 st = sh_st[blk % STB][ti * 16 + n];
+      const uint32_t at = (uint32_t)((blk * QT + ti) >> lgG) + 1u;
+      f32x4_t d[T];
+      mma_tile(blk & 1, ti, d);
 #pragma unroll
-              for (int r = 0; r < 4; ++r)
-                hbits |= (prefill_score(x[r], a.scale_log2, st.x, st.y) >= thr ? 1u : 0u) << (4 * tl + r);
-            }
+      for (int i = 0; i < 4 * T; i += 2) {
+        const bool h0 = prefill_score(d[i >> 2][i & 3], a.scale_log2, st.x, st.y) >= st.z;
+        const bool h1 = prefill_score(d[i >> 2][(i & 3) + 1], a.scale_log2, st.x, st.y) >= st.z;
+        if (__float_as_int(st.y) < 0) raise(i >> 1, h0 ? at : 0u, h1 ? at : 0u);
+      }
+    }
+  };
+  uint64_t x_ring[QT];    // of tile x of a block, see fetch: bytes of ring from the block's first head (FAR: and row)
+  uint32_t x_row[QT];
 #pragma unroll
-            for (int i = 0; i < 4 * T; ++i)   // (an instruction each: the low bit replaced)
-              hist[i >> 2][i & 3] = (hist[i >> 2][i & 3] & ~1u) | ((hbits >> i) & 1u);
+  for (int x = 0; x < QT; ++x) {
+    x_row[x] = (uint32_t)(x >> lgG) * 16u * row_bytes;
+    x_ring[x] = (uint64_t)(x & (G - 1)) * head_bytes + (FAR ? (uint64_t)(x >> lgG) * 16u * row_bytes64 : 0);
+  }
+  // A pipeline over the tiles, across blocks: under the tail of a tile run the next one's products (dn), whose queries were
+  // read under the tail before (qn).  So the next block is staged, and the barrier passed, in front of the last but one tile.
+  auto fast_block = [&](int blk, f32x4_t (&dn)[T], uint4 (&qn)[NCH]) __attribute__((always_inline)) {
+    const int cur = blk & 1, tt0 = blk * QT, jt0 = tt0 >> lgG;
+    const uint32_t slot0 = slot_of(jt0 * 16);
+    const uint64_t ring_blk = ring0 + (uint64_t)(tt0 & (G - 1)) * head_bytes + (FAR ? slot0 * row_bytes64 : 0);
+    // Ring offsets of tile x: the lane's row of the 16 and the column in it are in `lane_off`.  (One head's ring: where the rows
+    // reach beyond its end, they go on at its start.  Unsigned: the lower of the two is the one inside.)
+    const uint32_t first_blk = slot0 * row_bytes;
+    auto tile_off = [&](int x, uint32_t lane_off) __attribute__((always_inline)) -> uint32_t {
+      if (FAR) return lane_off;
+      const uint32_t first = first_blk + x_row[x];
+      return min(lane_off + first, lane_off + (first - (uint32_t)head_bytes));
+    };
+    uint32_t hits[QT];   // boolean ring: bit i, the tile's query found key i of the lane important
+    bool flagged = false;
+    if (TURN) flagged = __any(__float_as_int(sh_st[blk % STB][lane % QBLK].y) < 0);
+#pragma unroll
+    for (int ti = 0; ti < QT; ++ti) {
+      f32x4_t d[T];
+#pragma unroll
+      for (int tl = 0; tl < T; ++tl) d[tl] = dn[tl];
+      const int jt = jt0 + (ti >> lgG);
+      const float4 st = sh_st[blk % STB][ti * 16 + n];
+      if (ti == QT - 2) {
+        if (flagged) numberless(blk);
+        stage(blk + 1, qr, str);
+        __syncthreads();
+      }
+      if (ti + 1 < QT || blk + 1 < fast_end) mma(qn, dn);   // (uniform)
+      if (ti + 2 < QT) read_tile(cur, ti + 2, qn);
+      else read_tile(cur ^ 1, ti + 2 - QT, qn);
+      const __amdgpu_buffer_rsrc_t rr = make_rsrc(reinterpret_cast<const char*>(ring_blk + x_ring[ti]), ring_len);
+      if (MODE == SEED_BITS) {
+        uint32_t hbits = 0u;
+        float near = __builtin_inff();
+#pragma unroll
+        for (int i = 4 * T - 1; i >= 0; i -= 2) {   // key i of the lane's run: row i % 4 of key tile i / 4
+          const float x1 = st.z - d[i >> 2][i & 3], x0 = st.z - d[(i - 1) >> 2][(i - 1) & 3];
+          hbits = shift_in_sign(shift_in_sign(hbits, x1), x0);
+          near = least_abs(near, x1, x0);
+        }
+        if (__any(near <= st.w)) {   // (uniform, rare) what lies in the band is decided by the score
+          const float thr = importance_threshold(a.thr_scale, tau0 + jt * 16 + n);
+          hbits = 0u;
+#pragma unroll 1
+          for (int tl = 0; tl < T; ++tl) {
+            const f32x4_t x = tl == 0 ? d[0] : tl == 1 ? d[1] : tl == 2 ? d[T > 2 ? 2 : 0] : d[T > 2 ? 3 : 0];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              hbits |= (prefill_score(x[r], a.scale_log2, st.x, st.y) >= thr ? 1u : 0u) << (4 * tl + r);
           }
-          // the wave owns whole words of every query's row: plain stores
-          const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
-          const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 >> 5) * 4;
-          if (T == 4) {   // 16 keys per lane: two lane groups to a word
-            const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
-            __builtin_amdgcn_raw_buffer_store_b32(sw[0] | (sw[1] << 16), rr, (lg & 1) ? DEAD_OFFSET : at + (lg >> 1) * 4, 0, 0);
-          } else {        // 8 keys per lane: four lane groups to a word
-            const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
-            __builtin_amdgcn_raw_buffer_store_b32(w, rr, lg ? DEAD_OFFSET : at, 0, 0);
-          }
-        } else {
-          const float4 st = sh_st[cur][ti * 16 + n];
-          float pv[T][4];
+        }
+        hits[ti] = hbits;
+        // the wave owns whole words of every query's row: plain stores
+        if (T == 4) {   // 16 keys per lane: two lane groups to a word
+          const auto sw = __builtin_amdgcn_permlane16_swap(hbits, hbits, false, false);
+          const uint32_t at = tile_off(ti, n * row_bytes + (uint32_t)(pos_w0 >> 5) * 4 + (lg >> 1) * 4);
+          __builtin_amdgcn_raw_buffer_store_b32(sw[0] | (sw[1] << 16), rr, (lg & 1) ? DEAD_OFFSET : at, 0, 0);
+        } else {        // 8 keys per lane: four lane groups to a word
+          const uint32_t w = rows_allreduce_or(hbits << (8 * lg));
+          const uint32_t at = tile_off(ti, n * row_bytes + (uint32_t)(pos_w0 >> 5) * 4);
+          __builtin_amdgcn_raw_buffer_store_b32(w, rr, lg ? DEAD_OFFSET : at, 0, 0);
+        }
+      } else {
+        float pv[T][4];
+#pragma unroll
+        for (int tl = 0; tl < T; ++tl)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) pv[tl][r] = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
+        if (MODE == SEED_F32) {
+          const int tau = tau0 + jt * 16 + n;
 #pragma unroll
           for (int tl = 0; tl < T; ++tl)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              pv[tl][r] = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
-              hm[tl][r] = pv[tl][r] >= st.z ? tau : hm[tl][r];
+              hm[PACKED ? 0 : tl][r] = pv[tl][r] >= st.z ? tau : hm[PACKED ? 0 : tl][r];
               // (said to be read here: left alone, the compiler keeps the compares of all tiles of the block in
               // scalar registers, spills those, and selects at the end)
-              asm volatile("" : "+v"(hm[tl][r]));
+              asm volatile("" : "+v"(hm[PACKED ? 0 : tl][r]));
             }
-          const __amdgpu_buffer_rsrc_t rr = rows_rsrc(tt);
-          if (MODE == SEED_F32) {
-            const uint32_t at = row_of(tt, j) * row_bytes + (uint32_t)(pos_w0 + 4 * lg) * 4;
+          const uint32_t at = tile_off(ti, n * row_bytes + (uint32_t)(pos_w0 + 4 * lg) * 4);
 #pragma unroll
-            for (int tl = 0; tl < T; ++tl) {
-              const u32x4_t v = {__float_as_uint(pv[tl][0]), __float_as_uint(pv[tl][1]), __float_as_uint(pv[tl][2]),
-                                 __float_as_uint(pv[tl][3])};
-              __builtin_amdgcn_raw_buffer_store_b128(v, rr, at + tl * 64, 0, 0);
-            }
-          } else {
-            constexpr int PIECES = WKEYS / 8;        // 16-byte pieces of a query's row
-            constexpr int RPS = 64 / PIECES;         // rows per store of the wave
-            uint32_t pk[2 * T];
-#pragma unroll
-            for (int i = 0; i < 2 * T; ++i) pk[i] = pack_bf16x2(pv[i >> 1][2 * (i & 1)], pv[i >> 1][2 * (i & 1) + 1]);
-#pragma unroll
-            for (int h = 0; h < T / 2; ++h)
-              *reinterpret_cast<uint4*>(&sh_t[wv][n][lg * (4 * T) + h * 8]) =
-                  make_uint4(pk[4 * h], pk[4 * h + 1], pk[4 * h + 2], pk[4 * h + 3]);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
-#pragma unroll
-            for (int h = 0; h < 16 / RPS; ++h) {
-              const int qi = h * RPS + lane / PIECES, ch = lane % PIECES;
-              const u32x4_t v = *reinterpret_cast<const u32x4_t*>(&sh_t[wv][qi][ch * 8]);
-              __builtin_amdgcn_raw_buffer_store_b128(
-                  v, rr, row_of(tt, (tt >> lgG) * 16 + qi) * row_bytes + (uint32_t)(pos_w0 + ch * 8) * 2, 0, 2);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          for (int tl = 0; tl < T; ++tl) {
+            const u32x4_t v = {__float_as_uint(pv[tl][0]), __float_as_uint(pv[tl][1]), __float_as_uint(pv[tl][2]),
+                               __float_as_uint(pv[tl][3])};
+            __builtin_amdgcn_raw_buffer_store_b128(v, rr, at + tl * 64, 0, 0);
           }
+        } else {
+          constexpr int PIECES = WKEYS / 8;        // 16-byte pieces of a query's row
+          constexpr int RPS = 64 / PIECES;         // rows per store of the wave
+          uint32_t pk[2 * T];
+#pragma unroll
+          for (int i = 0; i < 2 * T; ++i) {
+            pk[i] = pack_bf16x2(pv[i >> 1][2 * (i & 1)], pv[i >> 1][2 * (i & 1) + 1]);
+            hm2[PACKED ? i : 0] = bit_select(above16x2(pk[i], __float_as_uint(st.w)), (uint32_t)(jt + 1) * 0x10001u,
+                                             hm2[PACKED ? i : 0]);
+          }
+#pragma unroll
+          for (int h = 0; h < T / 2; ++h)
+            *reinterpret_cast<uint4*>(&sh_t[wv][n][lg * (4 * T) + h * 8]) =
+                make_uint4(pk[4 * h], pk[4 * h + 1], pk[4 * h + 2], pk[4 * h + 3]);
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
+#pragma unroll
+          for (int h = 0; h < 16 / RPS; ++h) {
+            const int qi = h * RPS + lane / PIECES, ch = lane % PIECES;
+            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(&sh_t[wv][qi][ch * 8]);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rr, tile_off(ti, qi * row_bytes + (uint32_t)(pos_w0 + ch * 8) * 2), 0, 2);
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
       }
-      stage(cur ^ 1, qr, str);
-      asm volatile("; (keeps the two paths' staging from being merged behind the join)");
-      continue;
     }
-
-    // the general block: queries that see a part of the keys, units with holes, the ends of tails and units
+    if (HIST) {
+      if (run_n + QT > 32 || (run_n && run_tt + run_n != tt0)) settle();
+      if (!run_n) run_tt = tt0;
+      constexpr int LOW = QT == 4 ? 2 : 1;
+      static_assert(QT == 2 || QT == 4, "the latest hit of a block's tiles");
+      uint32_t low[2], any = hits[0] | hits[1];
+      low[0] = QT == 4 ? hits[QT - 1] | (hits[1] & ~hits[QT - 2]) : hits[1];
+      low[1] = QT == 4 ? hits[QT - 2] | hits[QT - 1] : 0u;
+      if (QT == 4) any |= low[1];
+#pragma unroll
+      for (int b = 0; b < SLICES; ++b)
+        slice[b] = bit_select(any, b < LOW ? low[b & 1] : (run_n >> b) & 1 ? ~0u : 0u, slice[b]);
+      seen_run |= any;
+      run_n += QT;
+    }
+  };
+  // the general block: queries that see a part of the keys, units with holes, the ends of tails and units
+  auto general_block = [&](int blk, int tt0) __attribute__((always_inline)) {
 #pragma unroll 1
     for (int ti = 0; ti < QT; ++ti) {
       const int tt = tt0 + ti, jt = tt >> lgG, g = tt & (G - 1);
-      if (tt >= ntt || jt < jt_first || wkey0 >= L) continue;   // (uniform) past the end / no key to be seen
+      if (tt >= ntt || jt < jt_wave || wkey0 >= L) continue;   // (uniform) past the end / no key to be seen
       f32x4_t d[T];
-      mma_tile(cur, ti, d);
+      mma_tile(blk & 1, ti, d);
       const int j = jt * 16 + n;                 // this lane's query
       const int tau = tau0 + j;
       const int vis = j < a.m ? tau - 1 : -1;    // the query sees positions <= vis
@@ -770,7 +880,7 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) seen |= (kp[tl][r] <= vis ? 1u : 0u) << (4 * tl + r);
       }
-      const float4 st = sh_st[cur][ti * 16 + n];
+      const float4 st = sh_st[blk % STB][ti * 16 + n];
       const float thr = MODE == SEED_BITS ? importance_threshold(a.thr_scale, tau) : st.z;
       float pv[T][4];
       uint32_t hbits = 0u;
@@ -782,7 +892,11 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
           const float e = prefill_score(d[tl][r], a.scale_log2, st.x, st.y);
           pv[tl][r] = s ? e : 0.f;
           const bool hit = s && e >= thr;
-          hm[tl][r] = hit ? tau : hm[tl][r];
+          if (PACKED) {
+            if (hit) hit_at(4 * tl + r, jt);
+          } else {
+            hm[PACKED ? 0 : tl][r] = hit ? tau : hm[PACKED ? 0 : tl][r];
+          }
           hbits |= (hit ? 1u : 0u) << (4 * tl + r);
         }
       if (!a.ring) continue;   // summary-only state: nothing is recorded but last_hit
@@ -835,7 +949,26 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
         }
       }
     }
-    stage(cur ^ 1, qr, str);
+  };
+  // Every wave passes the barrier of every block, whichever of the two loops it is in: behind it the next block is staged, and
+  // nobody reads this one any more.  (Loops of their own: where the two kinds of block share one, the compiler takes a block's loads
+  // for unfinished on some way round it and waits for everything, the ring stores of the block before included, at its top.)
+  for (int blk = blk_beg; blk < blk_end;) {
+    for (; blk < blk_end && !is_fast(blk); ++blk) {
+      fetch(min(blk + 1, blk_end - 1), qr, str);
+      general_block(blk, blk * QT);
+      stage(blk + 1, qr, str);
+      __syncthreads();
+    }
+    if (blk >= blk_end) break;
+    f32x4_t dn[T];
+    uint4 qn[NCH];
+    mma_tile(blk & 1, 0, dn);
+    read_tile(blk & 1, 1, qn);
+    for (; blk < blk_end && is_fast(blk); ++blk) {
+      fetch(min(blk + 1, blk_end - 1), qr, str);
+      fast_block(blk, dn, qn);
+    }
   }
 
   if (HIST) settle();
@@ -844,17 +977,19 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   __syncthreads();   // sh_pos of this wave is free
 #pragma unroll
   for (int tl = 0; tl < T; ++tl) {
+    int last[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      int v = hm[tl][r];
+      const int k = (int)((hm2[PACKED ? 2 * tl + (r >> 1) : 0] >> (16 * (r & 1))) & 0xffffu);
+      int v = PACKED ? (k ? tau0 + (k - 1) * 16 + n : 0) : hm[PACKED ? 0 : tl][r];
       v = max(v, __shfl_xor(v, 1));
       v = max(v, __shfl_xor(v, 2));
       v = max(v, __shfl_xor(v, 4));
-      hm[tl][r] = max(v, __shfl_xor(v, 8));
+      last[r] = max(v, __shfl_xor(v, 8));
     }
     if (n == 0)
       *reinterpret_cast<int4*>(&sh_pos[wv * WKEYS + (RUN ? lg * (4 * T) + tl * 4 : tl * 16 + 4 * lg)]) =
-          make_int4(hm[tl][0], hm[tl][1], hm[tl][2], hm[tl][3]);
+          make_int4(last[0], last[1], last[2], last[3]);
   }
   __syncthreads();
   const int key = wkey0 + lane;
@@ -868,14 +1003,12 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   }
 }
 
-// Pass 2 on 256-byte rows takes the registers of two waves per SIMD: four key tiles per wave hold 16 accumulators, 16 of the
-// next tile, 16 latest hits and, by the ring, 16 scores or histories beside the 64 of the keys (205 for bf16 scores, 253 for bits;
-// held to three waves it spills: 1.27 -> 1.76 ms).  fp32 rows of 512 bytes, two key tiles per wave, fit three (153 and 157 with
-// score rings).  It is bound by vector instructions: per tile of 16 queries x 64 keys 16 MFMAs and about 102 (bf16
-// scores), 108 to 114 (bits) others.  Kernel times: bf16 scores 1.39 -> 1.20 ms (ring written at 3.5 TB/s);
-// bits, 512 heads x 1024 x 8192, 3.22 -> 1.62 ms (one wave per SIMD and a score per pair before; 2.04 with compares
-// whose results went through scalar registers); fp32, 16 units of 2000 keys, 74 -> 39 us (the queries of a key block shared by
-// several workgroups).
+// Pass 2 on 256-byte rows takes the registers of two waves per SIMD (held to three it spills: 1.27 -> 1.76 ms); fp32 rows of
+// 512 bytes, two key tiles per wave, fit three.  Per tile of 16 queries x 64 keys, 16 MFMAs: bf16 scores 74 other vector instructions
+// (102 before), bits 46 (111), and 29 or 25 scalar ones (36 and 26).  Whole calls, us, before | now: 512 heads x 1024 queries x 4096 keys,
+// bf16 ring 1924 | 1843, without a ring 1481 | 1410; 512 x 1024 x 8192 with the boolean ring 2739 | 2320.  What still bounds it: with
+// bf16 scores the 3.76 GB of ring, which 450 us of the 640 to 750 they take alone do not hide behind the rest; else products, scalar and vector issue of
+// two waves that share a SIMD (products and LDS reads alone: 10.8 ns an MFMA on every SIMD, as it is 19).
 template <typename DT, int D, int MODE, bool FAR>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void corm_prefill_scores_kernel(
     const PrefillArgs a) {

@@ -24,6 +24,11 @@ SEEDS = [
     ("bf16", 2, 2, 128, 512, 64, 512, 0, 0.0, False),      # threshold 0: everything is important
     ("bf16", 2, 2, 128, 512, 64, 512, 0, 1e30, False),     # and one that nothing reaches
     ("bf16", 1, 40, 128, 300, 32, 320, 0, 2.5, False),     # many units with a block that is not whole
+    ("bf16", 8, 24, 128, 500, 300, 512, 0, 1.0, False),    # a block is half of the heads of 16 queries; 152 tiles, and the
+                                                           # ring's end inside a tile
+    ("bf16", 4, 48, 128, 700, 421, 704, 0, 1.0, False),    # a block is all heads of 16 queries
+    ("bf16", 2, 96, 64, 900, 770, 960, 0, 1.0, False),     # ... and of 32
+    ("f32", 1, 128, 128, 700, 600, 704, 0, 1.0, False),    # blocks of two tiles, runs of 16 blocks
 ]
 
 
