@@ -247,12 +247,15 @@ int launch_attend_record(const corm_desc* d, const Params& p, const LaunchCtx& c
 template <int RC>
 int launch_record_rc(const corm_desc* d, const Params& p, hipStream_t s) {
   const int G = d->Hq / d->Hkv;
-  const dim3 grid((p.nsplit + RC - 1) / RC, d->B * d->Hkv);
+  // workgroups that do a unit's out (record_out): four items each or one, by the parts a full unit has
+  const int items = G * (d->d / 64);
+  const int n_out = (d->Lcap + p.part_keys - 1) / p.part_keys <= OUT_WAVE_PARTS ? (items + WAVES - 1) / WAVES : items;
+  const dim3 grid((p.nsplit + RC - 1) / RC + n_out, d->B * d->Hkv);
   switch (G) {
-    case 1: hipLaunchKernelGGL((corm_record_kernel<1, RC>), grid, dim3(WG), 0, s, p, d->d); break;
-    case 2: hipLaunchKernelGGL((corm_record_kernel<2, RC>), grid, dim3(WG), 0, s, p, d->d); break;
-    case 4: hipLaunchKernelGGL((corm_record_kernel<4, RC>), grid, dim3(WG), 0, s, p, d->d); break;
-    case 8: hipLaunchKernelGGL((corm_record_kernel<8, RC>), grid, dim3(WG), 0, s, p, d->d); break;
+    case 1: hipLaunchKernelGGL((corm_record_kernel<1, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
+    case 2: hipLaunchKernelGGL((corm_record_kernel<2, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
+    case 4: hipLaunchKernelGGL((corm_record_kernel<4, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
+    case 8: hipLaunchKernelGGL((corm_record_kernel<8, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
     default: return CORM_EUNSUPPORTED;
   }
   return launch_status();

@@ -12,12 +12,91 @@ namespace {
 constexpr int OUT_WAVE_PARTS = 16;   // up to here one wave folds the partial rows of an item alone
 constexpr int OUT_BATCH = 8;         // of them in flight together
 
+// Global max and sum of Eq. 2 of a head, by one wave, from its split partials; the first 64 stay in registers between the
+// max and the sum.  (The same bits in every lane.)
+__device__ __forceinline__ float2 head_stats(const float* part0, int pstride, int nparts) {
+  const int lane = threadIdx.x & 63;
+  float2 first = make_float2(neg_inf(), 0.f);
+  if (lane < nparts) first = *reinterpret_cast<const float2*>(part0 + (size_t)lane * pstride);
+  float mx = first.x;
+  for (int s = lane + 64; s < nparts; s += 64) mx = fmaxf(mx, part0[(size_t)s * pstride]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  const float ms = mx == neg_inf() ? 0.f : mx;
+  float zt = first.y * exp2f(first.x - ms);
+  for (int s = lane + 64; s < nparts; s += 64) {
+    const float* ps = part0 + (size_t)s * pstride;
+    zt = fmaf(ps[1], exp2f(ps[0] - ms), zt);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) zt += __shfl_xor(zt, off);
+  return make_float2(ms, zt);
+}
+
+// out (Eq. 1) of a unit, by workgroups of their own in the record launch, the first n_out of a unit.  (Done by the workgroups that record, in
+// front of it, it lengthened their chain of latencies: 32 units x 4200 keys 5.3 -> 4.4 us, 16 units x 2600 of two heads 5.4 -> 4.2, 128 units
+// x 33000 24.5 -> 22.8.)  (head, block of 64 columns) items are dealt to them; lane = column, so every split's
+// partial row is read as one contiguous 256-byte piece and the loads of all splits are independent (no cross-lane
+// reduction, one memory latency per item).  Few splits: an item belongs to one wave,
+// the rows in whole batches (a remainder loop is a chain of latencies: 16 units of up to 15 splits 5.7 us, in batches 4.7, as by
+// the other way).  Many splits: to one workgroup, whose waves take the splits round-robin and meet in LDS.
+template <int G>
+__device__ __forceinline__ void record_out(const Params& p, int unit, int L, int nparts, int D, int wg, int n_out) {
+  __shared__ float sh_out[WAVES][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int b = unit / p.Hkv, hq0 = (unit - b * p.Hkv) * G;
+  const int pstride = D + 2, cblocks = D / 64;
+  const float* part_u = p.partials + (size_t)(b * p.Hq + hq0) * p.npart * pstride;
+  float* out_u = p.out + (size_t)(b * p.Hq + hq0) * D;
+  if (nparts <= OUT_WAVE_PARTS) {
+    for (int item = wg * WAVES + wv; item < G * cblocks; item += n_out * WAVES) {
+      const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
+      const float* part0 = part_u + (size_t)g * p.npart * pstride;
+      const float2 st = head_stats(part0, pstride, nparts);
+      float at = 0.f;
+      for (int s0 = 0; s0 < nparts; s0 += OUT_BATCH) {
+        float m[OUT_BATCH], v[OUT_BATCH];
+#pragma unroll
+        for (int u = 0; u < OUT_BATCH; ++u) {
+          const float* ps = part0 + (size_t)min(s0 + u, nparts - 1) * pstride;
+          m[u] = ps[0];
+          v[u] = ps[2 + c];
+        }
+#pragma unroll
+        for (int u = 0; u < OUT_BATCH; ++u) at = fmaf(s0 + u < nparts ? v[u] : 0.f, exp2f(m[u] - st.x), at);
+      }
+      out_u[(size_t)g * D + c] = L > 0 ? at / st.y : 0.f;
+    }
+    return;
+  }
+  for (int item = wg; item < G * cblocks; item += n_out) {   // (uniform over the workgroup)
+    const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
+    const float* part0 = part_u + (size_t)g * p.npart * pstride;
+    const float2 st = head_stats(part0, pstride, nparts);
+    float at = 0.f;
+#pragma unroll 4
+    for (int s = wv; s < nparts; s += WAVES) {
+      const float* ps = part0 + (size_t)s * pstride;
+      at = fmaf(ps[2 + c], exp2f(ps[0] - st.x), at);
+    }
+    sh_out[wv][lane] = at;
+    __syncthreads();
+    if (wv == 0) {
+      float tot = 0.f;
+#pragma unroll
+      for (int i = 0; i < WAVES; ++i) tot += sh_out[i][lane];
+      out_u[(size_t)g * D + c] = L > 0 ? tot / st.y : 0.f;
+    }
+    __syncthreads();
+  }
+}
+
 template <int G, int RECORD_CHUNKS>
-__global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const int D) {
+__global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const int D, const int n_out) {
   constexpr int RECORD_ROWS = RECORD_CHUNKS * CHUNK;  // keys per workgroup
   constexpr int KPT = RECORD_ROWS / WG;  // keys per thread
   constexpr int KPC = CHUNK / WG;        // of which per chunk
-  const int rsplit = blockIdx.x;         // this workgroup covers chunks [rsplit*RECORD_CHUNKS, +RECORD_CHUNKS)
+  const int rsplit = (int)blockIdx.x - n_out;   // this workgroup covers chunks [rsplit*RECORD_CHUNKS, +RECORD_CHUNKS); below 0: out
   const int unit = blockIdx.y;
   const UnitLen ul = unit_len(p, unit);
   const int L = ul.L;
@@ -25,8 +104,11 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   if (rsplit == 0 && tid == 0 && ul.flags && p.status) atomicOr(p.status, ul.flags);
   const int nlive = (L + CHUNK - 1) / CHUNK;                        // chunks that hold keys
   const int nparts = (L + p.part_keys - 1) / p.part_keys;           // attend partials that hold keys
-  const int nwg = max((L + RECORD_ROWS - 1) / RECORD_ROWS, 1);      // record workgroups that have work
-  if (rsplit >= nwg) return;
+  if (rsplit < 0) {
+    record_out<G>(p, unit, L, nparts, D, blockIdx.x, n_out);
+    return;
+  }
+  if (rsplit * RECORD_ROWS >= L) return;   // nothing to record here
 
   const int b = unit / p.Hkv;
   const int hkv = unit - b * p.Hkv;
@@ -37,7 +119,6 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   const int rend = min(rbeg + RECORD_ROWS, L);
 
   __shared__ float sh_M[G], sh_Z[G];
-  __shared__ float sh_out[WAVES][64];
   __shared__ int sh_cnt[RECORD_CHUNKS][WAVES];
 
   // this thread's keys: issue their loads first, they are consumed after the merge below
@@ -61,79 +142,14 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   const int tcur = p.t[b];
   const int tfirst = p.do_evict ? p.t_first[b] : tcur;
 
-  // global max and sum of Eq. 2 from the split partials (wave g handles head g, g + WAVES, ...); the first 64 partials
-  // stay in registers between the max and the sum
-  for (int g = wv; g < G; g += WAVES) {
-    const float* part0 = p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE;
-    float2 first = make_float2(neg_inf(), 0.f);
-    if (lane < nparts) first = *reinterpret_cast<const float2*>(part0 + (size_t)lane * PSTRIDE);
-    float mx = first.x;
-    for (int s = lane + 64; s < nparts; s += 64) mx = fmaxf(mx, part0[(size_t)s * PSTRIDE]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    const float ms = mx == neg_inf() ? 0.f : mx;
-    float zt = first.y * exp2f(first.x - ms);
-    for (int s = lane + 64; s < nparts; s += 64) {
-      const float* ps = part0 + (size_t)s * PSTRIDE;
-      zt = fmaf(ps[1], exp2f(ps[0] - ms), zt);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) zt += __shfl_xor(zt, off);
+  for (int g = wv; g < G; g += WAVES) {   // (wave g handles head g, g + WAVES, ...)
+    const float2 st = head_stats(p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE, PSTRIDE, nparts);
     if (lane == 0) {
-      sh_M[g] = ms;
-      sh_Z[g] = zt;
+      sh_M[g] = st.x;
+      sh_Z[g] = st.y;
     }
   }
   __syncthreads();
-
-  // out (Eq. 1): (head, block of 64 columns) items of the unit are dealt round-robin; lane = column, so every split's
-  // partial row is read as one contiguous 256-byte piece and the loads of all splits are independent (no cross-lane
-  // reduction, one memory latency per item).  Few splits: an item belongs to one wave, many items in flight, no barrier,
-  // the rows in whole batches (a remainder loop is a chain of latencies: 16 units of up to 15 splits 5.7 us, in batches 4.7, as by
-  // the other way).  Many splits: to one workgroup, whose waves take the splits round-robin and meet in LDS.
-  const int cblocks = D / 64;
-  if (nparts <= OUT_WAVE_PARTS) {
-    for (int item = rsplit * WAVES + wv; item < G * cblocks; item += nwg * WAVES) {
-      const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
-      const float* part0 = p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE;
-      const float ms = sh_M[g];
-      float at = 0.f;
-      for (int s0 = 0; s0 < nparts; s0 += OUT_BATCH) {
-        float m[OUT_BATCH], v[OUT_BATCH];
-#pragma unroll
-        for (int u = 0; u < OUT_BATCH; ++u) {
-          const float* ps = part0 + (size_t)min(s0 + u, nparts - 1) * PSTRIDE;
-          m[u] = ps[0];
-          v[u] = ps[2 + c];
-        }
-#pragma unroll
-        for (int u = 0; u < OUT_BATCH; ++u) at = fmaf(s0 + u < nparts ? v[u] : 0.f, exp2f(m[u] - ms), at);
-      }
-      p.out[(size_t)(b * p.Hq + hq0 + g) * D + c] = L > 0 ? at / sh_Z[g] : 0.f;
-    }
-  } else {
-    for (int item = rsplit; item < G * cblocks; item += nwg) {   // (uniform over the workgroup)
-      const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
-      const float* part0 = p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE;
-      const float ms = sh_M[g];
-      float at = 0.f;
-#pragma unroll 4
-      for (int s = wv; s < nparts; s += WAVES) {
-        const float* ps = part0 + (size_t)s * PSTRIDE;
-        at = fmaf(ps[2 + c], exp2f(ps[0] - ms), at);
-      }
-      sh_out[wv][lane] = at;
-      __syncthreads();
-      if (wv == 0) {
-        float tot = 0.f;
-#pragma unroll
-        for (int i = 0; i < WAVES; ++i) tot += sh_out[i][lane];
-        p.out[(size_t)(b * p.Hq + hq0 + g) * D + c] = L > 0 ? tot / sh_Z[g] : 0.f;
-      }
-      __syncthreads();
-    }
-  }
-  if (L == 0) return;  // an empty unit: nothing to record
 
   // record (Def. 3.1) and decide (Def. 4.1 + recent r) for the keys of this workgroup
   const bool step_ok = tcur >= 1 && tcur <= p.Tcap;

@@ -726,3 +726,44 @@ def test_a_step_of_small_units_with_events_brackets_the_launch_that_streams(case
         if step == 0:
             assert not bool((a.workspace == 0x5a).all())
             break
+
+
+# query heads per KV head, d, capacity: 15, 16 and 17 parts of a full unit (up to 16 a wave folds an item alone), 17 parts of
+# 512, and 70 (more than a wave holds one of per lane)
+OUTS = [(1, 64, 1900), (8, 128, 2048), (2, 128, 2100), (4, 128, 8600), (1, 128, 35700)]
+
+
+@pytest.mark.parametrize("case", range(len(OUTS)))
+def test_out_of_a_split_unit_whatever_its_parts(case):
+    """out of the split launches against softmax in 64 bits, for units of every number of parts, empty ones among them (out 0).
+    A weight's logit is a sum of d products of at most 8 / d each in the log2 domain, rounded d times; with exp2, the factors
+    between parts and the sums (over the parts of a key's lane, its wave and unit) less than 200 more roundings of terms that are
+    all weights times |v|."""
+    G, d, Lcap = OUTS[case]
+    print("[case]", OUTS[case], flush=True)
+    g = torch.Generator(device=DEV).manual_seed(case)
+    full = [0, 1, 15, 63, 64, 511, 512, 513, 1500, 1920, 2047, Lcap // 2 + 1, Lcap - 1, Lcap]
+    lens = [n for n in full if n <= Lcap]
+    B = len(lens)
+    st = corm.LayerState(B, G, 1, d, Lcap, Lcap, 16, 8, "f32", device=DEV, want_ring=False)
+    scale = float(torch.tensor(float(d)).rsqrt() * 1.4426950408889634)
+    q = torch.rand(B, G, d, device=DEV, generator=g) * 2 - 1
+    st.K[:] = (torch.rand(B, 1, Lcap, d, device=DEV, generator=g) * 2 - 1) * (8 / d / scale)
+    st.V[:] = torch.randn(B, 1, Lcap, d, device=DEV, generator=g)
+    st.pos[:] = torch.arange(Lcap, device=DEV).int()
+    st.lens[:] = torch.tensor(lens, device=DEV, dtype=torch.int32).view(B, 1)
+    st.out.fill_(7.0)
+    t = torch.full((B,), Lcap, dtype=torch.int32, device=DEV)
+    assert corm.corm_selected_path(st.desc) == 1
+    corm.corm_decode_attend(st.desc, q, st.K, st.V, st.lens, st.pos, t, st.ring, st.last_hit, st.out, st.workspace,
+                            status=st.status)
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == 0
+    for b, n in enumerate(lens):
+        if n == 0:
+            assert not st.out[b].any()
+            continue
+        k, v = st.K[b, 0, :n].double(), st.V[b, 0, :n].double()
+        a = torch.softmax(q[b].double() @ k.t().contiguous() / d ** 0.5, -1)
+        tol = 2.0 ** -24 * (8 * d + 200) * (a @ v.abs())
+        assert ((st.out[b].double() - a @ v).abs() <= tol).all(), n
