@@ -244,18 +244,18 @@ int launch_unit(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStre
 // append (if p.do_append) + attend + record: one fused launch or the attend / record pair
 int launch_attend_record(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStream_t s);
 
-template <int RC>
+template <int RC, int NT>
 int launch_record_rc(const corm_desc* d, const Params& p, hipStream_t s) {
   const int G = d->Hq / d->Hkv;
-  // workgroups that do a unit's out (record_out): four items each or one, by the parts a full unit has
+  // workgroups that do a unit's out (record_out): an item a wave each or one, by the parts a full unit has
   const int items = G * (d->d / 64);
-  const int n_out = (d->Lcap + p.part_keys - 1) / p.part_keys <= OUT_WAVE_PARTS ? (items + WAVES - 1) / WAVES : items;
+  const int n_out = (d->Lcap + p.part_keys - 1) / p.part_keys <= OUT_WAVE_PARTS ? (items + NT / 64 - 1) / (NT / 64) : items;
   const dim3 grid((p.nsplit + RC - 1) / RC + n_out, d->B * d->Hkv);
   switch (G) {
-    case 1: hipLaunchKernelGGL((corm_record_kernel<1, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
-    case 2: hipLaunchKernelGGL((corm_record_kernel<2, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
-    case 4: hipLaunchKernelGGL((corm_record_kernel<4, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
-    case 8: hipLaunchKernelGGL((corm_record_kernel<8, RC>), grid, dim3(WG), 0, s, p, d->d, n_out); break;
+    case 1: hipLaunchKernelGGL((corm_record_kernel<1, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
+    case 2: hipLaunchKernelGGL((corm_record_kernel<2, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
+    case 4: hipLaunchKernelGGL((corm_record_kernel<4, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
+    case 8: hipLaunchKernelGGL((corm_record_kernel<8, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
     default: return CORM_EUNSUPPORTED;
   }
   return launch_status();
@@ -265,9 +265,13 @@ int launch_record(const corm_desc* d, const Params& p, const LaunchCtx& c, hipSt
   // the largest workgroup that still leaves about four workgroups per compute unit
   const long units = (long)d->B * d->Hkv;
   const long want = 4L * c.cus;
-  if (units * ((p.nsplit + 3) / 4) >= want) return launch_record_rc<4>(d, p, s);
-  if (units * ((p.nsplit + 1) / 2) >= want) return launch_record_rc<2>(d, p, s);
-  return launch_record_rc<1>(d, p, s);
+  if (units * ((p.nsplit + 3) / 4) >= want) return launch_record_rc<4, WG>(d, p, s);
+  if (units * ((p.nsplit + 1) / 2) >= want) return launch_record_rc<2, WG>(d, p, s);
+  // A thread per key while the launch has at most two such workgroups per compute unit (eight heads a unit: three), else two keys a thread.
+  // Whole steps, us, a thread per key | two keys: 56 workgroups of one head 15.7 | 16.6, 560 of eight heads 46.8 | 48.6, 960 of one head
+  // 51.6 | 50.3, 1056 of eight 69.4 | 68.5, 1120 of four 63.8 | 62.5.
+  if (units * p.nsplit <= (d->Hq / d->Hkv == 8 ? 3L : 2L) * c.cus) return launch_record_rc<1, CHUNK>(d, p, s);
+  return launch_record_rc<1, WG>(d, p, s);
 }
 
 // Keys per attend workgroup on the split path: a whole chunk, or a half / a quarter of one while the

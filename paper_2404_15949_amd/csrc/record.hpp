@@ -8,7 +8,9 @@ namespace {
 // ---------------------------------------------------------------- record (+ keep flags)
 
 // RECORD_CHUNKS: 512-slot chunks per workgroup (more keys per workgroup amortize its fixed chain of
-// dependent loads; fewer keep the chip full when the launch has few units)
+// dependent loads; fewer keep the chip full when the launch has few units).  NT: threads.  A workgroup of one chunk has a thread per key: such
+// launches leave the chip mostly idle, and a thread's G scores per key run one after the other (9 units x 600 of 1600 slots, eight heads, 256
+// threads 9.4 us, 512 6.4; 16 units x 2600, two heads 5.1, 4.4; 32 units x 4200, one head: equal).
 constexpr int OUT_WAVE_PARTS = 16;   // up to here one wave folds the partial rows of an item alone
 constexpr int OUT_BATCH = 8;         // of them in flight together
 
@@ -40,7 +42,7 @@ __device__ __forceinline__ float2 head_stats(const float* part0, int pstride, in
 // reduction, one memory latency per item).  Few splits: an item belongs to one wave,
 // the rows in whole batches (a remainder loop is a chain of latencies: 16 units of up to 15 splits 5.7 us, in batches 4.7, as by
 // the other way).  Many splits: to one workgroup, whose waves take the splits round-robin and meet in LDS.
-template <int G>
+template <int G, int NT>
 __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int nparts, int D, int wg, int n_out) {
   __shared__ float sh_out[WAVES][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -49,7 +51,7 @@ __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int
   const float* part_u = p.partials + (size_t)(b * p.Hq + hq0) * p.npart * pstride;
   float* out_u = p.out + (size_t)(b * p.Hq + hq0) * D;
   if (nparts <= OUT_WAVE_PARTS) {
-    for (int item = wg * WAVES + wv; item < G * cblocks; item += n_out * WAVES) {
+    for (int item = wg * (NT / 64) + wv; item < G * cblocks; item += n_out * (NT / 64)) {
       const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
       const float* part0 = part_u + (size_t)g * p.npart * pstride;
       const float2 st = head_stats(part0, pstride, nparts);
@@ -73,13 +75,15 @@ __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int
     const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
     const float* part0 = part_u + (size_t)g * p.npart * pstride;
     const float2 st = head_stats(part0, pstride, nparts);
-    float at = 0.f;
+    if (wv < WAVES) {   // (four of them, whatever the workgroup: the order of the sums)
+      float at = 0.f;
 #pragma unroll 4
-    for (int s = wv; s < nparts; s += WAVES) {
-      const float* ps = part0 + (size_t)s * pstride;
-      at = fmaf(ps[2 + c], exp2f(ps[0] - st.x), at);
+      for (int s = wv; s < nparts; s += WAVES) {
+        const float* ps = part0 + (size_t)s * pstride;
+        at = fmaf(ps[2 + c], exp2f(ps[0] - st.x), at);
+      }
+      sh_out[wv][lane] = at;
     }
-    sh_out[wv][lane] = at;
     __syncthreads();
     if (wv == 0) {
       float tot = 0.f;
@@ -91,11 +95,13 @@ __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int
   }
 }
 
-template <int G, int RECORD_CHUNKS>
-__global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const int D, const int n_out) {
+template <int G, int RECORD_CHUNKS, int NT>
+__global__ __launch_bounds__(NT) void corm_record_kernel(const Params p, const int D, const int n_out) {
   constexpr int RECORD_ROWS = RECORD_CHUNKS * CHUNK;  // keys per workgroup
-  constexpr int KPT = RECORD_ROWS / WG;  // keys per thread
-  constexpr int KPC = CHUNK / WG;        // of which per chunk
+  constexpr int KPT = RECORD_ROWS / NT;  // keys per thread
+  constexpr int KPC = CHUNK / NT;        // of which per chunk
+  constexpr int NW = NT / 64;
+  static_assert(CHUNK % NT == 0 && NT >= 64 * WAVES, "whole keys per thread and chunk; the waves of record_out");
   const int rsplit = (int)blockIdx.x - n_out;   // this workgroup covers chunks [rsplit*RECORD_CHUNKS, +RECORD_CHUNKS); below 0: out
   const int unit = blockIdx.y;
   const UnitLen ul = unit_len(p, unit);
@@ -105,7 +111,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   const int nlive = (L + CHUNK - 1) / CHUNK;                        // chunks that hold keys
   const int nparts = (L + p.part_keys - 1) / p.part_keys;           // attend partials that hold keys
   if (rsplit < 0) {
-    record_out<G>(p, unit, L, nparts, D, blockIdx.x, n_out);
+    record_out<G, NT>(p, unit, L, nparts, D, blockIdx.x, n_out);
     return;
   }
   if (rsplit * RECORD_ROWS >= L) return;   // nothing to record here
@@ -119,7 +125,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   const int rend = min(rbeg + RECORD_ROWS, L);
 
   __shared__ float sh_M[G], sh_Z[G];
-  __shared__ int sh_cnt[RECORD_CHUNKS][WAVES];
+  __shared__ int sh_cnt[RECORD_CHUNKS][NW];
 
   // this thread's keys: issue their loads first, they are consumed after the merge below
   const int32_t* posb = p.pos + (size_t)unit * p.Lcap;
@@ -132,7 +138,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   float lg[KPT][G];
 #pragma unroll
   for (int k = 0; k < KPT; ++k) {
-    const int i = min(rbeg + k * WG + tid, max(rend - 1, 0));   // clamped: a live slot (or 0 in an empty unit)
+    const int i = min(rbeg + k * NT + tid, max(rend - 1, 0));   // clamped: a live slot (or 0 in an empty unit)
     my_pos[k] = posb[i];
     my_lh[k] = lhb[i];
     my_live[k] = p.lazy ? ((liveb[i >> 6] >> (i & 63)) & 1ull) != 0 : true;
@@ -142,7 +148,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   const int tcur = p.t[b];
   const int tfirst = p.do_evict ? p.t_first[b] : tcur;
 
-  for (int g = wv; g < G; g += WAVES) {   // (wave g handles head g, g + WAVES, ...)
+  for (int g = wv; g < G; g += NW) {   // (wave g handles head g, g + NW, ...)
     const float2 st = head_stats(p.partials + (size_t)(b * p.Hq + hq0 + g) * p.npart * PSTRIDE, PSTRIDE, nparts);
     if (lane == 0) {
       sh_M[g] = st.x;
@@ -164,7 +170,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
   for (int c = 0; c < RECORD_CHUNKS; ++c) kept[c] = 0;
 #pragma unroll
   for (int k = 0; k < KPT; ++k) {
-    const int i = rbeg + k * WG + tid;
+    const int i = rbeg + k * NT + tid;
     const bool live = i < rend && my_live[k];
     bool keep = false;
     if (p.ring_bits) {   // (uniform) boolean message: compare the fp32 score, set bits wave by wave
@@ -220,9 +226,9 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
     }
     if (p.do_evict && keepb && i < rend) keepb[i] = keep ? 1 : 0;
     const unsigned long long bal = __ballot(keep);
-    if (p.do_evict && lane == 0 && rbeg + k * WG + wv * 64 < rend) {
-      bitsb[((rbeg + k * WG) >> 6) + wv] = bal;
-      if (p.lazy) liveb[((rbeg + k * WG) >> 6) + wv] = bal;
+    if (p.do_evict && lane == 0 && rbeg + k * NT + wv * 64 < rend) {
+      bitsb[((rbeg + k * NT) >> 6) + wv] = bal;
+      if (p.lazy) liveb[((rbeg + k * NT) >> 6) + wv] = bal;
     }
     kept[k / KPC] += __popcll(bal);
   }
@@ -235,7 +241,7 @@ __global__ __launch_bounds__(WG) void corm_record_kernel(const Params p, const i
     if (tid < RECORD_CHUNKS && rsplit * RECORD_CHUNKS + tid < nlive) {
       int tot = 0;
 #pragma unroll
-      for (int i = 0; i < WAVES; ++i) tot += sh_cnt[tid][i];
+      for (int i = 0; i < NW; ++i) tot += sh_cnt[tid][i];
       const int chunk = rsplit * RECORD_CHUNKS + tid;
       p.counts[(size_t)unit * p.nsplit + chunk] = tot;
       // (a plain store: whoever lost a key stores the same)
