@@ -29,10 +29,10 @@ WorkspaceLayout workspace_layout(const corm_desc& d) {
   w.keepbits_off = align_up(w.unit_state_off + units * sizeof(int2), 256);
   w.partials_off = align_up(w.keepbits_off + units * w.kb_stride * sizeof(unsigned long long), 256);
   w.logits_off = align_up(w.partials_off + heads * w.nsplit * MAX_PARTS_PER_CHUNK * (d.d + 2) * sizeof(float), 256);
+  w.stage_meta_off = align_up(w.logits_off + heads * d.Lcap * sizeof(float), 256);   // (what lies in front of it is all that attend and record need)
   // (pass 2 of prompt seeding reads up to 63 queries past the last of a head: there is memory behind the last head's)
-  w.seed_stats_off = align_up(w.logits_off + heads * d.Lcap * sizeof(float), 256);
-  w.stage_meta_off = align_up(w.seed_stats_off + heads * d.w * sizeof(float4), 256);
-  w.stage_k_off = align_up(w.stage_meta_off + stage_rows * 2 * sizeof(int32_t), 256);
+  w.seed_stats_off = align_up(w.stage_meta_off + stage_rows * 2 * sizeof(int32_t), 256);
+  w.stage_k_off = align_up(w.seed_stats_off + heads * d.w * sizeof(float4), 256);
   w.stage_v_off = align_up(w.stage_k_off + stage_rows * row_bytes(&d), 256);
   w.seed_kb = row_bytes(&d) / 64 <= 4 ? PrefillGeom<256>::KB : PrefillGeom<512>::KB;
   w.seed_nkb = (d.Lcap + w.seed_kb - 1) / w.seed_kb;

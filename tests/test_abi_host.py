@@ -237,3 +237,14 @@ def test_current_stream_without_the_raw_handle(monkeypatch):
     monkeypatch.setattr(corm, "_raw_stream", lambda device: 100 + device)
     assert corm._stream(None) == 103
     assert corm._stream(7) == 7
+
+
+def test_static_scratch_is_not_charged_for_prompt_seeding():
+    """corm_decode_attend_static needs the counts, keep words, partials and logits alone: a window whose seeding statistics
+    would not fit the static scratch is no reason to refuse it (without a device the call ends at the device instead)."""
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are no memory")
+    desc = corm.corm_desc(1, 1, 1, 64, 512, 512, 4 << 20, 8, corm.CORM_F32, corm.CORM_F32, 1.0, 0.0)
+    p = 4096
+    rc = corm.lib().corm_decode_attend_static(ctypes.byref(desc), p, p, p, p, p, p, None, p, p, None, None, None)
+    assert rc == corm.CORM_EHIP
