@@ -114,7 +114,7 @@ enum { SEED_BF16 = 0, SEED_F32 = 1, SEED_BITS = 2 };
 //                 (or the next fp32, where that midpoint rounds down).  fp32: z = thr.  bf16, w: that smallest bf16 minus one
 //                 (as an integer: for scores that are numbers the order is the same) in both halves of a word, for whole blocks.
 //                 A row with a logit that is not finite (its reference or sum is not a finite number either), in which scores may
-//                 be no numbers, has the sign of y set and is decided by z throughout.
+//                 be no numbers, has the sign of y set: no block with such a row is a fast one, and general blocks decide by z.
 //   boolean ring  raw logits above z + w are important, those below z - w are not, and only those between
 //                 need the score itself.  The band is the threshold in the logit domain -+ a bound on every
 //                 rounding between a logit and its score (products, fma, exp2, 1/sum, the logarithms and z -+ w here: together
@@ -136,10 +136,7 @@ __device__ __forceinline__ float4 prefill_query_stats(const PrefillArgs& a, floa
     const uint32_t up = (__float_as_uint(thr) + 0xffffu) >> 16;   // the smallest bf16 >= thr (thr >= 0)
     s.z = up ? __uint_as_float(((up - 1u) << 16) + 0x8000u + (up & 1u)) : 0.f;
     s.w = __uint_as_float(((up - 1u) & 0xffffu) * 0x10001u);
-    if (!(fabsf(ms) < __builtin_inff()) || !(z < __builtin_inff())) {
-      s.y = -s.y;
-      s.w = __uint_as_float(0x7fff7fffu);   // (nothing is above)
-    }
+    if (!(fabsf(ms) < __builtin_inff()) || !(z < __builtin_inff())) s.y = -s.y;
   }
   return s;
 }
@@ -697,7 +694,8 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   }
   // Fast blocks (uniform over the wave): every query of the block exists and sees every key of the wave, and whole pieces can be
   // stored: straight-line code, the next tile's MFMAs under this tile's tail.  They follow one another; with FAR, but for a block
-  // whose rows go on at the ring's start.
+  // whose rows go on at the ring's start, and with a bf16 ring, but for a block with a marked row (prefill_query_stats).
+  // (Asked once the block is staged.)
   const int fast_beg = !rows_ok || pos_wmax == NEVER || (FAR && 16 * row_bytes64 > DEAD_OFFSET)
                            ? blk_end
                            : ((((max(pos_wmax - tau0 + 1, 0) + 15) / 16) << lgG) + QT - 1) / QT;
@@ -705,23 +703,8 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   auto is_fast = [&](int blk) __attribute__((always_inline)) {
     const int tt0 = blk * QT;
     return blk >= fast_beg && blk < fast_end &&
-           (!FAR || slot_of((tt0 >> lgG) * 16) <= slot_of(((tt0 + QT - 1) >> lgG) * 16 + 15));
-  };
-  // bf16 ring, a block with rows whose scores may be no numbers (rare): their hits by the scores themselves
-  auto numberless = [&](int blk) __attribute__((always_inline)) {
-#pragma unroll 1
-    for (int ti = 0; ti < QT; ++ti) {
-      const float4 st = sh_st[blk % STB][ti * 16 + n];
-      const uint32_t at = (uint32_t)((blk * QT + ti) >> lgG) + 1u;
-      f32x4_t d[T];
-      mma_tile(blk & 1, ti, d);
-#pragma unroll
-      for (int i = 0; i < 4 * T; i += 2) {
-        const bool h0 = prefill_score(d[i >> 2][i & 3], a.scale_log2, st.x, st.y) >= st.z;
-        const bool h1 = prefill_score(d[i >> 2][(i & 3) + 1], a.scale_log2, st.x, st.y) >= st.z;
-        if (__float_as_int(st.y) < 0) raise(i >> 1, h0 ? at : 0u, h1 ? at : 0u);
-      }
-    }
+           (!FAR || slot_of((tt0 >> lgG) * 16) <= slot_of(((tt0 + QT - 1) >> lgG) * 16 + 15)) &&
+           (!TURN || !__any(__float_as_int(sh_st[blk % STB][lane % QBLK].y) < 0));
   };
   uint64_t x_ring[QT];    // of tile x of a block, see fetch: bytes of ring from the block's first head (FAR: and row)
   uint32_t x_row[QT];
@@ -745,8 +728,6 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
       return min(lane_off + first, lane_off + (first - (uint32_t)head_bytes));
     };
     uint32_t hits[QT];   // boolean ring: bit i, the tile's query found key i of the lane important
-    bool flagged = false;
-    if (TURN) flagged = __any(__float_as_int(sh_st[blk % STB][lane % QBLK].y) < 0);
 #pragma unroll
     for (int ti = 0; ti < QT; ++ti) {
       f32x4_t d[T];
@@ -755,7 +736,6 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
       const int jt = jt0 + (ti >> lgG);
       const float4 st = sh_st[blk % STB][ti * 16 + n];
       if (ti == QT - 2) {
-        if (flagged) numberless(blk);
         stage(blk + 1, qr, str);
         __syncthreads();
       }

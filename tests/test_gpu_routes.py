@@ -337,6 +337,44 @@ def test_seed_with_logits_that_are_not_finite(dtype, d, c):
     assert not wrong, wrong
 
 
+# kv dtype, d, query heads per KV head, m: tails that end in a fast block of the kernel (64 queries; of fp32 rows of 512 bytes 32, over all heads)
+LASTS = [("bf16", 128, 1, 64), ("bf16", 128, 1, 128), ("bf16", 64, 1, 64), ("f32", 64, 1, 64), ("f32", 128, 1, 32), ("f32", 128, 1, 64),
+         ("bf16", 128, 2, 64), ("bf16", 64, 4, 16)]
+
+
+@pytest.mark.parametrize("ring", ["f32", "bf16", "bit", None])
+@pytest.mark.parametrize("case", range(len(LASTS)))
+def test_seed_latest_hit_of_rows_that_are_not_finite(case, ring):
+    """A key with +inf in one element makes the logit of a query +inf or -inf by that element's sign, and a row with +inf has no
+    finite sum: its scores are 0, that of the key itself no number; the others are finite rows with a score of 0 for the key.  At
+    threshold 0 every other key's latest hit is therefore the last step, whichever of the last 16 queries and those 16 before them have such a row;
+    the key's own is the last step one of whose heads has a finite row."""
+    dtype, d, G, m = LASTS[case]
+    print("[case]", LASTS[case], ring, flush=True)
+    P, Hkv = 600, 8
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV).manual_seed(case)
+    K = torch.randn(1, Hkv, P, d, device=DEV, generator=g).to(tdt)
+    K[:, :, 5, 0] = float("inf")
+    q = torch.randn(1, G * Hkv, m, d, device=DEV, generator=g).to(tdt)
+    up = torch.rand(1, Hkv, G, m, device=DEV, generator=g) < 0.5
+    up[:, ::2, :, -16:] = True            # the last 16 queries have such rows, those before them do not
+    up[:, ::2, :, :-16] = False
+    up[:, 1] = torch.arange(m, device=DEV) % 2 == 1
+    q[..., 0] = torch.where(up.view(1, G * Hkv, m), 1.0, -1.0).to(tdt)
+    st = corm.LayerState(1, G * Hkv, Hkv, d, P, 608, m + 1, 8, dtype, thr_scale=0.0, device=DEV, want_ring=ring is not None,
+                         score_dtype=ring or "bf16")
+    st.preload(K, torch.zeros_like(K))
+    t = torch.full((1,), P, dtype=torch.int32, device=DEV)
+    st.prefill_seed(q, t, torch.zeros_like(t))
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == 0
+    want = torch.full((1, Hkv, P), P, dtype=torch.int32, device=DEV)
+    steps = torch.arange(P - m + 1, P + 1, device=DEV, dtype=torch.int32)
+    want[:, :, 5] = torch.where(~up.all(2), steps, 0).amax(-1)
+    assert torch.equal(st.last_hit, want)
+
+
 @pytest.mark.parametrize("ring", ["f32", "bf16", "bit"])
 def test_seed_with_a_threshold_of_minus_zero(ring):
     """thr_scale = -0.0 passes the descriptor's check (it is not below 0) and is the threshold 0: every key is important to
