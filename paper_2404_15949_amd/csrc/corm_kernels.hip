@@ -354,7 +354,7 @@ int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void
   LaunchCtx ctx;
   rc = make_ctx(nullptr, &ctx);
   if (rc) return rc;
-  if ((m + 15) / 16 > 65535) return CORM_EUNSUPPORTED;   // grid rows of the clear / merge launches
+  if (m > SEED_MAX_TILES * 16) return CORM_EUNSUPPORTED;
   WorkspaceLayout wl;
   rc = check_workspace(desc, workspace, workspace_bytes, &wl);
   if (rc) return rc;

@@ -31,6 +31,12 @@ namespace {
 
 constexpr int PREFILL_XCDS = 8;   // accelerator dies of the device
 
+// Groups of 16 queries of a call: pass 2 keeps latest hits as 1 + such a number in 16 bits, and forms offsets into the queries of up to four
+// heads, of 512 bytes each, in 32; the clear launch has a grid row for each.
+constexpr int SEED_MAX_TILES = 65535;
+static_assert(SEED_MAX_TILES <= 0xffff, "latest hits: two keys to a word");
+static_assert(4ull * SEED_MAX_TILES * 16 * 512 <= 0xffffffffull, "offsets into a block's queries (a descriptor's length is below a half of it)");
+
 struct PrefillArgs {
   const void* q_tail;   // [B, Hq, m, d]
   const void* K;

@@ -248,3 +248,16 @@ def test_static_scratch_is_not_charged_for_prompt_seeding():
     p = 4096
     rc = corm.lib().corm_decode_attend_static(ctypes.byref(desc), p, p, p, p, p, p, None, p, p, None, None, None)
     assert rc == corm.CORM_EHIP
+
+
+def test_prompt_seeding_takes_as_many_queries_as_its_latest_hits_can_number():
+    """65535 groups of 16 queries are accepted (without a device the call ends at its workspace, which is too small); one query more is
+    not."""
+    desc = corm.corm_desc(1, 1, 1, 64, 512, 512, 4 << 20, 8, corm.CORM_BF16, corm.CORM_BF16, 1.0, 0.0)
+    p = 4096
+
+    def call(m):
+        return corm.lib().corm_prefill_seed(ctypes.byref(desc), p, m, p, p, p, p, p, p, p, None, None, None, p, 0, None, None)
+
+    assert call(65535 * 16) == corm.CORM_ECAPACITY
+    assert call(65535 * 16 + 1) == corm.CORM_EUNSUPPORTED

@@ -375,6 +375,31 @@ def test_seed_latest_hit_of_rows_that_are_not_finite(case, ring):
     assert torch.equal(st.last_hit, want)
 
 
+@pytest.mark.parametrize("score", ["f32", "bf16", "bit"])
+@pytest.mark.parametrize("dtype,d,G", [("bf16", 64, 1), ("f32", 128, 4)])
+def test_seed_of_as_many_queries_as_a_call_takes(dtype, d, G, score):
+    """65535 groups of 16 queries, each of which attends to one key (its logit is 79 or more above the others: a score of 1 against
+    thresholds of 1/2 and up): the latest hits are in the last groups, whose numbers fill 16 bits, and with fp32 rows of four
+    heads the queries reach beyond 2^31 bytes."""
+    print("[case]", dtype, d, G, score, flush=True)
+    m, P = 65535 * 16, 64
+    t_last = m + P
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    st = corm.LayerState(1, G, 1, d, P, t_last, m + 1, 8, dtype, thr_scale=0.5 * t_last, device=DEV, want_ring=False, score_dtype=score)
+    K = (30.0 * torch.eye(P, d, device=DEV)).to(tdt).view(1, 1, P, d)
+    st.preload(K, torch.zeros_like(K))
+    j = torch.arange(m, device=DEV)
+    key = (7 * j.view(1, m) + 3 * torch.arange(G, device=DEV).view(G, 1)) % P
+    q = torch.zeros(1, G, m, d, device=DEV, dtype=tdt).scatter_(3, key.view(1, G, m, 1), 30.0)
+    t = torch.full((1,), t_last, dtype=torch.int32, device=DEV)
+    st.prefill_seed(q, t, torch.zeros_like(t))
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == 0
+    want = torch.zeros(P, dtype=torch.int64, device=DEV)
+    want.scatter_reduce_(0, key.flatten(), (P + 1 + j).expand(G, m).flatten(), "amax")
+    assert bool((want > t_last - 64).all()) and torch.equal(st.last_hit[0, 0].long(), want)
+
+
 @pytest.mark.parametrize("ring", ["f32", "bf16", "bit"])
 def test_seed_with_a_threshold_of_minus_zero(ring):
     """thr_scale = -0.0 passes the descriptor's check (it is not below 0) and is the threshold 0: every key is important to
