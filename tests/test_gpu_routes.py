@@ -202,7 +202,10 @@ def test_few_long_units_are_not_left_to_a_few_serial_walks(U, d):
 # kv dtype, G, Hkv, d, Lcap: few units whose heads are shared by workgroups (1, 2, 4, 8 of them), lengths on both sides
 # of a part and of the number of parts one wave folds
 ROUTES = [("bf16", 8, 1, 64, 1000), ("f32", 8, 2, 64, 520), ("f32", 4, 3, 128, 700), ("bf16", 4, 40, 64, 900),
-          ("f32", 2, 30, 128, 515), ("bf16", 1, 4, 64, 1600), ("bf16", 1, 4, 64, 1601), ("f32", 2, 1, 64, 400)]
+          ("f32", 2, 30, 128, 515), ("bf16", 1, 4, 64, 1600), ("bf16", 1, 4, 64, 1601), ("f32", 2, 1, 64, 400),
+          # both sides of the workgroups up to which the record launch has a thread per key: 512, with eight heads a unit 768
+          ("f32", 1, 128, 64, 1600), ("f32", 1, 129, 64, 1600), ("bf16", 2, 128, 64, 1600), ("f32", 2, 129, 64, 1600),
+          ("bf16", 4, 128, 128, 1600), ("bf16", 4, 129, 64, 1600), ("bf16", 8, 192, 64, 1600), ("bf16", 8, 193, 128, 1600)]
 
 
 @pytest.mark.parametrize("ring", ["f32", "bit", None])
