@@ -244,34 +244,39 @@ int launch_unit(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStre
 // append (if p.do_append) + attend + record: one fused launch or the attend / record pair
 int launch_attend_record(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStream_t s);
 
-template <int RC, int NT>
-int launch_record_rc(const corm_desc* d, const Params& p, hipStream_t s) {
-  const int G = d->Hq / d->Hkv;
-  // workgroups that do a unit's out (record_out): an item a wave each or one, by the parts a full unit has
-  const int items = G * (d->d / 64);
-  const int n_out = (d->Lcap + p.part_keys - 1) / p.part_keys <= OUT_WAVE_PARTS ? (items + NT / 64 - 1) / (NT / 64) : items;
-  const dim3 grid((p.nsplit + RC - 1) / RC + n_out, d->B * d->Hkv);
-  switch (G) {
-    case 1: hipLaunchKernelGGL((corm_record_kernel<1, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
-    case 2: hipLaunchKernelGGL((corm_record_kernel<2, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
-    case 4: hipLaunchKernelGGL((corm_record_kernel<4, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
-    case 8: hipLaunchKernelGGL((corm_record_kernel<8, RC, NT>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
+template <int RC, int NT, bool APART>
+int launch_record_rc(const corm_desc* d, const Params& p, int n_out, hipStream_t s) {
+  const dim3 grid(d->B * d->Hkv, (p.nsplit + RC - 1) / RC + n_out);
+  switch (d->Hq / d->Hkv) {
+    case 1: hipLaunchKernelGGL((corm_record_kernel<1, RC, NT, APART>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
+    case 2: hipLaunchKernelGGL((corm_record_kernel<2, RC, NT, APART>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
+    case 4: hipLaunchKernelGGL((corm_record_kernel<4, RC, NT, APART>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
+    case 8: hipLaunchKernelGGL((corm_record_kernel<8, RC, NT, APART>), grid, dim3(NT), 0, s, p, d->d, n_out); break;
     default: return CORM_EUNSUPPORTED;
   }
   return launch_status();
 }
 
 int launch_record(const corm_desc* d, const Params& p, const LaunchCtx& c, hipStream_t s) {
+  const int G = d->Hq / d->Hkv;
+  const long units = (long)d->B * d->Hkv, want = 4L * c.cus;
   // the largest workgroup that still leaves about four workgroups per compute unit
-  const long units = (long)d->B * d->Hkv;
-  const long want = 4L * c.cus;
-  if (units * ((p.nsplit + 3) / 4) >= want) return launch_record_rc<4, WG>(d, p, s);
-  if (units * ((p.nsplit + 1) / 2) >= want) return launch_record_rc<2, WG>(d, p, s);
-  // A thread per key while the launch has at most two such workgroups per compute unit (eight heads a unit: three), else two keys a thread.
-  // Whole steps, us, a thread per key | two keys: 56 workgroups of one head 15.7 | 16.6, 560 of eight heads 46.8 | 48.6, 960 of one head
-  // 51.6 | 50.3, 1056 of eight 69.4 | 68.5, 1120 of four 63.8 | 62.5.
-  if (units * p.nsplit <= (d->Hq / d->Hkv == 8 ? 3L : 2L) * c.cus) return launch_record_rc<1, CHUNK>(d, p, s);
-  return launch_record_rc<1, WG>(d, p, s);
+  const int rc = units * ((p.nsplit + 3) / 4) >= want ? 4 : units * ((p.nsplit + 1) / 2) >= want ? 2 : 1;
+  // A thread per key while the launch has at most two such workgroups per compute unit (eight heads a unit: three, if they can be more than half full),
+  // else two keys a thread.  Whole steps, us, a thread per key | two keys: 256 workgroups of one head 16.5 | 16.9, 512 28.0 | 28.0, 640 36.0 | 35.0;
+  // two heads 512 29.2 | 29.5, 640 37.6 | 36.6; four heads 512 32.5 | 33.2, 640 41.6 | 41.5, 800 52.3 | 51.3; eight heads 256 27.0 | 29.8, 512 39.9 | 41.6,
+  // 768 65.6 | 66.0 and (384 units of two) 59.0 | 58.5, 840 68.0 | 67.5; 500 of 200 keys 31.0 | 31.2.
+  const int nt = rc == 1 && units * p.nsplit <= (G == 8 && d->Lcap > CHUNK / 2 ? 3L : 2L) * c.cus ? CHUNK : WG;
+  // workgroups that do a unit's out (record_out): an item a wave each or one, by the parts a full unit has
+  const int items = G * (d->d / 64), nrec = (p.nsplit + rc - 1) / rc;
+  const int n_out = (d->Lcap + p.part_keys - 1) / p.part_keys <= OUT_WAVE_PARTS ? (items + nt / 64 - 1) / (nt / 64) : items;
+  // Where units have one record workgroup each and there are more of them than three and a half per compute unit, it does out itself: the chip
+  // is full, and more workgroups only take longer to start (eight heads, us, apart | itself: 800 units x 450 keys 68.3 | 70.4, 1000 x 450
+  // 76.5 | 76.2, 1000 x 196 53.7 | 52.3, 2000 x 450 147 | 137, 3000 x 450 211 | 194, 1500 x 2000 364 | 361).
+  if (nrec == 1 && 2 * units > 7L * c.cus) return rc == 4 ? launch_record_rc<4, WG, false>(d, p, 0, s) : launch_record_rc<1, WG, false>(d, p, 0, s);
+  if (rc == 4) return launch_record_rc<4, WG, true>(d, p, n_out, s);
+  if (rc == 2) return launch_record_rc<2, WG, true>(d, p, n_out, s);
+  return nt == WG ? launch_record_rc<1, WG, true>(d, p, n_out, s) : launch_record_rc<1, CHUNK, true>(d, p, n_out, s);
 }
 
 // Keys per attend workgroup on the split path: a whole chunk, or a half / a quarter of one while the

@@ -35,15 +35,15 @@ __device__ __forceinline__ float2 head_stats(const float* part0, int pstride, in
   return make_float2(ms, zt);
 }
 
-// out (Eq. 1) of a unit, by workgroups of their own in the record launch, the first n_out of a unit.  (Done by the workgroups that record, in
-// front of it, it lengthened their chain of latencies: 32 units x 4200 keys 5.3 -> 4.4 us, 16 units x 2600 of two heads 5.4 -> 4.2, 128 units
-// x 33000 24.5 -> 22.8.)  (head, block of 64 columns) items are dealt to them; lane = column, so every split's
+// out (Eq. 1) of a unit, by the n_out workgroups that share it; stats(g, part0, nparts): global max and sum of a head.
+// (head, block of 64 columns) items are dealt to them; lane = column, so every split's
 // partial row is read as one contiguous 256-byte piece and the loads of all splits are independent (no cross-lane
 // reduction, one memory latency per item).  Few splits: an item belongs to one wave,
 // the rows in whole batches (a remainder loop is a chain of latencies: 16 units of up to 15 splits 5.7 us, in batches 4.7, as by
 // the other way).  Many splits: to one workgroup, whose waves take the splits round-robin and meet in LDS.
-template <int G, int NT>
-__device__ __forceinline__ void record_out(const Params& p, int unit, int L, int nparts, int D, int wg, int n_out) {
+template <int G, int NT, typename Stats>
+__device__ __forceinline__ void record_out(const Params& p, int unit, int L, int nparts, int D, int wg, int n_out,
+                                           const Stats& stats) {
   __shared__ float sh_out[WAVES][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int b = unit / p.Hkv, hq0 = (unit - b * p.Hkv) * G;
@@ -54,7 +54,7 @@ __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int
     for (int item = wg * (NT / 64) + wv; item < G * cblocks; item += n_out * (NT / 64)) {
       const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
       const float* part0 = part_u + (size_t)g * p.npart * pstride;
-      const float2 st = head_stats(part0, pstride, nparts);
+      const float2 st = stats(g, part0, nparts);
       float at = 0.f;
       for (int s0 = 0; s0 < nparts; s0 += OUT_BATCH) {
         float m[OUT_BATCH], v[OUT_BATCH];
@@ -74,7 +74,7 @@ __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int
   for (int item = wg; item < G * cblocks; item += n_out) {   // (uniform over the workgroup)
     const int g = item / cblocks, c = (item - g * cblocks) * 64 + lane;
     const float* part0 = part_u + (size_t)g * p.npart * pstride;
-    const float2 st = head_stats(part0, pstride, nparts);
+    const float2 st = stats(g, part0, nparts);
     if (wv < WAVES) {   // (four of them, whatever the workgroup: the order of the sums)
       float at = 0.f;
 #pragma unroll 4
@@ -95,32 +95,42 @@ __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int
   }
 }
 
-template <int G, int RECORD_CHUNKS, int NT>
+// A column of the grid is a unit, a row the same workgroup of every unit: first those that record, then (APART) n_out that do out alone.  So what
+// has work comes in front of what the units leave empty and spreads over the dies, whatever the rows.  (Unit by unit, with out in front, the
+// record workgroups of all units met on a few dies where a unit's workgroups were a multiple of 8, and on a full chip they waited
+// for those that did out: eight heads, 193 units x 1520 of 1600 slots 19.2 us, 64 x 12000 of 32768 51.5, before out had workgroups of its own 12.4 and 37.2.
+// Whole steps, us, unit by unit | row by row: 250 units x 1900 of 2048 slots, eight heads, 74.8 | 68.3; 120 x 460 of 3072 34.9 | 29.1, one head
+// 16.1 | 15.9; 200 x 2457 of 16384, four heads, 182 | 155; 30 x 16000 of 16384 57.3 | 59.2, where the dies that attended to the chunks record them unit by unit.)
+// Not APART: the workgroups that record share out, in front of the record, which lengthens their chain of latencies.
+template <int G, int RECORD_CHUNKS, int NT, bool APART>
 __global__ __launch_bounds__(NT) void corm_record_kernel(const Params p, const int D, const int n_out) {
   constexpr int RECORD_ROWS = RECORD_CHUNKS * CHUNK;  // keys per workgroup
   constexpr int KPT = RECORD_ROWS / NT;  // keys per thread
   constexpr int KPC = CHUNK / NT;        // of which per chunk
   constexpr int NW = NT / 64;
   static_assert(CHUNK % NT == 0 && NT >= 64 * WAVES, "whole keys per thread and chunk; the waves of record_out");
-  const int rsplit = (int)blockIdx.x - n_out;   // this workgroup covers chunks [rsplit*RECORD_CHUNKS, +RECORD_CHUNKS); below 0: out
-  const int unit = blockIdx.y;
+  const int PSTRIDE = D + 2;
+  const int unit = blockIdx.x;
   const UnitLen ul = unit_len(p, unit);
   const int L = ul.L;
+  const int nparts = (L + p.part_keys - 1) / p.part_keys;           // attend partials that hold keys
+  const int rsplit = blockIdx.y;   // this workgroup covers chunks [rsplit*RECORD_CHUNKS, +RECORD_CHUNKS)
+  const int nrec = (p.nsplit + RECORD_CHUNKS - 1) / RECORD_CHUNKS;
+  if (APART && rsplit >= nrec) {
+    record_out<G, NT>(p, unit, L, nparts, D, rsplit - nrec, n_out,
+                      [&](int, const float* part0, int nparts) { return head_stats(part0, PSTRIDE, nparts); });
+    return;
+  }
   const int tid = threadIdx.x;
   if (rsplit == 0 && tid == 0 && ul.flags && p.status) atomicOr(p.status, ul.flags);
   const int nlive = (L + CHUNK - 1) / CHUNK;                        // chunks that hold keys
-  const int nparts = (L + p.part_keys - 1) / p.part_keys;           // attend partials that hold keys
-  if (rsplit < 0) {
-    record_out<G, NT>(p, unit, L, nparts, D, blockIdx.x, n_out);
-    return;
-  }
-  if (rsplit * RECORD_ROWS >= L) return;   // nothing to record here
+  const int nwg = max((L + RECORD_ROWS - 1) / RECORD_ROWS, APART ? 0 : 1);   // record workgroups that have work
+  if (rsplit >= nwg) return;
 
   const int b = unit / p.Hkv;
   const int hkv = unit - b * p.Hkv;
   const int hq0 = hkv * G;
   const int lane = tid & 63, wv = tid >> 6;
-  const int PSTRIDE = D + 2;
   const int rbeg = rsplit * RECORD_ROWS;
   const int rend = min(rbeg + RECORD_ROWS, L);
 
@@ -156,6 +166,11 @@ __global__ __launch_bounds__(NT) void corm_record_kernel(const Params p, const i
     }
   }
   __syncthreads();
+
+  if (!APART) {
+    record_out<G, NT>(p, unit, L, nparts, D, rsplit, nwg, [&](int g, const float*, int) { return make_float2(sh_M[g], sh_Z[g]); });
+    if (L == 0) return;   // an empty unit: nothing to record
+  }
 
   // record (Def. 3.1) and decide (Def. 4.1 + recent r) for the keys of this workgroup
   const bool step_ok = tcur >= 1 && tcur <= p.Tcap;

@@ -794,8 +794,8 @@ def test_a_step_of_small_units_with_events_brackets_the_launch_that_streams(case
             break
 
 
-# query heads per KV head, d, capacity: 15, 16 and 17 parts of a full unit (up to 16 a wave folds an item alone), 17 parts of
-# 512, and 70 (more than a wave holds one of per lane)
+# query heads per KV head, d, capacity: 15, 16 and 17 parts of a full unit (up to 16 a wave folds an item alone), 68 parts of 128
+# keys and 70 of 512 (more than a wave holds one of per lane)
 OUTS = [(1, 64, 1900), (8, 128, 2048), (2, 128, 2100), (4, 128, 8600), (1, 128, 35700)]
 
 
@@ -833,3 +833,52 @@ def test_out_of_a_split_unit_whatever_its_parts(case):
         a = torch.softmax(q[b].double() @ k.t().contiguous() / d ** 0.5, -1)
         tol = 2.0 ** -24 * (8 * d + 200) * (a @ v.abs())
         assert ((st.out[b].double() - a @ v).abs() <= tol).all(), n
+
+
+# query heads per KV head, d, units, capacity: the record launch by its rules (workgroups of one, two and four chunks; a thread per key or
+# two keys a thread; out by workgroups of its own, by waves or whole ones, or by those that record)
+RECORDS = [(8, 64, 768, 512), (8, 64, 769, 512), (8, 128, 512, 256), (8, 128, 513, 256), (8, 64, 1024, 512), (8, 128, 600, 2048), (8, 64, 1030, 2100),
+           (4, 128, 130, 9000), (1, 64, 1100, 300), (2, 64, 600, 600), (4, 64, 40, 4096), (1, 128, 3, 20000)]
+
+
+@pytest.mark.parametrize("case", range(len(RECORDS)))
+def test_record_launch_by_its_rules(case):
+    """out and last_hit of one attend call over units of every fill, empty ones among them (out 0), against softmax in 64 bits.  Tolerance of out
+    as in test_out_of_a_split_unit_whatever_its_parts; a score within 1e-4 of c/t may fall on either side."""
+    G, d, U, Lcap = RECORDS[case]
+    print("[case]", RECORDS[case], flush=True)
+    g = torch.Generator(device=DEV).manual_seed(case)
+    st = corm.LayerState(1, G * U, U, d, Lcap, Lcap, 16, 8, "f32", device=DEV, want_ring=False)
+    lens = torch.randint(0, Lcap + 1, (U,), device=DEV, generator=g, dtype=torch.int32)
+    edges = [n for n in (Lcap, 0, 1, 511, 512, 513, 2048, 4095, 7 * 512, 8192) if n <= Lcap][:U]
+    lens[:len(edges)] = torch.tensor(edges, device=DEV, dtype=torch.int32)
+    scale = float(torch.tensor(float(d)).rsqrt() * 1.4426950408889634)
+    q = torch.rand(1, G * U, d, device=DEV, generator=g) * 2 - 1
+    st.K[:] = (torch.rand(1, U, Lcap, d, device=DEV, generator=g) * 2 - 1) * (8 / d / scale)
+    st.V[:] = torch.randn(1, U, Lcap, d, device=DEV, generator=g)
+    st.pos[:] = torch.arange(Lcap, device=DEV).int()
+    st.lens[0] = lens
+    st.out.fill_(7.0)
+    t = torch.full((1,), Lcap, dtype=torch.int32, device=DEV)
+    opts = corm.make_opts(path=1)
+    corm.corm_decode_attend(st.desc, q, st.K, st.V, st.lens, st.pos, t, st.ring, st.last_hit, st.out, st.workspace,
+                            status=st.status, opts=opts)
+    torch.cuda.synchronize()
+    assert int(st.status.item()) == 0
+    slot = torch.arange(Lcap, device=DEV)
+    step = max(1, 2 ** 21 // Lcap)
+    for u in range(0, U, step):
+        n = lens[u:u + step].long().view(-1, 1, 1)
+        held = slot.view(1, 1, -1) < n
+        k, v = st.K[0, u:u + step].double(), st.V[0, u:u + step].double()
+        qu = q.view(U, G, d)[u:u + step].double()
+        s = torch.matmul(k, qu.transpose(1, 2).contiguous()).transpose(1, 2) / d ** 0.5
+        a = torch.softmax(s.masked_fill(~held, float("-inf")), -1)
+        a = torch.where(held, a, 0.0)
+        tol = 2.0 ** -24 * (8 * d + 200) * torch.matmul(a, v.abs())
+        out = st.out.view(U, G, d)[u:u + step].double()
+        assert ((out - torch.matmul(a, v)).abs() <= tol).all(), u
+        assert not out[(n == 0).view(-1)].any()
+        sure = ((a * Lcap - 1).abs() > 1e-4).all(1)
+        hit = (a * Lcap >= 1).any(1)
+        assert torch.equal((st.last_hit[0, u:u + step] == Lcap)[sure], hit[sure]), u
