@@ -492,7 +492,7 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
   // One-dimensional grid of 8 * ceil(units / 8) * nkb * nseg workgroups.  Workgroups are dealt round-robin to the 8
   // XCDs, so id % 8 names the XCD; each XCD takes a contiguous range of units and runs the key blocks of a unit
   // one after the other: they all read the same tail queries, which then stay in that XCD's L2.  (As many workgroups as the chip
-  // holds, which take the blocks from a queue per XCD and then from the others': 1843 -> 1824 us, not kept.)
+  // holds, which take the blocks from a queue per XCD and then from the others': the whole call 1 % shorter, not kept.)
   const int per_xcd = (a.units + PREFILL_XCDS - 1) / PREFILL_XCDS;
   const int li = (int)(blockIdx.x / PREFILL_XCDS);
   const int seg = li % a.nseg, lk = li / a.nseg;
@@ -523,7 +523,7 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
 
   // Pass 2, bf16 ring: a wave's tile of stored scores is turned through LDS so that every query's consecutive
   // positions leave as one piece of its ring row (16 bytes per lane).  Rows are padded by 16 bytes.
-  // (Stored straight from the lanes that hold them, a lane's 16 bytes in pieces of 64: the whole call 1890 -> 1950 to 2010 us.)
+  // (Stored straight from the lanes that hold them, a lane's 16 bytes in pieces of 64: the whole call 3 to 6 % longer.)
   constexpr int TROW = WKEYS + 8;
   constexpr bool TURN = MODE == SEED_BF16;
   __shared__ __attribute__((aligned(16))) uint16_t sh_t[TURN ? WAVES : 1][TURN ? 16 : 1][TURN ? TROW : 1];
@@ -991,10 +991,11 @@ __device__ __forceinline__ void prefill_scores(const PrefillArgs& a) {
 
 // Pass 2 on 256-byte rows takes the registers of two waves per SIMD (held to three it spills: 1.27 -> 1.76 ms); fp32 rows of
 // 512 bytes, two key tiles per wave, fit three.  Per tile of 16 queries x 64 keys, 16 MFMAs: bf16 scores 74 other vector instructions
-// (102 before), bits 46 (111), and 29 or 25 scalar ones (36 and 26).  Whole calls, us, before | now: 512 heads x 1024 queries x 4096 keys,
-// bf16 ring 1924 | 1843, without a ring 1481 | 1410; 512 x 1024 x 8192 with the boolean ring 2739 | 2320.  What still bounds it: with
-// bf16 scores the 3.76 GB of ring, which 450 us of the 640 to 750 they take alone do not hide behind the rest; else products, scalar and vector issue of
-// two waves that share a SIMD (products and LDS reads alone: 10.8 ns an MFMA on every SIMD, as it is 19).
+// (102 with both kinds of block in one loop), bits 46 (111), and 29 or 25 scalar ones (36 and 26).  One loop | two, us, this kernel traced and the whole
+// call: 512 heads x 1024 queries x 4096 keys, bf16 ring 1264 | 1177 and 1858 | 1776 (calls in a row by themselves 1877 | 1792, without a ring 1453 | 1341);
+// 512 x 1024 x 8192 with the boolean ring 1628 | 1173 and 2677 | 2234.  Calls of 18 to 45 us, of a block or a few per wave, take 0 to 1 us longer.  What still
+// bounds it: with bf16 scores the 3.76 GB of ring, which 450 us of the 640 to 750 they take alone do not hide behind the rest; else products, scalar and
+// vector issue of two waves that share a SIMD (products and LDS reads alone: 10.8 ns an MFMA on every SIMD, as it is 19).
 template <typename DT, int D, int MODE, bool FAR>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 3))) void corm_prefill_scores_kernel(
     const PrefillArgs a) {
