@@ -266,7 +266,7 @@ int corm_decode_step_lazy(const corm_desc* desc, const void* q, const void* k_ne
  * if m < w nothing is evicted yet.  Result: the state m calls of corm_decode_step would leave (same keep
  * decisions for the same recorded scores; the scores themselves agree within fp32 rounding), without `out`.
  * q.K^T runs on the matrix cores (bf16: v_mfma_f32_16x16x32_bf16, fp32: v_mfma_f32_16x16x4_f32).
- * Errors: CORM_EINVAL also for m < 1 or m > w; device status CORM_DEV_BAD_STEP if t[b] - m < 0,
+ * Errors: CORM_EINVAL also for m < 1 or m > w; CORM_EUNSUPPORTED for m > 1048560; device status CORM_DEV_BAD_STEP if t[b] - m < 0,
  * t[b] > Tcap, or a position lies outside [0, Tcap). */
 int corm_prefill_seed(const corm_desc* desc, const void* q_tail, int32_t m, void* K, void* V, int32_t* lens,
                       int32_t* pos, int32_t* last_hit, const int32_t* t, int32_t* t_first, void* score_ring,

@@ -304,7 +304,8 @@ def test_seed_with_logits_that_are_not_finite(dtype, d, c):
     """A key with NaN of either sign, or an infinity of either sign, in one element: Def. 3.1 compares scores, so a score
     that is not a number is minor and one that is 0 reaches the threshold 0, on every ring type and whichever way the
     kernel decides.  The scores an fp32 ring holds are the witness; comparisons of them are exact.  Keys in front of the
-    first tail query take the kernel's fast blocks, those among the tail its general ones: both get a poisoned key."""
+    first tail query take the kernel's fast blocks (with a bf16 ring only those whose rows are finite), those among the tail its general
+    ones: both get a poisoned key."""
     print("[case]", dtype, d, c, flush=True)
     P, m, Hkv = 600, 80, len(POISON)
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
