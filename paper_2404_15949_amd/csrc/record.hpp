@@ -101,7 +101,8 @@ __device__ __forceinline__ void record_out(const Params& p, int unit, int L, int
 // for those that did out: eight heads, 193 units x 1520 of 1600 slots 19.2 us, 64 x 12000 of 32768 51.5, before out had workgroups of its own 12.4 and 37.2.
 // Whole steps, us, unit by unit | row by row: 250 units x 1900 of 2048 slots, eight heads, 74.8 | 68.3; 120 x 460 of 3072 34.9 | 29.1, one head
 // 16.1 | 15.9; 200 x 2457 of 16384, four heads, 182 | 155; 30 x 16000 of 16384 57.3 | 59.2, where the dies that attended to the chunks record them unit by unit.)
-// Not APART: the workgroups that record share out, in front of the record, which lengthens their chain of latencies.
+// Not APART: the workgroups that record share out, in front of the record, which lengthens their chain of latencies (this launch, us, so with two keys a
+// thread | apart, with the threads of the host's rule: 32 units x 4200 keys 5.2 | 4.0, 16 x 2600 of two heads 5.8 | 4.1, 9 x 600 of eight 10.5 | 6.3, 128 x 33000 24.6 | 24.1).
 template <int G, int RECORD_CHUNKS, int NT, bool APART>
 __global__ __launch_bounds__(NT) void corm_record_kernel(const Params p, const int D, const int n_out) {
   constexpr int RECORD_ROWS = RECORD_CHUNKS * CHUNK;  // keys per workgroup
